@@ -60,14 +60,25 @@ typedef __attribute__((ext_vector_type(2))) float f32x2;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 
 constexpr int BR = 128, BC = 32, NSTAGE = 4, NTHREADS = 256;
-// Geometry for head dimension DH (128 or 64): LDS rows of DH bf16, a tensor's 32-row block, a ring stage (X | tX), the
-// two rings.  DH = 128: 256-byte rows, 8 KiB blocks, 128 KiB of LDS; DH = 64: half of each.
-template <int DH>
+// TAN selects which tangents exist: TAN_ALL (tQ, tK, tV), TAN_QUERY (tQ only: "ZT" below, zero key/value tangents)
+// or TAN_NONE (plain attention forward, O and lse only: 2 of the 6 products; same code path).
+constexpr int TAN_NONE = 0, TAN_QUERY = 1, TAN_ALL = 2;
+// Geometry for head dimension DH (128 or 64): LDS rows of DH bf16, a tensor's 32-row block, a ring stage (X | tX, or X
+// alone in the plain forward), the two rings.  DH = 128: 256-byte rows, 8 KiB blocks, 128 KiB of LDS (64 in the plain
+// forward); DH = 64: half of each.  (With TAN_QUERY the tangent halves of the stages stay unused: Q and tQ of a tile
+// are staged through the V ring's area, which needs its full size.)
+template <int DH, int TAN = TAN_ALL>
 struct Geo {
     static_assert(DH == 128 || DH == 64, "head dimensions built natively");
     static constexpr int ROW_BYTES = DH * 2;
     static constexpr int TENSOR_BYTES = BC * ROW_BYTES;
-    static constexpr int KV_STAGE_BYTES = 2 * TENSOR_BYTES;        // K|tK or V|tV
+    static constexpr int KV_STAGE_BYTES = (TAN == TAN_NONE ? 1 : 2) * TENSOR_BYTES;        // K|tK or V|tV
+    // Workgroups that share a compute unit.  Where the registers allow two waves per SIMD, the second wave's matrix
+    // work covers the first one's softmax; the plain forward needs that most, with only 16 MFMAs per wave and key
+    // block to cover the arithmetic of 16 scores per lane (DH = 128, whole calls with one -> two workgroups: B2 H16
+    // L4096 320 -> 294 us, peaked rows B1 H4 L12000 514 -> 382 us, B4 H24 Lq8000 Lkv300 322 -> 270 us; three
+    // workgroups at DH = 64 gave nothing over two).
+    static constexpr int WG_PER_CU = DH == 64 || TAN == TAN_NONE ? 2 : 1;
     static constexpr int V_RING_BASE = NSTAGE * KV_STAGE_BYTES;    // K ring first, V ring behind it
     static constexpr int RING_BYTES = 2 * NSTAGE * KV_STAGE_BYTES;
     static constexpr int LDS_BYTES = RING_BYTES + 1024;           // + a KiB where prefetches land that nobody reads
@@ -297,10 +308,6 @@ constexpr int STAGGER_TICKS = 32;   // start offset between neighbouring residen
 // 8 key blocks 24.8 against 27.9 us, 16 blocks 33.6 against 37.8 us); below that the bf16 pairs run unless the caller insists.
 constexpr int F16_MIN_KEYS = 2048, F16_MIN_KEYS_MANY_TILES = 256, F16_MANY_TILES_PER_CU = 4;
 
-// TAN selects which tangents exist: TAN_ALL (tQ, tK, tV), TAN_QUERY (tQ only: "ZT" below, zero key/value tangents)
-// or TAN_NONE (plain attention forward, O and lse only: 2 of the 6 products; same code path, nothing else changes).
-constexpr int TAN_NONE = 0, TAN_QUERY = 1, TAN_ALL = 2;
-
 // One query tile (128 rows of one head), start to finish.  `vw` is the tile's index in the launch's list of
 // (head, query tile) pairs as a one-workgroup-per-tile launch would number its workgroups; n_tiles their count.
 template <int MODE, int TAN, int DH>
@@ -311,7 +318,7 @@ __device__ __forceinline__ void attn_jvp_tile(
     int Lq, int Lkv, float scale, int q_tiles, const float* __restrict__ stats, int* __restrict__ wg_flags,
     int H, int blhd, int out_bf16, int d_out, int out_blhd, int online_min_blocks, int lockstep_slots,
     const int vw, const int n_tiles) {
-    using G = Geo<DH>;
+    using G = Geo<DH, TAN>;
     constexpr int D = DH, ROW_BYTES = G::ROW_BYTES, TENSOR_BYTES = G::TENSOR_BYTES, KV_STAGE_BYTES = G::KV_STAGE_BYTES;
     constexpr int V_RING_BASE = G::V_RING_BASE;
     constexpr int NT = DH / 16;             // score steps per key block (16 of the head dimension each)
@@ -879,13 +886,15 @@ __device__ __forceinline__ void attn_jvp_tile(
             // the copies to and from arithmetic registers stay inside this block)
 #pragma unroll
             for (int db = 0; db < NDB; ++db) {
-                asm volatile("" : "+a"(accO[db]), "+a"(accAB[db]));
+                asm volatile("" : "+a"(accO[db]));
+                if constexpr (!PRIMAL) asm volatile("" : "+a"(accAB[db]));
 #pragma unroll
                 for (int e = 0; e < 16; ++e) {
                     if constexpr (!PRIMAL) accAB[db][e] = fmaf(accAB[db][e], pend_alpha, -pend_da * accO[db][e]);
                     accO[db][e] *= pend_alpha;
                 }
-                asm volatile("" : "+a"(accO[db]), "+a"(accAB[db]));
+                asm volatile("" : "+a"(accO[db]));
+                if constexpr (!PRIMAL) asm volatile("" : "+a"(accAB[db]));
             }
             pend = false;
         }
@@ -1260,7 +1269,7 @@ __device__ __forceinline__ void attn_jvp_tile(
         constexpr uint32_t OUT_ROW_BYTES = DH * 4;                 // a row of fp32 results
         constexpr int OUT_CHUNKS = DH / 4;                         // ... in 16-byte chunks (32, or 16 at head dimension 64)
         constexpr int ROWS_PER_STORE = 64 / OUT_CHUNKS;            // rows one store instruction covers (2, or 4)
-        const uint32_t stage_o = lds0 + (uint32_t)wave * (64u * OUT_ROW_BYTES), stage_t = stage_o + 32u * OUT_ROW_BYTES;
+        const uint32_t stage_o = lds0 + (uint32_t)wave * ((PRIMAL ? 32u : 64u) * OUT_ROW_BYTES), stage_t = stage_o + 32u * OUT_ROW_BYTES;
 #pragma unroll
         for (int db = 0; db < NDB; ++db)
 #pragma unroll
@@ -1317,7 +1326,7 @@ __device__ __forceinline__ void attn_jvp_tile(
 // path, so the next tile may start filling LDS at once.  Since gridDim.x is then a multiple of 8, tile w + k gridDim.x
 // runs on the same XCD as tile w, as the tile map in attn_jvp_tile assumes.
 template <int MODE, int TAN, int DH>
-__global__ __launch_bounds__(NTHREADS, DH == 64 ? 2 : 1) void attn_jvp_mfma_kernel(
+__global__ __launch_bounds__(NTHREADS, (Geo<DH, TAN>::WG_PER_CU)) void attn_jvp_mfma_kernel(
     const __hip_bfloat16* __restrict__ Q, const __hip_bfloat16* __restrict__ K, const void* __restrict__ V,
     const __hip_bfloat16* __restrict__ tQ, const __hip_bfloat16* __restrict__ tK, const void* __restrict__ tV,
     void* __restrict__ O, void* __restrict__ tO, float* __restrict__ LSE,
@@ -1362,19 +1371,21 @@ bool mfma_bf16_supports(const Problem& p) {
 // Dynamic-LDS limit of every instantiation a call may launch, raised once per device and before anything is enqueued.
 template <int DH>
 static hipError_t prepare_kernels(int dev) {
-    const void* kernels[] = {
-        (const void*)attn_jvp_mfma_kernel<MODE_BF16, TAN_ALL, DH>,
-        (const void*)attn_jvp_mfma_kernel<MODE_BF16_SPLIT, TAN_NONE, DH>, (const void*)attn_jvp_mfma_kernel<MODE_BF16_SPLIT, TAN_QUERY, DH>,
-        (const void*)attn_jvp_mfma_kernel<MODE_BF16_SPLIT, TAN_ALL, DH>,
-        (const void*)attn_jvp_mfma_kernel<MODE_F16, TAN_NONE, DH>, (const void*)attn_jvp_mfma_kernel<MODE_F16, TAN_QUERY, DH>,
-        (const void*)attn_jvp_mfma_kernel<MODE_F16, TAN_ALL, DH>,
-        (const void*)attn_jvp_mfma_kernel<MODE_F16_ONLINE, TAN_NONE, DH>, (const void*)attn_jvp_mfma_kernel<MODE_F16_ONLINE, TAN_QUERY, DH>,
-        (const void*)attn_jvp_mfma_kernel<MODE_F16_ONLINE, TAN_ALL, DH>};
-    for (const void* k : kernels) {
-        const hipError_t e = ensure_dynamic_lds(k, Geo<DH>::LDS_BYTES, dev);
-        if (e != hipSuccess) return e;
-    }
-    return hipSuccess;
+    auto raise = [&](auto tan) -> hipError_t {
+        constexpr int T = decltype(tan)::value;
+        const void* kernels[] = {(const void*)attn_jvp_mfma_kernel<MODE_BF16_SPLIT, T, DH>, (const void*)attn_jvp_mfma_kernel<MODE_F16, T, DH>,
+                                 (const void*)attn_jvp_mfma_kernel<MODE_F16_ONLINE, T, DH>};
+        for (const void* k : kernels) {
+            const hipError_t e = ensure_dynamic_lds(k, Geo<DH, T>::LDS_BYTES, dev);
+            if (e != hipSuccess) return e;
+        }
+        return hipSuccess;
+    };
+    hipError_t e = ensure_dynamic_lds((const void*)attn_jvp_mfma_kernel<MODE_BF16, TAN_ALL, DH>, Geo<DH>::LDS_BYTES, dev);
+    if (e == hipSuccess) e = raise(std::integral_constant<int, TAN_NONE>{});
+    if (e == hipSuccess) e = raise(std::integral_constant<int, TAN_QUERY>{});
+    if (e == hipSuccess) e = raise(std::integral_constant<int, TAN_ALL>{});
+    return e;
 }
 
 template <int DH>
@@ -1404,14 +1415,15 @@ static hipError_t launch_dh(const Problem& p_in) {
     // differ in length, they keep one workgroup per tile, which the hardware balances.
     bool resident = false;
     const bool short_tiles = (p.Lkv + BC - 1) / BC < LOCKSTEP_MIN_BLOCKS;
-    auto launch = [&](auto kern, const void* v, const void* tv, const float* stats, int* wg_flags) -> hipError_t {
-        constexpr int WG_PER_CU = DH == 64 ? 2 : 1;       // what the kernel's registers and LDS allow
+    auto launch = [&](auto kern, auto tan, const void* v, const void* tv, const float* stats, int* wg_flags) -> hipError_t {
+        using G = Geo<DH, decltype(tan)::value>;
+        constexpr int WG_PER_CU = G::WG_PER_CU;           // what the kernel's registers and LDS allow
         const bool follower = !resident && wg_flags != nullptr;      // a hand-over launch of the fp16 path
         const bool res = (resident || (follower && short_tiles)) && cus % 8 == 0 && blocks >= 2LL * WG_PER_CU * cus &&
                          !(p.flags & 16);   // 16: ATTN_JVP_FLAG_NO_RESIDENT
         const long long grid = res ? (long long)WG_PER_CU * cus : blocks;
         const int stagger = res && !follower ? STAGGER_TICKS : 0;
-        hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(NTHREADS), Geo<DH>::LDS_BYTES, p.stream,
+        hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(NTHREADS), G::LDS_BYTES, p.stream,
                            (const __hip_bfloat16*)p.q, (const __hip_bfloat16*)p.k, v,
                            (const __hip_bfloat16*)p.tq, (const __hip_bfloat16*)p.tk, tv,
                            p.o, p.to, p.lse, p.Lq, p.Lkv, p.scale, q_tiles, stats, wg_flags, p.H, p.layout, p.out_dtype,
@@ -1441,13 +1453,13 @@ static hipError_t launch_dh(const Problem& p_in) {
     auto run = [&](auto tan, const void* tv, const void* tv16) -> hipError_t {
         constexpr int T = decltype(tan)::value;
         resident = true;
-        if (!f16) return launch(attn_jvp_mfma_kernel<MODE_BF16_SPLIT, T, DH>, p.v, tv, nullptr, nullptr);
-        hipError_t err = launch(attn_jvp_mfma_kernel<MODE_F16, T, DH>, ws.v16, tv16, ws.stats, ws.wg_flags);
+        if (!f16) return launch(attn_jvp_mfma_kernel<MODE_BF16_SPLIT, T, DH>, tan, p.v, tv, nullptr, nullptr);
+        hipError_t err = launch(attn_jvp_mfma_kernel<MODE_F16, T, DH>, tan, ws.v16, tv16, ws.stats, ws.wg_flags);
         resident = false;
         lockstep = ws.lockstep_slots;
-        if (err == hipSuccess) err = launch(attn_jvp_mfma_kernel<MODE_F16_ONLINE, T, DH>, ws.v16, tv16, ws.stats, ws.wg_flags);
+        if (err == hipSuccess) err = launch(attn_jvp_mfma_kernel<MODE_F16_ONLINE, T, DH>, tan, ws.v16, tv16, ws.stats, ws.wg_flags);
         lockstep = 0;
-        if (err == hipSuccess) err = launch(attn_jvp_mfma_kernel<MODE_BF16_SPLIT, T, DH>, p.v, tv, nullptr, ws.wg_flags);
+        if (err == hipSuccess) err = launch(attn_jvp_mfma_kernel<MODE_BF16_SPLIT, T, DH>, tan, p.v, tv, nullptr, ws.wg_flags);
         return err;
     };
     if (p.tq == nullptr) {             // no tangents at all: plain attention forward
@@ -1456,7 +1468,7 @@ static hipError_t launch_dh(const Problem& p_in) {
         e = run(std::integral_constant<int, TAN_QUERY>{}, nullptr, nullptr);
     } else if (p.flags & 1) {
         resident = true;
-        e = launch(attn_jvp_mfma_kernel<MODE_BF16, TAN_ALL, DH>, p.v, p.tv, nullptr, nullptr);
+        e = launch(attn_jvp_mfma_kernel<MODE_BF16, TAN_ALL, DH>, std::integral_constant<int, TAN_ALL>{}, p.v, p.tv, nullptr, nullptr);
     } else {
         e = run(std::integral_constant<int, TAN_ALL>{}, p.tv, ws.tv16);
     }
