@@ -19,7 +19,8 @@ sys.path.insert(0, ROOT)
 PEAK_BF16_TFLOPS = 2516.6   # MI355X dense bf16 MFMA: 256 CU x 2.4 GHz x 4096 flop/clk/CU
 
 
-PEAK_FP32_TFLOPS = 157.3     # MI355X dense fp32 MFMA
+PEAK_FP32_TFLOPS = 157.3     # MI355X dense fp32 MFMA (and vector ALU)
+PEAK_F32_SPLIT_TFLOPS = PEAK_BF16_TFLOPS / 3     # fp32 products as three 16-bit MFMA products of split operands
 PEAK_HBM_GBS = 8000.0        # MI355X HBM3E
 
 
@@ -146,7 +147,7 @@ def main():
                     help="memory layout of the eight tensors: [B,H,L,d] (default) or [B,L,H,d]")
     ap.add_argument("--input-dtype", choices=["config", "fp32"], default="config",
                     help="fp32: hold the workload's inputs (the same values) in fp32, which takes the fp32 matrix-core kernel; "
-                         "priced against the fp32 MFMA peak")
+                         "priced against a third of the 16-bit MFMA peak (three products of split operands each)")
     ap.add_argument("--op", choices=["attention", "rmsnorm"], default="attention",
                     help="attention (default: the headline metric) or rmsnorm: the RMSNorm + JVP kernel on the q tensor "
                          "of the chosen workload (its QK-normalisation), an HBM-bound second workload with its own line")
@@ -283,10 +284,10 @@ def main():
     except OSError:
         pass
 
-    peak = PEAK_FP32_TFLOPS if f32 else PEAK_BF16_TFLOPS
+    peak = (PEAK_F32_SPLIT_TFLOPS if d in (32, 64, 96, 128) else PEAK_FP32_TFLOPS) if f32 else PEAK_BF16_TFLOPS
     # what the path computes in (inputs; matrix products; accumulation), by the route the library takes for this call
     if f32:
-        arithmetic = "f32 (fp32 MFMA, fp32 accumulate)" if d in (32, 64, 96, 128) else "f32 (vector ALU)"
+        arithmetic = "f32 (three fp16 MFMA products per fp32 product, fp32 accumulate)" if d in (32, 64, 96, 128) else "f32 (vector ALU)"
     elif not (d in (32, 64, 96, 128) and cfg.scale > 0):
         arithmetic = "bf16 in, f32 vector ALU"
     elif args.variant == "fast":

@@ -88,8 +88,11 @@ extern "C" {
                                      workspace of attn_jvp_workspace_bytes(...): the inputs are first copied there
                                      zero-padded to 64 and 128 columns (exact: the padding adds zeros to every
                                      product; half and a quarter of the matrix work are then spent on zeros).
-                                     fp32 inputs: d in {32, 64, 96, 128}, any finite scale, fp32 outputs; fp32 operands
-                                     and fp32 accumulation throughout (Alg. 2 as printed), no workspace, flags ignored.
+                                     fp32 inputs: d in {32, 64, 96, 128}, any finite scale, fp32 outputs; every product
+                                     as three 16-bit products of operands split into two fp16 terms each (22 to 23
+                                     bits), fp32 accumulation, no workspace, flags ignored.  Tiles whose values do not
+                                     fit the scaled fp16 ranges (a key block with values 16 times those of the first,
+                                     infinities, NaN) are computed again with fp32 products, at several times the cost.
                                      Accuracy contract of this path: l, r and the accumulators are fp32 running sums
                                      over the keys, so max |x - x_exact| / RMS(x) of o and to is within 1e-5 up to
                                      256 keys and grows like sqrt(Lkv) beyond: within 1.5e-5 sqrt(Lkv / 256)

@@ -1,46 +1,49 @@
-// fp32 matrix-core streaming kernel for attention forward + JVP (paper App. C.1, Alg. 2) on gfx950.
+// Matrix-core streaming kernel for attention forward + JVP (paper App. C.1, Alg. 2) on fp32 inputs, gfx950; head dims
+// 32, 64, 96, 128.
 //
-// The path for fp32 inputs at head dims 32, 64, 96, 128: every product runs on v_mfma_f32_32x32x2_f32 (fp32
-// operands, fp32 accumulation), the softmax weights stay fp32 and nothing is rounded to a narrower type.  What is
-// left is the rounding of the fp32 running sums themselves (l, r and, foremost, the accumulators, which take one
-// rounded addition per two keys): measured max error 5e-6 of RMS at 256 keys, the size the 1e-5 tolerance for fp32
-// inputs is stated for, growing like sqrt(Lkv) beyond (1.4e-5 at 4096 keys); that growth law is part of the
-// interface's accuracy contract.  The algorithm is Alg. 2: row reference m, rescale factor
-// alpha = exp(m_old - m_new) applied to l, r and both accumulators, A and B summed into one accumulator (they are
-// only ever added), epilogue O/l, lse = m + log l, tO = (A + B - (r/l) O_unnorm)/l.  Two things differ from the
-// printed algorithm: the softmax scale, which it leaves out, multiplies S and tS; and m trails the running row
-// maximum by up to 32 nats (it is moved only when a block exceeds it by more), which changes no result and makes
-// the rescaling of the accumulators rare.
+// The fp32 MFMAs run at a sixteenth of the rate of the 16-bit ones and share the vector ALU's arithmetic, so every
+// product is formed from operands SPLIT into two fp16 terms instead: x = 2^e (hi + lo) with hi = fp16(x 2^-e), lo =
+// fp16(x 2^-e - hi), and a b = hi hi + hi lo + lo hi, three 16-bit MFMAs with fp32 accumulation.  hi + lo carries 22 to
+// 23 bits, the dropped lo lo term is below 2^-22 of the product: rounding of the same size as that of the fp32 score
+// sums, and three (not sixteen) rounded additions per accumulator and 16 keys make the accumulators' own error smaller
+// than that of fp32 MFMAs, which take one per two keys.
+// Powers of two keep everything inside the fp16 range (they add no rounding):
+//   Q, tQ rows and K, tK rows: each row by its own largest element, to [2^12, 2^13).  The factors are undone on the
+//     scores, per lane for the query and per register for the key.
+//   V, tV: by the head's first key block, its largest |V| to [2^11, 2^12); tV shares V's factor times 2^eH.
+//   weights: P~ 2^12 with P~ = exp(S - m) against a row reference m that trails the row maximum by at most 2.68 nats
+//     (so that keys 25 nats below the maximum still count); H~ 2^(12 - eH) with 2^eH from the first block's tangent
+//     scores and |tV| / |V|.
+// A value outside these ranges becomes inf in fp16 and shows in l, r or the accumulators.  Such tiles, and those with
+// infinities or NaN in their inputs, are redone at the end with fp32 MFMAs (redo_fp32: Alg. 2 as printed, slow).  l and r
+// are summed in fp32 from the unrounded weights.
 //
-// Work split: a workgroup of 4 waves owns 128 query rows, 32 per wave; key blocks of BC = 32 rows.  Products are
-// taken transposed, S^T = K Q^T and O^T += V^T P~^T: the query index is the MFMA column (lane % 32), so each lane
-// holds, for ONE query row, 16 of the 32 scores of a block (the other 16 sit in lane ^ 32); row max and row sums are
-// per-lane loops plus one half-wave exchange, and the 16 weights a lane holds are exactly the B operands of the 16
-// reduction steps of the value products: no transposition, no LDS round trip for the weights.
+// Work split: a workgroup of 4 waves owns 128 query rows, 32 per wave; key blocks of BC = 32 rows.  Products are taken
+// transposed, S^T = K Q^T and O^T += V^T P~^T, on v_mfma_f32_32x32x16_f16: the query index is the MFMA column (lane %
+// 32), each lane holds 16 of the 32 scores of ONE query row, and the split weights are the B operands of the value
+// products as they stand.
 //
-//   score step t = 4u + e (u < D/8, e < 4): A = K[key = lane%32][8u + 4h + e], B = Q[query = lane%32][8u + 4h + e],
-//                                           h = lane/32; the reduction index is permuted the same way on both sides
-//   value step t < 16, column chunk c < D/32: A = V[key = 8(t/4) + 4h + t%4][32c + lane%32], B = weight register t
-//
-// K, tK, V, tV blocks are staged through LDS as fp32 in two stages by direct-to-LDS loads (no staging registers, no
-// LDS write instructions): one 1-KiB part per wave and MFMA step, issued from the second step of a phase on, one wait
-// and one barrier per block (a block is >= 6000 MFMA cycles per wave).  A 16-byte chunk of a row sits at position
-// chunk ^ (row & 7): the K-side reads (16 bytes per lane, one row per lane) and the V-side reads (4 bytes per lane,
-// one row per half-wave) then spread over the banks for every row width that is a multiple of 128 bytes.
-// Operands are read one MFMA step ahead; the three score chains (S, K tQ^T, tK Q^T) and the accumulators of the
-// column chunks are issued round-robin, so no MFMA waits for its predecessor; the weights of key step t + 1 are
-// computed in the shadow of step t's MFMAs.
-//
-// Registers per lane at D = 128: Q, tQ 64 + 64, the two accumulators 64 + 64, S and the two parts of tS 48, weights
-// 32, operands 24: one wave per SIMD, one workgroup per CU.
+// The split planes of K, tK (row-major) and V, tV (transposed [D][32 keys], keys in the order the score MFMAs leave
+// them in a lane's registers) go through two LDS stages each.  The four waves fetch fp32 blocks two (K) and one (V)
+// blocks ahead into registers and convert them behind the score MFMAs; behind the value MFMAs run the softmax and
+// weight splitting of the NEXT block.  One barrier per block.  Bound by the matrix pipe at D = 128 (144 MFMAs per wave
+// and block, about 480 other vector instructions): B2 H16 L4096 d128 2.19 ms = 376 TFLOP/s counted
+// (6.40 ms with fp32 MFMAs), the matrix pipe busy a bit more than half of the time; d = 64 1.17 ms (3.14), d = 32 0.87
+// (1.65).  Errors against 64 bits are 0.6 to 0.7 of those of the fp32-MFMA kernel in o and to, the same in lse.
 #include "launchers.h"
 #include <type_traits>
+#include <utility>
 #include <stdint.h>
 
 namespace attn_jvp {
 namespace {
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
+typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
 
 constexpr int BR = 128;          // query rows per workgroup
 constexpr int BC = 32;           // key rows per block
@@ -48,9 +51,34 @@ constexpr int NTHREADS = 256;
 constexpr int TAN_NONE = 0;      // no tangents: O, lse only
 constexpr int TAN_QUERY = 1;     // tQ only (tK = tV = 0)
 constexpr int TAN_ALL = 2;
-constexpr float MAX_SLACK = 32.f;     // nats by which a row's scores may exceed its reference m before m is moved
 constexpr float LOG2E = 1.4426950408889634f;
 constexpr float LN2 = 0.6931471805599453f;
+constexpr int ROW_TOP = 12;      // rows of Q, tQ, K, tK: largest element in [2^12, 2^13)
+constexpr int V_TOP = 11;        // first block of V: largest element in [2^11, 2^12), 4 binades in hand for later blocks
+constexpr int T_HEADROOM = 6;    // the first block's largest tangent score is scaled to [2^-6, 2^-5)
+constexpr float P_GAIN = 4096.f;          // the split weights are P~ 2^12 ...
+constexpr float P_SLACK = 2.68f;          // ... and stay below 2^16: nats by which a block may exceed the reference before it moves
+constexpr float FP32_SLACK = 32.f;        // redo_fp32: nats by which scores may exceed the reference
+
+#define FENCE() __builtin_amdgcn_sched_barrier(0)      // no instruction is scheduled across this point
+
+// Score products with the result in ARITHMETIC registers (the vector ALU reads every score; left to itself the compiler
+// puts the results of MFMAs into accumulation registers, which Q, tQ and the accumulators fill, and spills).  It does
+// not see inside: SCORE_RESULTS_LAND supplies the 11 wait states an 8-pass MFMA needs before its result may be read,
+// and the statements that follow it keep every result register live until then.  The build checks the compiled
+// assembly for both (lint_mfma_asm.py).  SMFMA0 starts a chain (C = 0), SMFMA continues it.
+#define SMFMA0(a, b, c) asm volatile("v_mfma_f32_32x32x16_f16 %0, %1, %2, 0" : "=&v"(c) : "v"(a), "a"(b))
+#define SMFMA(a, b, c) asm volatile("v_mfma_f32_32x32x16_f16 %0, %1, %2, %0" : "+v"(c) : "v"(a), "a"(b))
+#define SCORE_RESULTS_LAND() asm volatile("s_nop 7\n\ts_nop 3" ::: "memory")
+
+template <typename F, int... I>
+__device__ __forceinline__ void static_for_impl(F&& f, std::integer_sequence<int, I...>) {
+    (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, typename F>
+__device__ __forceinline__ void static_for(F&& f) {      // f(integral_constant<int, 0>) ... f(integral_constant<int, N-1>)
+    static_for_impl(static_cast<F&&>(f), std::make_integer_sequence<int, N>{});
+}
 
 __device__ __forceinline__ float xhalf_max(float x) {   // max of lane l and lane l^32, in both
     auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
@@ -60,32 +88,90 @@ __device__ __forceinline__ float xhalf_sum(float x) {
     auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
     return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
-template <int N, typename F>
-__device__ __forceinline__ void static_for(F&& f) {      // f(integral_constant<int, 0>) ... f(integral_constant<int, N-1>)
-    if constexpr (N > 0) {
-        static_for<N - 1>(f);
-        f(std::integral_constant<int, N - 1>{});
-    }
+__device__ __forceinline__ f32x16 mfma16(u32x4 a, u32x4 b, f32x16 c) {
+    return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c, 0, 0, 0);
 }
-
-// 128-bit direct-to-LDS load: 64 lanes x 16 B land at lds_base + 16 * lane (M0 carries lds_base); uniform 64-bit base
-// in scalar registers plus a per-lane 32-bit byte offset.  Inline assembly so that the kernel keeps its own account
-// of these loads: they are the only vector-memory loads in flight during the sweep, and an explicit wait plus the
-// barrier at the end of each block publish a stage before anyone reads it.  M0 is reserved: the compiler puts nothing
-// of its own there.
-__device__ __forceinline__ void load_lds_b128(const void* uniform_base, uint32_t lane_off, uint32_t lds_base) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
-                 :: "s"(lds_base), "v"(lane_off), "s"(uniform_base) : "memory");
-}
-
-#define FENCE() __builtin_amdgcn_sched_barrier(0)      // no instruction is scheduled across this point
-
-__device__ __forceinline__ f32x16 mfma(float a, float b, f32x16 c) {
+__device__ __forceinline__ f32x16 mfma32(float a, float b, f32x16 c) {
     return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
+}
+__device__ __forceinline__ uint32_t pack_f16(float lo, float hi) {
+    const f32x2 v = {lo, hi};
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, f16x2));
+}
+// Splitting a pair: hi = fp16(x s) of both halves, lo = fp16(x s - hi), with s a power of two, so that x s and the
+// difference (one mixed-precision fused multiply-add) are exact.  (v_fma_mixlo_f16 / mixhi_f16 would round to a half
+// register directly, in fewer instructions, but take 12 and 9 cycles each, the packed conversion 8 for both halves.)
+__device__ __forceinline__ uint32_t split_hi(float x0, float x1, float s) { return pack_f16(x0 * s, x1 * s); }
+__device__ __forceinline__ uint32_t split_lo(float x0, float x1, float s, uint32_t h) {
+    float r0, r1;
+    asm("v_fma_mix_f32 %0, %1, %2, -%3 op_sel:[0,0,0] op_sel_hi:[0,0,1]" : "=v"(r0) : "v"(x0), "v"(s), "v"(h));
+    asm("v_fma_mix_f32 %0, %1, %2, -%3 op_sel:[0,0,1] op_sel_hi:[0,0,1]" : "=v"(r1) : "v"(x1), "v"(s), "v"(h));
+    return pack_f16(r0, r1);
+}
+// max(a, |b|, |c|) (as assembly: fmaxf would first canonicalise every operand that comes from memory); a NaN is passed over
+__device__ __forceinline__ float max_abs3(float a, float b, float c) {
+    float d;
+    asm volatile("v_max3_f32 %0, %1, |%2|, |%3|" : "=v"(d) : "v"(a), "v"(b), "v"(c));
+    return d;
+}
+__device__ __forceinline__ float max3(float a, float b, float c) {
+    float d;
+    asm("v_max3_f32 %0, %1, %2, %3" : "=v"(d) : "v"(a), "v"(b), "v"(c));
+    return d;
+}
+template <int CTRL>
+__device__ __forceinline__ float max_dpp(float x) {      // x >= 0 on every lane
+    const int y = __builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xf, 0xf, true);
+    return __int_as_float(max(__float_as_int(x), y));    // non-negative floats order as integers
+}
+// biased exponent of a largest element, kept where 2^(ROW_TOP - e), 2^(e - ROW_TOP) and their like are normal numbers
+__device__ __forceinline__ int top_exponent(float mx) {
+    const int e = __float_as_int(mx) >> 23;
+    return e < 24 ? 24 : e;
+}
+__device__ __forceinline__ float pow2(int biased) { return __int_as_float(biased << 23); }
+__device__ __forceinline__ u32x4 lds_read_b128(uint32_t addr) {
+    return *reinterpret_cast<__attribute__((address_space(3))) const u32x4*>((uintptr_t)addr);
+}
+__device__ __forceinline__ void lds_write_b128(uint32_t addr, u32x4 v) {
+    *reinterpret_cast<__attribute__((address_space(3))) u32x4*>((uintptr_t)addr) = v;
+}
+__device__ __forceinline__ float lds_read_f32(uint32_t addr) {
+    return *reinterpret_cast<__attribute__((address_space(3))) const float*>((uintptr_t)addr);
+}
+__device__ __forceinline__ void lds_write_f32(uint32_t addr, float v) {
+    *reinterpret_cast<__attribute__((address_space(3))) float*>((uintptr_t)addr) = v;
+}
+__device__ __forceinline__ f32x4 lds_read_f32x4(uint32_t addr) {
+    return *reinterpret_cast<__attribute__((address_space(3))) const f32x4*>((uintptr_t)addr);
+}
+__device__ __forceinline__ f32x2 lds_read_f32x2(uint32_t addr) {
+    return *reinterpret_cast<__attribute__((address_space(3))) const f32x2*>((uintptr_t)addr);
 }
 
 template <int D, int TAN>
-__global__ __launch_bounds__(NTHREADS, D <= 64 ? 2 : 1) void attn_jvp_mfma_f32_kernel(
+struct Geo {
+    static constexpr int PLANE = BC * D * 2;                    // one fp16 plane of a tensor's block
+    static constexpr int PLANES = TAN == TAN_ALL ? 4 : 2;       // X hi, X lo (, tX hi, tX lo)
+    static constexpr int STAGE = PLANES * PLANE;                // K side or V side
+    static constexpr int V_BASE = 2 * STAGE;                    // two stages of K, then two of V
+    static constexpr int F_BASE = 4 * STAGE;                    // row factors: [2 stages][K, tK][32] floats
+    static constexpr int RED_BASE = F_BASE + 2 * 2 * BC * 4;    // scratch of the workgroup's reductions and votes
+    static constexpr int DUMMY_BASE = RED_BASE + 64;
+    static constexpr int LDS_BYTES = DUMMY_BASE + 256 + 2 * 2 * BC * 4;
+    static constexpr int WG_PER_CU = TAN == TAN_NONE || (TAN == TAN_QUERY && D == 32) ? 2 : 1;     // as the registers allow
+    static constexpr int LPR = D == 96 ? 16 : D / 8;            // lanes that convert one K row, 8 elements each (D = 96: 12 of 16)
+    static constexpr int K_ROWS = NTHREADS / LPR < BC ? NTHREADS / LPR : BC;    // rows per conversion pass
+    static constexpr int K_PASSES = BC / K_ROWS;
+    static constexpr int V_PASSES = (D + 63) / 64;              // a V pass: 64 columns (lanes) x 4 groups of 8 keys (waves)
+    // chunk swizzle of a K row (16-byte chunks): the 16 lanes a 128-bit read serves together cover all banks
+    static __device__ __forceinline__ int k_swizzle(int row) {
+        return D == 128 ? (row & 15) : D == 64 ? ((row >> 1) & 7) : ((row >> 2) & 3);
+    }
+};
+
+template <int D, int TAN>
+__global__ __launch_bounds__(NTHREADS, (Geo<D, TAN>::WG_PER_CU)) void attn_jvp_mfma_f32_kernel(
     const float* __restrict__ Q, const float* __restrict__ K, const float* __restrict__ V,
     const float* __restrict__ tQ, const float* __restrict__ tK, const float* __restrict__ tV,
     float* __restrict__ O, float* __restrict__ tO, float* __restrict__ LSE,
@@ -93,300 +179,713 @@ __global__ __launch_bounds__(NTHREADS, D <= 64 ? 2 : 1) void attn_jvp_mfma_f32_k
     // No implicit fusing of a product with a following sum: the compiler would fuse differently in each instantiation,
     // and the instantiations must agree bit for bit (absent tangents against zero tangents).  fmaf() stays fused.
 #pragma clang fp contract(off)
-    constexpr int CH = D / 4;                        // 16-byte chunks per row
-    constexpr int TILE_F4 = BC * CH;                 // chunks per staged block of one tensor
-    constexpr int PT = TILE_F4 / NTHREADS;           // chunks each lane moves per tensor per block
-    constexpr int NT = TAN == TAN_ALL ? 4 : 2;       // tensors staged: K, V (+ tK, tV)
-    constexpr int NC = D / 32;                       // 32-column chunks of the accumulators
-    static_assert(D % 32 == 0 && D <= 128 && TILE_F4 % NTHREADS == 0 && 2 * PT < D / 8, "head dim");
-
-    extern __shared__ float4 smem[];                 // [2 stages][NT tensors][TILE_F4]
-    auto tile = [&](int stage, int tensor) { return smem + (stage * NT + tensor) * TILE_F4; };
-    constexpr int T_K = 0, T_V = 1, T_TK = 2, T_TV = 3;
+    using G = Geo<D, TAN>;
+    constexpr bool TANGENT = TAN != TAN_NONE, KV_TANGENT = TAN == TAN_ALL;
+    constexpr int NT = D / 16;                       // score steps
+    constexpr int NC = D / 32;                       // 32-column blocks of the accumulators
+    constexpr int NX = KV_TANGENT ? 2 : 1;           // tensors on each of the K and V sides
+    extern __shared__ __attribute__((aligned(1024))) char smem[];
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)smem;
 
     const int tid = threadIdx.x;
-    const int lane = tid & 63, wave = tid >> 6;
-    const int j = lane & 31, h = lane >> 5;
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int c = lane & 31, g = lane >> 5;
 
     // consecutive workgroups go round-robin over the 8 XCDs: give each XCD a contiguous range of tiles, so that the
     // workgroups sharing one L2 stream the same heads' keys
     const int n_wg = gridDim.x;
     const int bid = (n_wg & 7) == 0 ? (int)(blockIdx.x & 7) * (n_wg >> 3) + (int)(blockIdx.x >> 3) : (int)blockIdx.x;
     const long bh = bid / q_tiles;
-    const int qrow = (bid % q_tiles) * BR + 32 * wave + j;
+    const int qrow = (bid % q_tiles) * BR + 32 * wave + c;
+    const int qload = qrow < Lq ? qrow : Lq - 1;     // rows past the end repeat the last one and are not stored
 
     // [B,H,L,d]: rows of a head contiguous; [B,L,H,d]: rows of a head H*d elements apart
     const long row_elems = blhd ? (long)H * D : D;
     const long bidx = bh / H, hidx = bh % H;
     const long q_base = blhd ? (bidx * Lq * H + hidx) * D : bh * (long)Lq * D;
     const long kv_base = blhd ? (bidx * Lkv * H + hidx) * D : bh * (long)Lkv * D;
-
-    // ---- this lane's slices of its query row: columns 8u + 4h .. + 3 ------------------------------------------------
-    float4 q[D / 8], tq[TAN != TAN_NONE ? D / 8 : 1];
-    {
-        const bool live = qrow < Lq;                 // rows past the end load row 0, compute on zeros, store nothing
-        const float* qp = Q + q_base + (long)(live ? qrow : 0) * row_elems + 4 * h;
-        const float* tqp = TAN != TAN_NONE ? tQ + q_base + (long)(live ? qrow : 0) * row_elems + 4 * h : nullptr;
-        const float keep = live ? 1.f : 0.f;
-#pragma unroll
-        for (int u = 0; u < D / 8; ++u) {
-            q[u] = *reinterpret_cast<const float4*>(qp + 8 * u);
-            q[u].x *= keep; q[u].y *= keep; q[u].z *= keep; q[u].w *= keep;
-            if constexpr (TAN != TAN_NONE) {
-                tq[u] = *reinterpret_cast<const float4*>(tqp + 8 * u);
-                tq[u].x *= keep; tq[u].y *= keep; tq[u].z *= keep; tq[u].w *= keep;
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < D / 8; ++u) {   // keep q in the accumulation half of the register file: only MFMAs read it
-            asm volatile("" : "+a"(q[u].x), "+a"(q[u].y), "+a"(q[u].z), "+a"(q[u].w));
-        }
-    }
-
-    // ---- staging of one block of one tensor: direct-to-LDS loads, 16 bytes per lane ---------------------------------
-    // One instruction fills 1 KiB of the tile linearly in the lane id; the swizzle is applied on the global side:
-    // the lane that fills chunk position pc of row `row` fetches chunk pc ^ (row & 7) of that row.  The lane's
-    // share (positions tid, tid + 256, ...) is the same in every block, so its byte offsets from the block's first
-    // row are computed once.  Rows past the end of a ragged last block re-read the block's first row (finite
-    // values; the softmax gives them weight zero).
-    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)smem;
-    uint32_t g_off[PT];
-    int s_row[PT];
-#pragma unroll
-    for (int n = 0; n < PT; ++n) {
-        const int idx = tid + NTHREADS * n;
-        const int row = idx / CH, pc = idx % CH;
-        s_row[n] = row;
-        g_off[n] = (uint32_t)((row * row_elems + 4 * (pc ^ (row & 7))) * (long)sizeof(float));
-    }
-    // part n (of PT) of one tensor's block: one instruction per wave
-    const uint32_t wave_lds = __builtin_amdgcn_readfirstlane(lds0 + (uint32_t)(64 * wave * sizeof(float4)));
-    auto stage_part = [&](const float* base, int j0, int stage, int tensor, int n) {
-        const char* blk = reinterpret_cast<const char*>(base + kv_base + (long)j0 * row_elems);     // uniform
-        const uint32_t dst = wave_lds + (uint32_t)(((stage * NT + tensor) * TILE_F4 + NTHREADS * n) * sizeof(float4));
-        if (j0 + BC <= Lkv) {                        // uniform
-            load_lds_b128(blk, g_off[n], dst);
-        } else {
-            const bool dead = j0 + s_row[n] >= Lkv;
-            load_lds_b128(blk, dead ? g_off[n] - (uint32_t)(s_row[n] * row_elems * sizeof(float)) : g_off[n], dst);
-        }
-    };
-    auto stage_in = [&](const float* base, int j0, int stage, int tensor) {
-#pragma unroll
-        for (int n = 0; n < PT; ++n) stage_part(base, j0, stage, tensor, n);
-    };
-
-    f32x16 acc_o[NC], acc_t[TAN != TAN_NONE ? NC : 1];
-#pragma unroll
-    for (int c = 0; c < NC; ++c) {
-        acc_o[c] = f32x16{};
-        if constexpr (TAN != TAN_NONE) acc_t[c] = f32x16{};
-    }
-    float m = -INFINITY, l = 0.f, r = 0.f;       // l, r: this lane's 16 keys per block only; halves meet in the epilogue
-
+    const int row_bytes = (int)(row_elems * sizeof(float));       // (32 rows are below 2^31 bytes: checked on the host)
     const int n_blocks = (Lkv + BC - 1) / BC;
-    stage_in(K, 0, 0, T_K);
-    stage_in(V, 0, 0, T_V);
-    if constexpr (TAN == TAN_ALL) {
-        stage_in(tK, 0, 0, T_TK);
-        stage_in(tV, 0, 0, T_TV);
+
+    // ---- fetching a block into registers ----------------------------------------------------------------------------
+    // K side: lane handles 8 consecutive elements (chunk k_sub) of row k_row (+ K_ROWS per pass).  V side: lane handles
+    // one column of the 8 keys 16 (wave >> 1) + 4 (wave & 1) + {0..3, 8..11}: the keys of one 16-byte chunk.
+    // Rows past the end of a ragged last block re-read a row inside it (finite values for finite inputs; their weight
+    // is zero), blocks past the end the last block.
+    // (No branches in here: lanes without a chunk or column of their own do their neighbour's once more, to the same place.)
+    const int k_sub = tid % G::LPR < D / 8 ? tid % G::LPR : D / 8 - 1;
+    const int k_row = tid / G::LPR < BC ? tid / G::LPR : tid / G::LPR - BC;
+    const int v_key0 = 16 * (wave >> 1) + 4 * (wave & 1);
+    const uint32_t k_off0 = (uint32_t)(32 * k_sub);              // chunk inside a row
+    constexpr int LAST_COLS = D % 64 == 0 ? 64 : D % 64;         // columns of the last V pass
+    const int v_lane_last = lane < LAST_COLS ? lane : LAST_COLS - 1;
+    // byte offsets of the lane's rows from the block's first one; the same in all blocks but a ragged last one
+    uint32_t k_rows[G::K_PASSES], v_rows[8];
+    auto set_k_rows = [&](int blk) __attribute__((always_inline)) {
+        const int left = Lkv - (blk < n_blocks ? blk : n_blocks - 1) * BC;
+#pragma unroll
+        for (int p = 0; p < G::K_PASSES; ++p) k_rows[p] = (k_row + p * G::K_ROWS < left ? (uint32_t)((k_row + p * G::K_ROWS) * row_bytes) : 0u) + k_off0;
+    };
+    auto set_v_rows = [&](int blk) __attribute__((always_inline)) {
+        const int left = Lkv - (blk < n_blocks ? blk : n_blocks - 1) * BC;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const int row = v_key0 + (i & 3) + 8 * (i >> 2);
+            v_rows[i] = (uint32_t)((row < left ? row : 0) * row_bytes) + 4 * (uint32_t)lane;
+        }
+    };
+    // The conversion jobs of a block are the K passes of K (and tK), then the V passes of V (and tV).  At most RING
+    // jobs' data are in registers at a time: the end of a job requests the data of the RING-th job after it.
+    constexpr int N_KJ = NX * G::K_PASSES, N_VJ = NX * G::V_PASSES, N_JOBS = N_KJ + N_VJ;
+    constexpr int RING = N_JOBS < 4 ? N_JOBS : TAN == TAN_NONE && D >= 96 ? 2 : 4;      // (two workgroups share a unit there: fewer registers)
+    static_assert(N_JOBS % RING == 0, "a job keeps its slot from block to block");
+    float raw[RING][8];
+    auto fetch_k = [&](int blk, auto J, float (&to)[8]) __attribute__((always_inline)) {
+        constexpr int jb = decltype(J)::value, x = jb / G::K_PASSES, p = jb % G::K_PASSES;
+        const char* base = reinterpret_cast<const char*>(x ? tK : K) + kv_base * 4 + (long)((blk < n_blocks ? blk : n_blocks - 1) * BC) * row_bytes;
+        const f32x4 a = *reinterpret_cast<const f32x4*>(base + k_rows[p]), b = *reinterpret_cast<const f32x4*>(base + k_rows[p] + 16);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) { to[i] = a[i]; to[4 + i] = b[i]; }
+    };
+    auto fetch_v = [&](int blk, auto J, float (&to)[8]) __attribute__((always_inline)) {
+        constexpr int jb = decltype(J)::value, x = (jb - N_KJ) / G::V_PASSES, p = (jb - N_KJ) % G::V_PASSES;
+        const char* base = reinterpret_cast<const char*>(x ? tV : V) + kv_base * 4 + (long)((blk < n_blocks ? blk : n_blocks - 1) * BC) * row_bytes;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const uint32_t at = 64 * (p + 1) <= D ? v_rows[i] : v_rows[i] + 4 * (uint32_t)(v_lane_last - lane);
+            to[i] = *reinterpret_cast<const float*>(base + at + 256 * p);
+        }
+    };
+
+    // ---- splitting what was fetched into the LDS planes, cut into parts for the MFMA shadows ------------------------
+    const uint32_t k_write = lds0 + (uint32_t)(k_row * (2 * D) + ((k_sub ^ G::k_swizzle(k_row)) << 4));
+    const uint32_t v_write = lds0 + G::V_BASE + (uint32_t)(lane * 64 + ((wave ^ ((lane >> 2) & 3)) << 4));
+    const uint32_t v_write_last = lds0 + G::V_BASE + (uint32_t)(v_lane_last * 64 + ((wave ^ ((v_lane_last >> 2) & 3)) << 4));
+    float v_scale[NX];                                   // set from the first block
+    uint32_t cv_h[4], cv_l[4];
+    float cv_mx, cv_m2, cv_sc;
+    // row factors: written by the first lane of a row (the others write to a place nobody reads: to one address their
+    // writes would queue up)
+    const uint32_t f_write = lds0 + (tid % G::LPR == 0 ? G::F_BASE + 4 * k_row : G::DUMMY_BASE + 4 * lane);
+    // (the DPP steps of a row maximum one per part: the MFMA between two of them is the wait they need)
+    constexpr int K_PARTS = 13, V_PARTS = 5;
+    auto split_part = [&](const float (&e)[8], float s, auto PART) __attribute__((always_inline)) {      // parts 0-3
+        constexpr int part = decltype(PART)::value, i = 2 * (part >> 1);
+        if constexpr ((part & 1) == 0) { cv_h[i] = split_hi(e[2 * i], e[2 * i + 1], s); cv_h[i + 1] = split_hi(e[2 * i + 2], e[2 * i + 3], s); }
+        else { cv_l[i] = split_lo(e[2 * i], e[2 * i + 1], s, cv_h[i]); cv_l[i + 1] = split_lo(e[2 * i + 2], e[2 * i + 3], s, cv_h[i + 1]); }
+    };
+    auto k_part = [&](auto J, auto ST, auto PART, const float (&e)[8]) __attribute__((always_inline)) {
+        constexpr int jb = decltype(J)::value, x = jb / G::K_PASSES, p = jb % G::K_PASSES, st = decltype(ST)::value, part = decltype(PART)::value;
+        if constexpr (part == 0) { cv_mx = max_abs3(fabsf(e[0]), e[1], e[2]); cv_m2 = max_abs3(fabsf(e[3]), e[4], e[5]); }
+        if constexpr (part == 1) cv_mx = max_abs3(cv_mx, e[6], e[7]);
+        if constexpr (part == 2) cv_mx = max_abs3(cv_mx, cv_m2, cv_m2);
+        if constexpr (part == 3) cv_mx = max_dpp<0xB1>(cv_mx);             // lanes ^ 1, ^ 2, mirrored in 8, mirrored in 16
+        if constexpr (part == 4) cv_mx = max_dpp<0x4E>(cv_mx);
+        if constexpr (part == 5 && G::LPR >= 8) cv_mx = max_dpp<0x141>(cv_mx);
+        if constexpr (part == 6 && G::LPR >= 16) cv_mx = max_dpp<0x140>(cv_mx);
+        if constexpr (part == 7) {
+            const int ex = top_exponent(cv_mx);
+            cv_sc = pow2(254 + ROW_TOP - ex);
+            lds_write_f32(f_write + (st * 2 + x) * (BC * 4) + 4 * p * G::K_ROWS, pow2(ex - ROW_TOP));
+        }
+        if constexpr (part >= 8 && part < 12) split_part(e, cv_sc, std::integral_constant<int, part - 8>{});
+        if constexpr (part == 12) {
+            const uint32_t at = k_write + st * G::STAGE + 2 * x * G::PLANE + p * G::K_ROWS * 2 * D;
+            lds_write_b128(at, u32x4{cv_h[0], cv_h[1], cv_h[2], cv_h[3]});
+            lds_write_b128(at + G::PLANE, u32x4{cv_l[0], cv_l[1], cv_l[2], cv_l[3]});
+        }
+    };
+    auto v_part = [&](auto J, auto ST, auto PART, const float (&e)[8]) __attribute__((always_inline)) {
+        constexpr int jb = decltype(J)::value, x = (jb - N_KJ) / G::V_PASSES, p = (jb - N_KJ) % G::V_PASSES;
+        constexpr int st = decltype(ST)::value, part = decltype(PART)::value;
+        if constexpr (part < 4) split_part(e, v_scale[x], PART);
+        if constexpr (part == 4) {
+            const uint32_t at = (64 * (p + 1) <= D ? v_write : v_write_last) + st * G::STAGE + 2 * x * G::PLANE + p * 4096;
+            lds_write_b128(at, u32x4{cv_h[0], cv_h[1], cv_h[2], cv_h[3]});
+            lds_write_b128(at + G::PLANE, u32x4{cv_l[0], cv_l[1], cv_l[2], cv_l[3]});
+        }
+    };
+    // The conversion of one block as a flat list of parts.  The last part of a job requests the RING-th job after it: of
+    // the same blocks (bk on the K side, bv on the V side) or of the next.
+    constexpr int N_PARTS = N_KJ * K_PARTS + N_VJ * V_PARTS;
+    auto fetch_job = [&](auto J, int bk, int bv) __attribute__((always_inline)) {
+        constexpr int j = decltype(J)::value;
+        if constexpr (j < N_KJ) fetch_k(bk, J, raw[j % RING]);
+        else fetch_v(bv, J, raw[j % RING]);
+    };
+    // block whose V an iteration requests, from the one it converts: its own if the ring is shorter than the list
+    constexpr int V_AHEAD = N_JOBS > RING ? 0 : 1;
+    auto fetch_ahead = [&](auto J, int bk, int bv) __attribute__((always_inline)) {
+        constexpr int j = decltype(J)::value + RING;
+        if constexpr (j < N_JOBS) fetch_job(std::integral_constant<int, j>{}, bk, bv);
+        else fetch_job(std::integral_constant<int, j - N_JOBS>{}, bk + 1, bv + 1);
+    };
+    auto convert_part = [&](auto IDX, auto KST, auto VST, int bk, int bv) __attribute__((always_inline)) {
+        constexpr int idx = decltype(IDX)::value;
+        if constexpr (idx < N_KJ * K_PARTS) {
+            using J = std::integral_constant<int, idx / K_PARTS>;
+            k_part(J{}, KST, std::integral_constant<int, idx % K_PARTS>{}, raw[J::value % RING]);
+            if constexpr (idx % K_PARTS == K_PARTS - 1) fetch_ahead(J{}, bk, bv);
+        } else {
+            constexpr int r = idx - N_KJ * K_PARTS;
+            using J = std::integral_constant<int, N_KJ + r / V_PARTS>;
+            v_part(J{}, VST, std::integral_constant<int, r % V_PARTS>{}, raw[J::value % RING]);
+            if constexpr (r % V_PARTS == V_PARTS - 1) fetch_ahead(J{}, bk, bv);
+        }
+    };
+    using I0 = std::integral_constant<int, 0>;
+    using I1 = std::integral_constant<int, 1>;
+
+    // ---- this lane's query row, columns 16 t + 8 g .. + 7, split; a negative scale goes into the signs --------------
+    const float sgn = scale < 0.f ? -1.f : 1.f;
+    const float abs_scale = fabsf(scale);
+    u32x4 qh[NT], ql[NT], tqh[TANGENT ? NT : 1], tql[TANGENT ? NT : 1];
+    float fq = 1.f, ftq = 1.f;                       // what the scaled rows have to be multiplied by
+    static_assert(RING >= N_KJ && RING >= N_VJ, "the jobs of either side fit the ring");
+    set_k_rows(0);
+    set_v_rows(0);
+    // everything the prologue needs is requested at once: K(0), this lane's query row (below), V(0), K(1)
+    float k0[N_KJ][8], k1[N_KJ][8], v0[N_VJ][8];
+    static_for<N_KJ>([&](auto J) { fetch_k(0, J, k0[decltype(J)::value]); });
+    float4 qraw[NT][2], tqraw[TANGENT ? NT : 1][2];
+    auto fetch_query = [&](const float* X, float4 (*a)[2]) __attribute__((always_inline)) {
+        const float* p = X + q_base + (long)qload * row_elems + 8 * g;
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+            a[t][0] = *reinterpret_cast<const float4*>(p + 16 * t);
+            a[t][1] = *reinterpret_cast<const float4*>(p + 16 * t + 4);
+        }
+    };
+    fetch_query(Q, qraw);
+    if constexpr (TANGENT) fetch_query(tQ, tqraw);
+    static_for<N_VJ>([&](auto J) { fetch_v(0, std::integral_constant<int, N_KJ + decltype(J)::value>{}, v0[decltype(J)::value]); });
+    set_k_rows(1);
+    static_for<N_KJ>([&](auto J) { fetch_k(1, J, k1[decltype(J)::value]); });
+    FENCE();
+    auto split_query = [&](const float4 (*a)[2], u32x4* hi, u32x4* lo, float& f) __attribute__((always_inline)) {
+        float mx = 0.f;
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+#pragma unroll
+            for (int u = 0; u < 2; ++u) mx = max_abs3(max_abs3(mx, a[t][u].x, a[t][u].y), a[t][u].z, a[t][u].w);
+        mx = xhalf_max(mx);
+        const int ex = top_exponent(mx);
+        const float s = sgn * pow2(254 + ROW_TOP - ex);
+        f = pow2(ex - ROW_TOP);
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+            const float e[8] = {a[t][0].x, a[t][0].y, a[t][0].z, a[t][0].w, a[t][1].x, a[t][1].y, a[t][1].z, a[t][1].w};
+            static_for<4>([&](auto PART) { split_part(e, s, PART); });
+            hi[t] = u32x4{cv_h[0], cv_h[1], cv_h[2], cv_h[3]};
+            lo[t] = u32x4{cv_l[0], cv_l[1], cv_l[2], cv_l[3]};
+            asm volatile("" : "+a"(hi[t]), "+a"(lo[t]));      // only MFMAs read them: keep them in accumulation registers
+        }
+        FENCE();
+    };
+    split_query(qraw, qh, ql, fq);
+    if constexpr (TANGENT) split_query(tqraw, tqh, tql, ftq);
+    // per-lane factor of the scores (after the key's own); not zero, so that masked scores stay -inf
+    const float sq = fmaxf(abs_scale, 1e-37f) * fq;
+
+    // ---- scores ----------------------------------------------------------------------------------------------------
+    uint32_t kaddr[NT];
+#pragma unroll
+    for (int t = 0; t < NT; ++t) kaddr[t] = lds0 + c * (2 * D) + (((2 * t + g) ^ G::k_swizzle(c)) << 4);
+    uint32_t vaddr[2];
+#pragma unroll
+    for (int t2 = 0; t2 < 2; ++t2) vaddr[t2] = lds0 + G::V_BASE + c * 64 + (((2 * t2 + g) ^ ((c >> 2) & 3)) << 4);
+    const uint32_t faddr = lds0 + G::F_BASE + 16 * g;         // register e holds key 8 (e / 4) + 4 g + e % 4
+
+    f32x16 s, ts1, ts2;      // K Q^T, K tQ^T, tK Q^T of the block under way (scaled; see `prepare` for the factors)
+    // one score step: 3, 6 or 9 products; small terms first.  `behind(k)` is issued behind product number k of the block.
+    constexpr int NS = KV_TANGENT ? 9 : TANGENT ? 6 : 3;
+    constexpr int M1 = NT * NS;
+    // Fragments X, tX: the high planes of the current and the next step, the low planes of the current one, which are
+    // used by the first third of a step's products and then make room for the next step's
+    u32x4 fh[2][NX], fl[NX];
+    auto read_k = [&](auto T, auto ST, auto LO) __attribute__((always_inline)) {
+        constexpr int t = decltype(T)::value, st = decltype(ST)::value;
+#pragma unroll
+        for (int x = 0; x < NX; ++x) {
+            const uint32_t at = kaddr[t] + st * G::STAGE + 2 * x * G::PLANE;
+            if constexpr (decltype(LO)::value) fl[x] = lds_read_b128(at + G::PLANE);
+            else fh[t & 1][x] = lds_read_b128(at);
+        }
+    };
+    auto scores = [&](auto ST, auto&& behind, auto&& first_values) __attribute__((always_inline)) {
+        read_k(I0{}, ST, I1{});
+        read_k(I0{}, ST, I0{});
+        static_for<NT>([&](auto T) {
+            constexpr int t = decltype(T)::value;
+            using Tn = std::integral_constant<int, t + 1 < NT ? t + 1 : t>;
+            if constexpr (t + 1 < NT) read_k(Tn{}, ST, I0{});
+            else first_values(I0{});      // (the value products' first fragments, into the registers that are free)
+            static_for<3>([&](auto W) {                      // lo hi, hi lo, hi hi
+                constexpr int w = decltype(W)::value;
+                constexpr int k0 = t * NS + w * (NS / 3);
+                const u32x4 kh = fh[t & 1][0], kl = fl[0];
+                if constexpr (w == 1 && t + 1 < NT) read_k(Tn{}, ST, I1{});
+                if constexpr (w == 1 && t + 1 == NT) first_values(I1{});
+                FENCE();
+                if constexpr (t == 0 && w == 0) SMFMA0(kl, qh[t], s);
+                else if constexpr (w == 0) SMFMA(kl, qh[t], s);
+                else if constexpr (w == 1) SMFMA(kh, ql[t], s);
+                else SMFMA(kh, qh[t], s);
+                behind(std::integral_constant<int, k0>{});
+                if constexpr (TANGENT) {
+                    FENCE();
+                    if constexpr (t == 0 && w == 0) SMFMA0(kl, tqh[t], ts1);
+                    else if constexpr (w == 0) SMFMA(kl, tqh[t], ts1);
+                    else if constexpr (w == 1) SMFMA(kh, tql[t], ts1);
+                    else SMFMA(kh, tqh[t], ts1);
+                    behind(std::integral_constant<int, k0 + 1>{});
+                }
+                if constexpr (KV_TANGENT) {
+                    const u32x4 tkh = fh[t & 1][NX - 1], tkl = fl[NX - 1];
+                    FENCE();
+                    if constexpr (t == 0 && w == 0) SMFMA0(tkl, qh[t], ts2);
+                    else if constexpr (w == 0) SMFMA(tkl, qh[t], ts2);
+                    else if constexpr (w == 1) SMFMA(tkh, ql[t], ts2);
+                    else SMFMA(tkh, qh[t], ts2);
+                    behind(std::integral_constant<int, k0 + 2>{});
+                }
+                FENCE();
+            });
+        });
+        SCORE_RESULTS_LAND();
+        FENCE();
+        asm volatile("" : "+v"(s));
+        if constexpr (TANGENT) asm volatile("" : "+v"(ts1));
+        if constexpr (KV_TANGENT) asm volatile("" : "+v"(ts2));
+        FENCE();
+    };
+
+    // ---- softmax of one block: prepare (key factors, row maximum, reference), then the weights pair by pair ----------
+    float m = -INFINITY;                             // row reference in nats: P~ = exp(S - m)
+    float l = 0.f, r = 0.f;      // this lane's 16 keys per block only; halves meet in the epilogue
+    float fqh = 0.f, ftqh = 0.f;                     // per-lane factors of the tangent scores, with 2^-eH
+    float go = 1.f, gt = 1.f, gr = 1.f / P_GAIN;                        // factors of the accumulators
+    float alpha = 1.f;
+    bool moved = false;
+    f32x16 acc_o[NC], acc_t[TANGENT ? NC : 1];
+#pragma unroll
+    for (int n = 0; n < NC; ++n) {
+        acc_o[n] = f32x16{};
+        if constexpr (TANGENT) acc_t[n] = f32x16{};
     }
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __syncthreads();
-
-    for (int blk = 0; blk < n_blocks; ++blk) {
-        const int cur = blk & 1, nxt = cur ^ 1;
-        const int j0 = blk * BC;
-        const bool has_next = blk + 1 < n_blocks;       // workgroup-uniform
-
-        // ---- phase 1: S^T = K Q^T, tS^T = K tQ^T + tK Q^T; next block's K, tK travel meanwhile ---------------------
-        // Three independent accumulation chains (S, K tQ^T, tK Q^T), issued round-robin so that no MFMA waits for the
-        // one before it; the operands of step u + 1 are read from LDS while the 12 MFMAs of step u run (the fences
-        // keep the compiler from sinking the reads down to their first use).
-        // (up to d = 64 two workgroups share a CU and each wave has 256 registers: there tS is one chain, and the
-        // other workgroup's waves fill the gaps)
-        constexpr bool THREE_CHAINS = D > 64;
-        f32x16 s = f32x16{}, ts = f32x16{}, ts2 = f32x16{};
-        {
-            // chunk (2u + h) ^ (j & 7) = 8 (u/4) + ((2 (u%4) + h) ^ (j & 7)): four lane-dependent addresses, the rest
-            // is an immediate offset
-            const float4* lk[4];
+    // (no instruction: keeps the accumulators in the accumulation registers across the score products, whose operands and
+    // results need the arithmetic ones)
+    auto pin_accumulators = [&]() __attribute__((always_inline)) {
 #pragma unroll
-            for (int w = 0; w < 4; ++w) lk[w] = tile(cur, T_K) + j * CH + ((2 * w + h) ^ (j & 7));
-            constexpr int TK_OFF = (T_TK - T_K) * TILE_F4;
-            float4 ka[2], tka[2];
-            ka[0] = lk[0][0];
-            if constexpr (TAN == TAN_ALL) tka[0] = lk[0][TK_OFF];
-#pragma unroll
-            for (int u = 0; u < D / 8; ++u) {
-                if (u + 1 < D / 8) {
-                    ka[(u + 1) & 1] = lk[(u + 1) & 3][8 * ((u + 1) >> 2)];
-                    if constexpr (TAN == TAN_ALL) tka[(u + 1) & 1] = lk[(u + 1) & 3][8 * ((u + 1) >> 2) + TK_OFF];
-                }
-                // the next block's K, tK: one 1-KiB part per wave and step, from the second step on, so that a load
-                // that has to queue for the memory pipe waits behind 12 MFMAs, not in front of them
-                if (has_next) {
-                    if (u >= 1 && u <= PT) stage_part(K, j0 + BC, nxt, T_K, u - 1);
-                    if constexpr (TAN == TAN_ALL)
-                        if (u > PT && u <= 2 * PT) stage_part(tK, j0 + BC, nxt, T_TK, u - PT - 1);
-                }
-                FENCE();
-                const float kv[4] = {ka[u & 1].x, ka[u & 1].y, ka[u & 1].z, ka[u & 1].w};
-                const float qv[4] = {q[u].x, q[u].y, q[u].z, q[u].w};
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    s = mfma(kv[e], qv[e], s);
-                    if constexpr (TAN != TAN_NONE) {
-                        const float tqv[4] = {tq[u].x, tq[u].y, tq[u].z, tq[u].w};
-                        ts = mfma(kv[e], tqv[e], ts);
-                    }
-                    if constexpr (TAN == TAN_ALL) {
-                        const float tkv[4] = {tka[u & 1].x, tka[u & 1].y, tka[u & 1].z, tka[u & 1].w};
-                        if constexpr (THREE_CHAINS) ts2 = mfma(tkv[e], qv[e], ts2);
-                        else ts = mfma(tkv[e], qv[e], ts);
-                    }
-                }
-                FENCE();
-            }
-            // the vector ALU reads the scores next: have the MFMAs deliver them in arithmetic registers (left alone, the
-            // compiler puts them in accumulation registers and copies all 48 out, one instruction each)
-            asm volatile("" : "+v"(s));
-            if constexpr (TAN != TAN_NONE) asm volatile("" : "+v"(ts));
-            if constexpr (TAN == TAN_ALL && THREE_CHAINS) {
-                asm volatile("" : "+v"(ts2));
-                ts += ts2;
-            }
+        for (int n = 0; n < NC; ++n) {
+            asm volatile("" : "+a"(acc_o[n]));
+            if constexpr (TANGENT) asm volatile("" : "+a"(acc_t[n]));
         }
-        // ---- online softmax of Alg. 2 on this lane's 16 keys: register e holds key j0 + 8(e/4) + 4h + e%4 -----------
-        // The running maximum m is a reference, not a result: it is taken over the rounded products S scale, and the
-        // exponent S scale - m is then formed by ONE fused multiply-add from the unrounded S, so that its rounding
-        // error is relative to the small difference, not to the size of the scores.
-        const bool ragged = j0 + BC > Lkv;              // last block: keys past the end weigh nothing
-        float mb = -INFINITY;
+    };
+    // key factors by quarters of the block (registers 4 q .. + 3), requested three quarters ahead of their use
+    f32x4 kf[3];
+    auto read_factors = [&](auto Qi, auto ST) __attribute__((always_inline)) {
+        constexpr int qi = decltype(Qi)::value;
+        if constexpr (qi < 4) kf[qi % 3] = lds_read_f32x4(faddr + decltype(ST)::value * (2 * BC * 4) + 32 * qi);
+    };
+    auto key_factors = [&](auto E2, auto ST) __attribute__((always_inline)) {     // registers 2 E2, 2 E2 + 1
+        constexpr int e0 = 2 * decltype(E2)::value, qi = e0 / 4;
 #pragma unroll
-        for (int e = 0; e < 16; ++e) {
-            const bool dead = ragged && j0 + 8 * (e / 4) + 4 * h + (e % 4) >= Lkv;     // (their tS is 0: K, tK rows are 0)
-            mb = fmaxf(mb, dead ? -INFINITY : s[e] * scale);
+        for (int i = 0; i < 2; ++i) {
+            s[e0 + i] *= kf[qi % 3][e0 % 4 + i];
+            if constexpr (TANGENT) ts1[e0 + i] *= kf[qi % 3][e0 % 4 + i];
         }
-        mb = xhalf_max(mb);                             // a block always holds a valid key: mb is finite
-        // m follows the row maximum with a slack: it moves only when a block's maximum exceeds it by more than
-        // MAX_SLACK nats, so that the rescaling of the accumulators (Alg. 2's alpha) is rare after the first block
-        // instead of happening whenever any of a wave's 32 rows meets a new maximum.  Any reference gives the same
-        // result; with fp32 weights up to e^MAX_SLACK nothing is lost (l and the accumulators stay below
-        // Lkv e^MAX_SLACK max|V|, far inside the fp32 range; weights below e^-87 of the reference, i.e. below
-        // e^-87 of the true maximum or less, flush to zero as they would anyway).
-        const float m_new = mb > m + MAX_SLACK ? mb : m;
-        const float alpha = __builtin_amdgcn_exp2f((m - m_new) * LOG2E);    // 0 on the first block (m = -inf), else 1 or tiny
-        m = m_new;
-        if (__builtin_expect(__any(alpha != 1.f), 0)) {
+        if constexpr (e0 % 4 == 2) read_factors(std::integral_constant<int, qi + 3>{}, ST);
+    };
+    auto mask_tail = [&](int blk) __attribute__((always_inline)) {         // keys past the end weigh nothing
+        const int jb = blk * BC + 4 * g;
+#pragma unroll
+        for (int e = 0; e < 16; ++e)
+            if (jb + 8 * (e / 4) + (e % 4) >= Lkv) {
+                s[e] = -INFINITY;
+                if constexpr (TANGENT) ts1[e] = 0.f;
+                if constexpr (KV_TANGENT) ts2[e] = 0.f;
+            }
+    };
+    auto row_max = [&]() __attribute__((always_inline)) -> float {
+        const float a = max3(max3(s[0], s[1], s[2]), max3(s[3], s[4], s[5]), max3(s[6], s[7], s[8]));
+        const float b = max3(max3(s[9], s[10], s[11]), max3(s[12], s[13], s[14]), s[15]);
+        return xhalf_max(fmaxf(a, b));
+    };
+    auto follow_max = [&](float mx) __attribute__((always_inline)) {       // Alg. 2's rescale, when a row needs it
+        const float mb = mx * sq;
+        const bool up = mb > m + P_SLACK;
+        if (__builtin_expect(__builtin_amdgcn_ballot_w64(up) != 0, 0)) {
+            const float m_new = up ? mb : m;
+            alpha = __builtin_amdgcn_exp2f((m - m_new) * LOG2E);
+            m = m_new;
+            l *= alpha; r *= alpha;
+            moved = true;
+        }
+    };
+    auto rescale = [&]() __attribute__((always_inline)) {
+        if (__builtin_expect(moved, 0)) {
             // (the empty statements tie the accumulators to the accumulation registers on entry and exit, so that the
             // copies to and from arithmetic registers stay inside this block)
 #pragma unroll
-            for (int c = 0; c < NC; ++c) {
-                asm volatile("" : "+a"(acc_o[c]));
-                acc_o[c] *= alpha;
-                asm volatile("" : "+a"(acc_o[c]));
-                if constexpr (TAN != TAN_NONE) {
-                    asm volatile("" : "+a"(acc_t[c]));
-                    acc_t[c] *= alpha;
-                    asm volatile("" : "+a"(acc_t[c]));
+            for (int n = 0; n < NC; ++n) {
+                asm volatile("" : "+a"(acc_o[n]));
+                acc_o[n] *= alpha;
+                asm volatile("" : "+a"(acc_o[n]));
+                if constexpr (TANGENT) {
+                    asm volatile("" : "+a"(acc_t[n]));
+                    acc_t[n] *= alpha;
+                    asm volatile("" : "+a"(acc_t[n]));
                 }
+            }
+            moved = false;
+        }
+    };
+    uint32_t ph[8], pl[8], hh[TANGENT ? 8 : 1], hl[TANGENT ? 8 : 1];        // split weights of the block under way ...
+    uint32_t nph[4], npl[4], nhh[4], nhl[4];         // ... and of the next: its pairs 4-7, while this block's are still needed
+    float p0, p1, h0, h1, u0, u1, x0, x1;
+    float lb = 0.f, rb = 0.f;                        // sums over the block, added to l, r at its end
+    constexpr int W_PARTS = TANGENT ? 8 : 4;
+    auto weight_part = [&](auto J, auto ST, auto PART) __attribute__((always_inline)) {      // registers 2 J, 2 J + 1
+        constexpr int j = decltype(J)::value, e = 2 * j, part = decltype(PART)::value;
+        constexpr bool waits = j >= 4;
+        uint32_t &wph = waits ? nph[j & 3] : ph[j], &wpl = waits ? npl[j & 3] : pl[j];
+        uint32_t &whh = waits ? nhh[j & 3] : hh[TANGENT ? j : 0], &whl = waits ? nhl[j & 3] : hl[TANGENT ? j : 0];
+        const float one = 1.f, gain = P_GAIN;
+        if constexpr (part == 0) {
+            x0 = fmaf(s[e], sq, -m) * LOG2E; x1 = fmaf(s[e + 1], sq, -m) * LOG2E;
+            if constexpr (KV_TANGENT) {                      // (used by part 4)
+                const f32x2 f = lds_read_f32x2(faddr + decltype(ST)::value * (2 * BC * 4) + BC * 4 + 32 * (e / 4) + 4 * (e % 4));
+                u0 = f[0]; u1 = f[1];
             }
         }
-        // weights of key step e: P~ = exp(S scale - m), H~ = P~ o tS; computed one step ahead of the value products
-        // that consume them, in the shadow of the previous step's MFMAs
-        float p[16], hh[16];
-        float row_p = 0.f, row_h = 0.f;
-        auto weigh = [&](auto e_tag) {
-            constexpr int e = decltype(e_tag)::value;
-            const bool dead = ragged && j0 + 8 * (e / 4) + 4 * h + (e % 4) >= Lkv;
-            p[e] = dead ? 0.f : __builtin_amdgcn_exp2f(fmaf(s[e], scale, -m_new) * LOG2E);
-            row_p += p[e];
-            if constexpr (TAN != TAN_NONE) {
-                hh[e] = p[e] * (ts[e] * scale);
-                row_h += hh[e];
+        if constexpr (part == 1) { p0 = __builtin_amdgcn_exp2f(x0); p1 = __builtin_amdgcn_exp2f(x1); }
+        if constexpr (part == 2) {
+            lb = j == 4 ? p0 + p1 : lb + (p0 + p1);
+            if (j == 3) l += lb;
+            wph = split_hi(p0, p1, gain);
+        }
+        if constexpr (part == 3) wpl = split_lo(p0, p1, gain, wph);
+        if constexpr (TANGENT) {
+            if constexpr (part == 4) {
+                if constexpr (KV_TANGENT) { u0 = (ts2[e] * u0) * fqh; u1 = (ts2[e + 1] * u1) * fqh; }
             }
-        };
+            if constexpr (part == 5) {
+                if constexpr (KV_TANGENT) { u0 = fmaf(ts1[e], ftqh, u0); u1 = fmaf(ts1[e + 1], ftqh, u1); }
+                else { u0 = ts1[e] * ftqh; u1 = ts1[e + 1] * ftqh; }
+                h0 = p0 * u0; h1 = p1 * u1;
+            }
+            if constexpr (part == 6) {
+                rb = j == 4 ? h0 + h1 : rb + (h0 + h1);
+                if (j == 3) r += rb;
+                whh = pack_f16(h0, h1);
+            }
+            if constexpr (part == 7) whl = split_lo(h0, h1, one, whh);
+        }
+    };
+    auto next_weights = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            ph[4 + i] = nph[i]; pl[4 + i] = npl[i];
+            if constexpr (TANGENT) { hh[4 + i] = nhh[i]; hl[4 + i] = nhl[i]; }
+        }
+    };
+    // the softmax of a block as a flat list: key factors by pairs, the row maximum, pairs 4-7, then pairs 0-3 (whose
+    // registers the first half of the value products has read by the time the list gets there: see the assertion below)
+    constexpr int S_PRE = 10, S_PARTS = S_PRE + 8 * W_PARTS;
+    float mx_row;
+    auto softmax_part = [&](auto IDX, auto ST, int blk) __attribute__((always_inline)) {
+        constexpr int idx = decltype(IDX)::value;
+        if constexpr (idx < 8) key_factors(IDX, ST);
+        else if constexpr (idx == 8) {
+            if ((blk + 1) * BC > Lkv) mask_tail(blk);
+            mx_row = row_max();
+        } else if constexpr (idx == 9) follow_max(mx_row);
+        else weight_part(std::integral_constant<int, ((idx - S_PRE) / W_PARTS + 4) & 7>{}, ST, std::integral_constant<int, (idx - S_PRE) % W_PARTS>{});
+    };
 
-        // ---- phase 2: O^T += V^T P~^T, (A+B)^T += V^T H~^T + tV^T P~^T ---------------------------------------------
-        {
-            // key row 8 (t/4) + 4h + t%4, float column 32c + j at chunk ^ (row & 7): four lane-dependent addresses
-            // (one per t%4), the rest is an immediate offset
-            const float* lv[4];
+    // ---- value products of a block, small terms first ----------------------------------------------------------------
+    constexpr int M2 = 2 * NC * NS;
+    auto read_v = [&](auto Gi, auto ST, auto LO) __attribute__((always_inline)) {
+        constexpr int gi = decltype(Gi)::value, t2 = gi / NC, n = gi % NC, st = decltype(ST)::value;
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
-                lv[i] = reinterpret_cast<const float*>(tile(cur, T_V)) + (4 * h + i) * D + ((((j >> 2) ^ (4 * h + i)) << 2) | (j & 3));
-            constexpr int TV_OFF = (T_TV - T_V) * TILE_F4 * 4;
-            // per key step t: 4 (8) operands, read one step ahead; the 4, 8 or 12 MFMAs of a step go round the column
-            // chunks, so consecutive ones never share an accumulator
-            float va[2][NC], tva[2][NC];
-#pragma unroll
-            for (int c = 0; c < NC; ++c) {
-                va[0][c] = lv[0][32 * c];
-                if constexpr (TAN == TAN_ALL) tva[0][c] = lv[0][32 * c + TV_OFF];
+        for (int x = 0; x < NX; ++x) {
+            const uint32_t at = vaddr[t2] + st * G::STAGE + 2 * x * G::PLANE + n * 2048;
+            if constexpr (decltype(LO)::value) fl[x] = lds_read_b128(at + G::PLANE);
+            else fh[gi & 1][x] = lds_read_b128(at);
+        }
+    };
+    auto values = [&](auto ST, auto&& behind) __attribute__((always_inline)) {
+        static_for<2 * NC>([&](auto Gi) {
+            constexpr int gi = decltype(Gi)::value, t2 = gi / NC, n = gi % NC;
+            using Gn = std::integral_constant<int, gi + 1 < 2 * NC ? gi + 1 : gi>;
+            if constexpr (gi + 1 < 2 * NC) read_v(Gn{}, ST, I0{});
+            const u32x4 wph = {ph[4 * t2], ph[4 * t2 + 1], ph[4 * t2 + 2], ph[4 * t2 + 3]};
+            const u32x4 wpl = {pl[4 * t2], pl[4 * t2 + 1], pl[4 * t2 + 2], pl[4 * t2 + 3]};
+            u32x4 whh = wph, whl = wpl;
+            if constexpr (TANGENT) {
+                whh = u32x4{hh[4 * t2], hh[4 * t2 + 1], hh[4 * t2 + 2], hh[4 * t2 + 3]};
+                whl = u32x4{hl[4 * t2], hl[4 * t2 + 1], hl[4 * t2 + 2], hl[4 * t2 + 3]};
             }
-            weigh(std::integral_constant<int, 0>{});
-            static_for<16>([&](auto t_tag) {
-                constexpr int t = decltype(t_tag)::value;
-                if constexpr (t + 1 < 16) {
-#pragma unroll
-                    for (int c = 0; c < NC; ++c) {
-                        constexpr int row_off = 8 * ((t + 1) >> 2) * D;
-                        va[(t + 1) & 1][c] = lv[(t + 1) & 3][row_off + 32 * c];
-                        if constexpr (TAN == TAN_ALL) tva[(t + 1) & 1][c] = lv[(t + 1) & 3][row_off + 32 * c + TV_OFF];
-                    }
-                }
-                if (has_next) {                      // next block's V, tV: as for K, tK above
-                    if (t >= 1 && t <= PT) stage_part(V, j0 + BC, nxt, T_V, t - 1);
-                    if constexpr (TAN == TAN_ALL)
-                        if (t > PT && t <= 2 * PT) stage_part(tV, j0 + BC, nxt, T_TV, t - PT - 1);
-                }
+            static_for<3>([&](auto W) {                      // lo hi, hi lo, hi hi
+                constexpr int w = decltype(W)::value;
+                constexpr int k0 = gi * NS + w * (NS / 3);
+                const u32x4 vh = fh[gi & 1][0], vl = fl[0];
+                if constexpr (w == 1 && gi + 1 < 2 * NC) read_v(Gn{}, ST, I1{});
                 FENCE();
-#pragma unroll
-                for (int c = 0; c < NC; ++c) acc_o[c] = mfma(va[t & 1][c], p[t], acc_o[c]);
-                if constexpr (TAN != TAN_NONE) {
-#pragma unroll
-                    for (int c = 0; c < NC; ++c) acc_t[c] = mfma(va[t & 1][c], hh[t], acc_t[c]);
+                acc_o[n] = mfma16(w == 0 ? vl : vh, w == 1 ? wpl : wph, acc_o[n]);
+                behind(std::integral_constant<int, k0>{});
+                if constexpr (TANGENT) {
+                    FENCE();
+                    acc_t[n] = mfma16(w == 0 ? vl : vh, w == 1 ? whl : whh, acc_t[n]);
+                    behind(std::integral_constant<int, k0 + 1>{});
                 }
-                if constexpr (TAN == TAN_ALL) {
-#pragma unroll
-                    for (int c = 0; c < NC; ++c) acc_t[c] = mfma(tva[t & 1][c], p[t], acc_t[c]);
+                if constexpr (KV_TANGENT) {
+                    const u32x4 tvh = fh[gi & 1][NX - 1], tvl = fl[NX - 1];
+                    FENCE();
+                    acc_t[n] = mfma16(w == 0 ? tvl : tvh, w == 1 ? wpl : wph, acc_t[n]);
+                    behind(std::integral_constant<int, k0 + 2>{});
                 }
-                if constexpr (t + 1 < 16) weigh(std::integral_constant<int, t + 1>{});
                 FENCE();
             });
-        }
-        l = fmaf(alpha, l, row_p);
-        r = fmaf(alpha, r, row_h);
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");    // this wave's share of the next stage has landed
-        __syncthreads();    // next stage written by all, this stage read by all
-    }
+        });
+    };
 
-    // ---- epilogue (Alg. 2, last lines): accumulator register 4g + i of chunk c is column 32c + 8g + 4h + i -----------
-    const float l_row = xhalf_sum(l);
-    const float r_row = xhalf_sum(r);
-    if (qrow < Lq) {
-        const float inv_l = 1.f / l_row;
-        const float mu = r_row * inv_l;              // rowsum(P o tS)
-        float* op = O + q_base + (long)qrow * row_elems + 4 * h;
-        float* top = TAN != TAN_NONE ? tO + q_base + (long)qrow * row_elems + 4 * h : nullptr;
+    // ---- prologue: K(0), K(1), V(0) split, weights of block 0 --------------------------------------------------------
+    auto nothing = [](auto) __attribute__((always_inline)) {};
+    static_for<N_KJ * K_PARTS>([&](auto IDX) {
+        constexpr int j = decltype(IDX)::value / K_PARTS;
+        k_part(std::integral_constant<int, j>{}, I0{}, std::integral_constant<int, decltype(IDX)::value % K_PARTS>{}, k0[j]);
+    });
+    {
+        float vm[2] = {0.f, 0.f};
+        static_for<N_VJ>([&](auto J) {                   // largest |V|, |tV| of block 0
+            constexpr int j = decltype(J)::value, x = j / G::V_PASSES;
 #pragma unroll
-        for (int c = 0; c < NC; ++c) {
+            for (int i = 0; i < 8; i += 2) vm[x] = max_abs3(vm[x], v0[j][i], v0[j][i + 1]);
+        });
+        __syncthreads();                                 // K(0) and its row factors are in
+        scores(I0{}, nothing, nothing);
+        static_for<3>([&](auto Qi) { read_factors(Qi, I0{}); });
+        static_for<8>([&](auto E2) { key_factors(E2, I0{}); });
+        if (BC > Lkv) mask_tail(0);
+        m = row_max() * sq;
+        float t0 = 0.f;                                  // largest tangent score of the block, unscaled
+        if constexpr (TANGENT) {
 #pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                float4 o4, t4;
-                o4.x = acc_o[c][4 * g + 0]; o4.y = acc_o[c][4 * g + 1];
-                o4.z = acc_o[c][4 * g + 2]; o4.w = acc_o[c][4 * g + 3];
-                if constexpr (TAN != TAN_NONE) {
-                    t4.x = fmaf(-mu, o4.x, acc_t[c][4 * g + 0]) * inv_l; t4.y = fmaf(-mu, o4.y, acc_t[c][4 * g + 1]) * inv_l;
-                    t4.z = fmaf(-mu, o4.z, acc_t[c][4 * g + 2]) * inv_l; t4.w = fmaf(-mu, o4.w, acc_t[c][4 * g + 3]) * inv_l;
-                    *reinterpret_cast<float4*>(top + 32 * c + 8 * g) = t4;
-                }
-                o4.x *= inv_l; o4.y *= inv_l; o4.z *= inv_l; o4.w *= inv_l;
-                *reinterpret_cast<float4*>(op + 32 * c + 8 * g) = o4;
+            for (int e = 0; e < 16; ++e) {
+                float u = ts1[e] * (abs_scale * ftq);
+                if constexpr (KV_TANGENT) u = fmaf(ts2[e] * lds_read_f32(faddr + BC * 4 + 32 * (e / 4) + 4 * (e % 4)), abs_scale * fq, u);
+                t0 = max_abs3(t0, u, u);
             }
         }
-        if (h == 0) LSE[bh * Lq + qrow] = fmaf(__builtin_amdgcn_logf(l_row), LN2, m);     // v_log_f32 is a binary log
+        // largest of the workgroup; and the word of the vote at the end is cleared
+        lds_write_f32(lds0 + G::RED_BASE + 48, 0.f);
+        float red[3] = {vm[0], vm[1], t0};
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+#pragma unroll
+            for (int o = 1; o < 64; o <<= 1) red[i] = fmaxf(red[i], __shfl_xor(red[i], o));
+            lds_write_f32(lds0 + G::RED_BASE + 4 * (4 * i + wave), red[i]);
+        }
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+            const f32x4 w = lds_read_f32x4(lds0 + G::RED_BASE + 16 * i);
+            red[i] = fmaxf(fmaxf(w[0], w[1]), fmaxf(w[2], w[3]));
+        }
+        // exponents; tV is scaled with V's factor times 2^-eH
+        const int eV = top_exponent(red[0]) - 127 - V_TOP;
+        int eH = 0;
+        if constexpr (TANGENT) {
+            eH = top_exponent(red[2]) - 127 + T_HEADROOM;
+            const int rho = top_exponent(red[1]) - top_exponent(red[0]);
+            eH = rho > eH ? rho : eH;
+            const int lo = -100 - eV > -100 ? -100 - eV : -100, hi = 100 - eV < 100 ? 100 - eV : 100;
+            eH = eH < lo ? lo : eH > hi ? hi : eH;           // every factor stays a normal number
+        }
+        go = ldexpf(1.f, eV - 12);
+        gt = ldexpf(1.f, eV + eH - 12);
+        v_scale[0] = ldexpf(1.f, -eV);
+        if constexpr (KV_TANGENT) v_scale[1] = ldexpf(1.f, -(eV + eH));
+        ftqh = ldexpf(abs_scale * ftq, 12 - eH);
+        fqh = ldexpf(abs_scale * fq, 12 - eH);
+        static_for<8 * W_PARTS>([&](auto IDX) {
+            weight_part(std::integral_constant<int, (decltype(IDX)::value / W_PARTS + 4) & 7>{}, I0{}, std::integral_constant<int, decltype(IDX)::value % W_PARTS>{});
+        });
+        // the first jobs of the sweep's first iteration: K(2), V(1); then V(0) -> stage 0, K(1) -> stage 1
+        set_k_rows(2);
+        set_v_rows(1);
+        static_for<RING>([&](auto J) { fetch_job(J, 2, 1); });
+        static_for<N_VJ * V_PARTS>([&](auto IDX) {
+            constexpr int j = decltype(IDX)::value / V_PARTS;
+            v_part(std::integral_constant<int, N_KJ + j>{}, I0{}, std::integral_constant<int, decltype(IDX)::value % V_PARTS>{}, v0[j]);
+        });
+        static_for<N_KJ * K_PARTS>([&](auto IDX) {
+            constexpr int j = decltype(IDX)::value / K_PARTS;
+            k_part(std::integral_constant<int, j>{}, I1{}, std::integral_constant<int, decltype(IDX)::value % K_PARTS>{}, k1[j]);
+        });
+        __syncthreads();
+    }
+
+    // ---- sweep: iteration b does the scores of block b + 1 over the conversion of K(b + 2) and V(b + 1), then the values of
+    // block b over the softmax of block b + 1.  Stage of a block: its index & 1.
+    auto iteration = [&](auto PAR, int b) __attribute__((always_inline)) {
+        constexpr int par = decltype(PAR)::value;
+        using Cur = std::integral_constant<int, par>;
+        using Nxt = std::integral_constant<int, par ^ 1>;
+        next_weights();
+        pin_accumulators();
+        if (__builtin_expect(b + 3 >= n_blocks - 1, 0)) {        // from here on requests may be for the last block
+            set_k_rows(b + 3);
+            set_v_rows(b + 1 + V_AHEAD);
+        }
+        scores(Nxt{}, [&](auto Kk) __attribute__((always_inline)) {
+            constexpr int k = decltype(Kk)::value;
+            constexpr int first = k * N_PARTS / M1, last = (k + 1) * N_PARTS / M1;
+            static_for<last - first>([&](auto I) { convert_part(std::integral_constant<int, first + decltype(I)::value>{}, Cur{}, Nxt{}, b + 2, b + 1); });
+        }, [&](auto LO) __attribute__((always_inline)) {
+            read_v(I0{}, Cur{}, LO);
+            if constexpr (decltype(LO)::value) static_for<3>([&](auto Qi) { read_factors(Qi, Nxt{}); });
+        });
+        static_assert((S_PRE + 4 * W_PARTS) * M2 / S_PARTS >= M2 / 2, "pairs 0-3 come behind the second half of the value products");
+        values(Cur{}, [&](auto Kk) __attribute__((always_inline)) {
+            constexpr int k = decltype(Kk)::value;
+            constexpr int first = k * S_PARTS / M2, last = (k + 1) * S_PARTS / M2;
+            static_for<last - first>([&](auto I) { softmax_part(std::integral_constant<int, first + decltype(I)::value>{}, Nxt{}, b + 1); });
+        });
+        rescale();
+        __syncthreads();     // the next block's planes are written by all, this one's read by all
+    };
+    // (The last iteration prepares a block past the end: a copy of the last one, all of whose keys are masked.  One loop
+    // body for all blocks; a copy of it for the tail made the register allocator move accumulators and operands around.)
+    for (int b = 0;;) {
+        iteration(I0{}, b);
+        if (++b >= n_blocks) break;
+        iteration(I1{}, b);
+        if (++b >= n_blocks) break;
+    }
+
+    // ---- did everything stay in range?  Then every accumulator is finite; if one is not, the workgroup redoes its tile ----
+    float bad = l * 0.f + r * 0.f;         // NaN once anything is inf or NaN
+#pragma unroll
+    for (int n = 0; n < NC; ++n)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+            bad = fmaf(acc_o[n][e], 0.f, bad);
+            if constexpr (TANGENT) bad = fmaf(acc_t[n][e], 0.f, bad);
+        }
+    float l_row = xhalf_sum(l), r_row = xhalf_sum(r);
+    if (__builtin_amdgcn_ballot_w64(bad != 0.f || bad != bad) != 0 && lane == 0) lds_write_f32(lds0 + G::RED_BASE + 48, 1.f);
+    __syncthreads();
+    const bool redo = __builtin_amdgcn_readfirstlane(__float_as_int(lds_read_f32(lds0 + G::RED_BASE + 48))) != 0;
+    if (__builtin_expect(redo, 0)) {
+        // ---- Alg. 2 in fp32 throughout: operands straight from memory, v_mfma_f32_32x32x2_f32.  Score step 4u + e: A =
+        // K[key = c][8u + 4g + e], B = Q[query = c][8u + 4g + e]; value step t: A = V[key 8(t/4) + 4g + t%4][32n + c],
+        // B = weight register t.  The row reference trails the running maximum by up to FP32_SLACK nats.
+#pragma unroll
+        for (int n = 0; n < NC; ++n) {
+            acc_o[n] = f32x16{};
+            if constexpr (TANGENT) acc_t[n] = f32x16{};
+        }
+        m = -INFINITY; l_row = 0.f; r_row = 0.f; go = 1.f; gt = 1.f; gr = 1.f;
+        const float* qp = Q + q_base + (long)qload * row_elems + 4 * g;
+        const float* tqp = TANGENT ? tQ + q_base + (long)qload * row_elems + 4 * g : nullptr;
+        for (int blk = 0; blk < n_blocks; ++blk) {
+            const int j0 = blk * BC;
+            const int krow = j0 + c < Lkv ? j0 + c : Lkv - 1;
+            const long koff = kv_base + (long)krow * row_elems + 4 * g;
+            s = f32x16{}; ts1 = f32x16{};
+#pragma unroll 1
+            for (int u = 0; u < D / 8; ++u) {
+                const float4 ka = *reinterpret_cast<const float4*>(K + koff + 8 * u);
+                const float4 qa = *reinterpret_cast<const float4*>(qp + 8 * u);
+                const float kv[4] = {ka.x, ka.y, ka.z, ka.w}, qv[4] = {qa.x, qa.y, qa.z, qa.w};
+#pragma unroll
+                for (int e = 0; e < 4; ++e) s = mfma32(kv[e], qv[e], s);
+                if constexpr (TANGENT) {
+                    const float4 ta = *reinterpret_cast<const float4*>(tqp + 8 * u);
+                    const float tv[4] = {ta.x, ta.y, ta.z, ta.w};
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) ts1 = mfma32(kv[e], tv[e], ts1);
+                }
+                if constexpr (KV_TANGENT) {
+                    const float4 tka = *reinterpret_cast<const float4*>(tK + koff + 8 * u);
+                    const float tkv[4] = {tka.x, tka.y, tka.z, tka.w};
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) ts1 = mfma32(tkv[e], qv[e], ts1);
+                }
+            }
+            float mb = -INFINITY;
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+                const bool dead = j0 + 8 * (e / 4) + 4 * g + (e % 4) >= Lkv;
+                mb = fmaxf(mb, dead ? -INFINITY : s[e] * scale);
+            }
+            mb = xhalf_max(mb);
+            const float m_new = mb > m + FP32_SLACK ? mb : m;
+            alpha = __builtin_amdgcn_exp2f((m - m_new) * LOG2E);    // 0 on the first block (m = -inf), else 1 or tiny
+            m = m_new;
+            moved = __builtin_amdgcn_ballot_w64(alpha != 1.f) != 0;
+            rescale();
+            float p[16], h[16];
+            float row_p = 0.f, row_h = 0.f;
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+                const bool dead = j0 + 8 * (e / 4) + 4 * g + (e % 4) >= Lkv;
+                p[e] = dead ? 0.f : __builtin_amdgcn_exp2f(fmaf(s[e], scale, -m) * LOG2E);
+                row_p += p[e];
+                if constexpr (TANGENT) {
+                    h[e] = dead ? 0.f : p[e] * (ts1[e] * scale);
+                    row_h += h[e];
+                }
+            }
+            l_row = fmaf(alpha, l_row, row_p);
+            r_row = fmaf(alpha, r_row, row_h);
+#pragma unroll
+            for (int t = 0; t < 16; ++t) {
+                FENCE();       // (few registers are left for loads issued ahead)
+                int row = j0 + 8 * (t / 4) + 4 * g + (t % 4);
+                row = row < Lkv ? row : Lkv - 1;
+                const long voff = kv_base + (long)row * row_elems + c;
+#pragma unroll
+                for (int n = 0; n < NC; ++n) {
+                    const float va = V[voff + 32 * n];
+                    acc_o[n] = mfma32(va, p[t], acc_o[n]);
+                    if constexpr (TANGENT) acc_t[n] = mfma32(va, h[t], acc_t[n]);
+                    if constexpr (KV_TANGENT) acc_t[n] = mfma32(tV[voff + 32 * n], p[t], acc_t[n]);
+                }
+            }
+        }
+        l_row = xhalf_sum(l_row);
+        r_row = xhalf_sum(r_row);
+    }
+
+    // ---- epilogue (Alg. 2, last lines): accumulator register 4k + i of column block n is column 32n + 8k + 4g + i -----
+    if (qrow < Lq) {
+        const float inv_l = 1.f / l_row;
+        const float mu = r_row * inv_l * gr;         // rowsum(P o tS), in the accumulators' scale
+        const float fo = go * inv_l, ft = gt * inv_l;
+        float* op = O + q_base + (long)qrow * row_elems + 4 * g;
+        float* top = TANGENT ? tO + q_base + (long)qrow * row_elems + 4 * g : nullptr;
+#pragma unroll
+        for (int n = 0; n < NC; ++n) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                float4 o4, t4;
+                o4.x = acc_o[n][4 * k + 0]; o4.y = acc_o[n][4 * k + 1];
+                o4.z = acc_o[n][4 * k + 2]; o4.w = acc_o[n][4 * k + 3];
+                if constexpr (TANGENT) {
+                    t4.x = fmaf(-mu, o4.x, acc_t[n][4 * k + 0]) * ft; t4.y = fmaf(-mu, o4.y, acc_t[n][4 * k + 1]) * ft;
+                    t4.z = fmaf(-mu, o4.z, acc_t[n][4 * k + 2]) * ft; t4.w = fmaf(-mu, o4.w, acc_t[n][4 * k + 3]) * ft;
+                    *reinterpret_cast<float4*>(top + 32 * n + 8 * k) = t4;
+                }
+                o4.x *= fo; o4.y *= fo; o4.z *= fo; o4.w *= fo;
+                *reinterpret_cast<float4*>(op + 32 * n + 8 * k) = o4;
+            }
+        }
+        if (g == 0) LSE[bh * Lq + qrow] = fmaf(__builtin_amdgcn_logf(l_row), LN2, m);     // v_log_f32 is a binary log
     }
 }
 
@@ -395,8 +894,7 @@ hipError_t launch_one(const Problem& p) {
     const int q_tiles = (p.Lq + BR - 1) / BR;
     const long long blocks = (long long)q_tiles * p.B * p.H;
     if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
-    constexpr int NT = TAN == TAN_ALL ? 4 : 2;
-    constexpr int smem = 2 * NT * BC * D * (int)sizeof(float);
+    constexpr int smem = Geo<D, TAN>::LDS_BYTES;
     auto kern = attn_jvp_mfma_f32_kernel<D, TAN>;
     int dev = 0, cus = 0;
     hipError_t e = device_cus(&dev, &cus);

@@ -221,3 +221,61 @@ def test_video_length_key_sequence():
     B, H, Lq, Lkv, d = 1, 2, 200, 32760, 128
     t = random_inputs(3276, B, H, Lq, Lkv, d, tangent_std=0.5)
     compare(to_np(run(t, sc(d))), oracle(t, sc(d)), "mfma-f32 Lkv=32760", Lkv)
+
+
+# The kernel splits every operand into two fp16 terms, scaled by powers of two that come from the row (Q, tQ, K, tK) or
+# from the first key block (V, tV, the tangent scores); what does not fit must end in the fp32 pass over the tile.
+RANGE_CASES = ["v-grows", "v-starts-at-zero", "v-shrinks", "k-rows-spread", "tiny-tangents", "huge-tangents", "late-tangents",
+               "tiny-queries", "one-dominant-key"]
+
+
+@pytest.mark.parametrize("d", [32, 64, 96, 128])
+@pytest.mark.parametrize("case", RANGE_CASES)
+def test_magnitudes_outside_one_scale(case, d):
+    """Lkv = 70: two full key blocks and a ragged one.  Tolerance: that of every other case at this length."""
+    B, H, Lq, Lkv = 1, 2, 131, 70
+    t = random_inputs(4000 + d + 7 * RANGE_CASES.index(case), B, H, Lq, Lkv, d)
+    g = torch.Generator().manual_seed(d)
+    if case == "v-grows":
+        t["v"][:, :, 40:] *= 1e4
+        t["tv"][:, :, 40:] *= 1e4
+    elif case == "v-starts-at-zero":
+        t["v"][:, :, :32] = 0.0
+        t["tv"][:, :, :32] = 0.0
+    elif case == "v-shrinks":
+        t["v"][:, :, 33:] *= 1e-3
+        t["tv"][:, :, 33:] *= 1e-3
+    elif case == "k-rows-spread":
+        f = 10.0 ** (-6.0 * torch.rand(B, H, Lkv, 1, generator=g))
+        t["k"] *= f
+        t["tk"] *= f
+    elif case in ("tiny-tangents", "huge-tangents"):
+        for n in ("tq", "tk", "tv"):
+            t[n] *= 1e-18 if case[0] == "t" else 1e12
+    elif case == "late-tangents":          # no tangent score and no tV in the first block
+        t["tq"].zero_()
+        t["tk"][:, :, :32] = 0.0
+        t["tv"][:, :, :32] = 0.0
+    elif case == "tiny-queries":
+        t["q"] *= 1e-25
+    else:                                   # the others 20 nats below one key: their share is within the tolerance
+        t["k"][:, :, 5] = t["q"].mean(dim=2)
+        t["q"] = t["q"] * 0.05 + 6.0 * t["k"][:, :, 5:6]
+    s_max = float((t["q"].double() @ t["k"].double().transpose(-1, -2)).abs().max()) * sc(d)
+    compare(to_np(run(t, sc(d))), oracle(t, sc(d)), f"mfma-f32 {case} d={d}", Lkv, extra_tol=40 * 2.0 ** -24 * s_max)
+
+
+def test_infinities_and_nan_as_in_the_vector_kernel():
+    """An infinite or NaN element of V must show in its column only, and the rest be right; the vector kernel, which
+    multiplies in fp32 throughout, says where."""
+    d, Lkv = 64, 70
+    for bad in (float("inf"), float("-inf"), float("nan")):
+        t = random_inputs(77, 1, 1, 40, Lkv, d, qk_gain=0.5)
+        t["v"][0, 0, 50, 3] = bad
+        got = to_np(run(t, sc(d)))
+        want = to_np(run(t, sc(d), kernel=binding.KERNEL_FP32))
+        for a, b in zip(got, want):
+            np.testing.assert_array_equal(np.isnan(a), np.isnan(b))
+            np.testing.assert_array_equal(np.isposinf(a), np.isposinf(b))
+            fin = np.isfinite(b)
+            assert np.abs(a[fin] - b[fin]).max() <= 2e-5 * np.sqrt((b[fin] ** 2).mean())
