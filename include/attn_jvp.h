@@ -84,10 +84,10 @@ extern "C" {
                                      fp32 and d in {32, 64, 96, 128} -> fp32 MFMA kernel; everything else -> vector kernel */
 #define ATTN_JVP_KERNEL_FP32 1    /* fp32 vector-ALU streaming kernel: any dtype, d in {32, 64, 128, 256}, slow */
 #define ATTN_JVP_KERNEL_MFMA 2    /* matrix-core kernels.
-                                     bf16 inputs: scale > 0, d in {64, 128} (built natively); d in {32, 96} given a
-                                     workspace of attn_jvp_workspace_bytes(...): the inputs are first copied there
-                                     zero-padded to 64 and 128 columns (exact: the padding adds zeros to every
-                                     product; half and a quarter of the matrix work are then spent on zeros).
+                                     bf16 inputs: scale > 0, d in {64, 128}; d in {32, 96} given a workspace of
+                                     attn_jvp_workspace_bytes(...).  64, 96 and 128 are built natively; at 32 the
+                                     inputs are first copied into the workspace zero-padded to 64 columns (exact: the
+                                     padding adds zeros to every product; half of the matrix work is spent on zeros).
                                      fp32 inputs: d in {32, 64, 96, 128}, any finite scale, fp32 outputs; every product
                                      as three 16-bit products of operands split into two fp16 terms each (22 to 23
                                      bits), fp32 accumulation, no workspace, flags ignored.  Tiles whose values do not
@@ -211,9 +211,9 @@ size_t attn_jvp_static_scratch_bytes(void);
  * Bytes of scratch the MFMA kernel can use for this shape (0 if it has no use for any).  d = 128: the fp16 value
  * path's 2 fp16 copies of V and tV (Lkv rounded up to a multiple of 32 keys: they are kept as whole 32-key blocks), 32 bytes of statistics per (batch, head), 4 bytes per 128-row query tile and
  * 32 bytes per (batch, head) and 1024 rows of the longer sequence, each part rounded up to 256 bytes, and 512 bytes
- * of counters (d = 64 likewise, with its own row width).  d in {32, 96}: in front of that, bf16 copies of the six inputs
- * zero-padded to 64 and 128 columns (without them the MFMA kernel does not take these head dimensions), and the
- * rest sized for the padded width.  Pure host arithmetic.
+ * of counters (d = 64 likewise, with its own row width).  d in {32, 96}: in front of that, room for bf16 copies of the
+ * six inputs zero-padded to 64 and 128 columns (used at 32 only; without a workspace of this size the MFMA kernel takes
+ * neither head dimension), and the rest sized for the padded width.  Pure host arithmetic.
  */
 size_t attn_jvp_workspace_bytes(int B, int H, int Lq, int Lkv, int d);
 

@@ -1,4 +1,4 @@
-// bf16 matrix-core (MFMA) streaming kernel for attention forward + JVP (paper Alg. 2), head dimension 128 or 64.
+// bf16 matrix-core (MFMA) streaming kernel for attention forward + JVP (paper Alg. 2), head dimension 128, 96 or 64.
 //
 // One workgroup = 4 wavefronts = 128 query rows; each wavefront owns 32 query rows for the whole
 // key/value sweep.  All contractions of Alg. 2's inner loop run on v_mfma_f32_32x32x16_bf16 in the
@@ -63,13 +63,15 @@ constexpr int BR = 128, BC = 32, NSTAGE = 4, NTHREADS = 256;
 // TAN selects which tangents exist: TAN_ALL (tQ, tK, tV), TAN_QUERY (tQ only: "ZT" below, zero key/value tangents)
 // or TAN_NONE (plain attention forward, O and lse only: 2 of the 6 products; same code path).
 constexpr int TAN_NONE = 0, TAN_QUERY = 1, TAN_ALL = 2;
-// Geometry for head dimension DH (128 or 64): LDS rows of DH bf16, a tensor's 32-row block, a ring stage (X | tX, or X
+// Geometry for head dimension DH (128, 96 or 64): LDS rows of DH bf16, a tensor's 32-row block, a ring stage (X | tX, or X
 // alone in the plain forward), the two rings.  DH = 128: 256-byte rows, 8 KiB blocks, 128 KiB of LDS (64 in the plain
-// forward); DH = 64: half of each.  (With TAN_QUERY the tangent halves of the stages stay unused: Q and tQ of a tile
+// forward); DH = 64: half of each; DH = 96: three quarters, without the quarter of the products, copies and LDS traffic
+// that running it on inputs padded to 128 columns spends on zeros (B1 H12 L5000 433 -> 350 us a call, B1 H14 L11894
+// 2690 -> 2199, cross-attention B1 H12 Lq32760 Lkv512 353 -> 261, B1 H13 L1578 86 -> 64).  (With TAN_QUERY the tangent halves of the stages stay unused: Q and tQ of a tile
 // are staged through the V ring's area, which needs its full size.)
 template <int DH, int TAN = TAN_ALL>
 struct Geo {
-    static_assert(DH == 128 || DH == 64, "head dimensions built natively");
+    static_assert(DH == 128 || DH == 96 || DH == 64, "head dimensions built natively");
     static constexpr int ROW_BYTES = DH * 2;
     static constexpr int TENSOR_BYTES = BC * ROW_BYTES;
     static constexpr int KV_STAGE_BYTES = (TAN == TAN_NONE ? 1 : 2) * TENSOR_BYTES;        // K|tK or V|tV
@@ -82,13 +84,28 @@ struct Geo {
     static constexpr int V_RING_BASE = NSTAGE * KV_STAGE_BYTES;    // K ring first, V ring behind it
     static constexpr int RING_BYTES = 2 * NSTAGE * KV_STAGE_BYTES;
     static constexpr int LDS_BYTES = RING_BYTES + 1024;           // + a KiB where prefetches land that nobody reads
-    static constexpr int LANES_PER_ROW = ROW_BYTES / 16;           // 16-byte chunks of a row
-    static constexpr int ROWS_PER_COPY = 64 / LANES_PER_ROW;       // rows one direct-to-LDS instruction (64 x 16 B) moves
-    static constexpr int COPIES_PER_WAVE = BC / ROWS_PER_COPY / 4; // ... and how many of them a wave issues per tensor block
+    static constexpr int CHUNKS_PER_ROW = ROW_BYTES / 16;          // 16-byte chunks of a row
+    static constexpr int PIECES = TENSOR_BYTES / 1024;             // direct-to-LDS instructions (64 x 16 B) per tensor block: 8, 6 or 4
+    // ... and how many a wave issues for a pair (X, tX), or for X alone (WITH_TANGENT false).  At DH = 96, X alone has 6
+    // for 4 waves: two each, the last two waves copying their first one twice.
+    static constexpr int copies_per_wave(bool with_tangent) { return ((with_tangent ? 2 : 1) * PIECES + 3) / 4; }
+    // Copy i of a wave: which tensor (0 X, 1 tX) and which 1-KiB piece of its block.  DH = 128, 64: a wave has the same
+    // pieces of X and tX; DH = 96: twelve pieces dealt in order.
+    static __device__ __forceinline__ int copy_tensor(bool with_tangent, int wave, int i) {
+        return !with_tangent ? 0 : DH == 96 ? wave >> 1 : i & 1;
+    }
+    static __device__ __forceinline__ int copy_piece(bool with_tangent, int wave, int i) {
+        if (DH == 96) return with_tangent ? (wave & 1) * 3 + i : wave + 4 * i < PIECES ? wave + 4 * i : wave;
+        return wave * (PIECES / 4) + (with_tangent ? i >> 1 : i);
+    }
+    // row and chunk of a block that lane `lane` of a piece fills (the LDS side is linear in the lane id)
+    static __device__ __forceinline__ int piece_row(int piece, int lane) { return (piece * 64 + lane) / CHUNKS_PER_ROW; }
+    static __device__ __forceinline__ int piece_chunk(int piece, int lane) { return (piece * 64 + lane) % CHUNKS_PER_ROW; }
     // swizzles, applied to the 16-byte chunk index of a row (on the global side of the copies): K, tK for row-wise
-    // 128-bit reads, V, tV for the transposing 64-bit reads
-    static __device__ __forceinline__ int k_swizzle(int row) { return DH == 128 ? (row & 15) : ((row >> 1) & 7); }
-    static __device__ __forceinline__ int v_swizzle(int row) { return DH == 128 ? ((row & 3) << 2) : (((row >> 1) & 1) << 2); }
+    // 128-bit reads, V, tV for the transposing 64-bit reads.  (DH = 96: rows of 192 bytes start 16 banks apart by
+    // themselves, four rows cover the banks; that is all the transposing reads need.)
+    static __device__ __forceinline__ int k_swizzle(int row) { return DH == 128 ? (row & 15) : DH == 96 ? ((row >> 2) & 3) : ((row >> 1) & 7); }
+    static __device__ __forceinline__ int v_swizzle(int row) { return DH == 128 ? ((row & 3) << 2) : DH == 96 ? 0 : (((row >> 1) & 1) << 2); }
 };
 constexpr int PRESCAN_BLOCKS = NSTAGE;   // key blocks sampled for the fp16 path's exponent reference: the first four, which start the K ring anyway
 
@@ -218,16 +235,13 @@ __device__ __forceinline__ void issue_pair_clamped(const char* Xh, const char* t
                                                    uint32_t stage_base, int wave, int lane) {
     using G = Geo<DH>;
 #pragma unroll
-    for (int i = 0; i < G::COPIES_PER_WAVE; ++i) {
-        const int rowblk = wave * G::COPIES_PER_WAVE + i;
-        const int row = rowblk * G::ROWS_PER_COPY + lane / G::LANES_PER_ROW;
-        const int pc = lane % G::LANES_PER_ROW;
+    for (int i = 0; i < G::copies_per_wave(WITH_TANGENT); ++i) {
+        const int piece = G::copy_piece(WITH_TANGENT, wave, i), which = G::copy_tensor(WITH_TANGENT, wave, i);
+        const int row = G::piece_row(piece, lane), pc = G::piece_chunk(piece, lane);
         int grow = j0 + row;
         grow = grow < Lkv ? grow : Lkv - 1;
         const long goff = (long)grow * row_stride + ((pc ^ (VSWZ ? G::v_swizzle(row) : G::k_swizzle(row))) << 4);
-        const uint32_t dst = stage_base + rowblk * 1024;
-        ATTN_JVP_LOAD_LDS(Xh + goff, dst);
-        if constexpr (WITH_TANGENT) ATTN_JVP_LOAD_LDS(tXh + goff, dst + G::TENSOR_BYTES);
+        ATTN_JVP_LOAD_LDS((which ? tXh : Xh) + goff, stage_base + which * G::TENSOR_BYTES + piece * 1024);
     }
 }
 // The fp16 copies of V and tV that the pre-pass leaves in the workspace are stored TRANSPOSED, key block by key block:
@@ -249,28 +263,30 @@ __device__ __forceinline__ void issue_pair_v16t(const char* Xh, const char* tXh,
     const int b = blk < n_blocks ? blk : n_blocks - 1;      // past the end: any finite data (the weights there are zero)
     const uint32_t lo = v16t_lane_offset(lane);
 #pragma unroll
-    for (int i = 0; i < G::COPIES_PER_WAVE; ++i) {
-        const int piece = wave * G::COPIES_PER_WAVE + i;
+    for (int i = 0; i < G::copies_per_wave(WITH_TANGENT); ++i) {
+        const int piece = G::copy_piece(WITH_TANGENT, wave, i), which = G::copy_tensor(WITH_TANGENT, wave, i);
         const long goff = (long)b * G::TENSOR_BYTES + piece * 1024 + lo;
-        const uint32_t dst = stage_base + piece * 1024;
-        ATTN_JVP_LOAD_LDS(Xh + goff, dst);
-        if constexpr (WITH_TANGENT) ATTN_JVP_LOAD_LDS(tXh + goff, dst + G::TENSOR_BYTES);
+        ATTN_JVP_LOAD_LDS((which ? tXh : Xh) + goff, stage_base + which * G::TENSOR_BYTES + piece * 1024);
     }
 }
 // Same copy for a block known to lie entirely inside the sequence: the per-lane byte offsets (row and swizzled
 // chunk) never change, so they are computed once and only the uniform block base advances.
-struct LaneOffsets { uint32_t k[2], v[2]; };
-template <int DH, bool V16T>
-__device__ __forceinline__ LaneOffsets make_lane_offsets(int wave, int lane, int k_stride, int v_stride) {
+template <int DH, bool WITH_TANGENT>
+struct LaneOffsets {
+    static constexpr int N = DH == 96 ? Geo<DH>::copies_per_wave(WITH_TANGENT) : Geo<DH>::PIECES / 4;   // different pieces of a wave
+    uint32_t k[N], v[N];
+};
+template <int DH, bool WITH_TANGENT, bool V16T>
+__device__ __forceinline__ LaneOffsets<DH, WITH_TANGENT> make_lane_offsets(int wave, int lane, int k_stride, int v_stride) {
     using G = Geo<DH>;
-    LaneOffsets o = {};
+    using L = LaneOffsets<DH, WITH_TANGENT>;
+    L o = {};
 #pragma unroll
-    for (int i = 0; i < G::COPIES_PER_WAVE; ++i) {
-        const int row = (wave * G::COPIES_PER_WAVE + i) * G::ROWS_PER_COPY + lane / G::LANES_PER_ROW;
-        const int pc = lane % G::LANES_PER_ROW;
+    for (int i = 0; i < L::N; ++i) {
+        const int piece = G::copy_piece(WITH_TANGENT, wave, DH != 96 && WITH_TANGENT ? 2 * i : i);
+        const int row = G::piece_row(piece, lane), pc = G::piece_chunk(piece, lane);
         o.k[i] = row * k_stride + ((pc ^ G::k_swizzle(row)) << 4);
-        o.v[i] = V16T ? (wave * G::COPIES_PER_WAVE + i) * 1024 + v16t_lane_offset(lane)
-                      : row * v_stride + ((pc ^ G::v_swizzle(row)) << 4);
+        o.v[i] = V16T ? piece * 1024 + v16t_lane_offset(lane) : row * v_stride + ((pc ^ G::v_swizzle(row)) << 4);
     }
     return o;
 }
@@ -324,6 +340,7 @@ __device__ __forceinline__ void attn_jvp_tile(
     constexpr int NT = DH / 16;             // score steps per key block (16 of the head dimension each)
     constexpr int NDB = DH / 32;            // 32-wide column blocks of the accumulators
     constexpr int NG = 2 * NDB;             // value groups per key block: (half of the block's keys) x (column block)
+    constexpr int COPIES = Geo<DH>::copies_per_wave(TAN == TAN_ALL);     // direct-to-LDS instructions per wave, key block and side (K or V)
     constexpr bool SPLIT = MODE == MODE_BF16_SPLIT;
     constexpr bool F16 = MODE == MODE_F16 || MODE == MODE_F16_ONLINE;   // fp16 weights and value operands
     constexpr bool PRESCAN = MODE == MODE_F16;                          // fixed reference from a key sample
@@ -423,15 +440,13 @@ __device__ __forceinline__ void attn_jvp_tile(
 #pragma unroll
         for (int j = 0; j < 4; ++j)
 #pragma unroll
-            for (int i = 0; i < G::COPIES_PER_WAVE; ++i) {
-                const int rowblk = wave * G::COPIES_PER_WAVE + i;
-                const int row = rowblk * G::ROWS_PER_COPY + lane / G::LANES_PER_ROW;
-                const int pc = lane % G::LANES_PER_ROW;
+            for (int i = 0; i < G::copies_per_wave(!PRIMAL); ++i) {
+                const int piece = G::copy_piece(!PRIMAL, wave, i), which = G::copy_tensor(!PRIMAL, wave, i);
+                const int row = G::piece_row(piece, lane), pc = G::piece_chunk(piece, lane);
                 int grow = tile_row0 + 32 * j + row;
                 grow = grow < Lq ? grow : Lq - 1;
                 const long goff = (long)grow * k_stride + ((pc ^ G::k_swizzle(row)) << 4);
-                ATTN_JVP_LOAD_LDS(Qh + goff, lds0 + Q_STAGE + (uint32_t)j * TENSOR_BYTES + rowblk * 1024);
-                if constexpr (!PRIMAL) ATTN_JVP_LOAD_LDS(tQh + goff, lds0 + TQ_STAGE + (uint32_t)j * TENSOR_BYTES + rowblk * 1024);
+                ATTN_JVP_LOAD_LDS((which ? tQh : Qh) + goff, lds0 + (which ? TQ_STAGE : Q_STAGE) + (uint32_t)j * TENSOR_BYTES + piece * 1024);
             }
     }
     auto start_v_ring = [&]() __attribute__((always_inline)) { copy_v(0); copy_v(1); copy_v(2); };
@@ -831,10 +846,8 @@ __device__ __forceinline__ void attn_jvp_tile(
         static_for<4>([&](auto J) { softmax_pair(J, B0{}); });   // pairs 0-3 of block 0; pairs 4-7 follow in iteration 0
         // V(0) and V(1) have landed (the first iteration reads V(0) before its own barrier, and publishes V(1) with
         // it); the copies of V(2), issued last, may still be under way
-        // (a wave issues G::COPIES_PER_WAVE instructions per tensor block)
-        if constexpr (G::COPIES_PER_WAVE * (ZT ? 1 : 2) == 4) asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
-        else if constexpr (G::COPIES_PER_WAVE * (ZT ? 1 : 2) == 2) asm volatile("s_waitcnt vmcnt(2)" ::: "memory");
-        else asm volatile("s_waitcnt vmcnt(1)" ::: "memory");
+        // (a wave issues COPIES instructions per block and side)
+        asm volatile("s_waitcnt vmcnt(%0)" :: "n"(COPIES) : "memory");
         __syncthreads();
     }
 
@@ -910,7 +923,7 @@ __device__ __forceinline__ void attn_jvp_tile(
     constexpr int KPRE = 3, KRING = KPRE + 1, VPRE = 2, VRING = VPRE + 1;
     constexpr int KFIRST = NG == 8 ? 2 : 1;   // value group after which the next iteration's first score fragments are requested
     static_assert(KPRE < NT && KFIRST + KPRE <= NG && VPRE < NG, "the fragment rings fit the key block's steps and groups");
-    const LaneOffsets lofs = make_lane_offsets<DH, F16>(wave, lane, k_stride, v_stride);
+    const auto lofs = make_lane_offsets<DH, !ZT, F16>(wave, lane, k_stride, v_stride);
     const int n_full = Lkv / BC;                       // blocks that need no row clamping
     bf16x8 kfr[KRING], tkfr[KRING], vfr[VRING], tvfr[VRING];
     auto read_k = [&](auto T, auto ST) __attribute__((always_inline)) {     // score step T of the block in K stage ST
@@ -936,26 +949,28 @@ __device__ __forceinline__ void attn_jvp_tile(
     // stall the in-order instruction stream behind the queue.
     auto issue_copy_piece = [&](auto FULLc, auto IDX, int b) __attribute__((always_inline)) {
         constexpr int idx = decltype(IDX)::value;
-        constexpr int i = idx >> 2, which = idx & 3;      // row group of this wave; 0 K, 1 tK, 2 V, 3 tV
-        static_assert(i < G::COPIES_PER_WAVE, "one piece per value group covers exactly the iteration's copies");
-        if constexpr (ZT && (which & 1)) return;          // no tangent tensors to copy
-        const int blk = which < 2 ? b + 4 : b + 3;
-        const char* base = which == 0 ? Kh : which == 1 ? tKh : which == 2 ? Vh : tVh;
-        const uint32_t dst = lds0 + (which < 2 ? 0 : V_RING_BASE) + (uint32_t)(blk & 3) * KV_STAGE_BYTES +
-                             (which & 1) * TENSOR_BYTES + (wave * G::COPIES_PER_WAVE + i) * 1024;
-        if constexpr (F16 && which >= 2) {                 // a whole transposed block of the fp16 copies: nothing to clamp but the block index
+        // K's copies first, then V's (DH = 96); or piece by piece K, tK, V, tV (0 .. 3), skipping absent tangents
+        if constexpr (DH == 96 && idx >= 2 * COPIES) return;
+        if constexpr (DH != 96 && ZT && (idx & 1)) return;
+        constexpr bool v_side = DH == 96 ? idx >= COPIES : (idx & 2) != 0;
+        constexpr int i = DH == 96 ? idx % COPIES : ZT ? idx >> 2 : (idx >> 2) * 2 + (idx & 1);     // copy i of that side
+        constexpr int lo_i = DH == 96 ? i : idx >> 2;
+        static_assert(i < COPIES, "one piece per value group covers exactly the iteration's copies");
+        const int blk = v_side ? b + 3 : b + 4;
+        const int piece = G::copy_piece(!ZT, wave, i), which = G::copy_tensor(!ZT, wave, i);
+        const char* base = v_side ? (which ? tVh : Vh) : (which ? tKh : Kh);
+        const uint32_t dst = lds0 + (v_side ? V_RING_BASE : 0) + (uint32_t)(blk & 3) * KV_STAGE_BYTES + which * TENSOR_BYTES + piece * 1024;
+        if constexpr (F16 && v_side) {                     // a whole transposed block of the fp16 copies: nothing to clamp but the block index
             const int bc = decltype(FULLc)::value ? blk : (blk < n_blocks ? blk : n_blocks - 1);
-            load_lds_b128(base + (long)bc * TENSOR_BYTES, lofs.v[i], __builtin_amdgcn_readfirstlane(dst));
+            load_lds_b128(base + (long)bc * TENSOR_BYTES, lofs.v[lo_i], __builtin_amdgcn_readfirstlane(dst));
         } else if constexpr (decltype(FULLc)::value) {
-            const uint32_t lo = which < 2 ? lofs.k[i] : lofs.v[i];
-            load_lds_b128(base + (long)blk * (BC * (which < 2 ? k_stride : v_stride)), lo, __builtin_amdgcn_readfirstlane(dst));
+            load_lds_b128(base + (long)blk * (BC * (v_side ? v_stride : k_stride)), v_side ? lofs.v[lo_i] : lofs.k[lo_i], __builtin_amdgcn_readfirstlane(dst));
         } else {
-            const int row = (wave * G::COPIES_PER_WAVE + i) * G::ROWS_PER_COPY + lane / G::LANES_PER_ROW;
-            const int pc = lane % G::LANES_PER_ROW;
+            const int row = G::piece_row(piece, lane), pc = G::piece_chunk(piece, lane);
             int grow = blk * BC + row;
             grow = grow < Lkv ? grow : Lkv - 1;
-            const int chunk = pc ^ (which < 2 ? G::k_swizzle(row) : G::v_swizzle(row));
-            ATTN_JVP_LOAD_LDS(base + (long)grow * (which < 2 ? k_stride : v_stride) + (chunk << 4), dst);
+            const int chunk = pc ^ (v_side ? G::v_swizzle(row) : G::k_swizzle(row));
+            ATTN_JVP_LOAD_LDS(base + (long)grow * (v_side ? v_stride : k_stride) + (chunk << 4), dst);
         }
     };
 
@@ -971,8 +986,12 @@ __device__ __forceinline__ void attn_jvp_tile(
         constexpr bool FULL = decltype(FULLc)::value;
         constexpr int PRODUCTS = PRIMAL ? 1 : ZT ? 2 : 3;         // matrix products per score step / per weight term
         constexpr int GROUP_MFMAS = SPLIT ? 2 * PRODUCTS : PRODUCTS;
-        constexpr int SPP = NT / 4;                                // phase 1: score steps per pair of score elements (2, or 1 at head dimension 64)
-        constexpr int PPG = 8 / NG;                                // phase 2: pairs per value group in each half of the groups (1, or 2)
+        // phase 1: score steps per pair of score elements (2, or 1 at head dimension 64); phase 2: pairs per value group
+        // in each half of the groups (1, or 2).  Head dimension 96, where 6 steps and 3 groups do not divide by 4 pairs:
+        // the pairs' parts are dealt in order over the MFMAs there are (EVEN false).
+        constexpr bool EVEN = NT % 4 == 0;
+        constexpr int SPP = EVEN ? NT / 4 : 1;
+        constexpr int PPG = EVEN ? 8 / NG : 0;
         using NS_P1 = std::integral_constant<int, SPP * PRODUCTS>;
         using NS_P2 = std::integral_constant<int, GROUP_MFMAS>;
         using K1 = std::integral_constant<int, (U + 1) & 3>;    // K stage of block b+1
@@ -983,21 +1002,29 @@ __device__ __forceinline__ void attn_jvp_tile(
         f32x16& s = SV(Bnext{});
         f32x16& ts = TSV(Bnext{});
         // ---- phase 1
+        auto behind_score = [&](auto SLOT) __attribute__((always_inline)) {      // MFMA number SLOT of the block's
+            constexpr int slot = decltype(SLOT)::value;
+            if constexpr (EVEN)
+                softmax_slot(std::integral_constant<int, 4 + slot / (SPP * PRODUCTS)>{}, std::integral_constant<int, slot % (SPP * PRODUCTS)>{}, NS_P1{}, Bcur{});
+            else
+                static_for<20>([&](auto Kc) {
+                    constexpr int k = decltype(Kc)::value;
+                    if constexpr (k * (NT * PRODUCTS) / 20 == slot) softmax_part(std::integral_constant<int, 4 + k / 5>{}, std::integral_constant<int, k % 5>{}, Bcur{});
+                });
+        };
         static_for<NT>([&](auto T) {
             constexpr int t = decltype(T)::value;
-            using J = std::integral_constant<int, 4 + t / SPP>;
-            constexpr int s0 = (t % SPP) * PRODUCTS;
             if constexpr (t == 0) SMFMA0(kfr[t % KRING], qf[t], s); else SMFMA(kfr[t % KRING], qf[t], s);
-            softmax_slot(J{}, std::integral_constant<int, s0>{}, NS_P1{}, Bcur{});
+            behind_score(std::integral_constant<int, t * PRODUCTS>{});
             FENCE();
             if constexpr (!PRIMAL) {
                 if constexpr (t == 0) SMFMA0(kfr[t % KRING], tqf[t], ts); else SMFMA(kfr[t % KRING], tqf[t], ts);
-                softmax_slot(J{}, std::integral_constant<int, s0 + 1>{}, NS_P1{}, Bcur{});
+                behind_score(std::integral_constant<int, t * PRODUCTS + 1>{});
                 FENCE();
             }
             if constexpr (!ZT) {
                 SMFMA(tkfr[t % KRING], qf[t], ts);
-                softmax_slot(J{}, std::integral_constant<int, s0 + 2>{}, NS_P1{}, Bcur{});
+                behind_score(std::integral_constant<int, t * PRODUCTS + 2>{});
                 FENCE();
             }
             if constexpr (t + KPRE < NT) read_k(std::integral_constant<int, t + KPRE>{}, K1{});
@@ -1006,11 +1033,8 @@ __device__ __forceinline__ void attn_jvp_tile(
         });
         // ---- middle
         SCORE_RESULTS_LAND();
-        // all but the newest copies (8 instructions per wave and iteration, 4 without tangents) landed: K(b+2), V(b+1) are in
-        // (G::COPIES_PER_WAVE instructions per tensor block: 8 per iteration at head dimension 128, 4 at 64, half without tangents)
-        if constexpr (G::COPIES_PER_WAVE * (ZT ? 2 : 4) == 8) asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
-        else if constexpr (G::COPIES_PER_WAVE * (ZT ? 2 : 4) == 4) asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
-        else asm volatile("s_waitcnt vmcnt(2)" ::: "memory");
+        // all but the newest copies (an iteration's: COPIES instructions per wave for K and as many for V) landed: K(b+2), V(b+1) are in
+        asm volatile("s_waitcnt vmcnt(%0)" :: "n"(2 * COPIES) : "memory");
         // ... and visible to all waves after the barrier; all waves are done with K(b) and V(b-1).  A bare barrier:
         // the LDS reads still in flight (first value fragments of block b) read stages nobody overwrites yet.
         __builtin_amdgcn_s_barrier();
@@ -1030,6 +1054,8 @@ __device__ __forceinline__ void attn_jvp_tile(
                     // score products' results have landed by then; the build's assembly check counts the wait states)
                     constexpr int first = GROUP_MFMAS >= 3 ? 1 : 0;
                     // (head dimension 64: two pairs per group, the second one behind the next MFMA where there is one)
+                    if constexpr (!EVEN && gi == 1 && GROUP_MFMAS >= first + 2 && slot == first + 1)
+                        softmax_part(std::integral_constant<int, 2>{}, std::integral_constant<int, 0>{}, Bnext{});
                     if constexpr (PPG == 2 && GROUP_MFMAS >= first + 2 && slot == first + 1)
                         softmax_part(std::integral_constant<int, 2 * gi + 1>{}, std::integral_constant<int, 0>{}, Bnext{});
                     if constexpr (slot == first) {
@@ -1045,10 +1071,20 @@ __device__ __forceinline__ void attn_jvp_tile(
                             }
                             if constexpr (ONLINE) online_check(Bnext{});
                         }
-                        softmax_part(std::integral_constant<int, PPG * gi>{}, std::integral_constant<int, 0>{}, Bnext{});
+                        if constexpr (EVEN) softmax_part(std::integral_constant<int, PPG * gi>{}, std::integral_constant<int, 0>{}, Bnext{});
+                        else softmax_part(std::integral_constant<int, gi + (gi == 2)>{}, std::integral_constant<int, 0>{}, Bnext{});     // pairs 0, 1 and 2, 3
+                        if constexpr (!EVEN && gi == 1 && GROUP_MFMAS < first + 2)
+                            softmax_part(std::integral_constant<int, 2>{}, std::integral_constant<int, 0>{}, Bnext{});
                         if constexpr (PPG == 2 && GROUP_MFMAS < first + 2)
                             softmax_part(std::integral_constant<int, 2 * gi + 1>{}, std::integral_constant<int, 0>{}, Bnext{});
                     }
+                } else if constexpr (!EVEN) {
+                    constexpr int lslot = (gi - NG / 2) * GROUP_MFMAS + slot;       // sixteen late parts over the second half's MFMAs
+                    static_for<16>([&](auto Kc) {
+                        constexpr int k = decltype(Kc)::value;
+                        if constexpr (k * (NG / 2 * GROUP_MFMAS) / 16 == lslot)
+                            softmax_part(std::integral_constant<int, k / 4>{}, std::integral_constant<int, 1 + k % 4>{}, Bnext{});
+                    });
                 } else if constexpr (PPG == 1) {
                     softmax_late_slot(std::integral_constant<int, gi - NG / 2>{}, SLOT, NS_P2{}, Bnext{});
                 } else {
@@ -1144,7 +1180,7 @@ __device__ __forceinline__ void attn_jvp_tile(
             const long bhn = bidn / q_tiles;
             const int rown0 = (bidn % q_tiles) * BR;
             const long qbn = blhd ? ((bhn / H) * Lq * H + bhn % H) * D : bhn * (long)Lq * D;
-            constexpr int LINES = ROW_BYTES / 128;                 // 128-byte lines per row (2, or 1 at head dimension 64)
+            constexpr int LINES = (ROW_BYTES + 127) / 128;         // 128-byte lines per row (2, or 1 at head dimension 64)
 #pragma unroll
             for (int u = 0; u < (BR * LINES + NTHREADS - 1) / NTHREADS; ++u) {
                 const int idx = (int)tid + NTHREADS * u;
@@ -1268,7 +1304,8 @@ __device__ __forceinline__ void attn_jvp_tile(
         typedef __attribute__((address_space(3))) f32x4 lds_float4;
         constexpr uint32_t OUT_ROW_BYTES = DH * 4;                 // a row of fp32 results
         constexpr int OUT_CHUNKS = DH / 4;                         // ... in 16-byte chunks (32, or 16 at head dimension 64)
-        constexpr int ROWS_PER_STORE = 64 / OUT_CHUNKS;            // rows one store instruction covers (2, or 4)
+        constexpr int ROWS_PER_STORE = 64 / OUT_CHUNKS;            // rows one store instruction covers (2, or 4; 2 by 48 lanes at head dimension 96)
+        auto out_swizzle = [](int row) { return DH == 96 ? (row >> 1) & 7 : row & (OUT_CHUNKS - 1); };
         const uint32_t stage_o = lds0 + (uint32_t)wave * ((PRIMAL ? 32u : 64u) * OUT_ROW_BYTES), stage_t = stage_o + 32u * OUT_ROW_BYTES;
 #pragma unroll
         for (int db = 0; db < NDB; ++db)
@@ -1281,7 +1318,7 @@ __device__ __forceinline__ void attn_jvp_tile(
                 t4.y = (accAB[db][4 * v4 + 1] - mu * a1) * ft;
                 t4.z = (accAB[db][4 * v4 + 2] - mu * a2) * ft;
                 t4.w = (accAB[db][4 * v4 + 3] - mu * a3) * ft;
-                const uint32_t at = (uint32_t)c * OUT_ROW_BYTES + (uint32_t)(((8 * db + 2 * v4 + g) ^ (c & (OUT_CHUNKS - 1))) << 4);
+                const uint32_t at = (uint32_t)c * OUT_ROW_BYTES + (uint32_t)(((8 * db + 2 * v4 + g) ^ out_swizzle(c)) << 4);
                 *reinterpret_cast<lds_float4*>((uintptr_t)(stage_o + at)) = f32x4{o4.x, o4.y, o4.z, o4.w};
                 if constexpr (!PRIMAL) *reinterpret_cast<lds_float4*>((uintptr_t)(stage_t + at)) = f32x4{t4.x, t4.y, t4.z, t4.w};
             }
@@ -1291,12 +1328,12 @@ __device__ __forceinline__ void attn_jvp_tile(
         const int o_row = out_blhd ? H * d_out : d_out;
         const long o_base = out_blhd ? (bidx * Lq * H + hidx) * d_out : bh * (long)Lq * d_out;
         const int chunk = lane % OUT_CHUNKS;         // 16-byte chunk of the row this lane stores: columns 4 chunk .. +3
-        if (4 * chunk < d_out) {
+        if (4 * chunk < d_out && lane < ROWS_PER_STORE * OUT_CHUNKS) {
 #pragma unroll
             for (int i = 0; i < 32 / ROWS_PER_STORE; ++i) {
                 const int r = ROWS_PER_STORE * i + lane / OUT_CHUNKS;      // row of the wave's 32
                 const int row = q0 + r;
-                const uint32_t at = (uint32_t)r * OUT_ROW_BYTES + (uint32_t)((chunk ^ (r & (OUT_CHUNKS - 1))) << 4);
+                const uint32_t at = (uint32_t)r * OUT_ROW_BYTES + (uint32_t)((chunk ^ out_swizzle(r)) << 4);
                 const f32x4 ov = *reinterpret_cast<const lds_float4*>((uintptr_t)(stage_o + at));
                 f32x4 tv_ = ov;
                 if constexpr (!PRIMAL) tv_ = *reinterpret_cast<const lds_float4*>((uintptr_t)(stage_t + at));
@@ -1356,16 +1393,16 @@ __global__ __launch_bounds__(NTHREADS, (Geo<DH, TAN>::WG_PER_CU)) void attn_jvp_
 // scale > 0: the kernel masks padded keys with a raw score of -inf and takes row maxima before scaling.
 // tk and tv are either both given or both absent (zero key/value tangents); single bf16 weights (FAST) are not built
 // for the latter.
-// Head dimensions 128 and 64 are built natively; 32 and 96 run on zero-padded copies (to 64 and 128 columns), which
-// need the caller's workspace.
-static bool padded_head_dim(const Problem& p) {
+// Head dimensions 128, 96 and 64 are built natively; 32 runs on zero-padded copies (64 columns), which need the caller's
+// workspace.  96 is taken with such a workspace only, too: without one the interface refuses it.
+static bool workspace_head_dim(const Problem& p) {
     return (p.d == 32 || p.d == 96) && p.workspace != nullptr &&
            (reinterpret_cast<uintptr_t>(p.workspace) & 255u) == 0 &&
            p.workspace_bytes >= pad_workspace_bytes(p.B, p.H, p.Lq, p.Lkv, p.d);
 }
 bool mfma_bf16_supports(const Problem& p) {
     const bool zt = p.tk == nullptr && p.tv == nullptr;     // (the API admits absent tangents only as tk+tv or tq+tk+tv)
-    return p.in_dtype == 0 && (p.d == 128 || p.d == 64 || padded_head_dim(p)) && p.scale > 0.f && !(zt && (p.flags & 1));
+    return p.in_dtype == 0 && (p.d == 128 || p.d == 64 || workspace_head_dim(p)) && p.scale > 0.f && !(zt && (p.flags & 1));
 }
 
 // Dynamic-LDS limit of every instantiation a call may launch, raised once per device and before anything is enqueued.
@@ -1477,7 +1514,7 @@ static hipError_t launch_dh(const Problem& p_in) {
 
 hipError_t launch_mfma_bf16(const Problem& p) {
     if (!mfma_bf16_supports(p)) return hipErrorInvalidValue;
-    return p.d <= 64 ? launch_dh<64>(p) : launch_dh<128>(p);     // 32 runs on copies padded to 64 columns, 96 to 128
+    return p.d <= 64 ? launch_dh<64>(p) : p.d == 96 ? launch_dh<96>(p) : launch_dh<128>(p);     // 32 runs on copies padded to 64 columns
 }
 
 }  // namespace attn_jvp

@@ -8,6 +8,7 @@
 #include <hip/hip_bf16.h>
 #include <hip/hip_fp16.h>
 #include <stdint.h>
+#include <type_traits>
 
 namespace attn_jvp {
 namespace {
@@ -42,10 +43,11 @@ constexpr int NORM_ROW_STEP = 16;   // row norms of Q, tQ, K, tK are taken from 
 // Slot 0, 1: abs max of V, tV over every element; slots 2..5: largest squared row norm of Q, tQ, K, tK over the
 // sampled rows.  Every block writes its result (zero for an empty range or an absent tensor) to
 // partials[(head * gridDim.x + blockIdx.x) * 8 + tensor]: nothing needs clearing, and no two blocks share a word.
-// A row of DH bf16 is read by DH / 8 adjacent lanes (16 bytes each); 256 threads cover 16 rows per pass (32 at DH = 64).
+// A row of DH bf16 is read by DH / 8 adjacent lanes (16 bytes each); 256 threads cover 16 rows per pass (32 at DH = 64;
+// at DH = 96 by 12 of 16 lanes, so that a row's lanes can still be summed by exchanges).
 template <int DH>
 __global__ __launch_bounds__(256) void head_stats_kernel(StatsArgs a, float* __restrict__ partials) {
-    constexpr int LPR = DH / 8;              // lanes per row
+    constexpr int LPR = DH == 96 ? 16 : DH / 8;          // lanes per row
     constexpr int RPP = 256 / LPR;           // rows per pass of the block
     const int which = blockIdx.z;
     const int L = a.L[which];
@@ -58,6 +60,7 @@ __global__ __launch_bounds__(256) void head_stats_kernel(StatsArgs a, float* __r
     }
     const __hip_bfloat16* __restrict__ X = a.x[which];
     const int sub = threadIdx.x % LPR;
+    const bool mine = sub < DH / 8;
     const int r_in = threadIdx.x / LPR;
     float best = 0.f;
     auto fold = [&](const uint4& w) {
@@ -81,7 +84,7 @@ __global__ __launch_bounds__(256) void head_stats_kernel(StatsArgs a, float* __r
 #pragma unroll
             for (int u = 0; u < 4; ++u) {            // four independent 16-byte loads in flight per lane
                 const int row = row0 + rr + RPP * u;
-                w[u] = row < L ? ld16(X + row_offset<DH>(bh, row, L, a.H, a.blhd) + sub * 8) : make_uint4(0, 0, 0, 0);
+                w[u] = row < L && mine ? ld16(X + row_offset<DH>(bh, row, L, a.H, a.blhd) + sub * 8) : make_uint4(0, 0, 0, 0);
             }
 #pragma unroll
             for (int u = 0; u < 4; ++u) fold(w[u]);
@@ -94,11 +97,11 @@ __global__ __launch_bounds__(256) void head_stats_kernel(StatsArgs a, float* __r
 #pragma unroll
         for (int u = 0; u < NU; ++u) {
             const int row = row0 + NORM_ROW_STEP * (r_in + RPP * u);
-            w[u] = row < L ? ld16(X + row_offset<DH>(bh, row, L, a.H, a.blhd) + sub * 8) : make_uint4(0, 0, 0, 0);
+            w[u] = row < L && mine ? ld16(X + row_offset<DH>(bh, row, L, a.H, a.blhd) + sub * 8) : make_uint4(0, 0, 0, 0);
         }
 #pragma unroll
         for (int u = 0; u < NU; ++u) fold(w[u]);
-        if (L - 1 >= row0 && L - 1 < row0 + ROWS_PER_BLOCK && r_in == 0) fold(ld16(X + row_offset<DH>(bh, L - 1, L, a.H, a.blhd) + sub * 8));
+        if (L - 1 >= row0 && L - 1 < row0 + ROWS_PER_BLOCK && r_in == 0) fold(!mine ? make_uint4(0, 0, 0, 0) : ld16(X + row_offset<DH>(bh, L - 1, L, a.H, a.blhd) + sub * 8));
     }
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) best = fmaxf(best, __shfl_xor(best, o));
@@ -126,7 +129,8 @@ __global__ __launch_bounds__(256) void convert_values_kernel(const __hip_bfloat1
                                                              int Lkv, int H, int blhd) {
     constexpr int LPR = DH / 8;              // 16-byte chunks per source row
     constexpr int TILE_ROW = DH + 4;         // halves per row of the LDS tile
-    constexpr int IN_CHUNKS = 32 * LPR / 256, OUT_CHUNKS = DH * 4 / 256;   // per thread and tensor
+    constexpr int IN_TOTAL = 32 * LPR, OUT_TOTAL = DH * 4;                 // chunks per tensor ...
+    constexpr int IN_CHUNKS = (IN_TOTAL + 255) / 256, OUT_CHUNKS = (OUT_TOTAL + 255) / 256;   // ... and per thread, at most
     const long bh = blockIdx.y;
     __shared__ float head_stats[8];
     __shared__ __half tile[2][32 * TILE_ROW];
@@ -159,6 +163,7 @@ __global__ __launch_bounds__(256) void convert_values_kernel(const __hip_bfloat1
 #pragma unroll
             for (int u = 0; u < IN_CHUNKS; ++u) {
                 const int q = threadIdx.x + 256 * u, row = q / LPR, sub = q % LPR;
+                if (IN_TOTAL % 256 != 0 && q >= IN_TOTAL) break;
                 const int key = blk * 32 + row;
                 uint4 a = make_uint4(0, 0, 0, 0);
                 if (key < Lkv) a = *reinterpret_cast<const uint4*>(src[x] + row_offset<DH>(bh, key, Lkv, H, blhd) + sub * 8);
@@ -176,6 +181,7 @@ __global__ __launch_bounds__(256) void convert_values_kernel(const __hip_bfloat1
 #pragma unroll
             for (int u = 0; u < OUT_CHUNKS; ++u) {
                 const int o = threadIdx.x + 256 * u, col = o >> 2, chunk = o & 3;    // 16-byte piece `chunk` of row `col`
+                if (OUT_TOTAL % 256 != 0 && o >= OUT_TOTAL) break;
                 const int key0 = 16 * (chunk >> 1) + 4 * (chunk & 1);
                 alignas(16) __half v[8];
 #pragma unroll
@@ -295,18 +301,17 @@ hipError_t launch_f16_prepass(const Problem& p, int cus, F16Workspace* out) {
     sa.H = p.H;
     sa.blhd = p.layout;
     auto bf = [](const void* x) { return static_cast<const __hip_bfloat16*>(x); };
-    if (p.d == 64)
-        hipLaunchKernelGGL(head_stats_kernel<64>, dim3(l.n_partials, (unsigned)heads, 6), dim3(256), 0, p.stream, sa, partials);
-    else
-        hipLaunchKernelGGL(head_stats_kernel<128>, dim3(l.n_partials, (unsigned)heads, 6), dim3(256), 0, p.stream, sa, partials);
     const int n_blocks = (p.Lkv + 31) / 32;
-    int cx = n_blocks < 512 ? n_blocks : 512;
-    if (p.d == 64)
-        hipLaunchKernelGGL(convert_values_kernel<64>, dim3(cx, (unsigned)heads), dim3(256), 0, p.stream, bf(p.v), bf(p.tv), partials,
+    const int cx = n_blocks < 512 ? n_blocks : 512;
+    auto launch = [&](auto dh) {
+        constexpr int DH = decltype(dh)::value;
+        hipLaunchKernelGGL(head_stats_kernel<DH>, dim3(l.n_partials, (unsigned)heads, 6), dim3(256), 0, p.stream, sa, partials);
+        hipLaunchKernelGGL(convert_values_kernel<DH>, dim3(cx, (unsigned)heads), dim3(256), 0, p.stream, bf(p.v), bf(p.tv), partials,
                            l.n_partials, stats, tickets, V16, tV16, n_blocks, p.scale, p.Lkv, p.H, p.layout);
-    else
-        hipLaunchKernelGGL(convert_values_kernel<128>, dim3(cx, (unsigned)heads), dim3(256), 0, p.stream, bf(p.v), bf(p.tv), partials,
-                           l.n_partials, stats, tickets, V16, tV16, n_blocks, p.scale, p.Lkv, p.H, p.layout);
+    };
+    if (p.d == 64) launch(std::integral_constant<int, 64>{});
+    else if (p.d == 96) launch(std::integral_constant<int, 96>{});
+    else launch(std::integral_constant<int, 128>{});
     out->stats = stats;
     out->wg_flags = wg_flags;
     out->v16 = V16;

@@ -70,9 +70,10 @@ struct F16Workspace {
 };
 size_t f16_workspace_bytes(int B, int H, int Lq, int Lkv, int d);
 
-// Head dimensions the MFMA kernel is not built for (32 and 96): the inputs are first copied, zero-padded to the next
-// width it is built for (64 and 128 columns), into the front of the workspace ([B,H,L,width] bf16 each, absent
-// tangents skipped); the padded columns add exact zeros to every product.  Width, bytes of that area, and the copy.
+// Head dimension 32, which the MFMA kernel is not built for: the inputs are first copied, zero-padded to 64 columns, into
+// the front of the workspace ([B,H,L,width] bf16 each, absent tangents skipped); the padded columns add exact zeros to
+// every product.  Width, bytes of that area, and the copy.  (96 is built natively and makes no copies, but the size that
+// the interface reports for it still has the room for copies of 128 columns.)
 constexpr int MFMA_HEAD_DIM = 128;
 inline int padded_head_dim_of(int d) { return d <= 64 ? 64 : MFMA_HEAD_DIM; }
 size_t pad_workspace_bytes(int B, int H, int Lq, int Lkv, int d);
