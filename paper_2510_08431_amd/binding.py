@@ -5,6 +5,7 @@ the computation runs inside the library's kernels.  There is no CPU or eager fal
 if the shared library is missing, loading raises.
 """
 import ctypes
+import functools
 import os
 
 import torch
@@ -87,18 +88,31 @@ def attn_jvp_workspace_bytes(B, H, Lq, Lkv, d):
 _workspaces = {}
 
 
-def _workspace(device, stream, nbytes):
+@functools.lru_cache(maxsize=1024)
+def _workspace_bytes(B, H, Lq, Lkv, d):
+    return int(load_library().attn_jvp_workspace_bytes(B, H, Lq, Lkv, d))      # (host arithmetic on the five numbers)
+
+
+def _workspace(device, stream, raw_stream, nbytes):
     """A scratch tensor from torch's allocator per (device, stream), grown on demand and reused across calls.
 
     Calls enqueued on one stream run in order, so they can share scratch; calls on different streams may overlap
-    and get separate buffers.  Callers that want to own the memory pass their own `workspace`."""
-    key = (device, stream.cuda_stream)
+    and get separate buffers.  Callers that want to own the memory pass their own `workspace`.  `stream` may be None:
+    the current one, whose handle raw_stream is."""
+    key = (device, raw_stream)
     ws = _workspaces.get(key)
     if ws is None or ws.numel() < nbytes:
+        if stream is None:
+            stream = torch.cuda.current_stream(device)
         with torch.cuda.stream(stream):      # so that torch's caching allocator ties the block to this stream
             ws = torch.empty(nbytes, dtype=torch.uint8, device=device)
         _workspaces[key] = ws
     return ws
+
+
+def _raw_stream(device):
+    """Handle of torch's current stream, without the Stream object that torch.cuda.current_stream makes (2 us)."""
+    return torch._C._cuda_getCurrentRawStream(device.index)
 
 
 def _ptr(t):
@@ -106,36 +120,46 @@ def _ptr(t):
 
 
 def _check_inputs(q, k, v, tq, tk, tv, layout=LAYOUT_BHLD):
-    if q.dim() != 4 or k.dim() != 4:
+    qs, ks = q.shape, k.shape
+    if len(qs) != 4 or len(ks) != 4:
         raise ValueError("q and k must be [B, H, L, d] (or [B, L, H, d] with layout=LAYOUT_BLHD)")
     if layout == LAYOUT_BLHD:
-        B, Lq, H, d = q.shape
-        Lkv = k.shape[1]
-        shape = lambda L: (B, L, H, d)
+        B, Lq, H, d = qs
+        Lkv = ks[1]
+        kv_shape = (B, Lkv, H, d)
     elif layout == LAYOUT_BHLD:
-        B, H, Lq, d = q.shape
-        Lkv = k.shape[2]
-        shape = lambda L: (B, H, L, d)
+        B, H, Lq, d = qs
+        Lkv = ks[2]
+        kv_shape = (B, H, Lkv, d)
     else:
         raise ValueError(f"unknown layout {layout}")
     if (tk is None) != (tv is None):
         raise ValueError("tk and tv must both be given or both be None (zero key/value tangents)")
     if tq is None and tk is not None:
         raise ValueError("tq=None means no tangents at all: tk and tv must be None too")
-    for name, t, L in (("q", q, Lq), ("tq", tq, Lq), ("k", k, Lkv), ("v", v, Lkv), ("tk", tk, Lkv), ("tv", tv, Lkv)):
+    dtype, device = q.dtype, q.device
+    for name, t, shape in (("q", q, qs), ("tq", tq, qs), ("k", k, kv_shape), ("v", v, kv_shape), ("tk", tk, kv_shape), ("tv", tv, kv_shape)):
         if t is None:
             continue
-        if tuple(t.shape) != shape(L):
-            raise ValueError(f"{name} has shape {tuple(t.shape)}, expected {shape(L)}")
-        if t.dtype != q.dtype or t.device != q.device:
+        if t.shape != shape:
+            raise ValueError(f"{name} has shape {tuple(t.shape)}, expected {tuple(shape)}")
+        if t.dtype is not dtype or t.device != device:
             raise ValueError(f"{name}: dtype/device differ from q")
         if not t.is_contiguous():
             raise ValueError(f"{name} must be contiguous")
-    if q.dtype not in _DTYPE_CODE:
-        raise ValueError(f"unsupported dtype {q.dtype}")
+    if dtype not in _DTYPE_CODE:
+        raise ValueError(f"unsupported dtype {dtype}")
     if not q.is_cuda:
         raise ValueError("tensors must live on the GPU; there is no CPU path")
     return B, H, Lq, Lkv, d
+
+
+def _call(device, fn, *args):
+    """fn(*args) with `device` current: the library enqueues on the current device."""
+    if torch.cuda.current_device() == device.index:      # (entering the context manager costs 3 us)
+        return fn(*args)
+    with torch.cuda.device(device):
+        return fn(*args)
 
 
 def attn_jvp_fwd_ex(q, k, v, tq, tk, tv, scale, out=None, out_dtype=torch.float32, kernel=KERNEL_AUTO, stream=None,
@@ -152,12 +176,13 @@ def attn_jvp_fwd_ex(q, k, v, tq, tk, tv, scale, out=None, out_dtype=torch.float3
     torch.cuda.Event(enable_timing=True) that the library records right before and after the main kernel.
     Returns (o, to, lse); asynchronous.
     """
-    lib = load_library()
+    lib = _lib or load_library()
     B, H, Lq, Lkv, d = _check_inputs(q, k, v, tq, tk, tv, layout)
+    device = q.device
     if out is None:
-        o = torch.empty(q.shape, dtype=out_dtype, device=q.device)     # same layout as q
+        o = torch.empty_like(q, dtype=out_dtype, memory_format=torch.contiguous_format)     # same layout as q
         to = torch.empty_like(o) if tq is not None else None
-        lse = torch.empty(B, H, Lq, dtype=torch.float32, device=q.device)
+        lse = torch.empty((B, H, Lq), dtype=torch.float32, device=device)
     else:
         o, to, lse = out
         out_dtype = o.dtype
@@ -166,33 +191,28 @@ def attn_jvp_fwd_ex(q, k, v, tq, tk, tv, scale, out=None, out_dtype=torch.float3
             raise ValueError("out must be (o, to, lse) with o, to shaped like q and lse [B, H, Lq]")
     if out_dtype not in (torch.float32, q.dtype):
         raise ValueError("out_dtype must be float32 or the input dtype")
-    opts = AttnJvpOpts()
-    opts.in_dtype = _DTYPE_CODE[q.dtype]
-    opts.out_dtype = 0 if out_dtype == torch.float32 else 1
-    if stream is None:
-        stream = torch.cuda.current_stream(q.device)
-    opts.stream = stream.cuda_stream
-    opts.kernel = int(kernel)
-    opts.flags = int(flags)
-    opts.layout = int(layout)
+    raw_stream = _raw_stream(device) if stream is None else stream.cuda_stream
     entry = lib.attn_jvp_fwd_ex
     if isinstance(workspace, str) and workspace == "static":
         entry = lib.attn_jvp_fwd_static
         workspace = None
     if isinstance(workspace, str) and workspace == "auto":
-        need = lib.attn_jvp_workspace_bytes(B, H, Lq, Lkv, d) if q.dtype == torch.bfloat16 else 0
-        workspace = _workspace(q.device, stream, need) if need else None
+        need = _workspace_bytes(B, H, Lq, Lkv, d) if q.dtype == torch.bfloat16 else 0
+        workspace = _workspace(device, stream, raw_stream, need) if need else None
+    opts = AttnJvpOpts(_DTYPE_CODE[q.dtype], 0 if out_dtype == torch.float32 else 1, raw_stream, int(kernel), int(flags))
+    opts.layout = int(layout)
     if workspace is not None:
         opts.workspace = workspace.data_ptr()
         opts.workspace_bytes = workspace.numel() * workspace.element_size()
     if timing_events is not None:
+        if stream is None:
+            stream = torch.cuda.current_stream(device)
         for i, ev in enumerate(timing_events):
             if not ev.cuda_event:      # torch creates the HIP event lazily, at its first record
                 ev.record(stream)
             opts.timing_events[i] = ev.cuda_event
-    with torch.cuda.device(q.device):
-        rc = entry(q.data_ptr(), k.data_ptr(), v.data_ptr(), _ptr(tq), _ptr(tk), _ptr(tv),
-                   o.data_ptr(), _ptr(to), lse.data_ptr(), B, H, Lq, Lkv, d, float(scale), ctypes.byref(opts))
+    rc = _call(device, entry, q.data_ptr(), k.data_ptr(), v.data_ptr(), _ptr(tq), _ptr(tk), _ptr(tv),
+               o.data_ptr(), _ptr(to), lse.data_ptr(), B, H, Lq, Lkv, d, float(scale), ctypes.byref(opts))
     if rc != 0:
         raise AttnJvpError(rc, attn_jvp_strerror(rc))
     return o, to, lse
@@ -215,7 +235,7 @@ def attn_jvp_rmsnorm_fwd(x, tx, w, eps, out=None, stream=None):
 
     x, tx: [..., d] bf16 or fp32, contiguous, on the GPU; w: [d] float32.  out: optional (y, ty) to write into
     (may be (x, tx) themselves).  Returns (y, ty); asynchronous."""
-    lib = load_library()
+    lib = _lib or load_library()
     if x.dtype not in _DTYPE_CODE or tx.dtype != x.dtype or tuple(tx.shape) != tuple(x.shape):
         raise ValueError("x and tx must have the same shape and dtype (bf16 or fp32)")
     if not (x.is_cuda and tx.is_cuda and w.is_cuda):
@@ -232,11 +252,9 @@ def attn_jvp_rmsnorm_fwd(x, tx, w, eps, out=None, stream=None):
         y, ty = out
         if y.dtype != x.dtype or ty.dtype != x.dtype or tuple(y.shape) != tuple(x.shape) or tuple(ty.shape) != tuple(x.shape):
             raise ValueError("out must be (y, ty) shaped and typed like x")
-    if stream is None:
-        stream = torch.cuda.current_stream(x.device)
-    with torch.cuda.device(x.device):
-        rc = lib.attn_jvp_rmsnorm_fwd(x.data_ptr(), tx.data_ptr(), w.data_ptr(), y.data_ptr(), ty.data_ptr(),
-                                      rows, d, float(eps), _DTYPE_CODE[x.dtype], stream.cuda_stream)
+    raw_stream = _raw_stream(x.device) if stream is None else stream.cuda_stream
+    rc = _call(x.device, lib.attn_jvp_rmsnorm_fwd, x.data_ptr(), tx.data_ptr(), w.data_ptr(), y.data_ptr(), ty.data_ptr(),
+               rows, d, float(eps), _DTYPE_CODE[x.dtype], raw_stream)
     if rc != 0:
         raise AttnJvpError(rc, attn_jvp_strerror(rc))
     return y, ty
@@ -276,7 +294,7 @@ def attn_jvp_fwd(q, k, v, tq, tk, tv, scale, out=None):
     B, H, Lq, Lkv, d = _check_inputs(q, k, v, tq, tk, tv)
     if q.dtype != torch.bfloat16:
         raise ValueError("attn_jvp_fwd takes bf16 inputs; use attn_jvp_fwd_ex for fp32")
-    if torch.cuda.current_stream(q.device).cuda_stream != 0:
+    if _raw_stream(q.device) != 0:
         return attn_jvp_fwd_ex(q, k, v, tq, tk, tv, scale, out=out, workspace=None)
     if out is None:
         o = torch.empty(B, H, Lq, d, dtype=torch.float32, device=q.device)
@@ -284,9 +302,8 @@ def attn_jvp_fwd(q, k, v, tq, tk, tv, scale, out=None):
         lse = torch.empty(B, H, Lq, dtype=torch.float32, device=q.device)
     else:
         o, to, lse = out
-    with torch.cuda.device(q.device):
-        rc = lib.attn_jvp_fwd(q.data_ptr(), k.data_ptr(), v.data_ptr(), _ptr(tq), _ptr(tk), _ptr(tv),
-                              o.data_ptr(), _ptr(to), lse.data_ptr(), B, H, Lq, Lkv, d, float(scale))
+    rc = _call(q.device, lib.attn_jvp_fwd, q.data_ptr(), k.data_ptr(), v.data_ptr(), _ptr(tq), _ptr(tk), _ptr(tv),
+               o.data_ptr(), _ptr(to), lse.data_ptr(), B, H, Lq, Lkv, d, float(scale))
     if rc != 0:
         raise AttnJvpError(rc, attn_jvp_strerror(rc))
     return o, to, lse

@@ -42,6 +42,7 @@
 #include "launchers.h"
 #include "f16_scales.h"
 #include <hip/hip_bf16.h>
+#include <atomic>
 #include <stdint.h>
 #include <type_traits>
 #include <utility>
@@ -1408,6 +1409,8 @@ bool mfma_bf16_supports(const Problem& p) {
 // Dynamic-LDS limit of every instantiation a call may launch, raised once per device and before anything is enqueued.
 template <int DH>
 static hipError_t prepare_kernels(int dev) {
+    static std::atomic<unsigned long long> done{0};        // one bit per device (device_cus admits 64)
+    if (done.load(std::memory_order_acquire) >> dev & 1) return hipSuccess;
     auto raise = [&](auto tan) -> hipError_t {
         constexpr int T = decltype(tan)::value;
         const void* kernels[] = {(const void*)attn_jvp_mfma_kernel<MODE_BF16_SPLIT, T, DH>, (const void*)attn_jvp_mfma_kernel<MODE_F16, T, DH>,
@@ -1422,6 +1425,7 @@ static hipError_t prepare_kernels(int dev) {
     if (e == hipSuccess) e = raise(std::integral_constant<int, TAN_NONE>{});
     if (e == hipSuccess) e = raise(std::integral_constant<int, TAN_QUERY>{});
     if (e == hipSuccess) e = raise(std::integral_constant<int, TAN_ALL>{});
+    if (e == hipSuccess) done.fetch_or(1ull << dev, std::memory_order_release);
     return e;
 }
 
