@@ -82,7 +82,8 @@ extern "C" {
 /* attn_jvp_opts.kernel */
 #define ATTN_JVP_KERNEL_AUTO 0    /* bf16, scale > 0 and d in {64, 128} (or d in {32, 96} with a workspace) -> bf16 MFMA kernel;
                                      fp32 and d in {32, 64, 96, 128} -> fp32 MFMA kernel; everything else -> vector kernel */
-#define ATTN_JVP_KERNEL_FP32 1    /* fp32 vector-ALU streaming kernel: any dtype, d in {32, 64, 128, 256}, slow */
+#define ATTN_JVP_KERNEL_FP32 1    /* fp32 streaming kernels, any dtype: d in {32, 64, 128} on the vector ALU (slow), d = 256
+                                     on fp32 matrix instructions */
 #define ATTN_JVP_KERNEL_MFMA 2    /* matrix-core kernels.
                                      bf16 inputs: scale > 0, d in {64, 128}; d in {32, 96} given a workspace of
                                      attn_jvp_workspace_bytes(...).  64, 96 and 128 are built natively; at 32 the

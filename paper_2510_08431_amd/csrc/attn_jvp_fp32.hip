@@ -1,10 +1,11 @@
 // fp32 vector-ALU streaming kernel for attention forward + JVP (paper Alg. 2).
 //
 // Reference-grade GPU path: every product and sum is an fp32 FMA on the vector ALU, so it meets
-// the fp32 tolerance, and it accepts bf16 inputs too (upcast exactly).  It is the path for fp32
-// inputs and head dims the matrix-core kernel does not cover; it is not tuned for speed.
+// the fp32 tolerance, and it accepts bf16 inputs too (upcast exactly).  It is the cross-check for the
+// matrix-core kernels and the path for what they do not cover; it is not tuned for speed.  (d = 256
+// runs on fp32 matrix instructions, attn_jvp_fp32_d256.hip.)
 //
-// Work split: a workgroup of 256 lanes owns BR = 64 query rows (16 for d = 256); each row is shared by 4 (16)
+// Work split: a workgroup of 256 lanes owns BR = 64 query rows; each row is shared by 4
 // neighbouring lanes, lane part p holding the float4 chunks p, p+4, p+8, ... of q, tq and of the
 // accumulators.  Key/value tiles of BC = 32 rows (K, tK, V, tV) are staged in LDS as fp32.
 // Per tile: partial dot products reduced over the 4 lanes -> S, tS; row max; P~ = exp(S - m);
@@ -18,9 +19,7 @@ namespace {
 
 constexpr int BC = 32;       // key rows per tile
 constexpr int NTHREADS = 256;
-// lanes sharing one query row: 4 up to d = 128, 16 for d = 256 (keeps q, tq and the two accumulators of a lane at 64
-// registers; with 4 lanes the d = 256 kernel spilled and ran 14x slower per flop)
-constexpr int lanes_per_row(int d) { return d > 128 ? 16 : 4; }
+constexpr int LPR = 4;       // lanes sharing one query row
 
 template <typename T> struct Ld;
 template <> struct Ld<float> {
@@ -51,7 +50,6 @@ __global__ __launch_bounds__(NTHREADS) void attn_jvp_fp32_kernel(
     const TIn* __restrict__ tQ, const TIn* __restrict__ tK, const TIn* __restrict__ tV,
     TOut* __restrict__ O, TOut* __restrict__ tO, float* __restrict__ LSE,
     int Lq, int Lkv, float scale, int H, int blhd) {
-    constexpr int LPR = lanes_per_row(D);
     constexpr int BR = NTHREADS / LPR;          // query rows per workgroup
     constexpr int NCH = D / (4 * LPR);          // float4 chunks per lane
     extern __shared__ float4 smem[];            // 4 tiles of BC x D floats
@@ -175,7 +173,7 @@ __global__ __launch_bounds__(NTHREADS) void attn_jvp_fp32_kernel(
 
 template <typename TIn, typename TOut, int D>
 hipError_t launch_one(const Problem& p) {
-    constexpr int BR = NTHREADS / lanes_per_row(D);
+    constexpr int BR = NTHREADS / LPR;
     dim3 grid((p.Lq + BR - 1) / BR, p.B * p.H);
     size_t smem = 4ull * BC * D * sizeof(float);
     auto kern = attn_jvp_fp32_kernel<TIn, TOut, D>;
@@ -197,7 +195,6 @@ hipError_t launch_d(const Problem& p) {
         case 32: return launch_one<TIn, TOut, 32>(p);
         case 64: return launch_one<TIn, TOut, 64>(p);
         case 128: return launch_one<TIn, TOut, 128>(p);
-        case 256: return launch_one<TIn, TOut, 256>(p);
         default: return hipErrorInvalidValue;
     }
 }
@@ -210,6 +207,7 @@ bool fp32_vector_supports(const Problem& p) {
 
 hipError_t launch_fp32_vector(const Problem& p) {
     if (!fp32_vector_supports(p)) return hipErrorInvalidValue;
+    if (p.d == 256) return launch_fp32_d256(p);
     if (p.in_dtype == 1) return launch_d<float, float>(p);                      // fp32 in -> fp32 out either way
     if (p.out_dtype == 0) return launch_d<__hip_bfloat16, float>(p);
     return launch_d<__hip_bfloat16, __hip_bfloat16>(p);

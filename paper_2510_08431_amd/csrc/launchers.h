@@ -46,7 +46,8 @@ hipError_t ensure_dynamic_lds(const void* kern, int bytes, int dev);
 
 // Each returns hipSuccess/hip error of the launch, or hipErrorInvalidValue when the
 // (dtype, d) combination is not built for that kernel.
-hipError_t launch_fp32_vector(const Problem& p);
+hipError_t launch_fp32_vector(const Problem& p);      // d = 256: launch_fp32_d256
+hipError_t launch_fp32_d256(const Problem& p);
 hipError_t launch_mfma_bf16(const Problem& p);
 hipError_t launch_mfma_f32(const Problem& p);
 bool mfma_bf16_supports(const Problem& p);
