@@ -353,7 +353,6 @@ __device__ __forceinline__ void attn_jvp_tile(
     // those; the online fp16 kernel works on exactly the tiles flagged 1 and sets 3 (done), or 2 if it has to
     // abandon one itself; the bf16-pair kernel, given the flags, works on exactly the tiles flagged 2.
     if constexpr (ONLINE) {
-        if (wg_flags[vw] != 1) return;
         // Lock-step start of the tiles that share an XCD's L2 (lockstep_slots = workgroups an XCD holds at a time, 0 =
         // off).  The tiles of this tier take different times (moves of the reference), and over many rounds of
         // tiles the workgroups of an XCD drift apart until each streams K and V from memory on its own.  Each
@@ -375,8 +374,6 @@ __device__ __forceinline__ void attn_jvp_tile(
             }
             __syncthreads();
         }
-    } else if constexpr (!F16) {
-        if (wg_flags != nullptr && wg_flags[vw] != 2) return;
     }
     extern __shared__ __attribute__((aligned(1024))) char smem[];
     const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)smem;
@@ -1381,9 +1378,26 @@ __global__ __launch_bounds__(NTHREADS, (Geo<DH, TAN>::WG_PER_CU)) void attn_jvp_
         const unsigned long long wait = (unsigned long long)((blockIdx.x >> 3) & 31) * (unsigned)stagger_ticks;
         while (wall_clock64() - t0 < wait) __builtin_amdgcn_s_sleep(8);
     }
-    for (int vw = blockIdx.x; vw < n_tiles; vw += gridDim.x)
+    auto tile = [&](int vw) __attribute__((always_inline)) {
         attn_jvp_tile<MODE, TAN, DH>(Q, K, V, tQ, tK, tV, O, tO, LSE, Lq, Lkv, scale, q_tiles, stats, wg_flags, H, blhd, out_bf16,
                                  d_out, out_blhd, online_min_blocks, lockstep_slots, vw, n_tiles);
+    };
+    if constexpr (MODE == MODE_F16_ONLINE || MODE == MODE_BF16_SPLIT) {
+        // A hand-over launch of the fp16 path works on flagged tiles only, as a rule on none.  A workgroup looks at the
+        // flags of 64 of its tiles at once, one per lane: one memory latency, where a look per tile took one each
+        // (a dozen tiles per workgroup: 5.4 -> 4.5 and 4.2 -> 3.0 us for the two launches).  Every wave finds the same tiles: a flag changes only when its tile is
+        // done, by its own workgroup, and all waves have read the flags before that.  (The pairs without flags: every tile.)
+        const int stride = (int)gridDim.x;
+        for (long first = blockIdx.x; first < n_tiles; first += 64L * stride) {
+            const long mine = first + (long)(threadIdx.x & 63) * stride;
+            const bool mark = mine < n_tiles && (wg_flags == nullptr || wg_flags[mine] == (MODE == MODE_F16_ONLINE ? 1 : 2));
+            unsigned long long todo = __builtin_amdgcn_ballot_w64(mark);
+            __syncthreads();
+            for (; todo != 0; todo &= todo - 1) tile((int)(first + (long)__builtin_ctzll(todo) * stride));
+        }
+    } else {
+        for (int vw = blockIdx.x; vw < n_tiles; vw += gridDim.x) tile(vw);
+    }
     // (a hand-over launch may have requested lines for a next tile that turned out not to be its own: no direct-to-LDS
     // load is left in flight when the wave ends)
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
