@@ -319,6 +319,12 @@ constexpr int LOCKSTEP_MIN_BLOCKS = 1024;            // tiles of at least 1.3 ms
 constexpr unsigned long long LOCKSTEP_WAIT_TICKS = 10000;   // 100 us of the 100 MHz wall clock
 constexpr int LOCKSTEP_MAX_POLLS = 2048;
 constexpr int STAGGER_TICKS = 32;   // start offset between neighbouring resident workgroups of an XCD (0.32 us; 31 steps = 10 us)
+// Two workgroups of a compute unit cover each other's fixed cost per tile by themselves, so there the staggered start
+// has to earn its up to 10 us over several rounds of tiles.  Without it, us before -> after: no tangents, d 128, two
+// rounds 293 -> 286, three 426 -> 419, four 560 -> 555; d 96 three rounds 264 -> 256; d 64, two 403 -> 395, three 591 ->
+// 584; no clear sign at six rounds (d 128 165 -> 167, d 64 106 -> 101), and worse at twelve (259 -> 265, 297 -> 307).
+// With one workgroup per unit its absence gives nothing from two to twelve rounds (425 -> 428, 422 -> 419, 723 -> 723).
+constexpr int STAGGER_MIN_ROUNDS_OF_PAIRS = 5;
 // The fp16 path costs a pre-pass per call (two small launches, ~20 us plus the conversion of V and tV) and a key sample per
 // tile; per key block it is a quarter faster than the bf16 pairs.  It pays from 2048 keys on, and from 256 keys on when
 // the call has at least four tiles per compute unit to spread the pre-pass over (measured per tile, 12 tiles per unit:
@@ -1477,7 +1483,8 @@ static hipError_t launch_dh(const Problem& p_in) {
         const bool res = (resident || (follower && short_tiles)) && cus % 8 == 0 && blocks >= 2LL * WG_PER_CU * cus &&
                          !(p.flags & 16);   // 16: ATTN_JVP_FLAG_NO_RESIDENT
         const long long grid = res ? (long long)WG_PER_CU * cus : blocks;
-        const int stagger = res && !follower ? STAGGER_TICKS : 0;
+        const bool staggered = WG_PER_CU == 1 || blocks >= STAGGER_MIN_ROUNDS_OF_PAIRS * grid;
+        const int stagger = res && !follower && staggered ? STAGGER_TICKS : 0;
         hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(NTHREADS), G::LDS_BYTES, p.stream,
                            (const __hip_bfloat16*)p.q, (const __hip_bfloat16*)p.k, v,
                            (const __hip_bfloat16*)p.tq, (const __hip_bfloat16*)p.tk, tv,
