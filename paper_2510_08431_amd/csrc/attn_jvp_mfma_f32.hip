@@ -27,8 +27,8 @@
 // them in a lane's registers) go through two LDS stages each.  The four waves fetch fp32 blocks two (K) and one (V)
 // blocks ahead into registers and convert them behind the score MFMAs; behind the value MFMAs run the softmax and
 // weight splitting of the NEXT block.  One barrier per block.  Bound by the matrix pipe at D = 128 (144 MFMAs per wave
-// and block, about 480 other vector instructions): B2 H16 L4096 d128 2.19 ms = 376 TFLOP/s counted
-// (6.40 ms with fp32 MFMAs), the matrix pipe busy a bit more than half of the time; d = 64 1.17 ms (3.14), d = 32 0.87
+// and block, about 550 other vector instructions): B2 H16 L4096 d128 2.19 ms = 376 TFLOP/s counted
+// (6.40 ms with fp32 MFMAs), the matrix pipe busy 57 % of the time; d = 64 1.17 ms (3.14), d = 32 0.87
 // (1.65).  Errors against 64 bits are 0.6 to 0.7 of those of the fp32-MFMA kernel in o and to, the same in lse.
 #include "launchers.h"
 #include <type_traits>
