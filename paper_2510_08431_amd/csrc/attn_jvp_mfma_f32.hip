@@ -14,9 +14,12 @@
 //   weights: P~ 2^12 with P~ = exp(S - m) against a row reference m that trails the row maximum by at most 2.68 nats
 //     (so that keys 25 nats below the maximum still count); H~ 2^(12 - eH) with 2^eH from the first block's tangent
 //     scores and |tV| / |V|.
-// A value outside these ranges becomes inf in fp16 and shows in l, r or the accumulators.  Such tiles, and those with
-// infinities or NaN in their inputs, are redone at the end with fp32 MFMAs (redo_fp32: Alg. 2 as printed, slow).  l and r
-// are summed in fp32 from the unrounded weights.
+// Values that these scales do not suit send the workgroup's tile to a pass with fp32 MFMAs at the end (redo_fp32: Alg. 2 as
+// printed, slow), as do infinities and NaN in the inputs.  Too large a value becomes inf in fp16 and shows in l, r or
+// the accumulators.  Too small ones would sink into fp16 subnormals unseen: the conversion looks at the largest of each
+// eight values of V and tV that it splits, and a row whose results come out small against what the split resolves is
+// found at the end (the weights of keys that hold the scale up may be nil).  l and r are summed in fp32 from the unrounded
+// weights.
 //
 // Work split: a workgroup of 4 waves owns 128 query rows, 32 per wave; key blocks of BC = 32 rows.  Products are taken
 // transposed, S^T = K Q^T and O^T += V^T P~^T, on v_mfma_f32_32x32x16_f16: the query index is the MFMA column (lane %
@@ -55,6 +58,10 @@ constexpr float LOG2E = 1.4426950408889634f;
 constexpr float LN2 = 0.6931471805599453f;
 constexpr int ROW_TOP = 12;      // rows of Q, tQ, K, tK: largest element in [2^12, 2^13)
 constexpr int V_TOP = 11;        // first block of V: largest element in [2^11, 2^12), 4 binades in hand for later blocks
+constexpr int V_FLOOR = -3;      // eight keys of a column are known to 2^-22 of their largest if that is 2^-3 or more, scaled,
+constexpr uint32_t V_SPAN = 19u << 23;    // ... and fit into fp16 up to 2^16: 19 binades
+constexpr uint32_t V_AMPLE = 9u << 23;    // 2^6: where V is that large tV may be smaller than 2^-3, its share of tO is known well enough
+constexpr float ROW_FLOOR = 65536.f;      // (2^8)^2: see the check at the end of the sweep
 constexpr int T_HEADROOM = 6;    // the first block's largest tangent score is scaled to [2^-6, 2^-5)
 constexpr float P_GAIN = 4096.f;          // the split weights are P~ 2^12 ...
 constexpr float P_SLACK = 2.68f;          // ... and stay below 2^16: nats by which a block may exceed the reference before it moves
@@ -108,10 +115,10 @@ __device__ __forceinline__ uint32_t split_lo(float x0, float x1, float s, uint32
     asm("v_fma_mix_f32 %0, %1, %2, -%3 op_sel:[0,0,1] op_sel_hi:[0,0,1]" : "=v"(r1) : "v"(x1), "v"(s), "v"(h));
     return pack_f16(r0, r1);
 }
-// max(a, |b|, |c|) (as assembly: fmaxf would first canonicalise every operand that comes from memory); a NaN is passed over
+// max(|a|, |b|, |c|) (as assembly: fmaxf would first canonicalise every operand that comes from memory); a NaN is passed over
 __device__ __forceinline__ float max_abs3(float a, float b, float c) {
     float d;
-    asm volatile("v_max3_f32 %0, %1, |%2|, |%3|" : "=v"(d) : "v"(a), "v"(b), "v"(c));
+    asm volatile("v_max3_f32 %0, |%1|, |%2|, |%3|" : "=v"(d) : "v"(a), "v"(b), "v"(c));
     return d;
 }
 __device__ __forceinline__ float max3(float a, float b, float c) {
@@ -263,13 +270,16 @@ __global__ __launch_bounds__(NTHREADS, (Geo<D, TAN>::WG_PER_CU)) void attn_jvp_m
     const uint32_t v_write = lds0 + G::V_BASE + (uint32_t)(lane * 64 + ((wave ^ ((lane >> 2) & 3)) << 4));
     const uint32_t v_write_last = lds0 + G::V_BASE + (uint32_t)(v_lane_last * 64 + ((wave ^ ((v_lane_last >> 2) & 3)) << 4));
     float v_scale[NX];                                   // set from the first block
+    uint32_t v_low[NX];          // (bits of) the smallest value that the scale suits, 2^V_FLOOR scaled
+    uint64_t misfit = 0;         // lanes that have met values their tensor's scale does not suit
+    uint64_t v_small[G::V_PASSES];       // lanes whose V of the block under way is small or zero
     uint32_t cv_h[4], cv_l[4];
     float cv_mx, cv_m2, cv_sc;
     // row factors: written by the first lane of a row (the others write to a place nobody reads: to one address their
     // writes would queue up)
     const uint32_t f_write = lds0 + (tid % G::LPR == 0 ? G::F_BASE + 4 * k_row : G::DUMMY_BASE + 4 * lane);
     // (the DPP steps of a row maximum one per part: the MFMA between two of them is the wait they need)
-    constexpr int K_PARTS = 13, V_PARTS = 5;
+    constexpr int K_PARTS = 13, V_PARTS = 6;
     auto split_part = [&](const float (&e)[8], float s, auto PART) __attribute__((always_inline)) {      // parts 0-3
         constexpr int part = decltype(PART)::value, i = 2 * (part >> 1);
         if constexpr ((part & 1) == 0) { cv_h[i] = split_hi(e[2 * i], e[2 * i + 1], s); cv_h[i + 1] = split_hi(e[2 * i + 2], e[2 * i + 3], s); }
@@ -277,7 +287,7 @@ __global__ __launch_bounds__(NTHREADS, (Geo<D, TAN>::WG_PER_CU)) void attn_jvp_m
     };
     auto k_part = [&](auto J, auto ST, auto PART, const float (&e)[8]) __attribute__((always_inline)) {
         constexpr int jb = decltype(J)::value, x = jb / G::K_PASSES, p = jb % G::K_PASSES, st = decltype(ST)::value, part = decltype(PART)::value;
-        if constexpr (part == 0) { cv_mx = max_abs3(fabsf(e[0]), e[1], e[2]); cv_m2 = max_abs3(fabsf(e[3]), e[4], e[5]); }
+        if constexpr (part == 0) { cv_mx = max_abs3(e[0], e[1], e[2]); cv_m2 = max_abs3(e[3], e[4], e[5]); }
         if constexpr (part == 1) cv_mx = max_abs3(cv_mx, e[6], e[7]);
         if constexpr (part == 2) cv_mx = max_abs3(cv_mx, cv_m2, cv_m2);
         if constexpr (part == 3) cv_mx = max_dpp<0xB1>(cv_mx);             // lanes ^ 1, ^ 2, mirrored in 8, mirrored in 16
@@ -299,8 +309,19 @@ __global__ __launch_bounds__(NTHREADS, (Geo<D, TAN>::WG_PER_CU)) void attn_jvp_m
     auto v_part = [&](auto J, auto ST, auto PART, const float (&e)[8]) __attribute__((always_inline)) {
         constexpr int jb = decltype(J)::value, x = (jb - N_KJ) / G::V_PASSES, p = (jb - N_KJ) % G::V_PASSES;
         constexpr int st = decltype(ST)::value, part = decltype(PART)::value;
-        if constexpr (part < 4) split_part(e, v_scale[x], PART);
-        if constexpr (part == 4) {
+        if constexpr (part == 0) {                       // do the eight values, one column of eight keys, suit the scale?
+            const uint32_t top = __float_as_uint(max_abs3(max_abs3(max_abs3(max_abs3(e[0], e[1], e[2]), e[3], e[4]), e[5], e[6]), e[7], e[7]));
+            const uint32_t above = top - v_low[x];       // (wraps around for smaller ones)
+            if constexpr (x == 0) {
+                misfit |= __builtin_amdgcn_ballot_w64(above >= V_SPAN && top != 0);
+                if constexpr (KV_TANGENT) v_small[p] = __builtin_amdgcn_ballot_w64(top < v_low[0] + V_AMPLE);
+            } else {
+                misfit |= __builtin_amdgcn_ballot_w64(top >= v_low[1] + V_SPAN) |
+                          (__builtin_amdgcn_ballot_w64(above >= V_SPAN && top != 0) & v_small[p]);
+            }
+        }
+        if constexpr (part >= 1 && part < 5) split_part(e, v_scale[x], std::integral_constant<int, part - 1>{});
+        if constexpr (part == 5) {
             const uint32_t at = (64 * (p + 1) <= D ? v_write : v_write_last) + st * G::STAGE + 2 * x * G::PLANE + p * 4096;
             lds_write_b128(at, u32x4{cv_h[0], cv_h[1], cv_h[2], cv_h[3]});
             lds_write_b128(at + G::PLANE, u32x4{cv_l[0], cv_l[1], cv_l[2], cv_l[3]});
@@ -708,7 +729,11 @@ __global__ __launch_bounds__(NTHREADS, (Geo<D, TAN>::WG_PER_CU)) void attn_jvp_m
         go = ldexpf(1.f, eV - 12);
         gt = ldexpf(1.f, eV + eH - 12);
         v_scale[0] = ldexpf(1.f, -eV);
-        if constexpr (KV_TANGENT) v_scale[1] = ldexpf(1.f, -(eV + eH));
+        v_low[0] = (uint32_t)(eV + V_FLOOR + 127) << 23;
+        if constexpr (KV_TANGENT) {
+            v_scale[1] = ldexpf(1.f, -(eV + eH));
+            v_low[1] = (uint32_t)(eV + eH + V_FLOOR + 127) << 23;
+        }
         ftqh = ldexpf(abs_scale * ftq, 12 - eH);
         fqh = ldexpf(abs_scale * fq, 12 - eH);
         static_for<8 * W_PARTS>([&](auto IDX) {
@@ -767,16 +792,26 @@ __global__ __launch_bounds__(NTHREADS, (Geo<D, TAN>::WG_PER_CU)) void attn_jvp_m
         if (++b >= n_blocks) break;
     }
 
-    // ---- did everything stay in range?  Then every accumulator is finite; if one is not, the workgroup redoes its tile ----
+    // ---- did the scales suit?  If not, the workgroup redoes its tile ------------------------------------------------------
+    // Too large: something is inf or NaN.  Too small: the lanes that converted V and tV have seen it (misfit), or a row's
+    // results are small against what the fp16 terms resolve.  The terms are whole multiples of 2^-24: an accumulator
+    // is out by up to l 2^12 2^-25 for V's rounding, and for that of the weights by 2^-25 of the V (up to 2^12) of every key
+    // that counts; a row whose largest |O| is 2^8 sqrt(l) knows it to 2^-21 for the one, 2^-21 sqrt(keys / l) / 4 or so
+    // for the other.  (Ordinary rows are at 2^21 sqrt(l) and above; it takes weights on keys whose V is small
+    // beside the others', a sink without values for one, to come near the line.)
     float bad = l * 0.f + r * 0.f;         // NaN once anything is inf or NaN
+    float top_o = 0.f;
 #pragma unroll
     for (int n = 0; n < NC; ++n)
 #pragma unroll
         for (int e = 0; e < 16; ++e) {
             bad = fmaf(acc_o[n][e], 0.f, bad);
             if constexpr (TANGENT) bad = fmaf(acc_t[n][e], 0.f, bad);
+            top_o = fmaxf(top_o, fabsf(acc_o[n][e]));
         }
     float l_row = xhalf_sum(l), r_row = xhalf_sum(r);
+    top_o = xhalf_max(top_o);
+    if (misfit != 0 || top_o * top_o < l_row * ROW_FLOOR) bad = 1.f;
     if (__builtin_amdgcn_ballot_w64(bad != 0.f || bad != bad) != 0 && lane == 0) lds_write_f32(lds0 + G::RED_BASE + 48, 1.f);
     __syncthreads();
     const bool redo = __builtin_amdgcn_readfirstlane(__float_as_int(lds_read_f32(lds0 + G::RED_BASE + 48))) != 0;
