@@ -61,8 +61,8 @@ constexpr int V_TOP = 11;        // first block of V: largest element in [2^11, 
 constexpr int V_FLOOR = -3;      // eight keys of a column are known to 2^-22 of their largest if that is 2^-3 or more, scaled,
 constexpr uint32_t V_SPAN = 19u << 23;    // ... and fit into fp16 up to 2^16: 19 binades
 constexpr uint32_t V_AMPLE = 9u << 23;    // 2^6: where V is that large tV may be smaller than 2^-3, its share of tO is known well enough
-constexpr float ROW_FLOOR = 65536.f;      // (2^8)^2: see the check at the end of the sweep
-constexpr int T_HEADROOM = 6;    // the first block's largest tangent score is scaled to [2^-6, 2^-5)
+constexpr float ROW_FLOOR = 16384.f;      // (2^7)^2: see the check at the end of the sweep
+constexpr int T_HEADROOM = 4;    // the first block's largest tangent score is scaled to [2^-4, 2^-3)
 constexpr float P_GAIN = 4096.f;          // the split weights are P~ 2^12 ...
 constexpr float P_SLACK = 2.68f;          // ... and stay below 2^16: nats by which a block may exceed the reference before it moves
 constexpr float FP32_SLACK = 32.f;        // redo_fp32: nats by which scores may exceed the reference
@@ -794,24 +794,33 @@ __global__ __launch_bounds__(NTHREADS, (Geo<D, TAN>::WG_PER_CU)) void attn_jvp_m
 
     // ---- did the scales suit?  If not, the workgroup redoes its tile ------------------------------------------------------
     // Too large: something is inf or NaN.  Too small: the lanes that converted V and tV have seen it (misfit), or a row's
-    // results are small against what the fp16 terms resolve.  The terms are whole multiples of 2^-24: an accumulator
-    // is out by up to l 2^12 2^-25 for V's rounding, and for that of the weights by 2^-25 of the V (up to 2^12) of every key
-    // that counts; a row whose largest |O| is 2^8 sqrt(l) knows it to 2^-21 for the one, 2^-21 sqrt(keys / l) / 4 or so
-    // for the other.  (Ordinary rows are at 2^21 sqrt(l) and above; it takes weights on keys whose V is small
-    // beside the others', a sink without values for one, to come near the line.)
+    // results are small against what the fp16 terms resolve.  These are whole multiples of 2^-24: an accumulator is out by up
+    // to l 2^12 2^-25 for the rounding of V (tV), and for that of the weights by 2^-25 of the V (2^9 as a rule, up to
+    // 2^12) of every key that counts.  A row whose largest |O| or |A + B| is 2^7 max(l, sqrt(l)) knows it to 2^-20 at worst
+    // for the one and 2^-24 sqrt(keys / l) or so for the other.  Ordinary rows are at 2^21 sqrt(l) and 2^16 sqrt(l).
+    // It takes weights on keys whose V is small beside the others', a sink without values for one, or tangent scores small
+    // beside those of the tile's first block, to come near the line.  (A row without tangents has exact zeros.)
+    auto too_small = [](float top, float l) __attribute__((always_inline)) { return top * top < ROW_FLOOR * l * fmaxf(l, 1.f); };
     float bad = l * 0.f + r * 0.f;         // NaN once anything is inf or NaN
-    float top_o = 0.f;
+    float top_o = 0.f, top_t = 0.f;
 #pragma unroll
     for (int n = 0; n < NC; ++n)
 #pragma unroll
         for (int e = 0; e < 16; ++e) {
             bad = fmaf(acc_o[n][e], 0.f, bad);
-            if constexpr (TANGENT) bad = fmaf(acc_t[n][e], 0.f, bad);
             top_o = fmaxf(top_o, fabsf(acc_o[n][e]));
+            if constexpr (TANGENT) {
+                bad = fmaf(acc_t[n][e], 0.f, bad);
+                top_t = fmaxf(top_t, fabsf(acc_t[n][e]));
+            }
         }
     float l_row = xhalf_sum(l), r_row = xhalf_sum(r);
     top_o = xhalf_max(top_o);
-    if (misfit != 0 || top_o * top_o < l_row * ROW_FLOOR) bad = 1.f;
+    if (misfit != 0 || too_small(top_o, l_row)) bad = 1.f;
+    if constexpr (TANGENT) {
+        top_t = xhalf_max(top_t);
+        if (too_small(top_t, l_row) && (r_row != 0.f || top_t != 0.f)) bad = 1.f;
+    }
     if (__builtin_amdgcn_ballot_w64(bad != 0.f || bad != bad) != 0 && lane == 0) lds_write_f32(lds0 + G::RED_BASE + 48, 1.f);
     __syncthreads();
     const bool redo = __builtin_amdgcn_readfirstlane(__float_as_int(lds_read_f32(lds0 + G::RED_BASE + 48))) != 0;

@@ -125,3 +125,38 @@ def test_columns_of_different_magnitude(d):
     t["v"][..., 5] = 0.0
     t["tv"][..., 5] = 0.0
     check(t, "columns over nine decades, one of zeros", rows=False)
+
+
+@DIMS
+@pytest.mark.parametrize("names", [NAMES, ("q", "k", "v", "tq")], ids=["all", "query"])
+@pytest.mark.parametrize("f", [1e-3, 1e-5, 1e-8])
+def test_query_tangents_of_different_magnitude(f, names, d):
+    """Half of the rows of every tile have query tangents f times the others'; without key tangents their tO is smaller by
+    the same factor."""
+    t = inputs(5, 150, 256, d)
+    t["tq"][:, :, ::2] *= f
+    if "tk" in names:              # ... and with them, if those are small as well
+        t["tk"] *= f
+        t["tv"] *= f
+    check(t, f"tq rows x {f:g}", names=names, columns=False)
+
+
+@DIMS
+@pytest.mark.parametrize("f", [1e4, 1e8])
+def test_large_tangents_of_keys_without_weight(f, d):
+    t = inputs(6, 150, 256, d)
+    drop(t, slice(0, 32), 80.0)
+    t["tk"][:, :, :32, 1:] *= f
+    check(t, f"tk-first-block x {f:g}")
+    t = inputs(7, 150, 256, d)
+    drop(t, slice(0, 32), 1e7 / d ** 0.5)              # a mask of -1e7 in K, seen by the query tangents too
+    t["tq"][..., 0] = 1.0
+    check(t, "mask of -1e7, tangents there")
+
+
+@DIMS
+def test_rows_without_tangents(d):
+    """Zero query tangents in some rows and none elsewhere: their tO is exactly zero."""
+    t = inputs(8, 150, 256, d)
+    t["tq"][:, :, 100:] = 0.0
+    check(t, "rows without tangents", names=("q", "k", "v", "tq"), columns=False)
