@@ -218,8 +218,9 @@ __global__ __launch_bounds__(NTHREADS, (Geo<D, TAN>::WG_PER_CU)) void attn_jvp_m
     // ---- fetching a block into registers ----------------------------------------------------------------------------
     // K side: lane handles 8 consecutive elements (chunk k_sub) of row k_row (+ K_ROWS per pass).  V side: lane handles
     // one column of the 8 keys 16 (wave >> 1) + 4 (wave & 1) + {0..3, 8..11}: the keys of one 16-byte chunk.
-    // Rows past the end of a ragged last block re-read a row inside it (finite values for finite inputs; their weight
-    // is zero), blocks past the end the last block.
+    // Rows past the end of a ragged last block re-read rows inside it (finite values for finite inputs; their weight
+    // is zero; those of V in turn, so that eight keys stay as many different ones as there are, or nearly), blocks past the end the
+    // last block.
     // (No branches in here: lanes without a chunk or column of their own do their neighbour's once more, to the same place.)
     const int k_sub = tid % G::LPR < D / 8 ? tid % G::LPR : D / 8 - 1;
     const int k_row = tid / G::LPR < BC ? tid / G::LPR : tid / G::LPR - BC;
@@ -236,10 +237,11 @@ __global__ __launch_bounds__(NTHREADS, (Geo<D, TAN>::WG_PER_CU)) void attn_jvp_m
     };
     auto set_v_rows = [&](int blk) __attribute__((always_inline)) {
         const int left = Lkv - (blk < n_blocks ? blk : n_blocks - 1) * BC;
+        const int turn = (int)(0x80000000u >> __builtin_clz(left)) - 1;      // (a power of two up to left, less 1)
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
-            const int row = v_key0 + (i & 3) + 8 * (i >> 2);
-            v_rows[i] = (uint32_t)((row < left ? row : 0) * row_bytes) + 4 * (uint32_t)lane;
+            const int key = v_key0 + (i & 3) + 8 * (i >> 2), row = key < left ? key : key & turn;
+            v_rows[i] = (uint32_t)(row * row_bytes) + 4 * (uint32_t)lane;
         }
     };
     // The conversion jobs of a block are the K passes of K (and tK), then the V passes of V (and tV).  At most RING
@@ -272,6 +274,7 @@ __global__ __launch_bounds__(NTHREADS, (Geo<D, TAN>::WG_PER_CU)) void attn_jvp_m
     float v_scale[NX];                                   // set from the first block
     uint32_t v_low[NX];          // (bits of) the smallest value that the scale suits, 2^V_FLOOR scaled
     uint64_t misfit = 0;         // lanes that have met values their tensor's scale does not suit
+    uint64_t v_heed = ~0ull;     // (0: the block under way is one key, and one value of a column may well be small)
     uint64_t v_small[G::V_PASSES];       // lanes whose V of the block under way is small or zero
     uint32_t cv_h[4], cv_l[4];
     float cv_mx, cv_m2, cv_sc;
@@ -313,11 +316,11 @@ __global__ __launch_bounds__(NTHREADS, (Geo<D, TAN>::WG_PER_CU)) void attn_jvp_m
             const uint32_t top = __float_as_uint(max_abs3(max_abs3(max_abs3(max_abs3(e[0], e[1], e[2]), e[3], e[4]), e[5], e[6]), e[7], e[7]));
             const uint32_t above = top - v_low[x];       // (wraps around for smaller ones)
             if constexpr (x == 0) {
-                misfit |= __builtin_amdgcn_ballot_w64(above >= V_SPAN && top != 0);
+                misfit |= __builtin_amdgcn_ballot_w64(above >= V_SPAN && top != 0) & v_heed;
                 if constexpr (KV_TANGENT) v_small[p] = __builtin_amdgcn_ballot_w64(top < v_low[0] + V_AMPLE);
             } else {
                 misfit |= __builtin_amdgcn_ballot_w64(top >= v_low[1] + V_SPAN) |
-                          (__builtin_amdgcn_ballot_w64(above >= V_SPAN && top != 0) & v_small[p]);
+                          (__builtin_amdgcn_ballot_w64(above >= V_SPAN && top != 0) & v_small[p] & v_heed);
             }
         }
         if constexpr (part >= 1 && part < 5) split_part(e, v_scale[x], std::integral_constant<int, part - 1>{});
@@ -765,6 +768,7 @@ __global__ __launch_bounds__(NTHREADS, (Geo<D, TAN>::WG_PER_CU)) void attn_jvp_m
         if (__builtin_expect(b + 3 >= n_blocks - 1, 0)) {        // from here on requests may be for the last block
             set_k_rows(b + 3);
             set_v_rows(b + 1 + V_AHEAD);
+            if (b + 1 >= n_blocks - 1 && Lkv % BC == 1) v_heed = 0;
         }
         scores(Nxt{}, [&](auto Kk) __attribute__((always_inline)) {
             constexpr int k = decltype(Kk)::value;
