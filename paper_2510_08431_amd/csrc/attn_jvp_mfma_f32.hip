@@ -18,8 +18,9 @@
 // printed, slow), as do infinities and NaN in the inputs.  Too large a value becomes inf in fp16 and shows in l, r or
 // the accumulators.  Too small ones would sink into fp16 subnormals unseen: the conversion looks at the largest of each
 // eight values of V and tV that it splits, and a row whose results come out small against what the split resolves is
-// found at the end (the weights of keys that hold the scale up may be nil).  l and r are summed in fp32 from the unrounded
-// weights.
+// found at the end (the weights of keys that hold the scale up may be nil).  Likewise the rows of Q, tQ, K and tK are looked
+// at for elements far below their row's largest; where it is keys, their weights decide.  l and r are summed in fp32 from the
+// unrounded weights.
 //
 // Work split: a workgroup of 4 waves owns 128 query rows, 32 per wave; key blocks of BC = 32 rows.  Products are taken
 // transposed, S^T = K Q^T and O^T += V^T P~^T, on v_mfma_f32_32x32x16_f16: the query index is the MFMA column (lane %
@@ -57,6 +58,9 @@ constexpr int TAN_ALL = 2;
 constexpr float LOG2E = 1.4426950408889634f;
 constexpr float LN2 = 0.6931471805599453f;
 constexpr int ROW_TOP = 12;      // rows of Q, tQ, K, tK: largest element in [2^12, 2^13)
+constexpr int EVEN_SPAN = 15;    // a row's eight neighbouring elements are known to 2^-22 of their largest if that is 2^-15 of the
+                                 // row's or more (2^-3 scaled); a row with smaller ones is called uneven
+constexpr float UNEVEN_SHARE = 0x1p-32f;    // share of a row's weights that uneven keys may have (2^-20 e^-8)
 constexpr int V_TOP = 11;        // first block of V: largest element in [2^11, 2^12), 4 binades in hand for later blocks
 constexpr int V_FLOOR = -3;      // eight keys of a column are known to 2^-22 of their largest if that is 2^-3 or more, scaled,
 constexpr uint32_t V_SPAN = 19u << 23;    // ... and fit into fp16 up to 2^16: 19 binades
@@ -137,6 +141,11 @@ __device__ __forceinline__ int top_exponent(float mx) {
     return e < 24 ? 24 : e;
 }
 __device__ __forceinline__ float pow2(int biased) { return __int_as_float(biased << 23); }
+// is the largest of some elements, not zero, below what the scale that the row's largest element sets suits?
+__device__ __forceinline__ bool below_span(float own, float row) {
+    const float low = fmaxf(row * pow2(127 - EVEN_SPAN), pow2(24 - EVEN_SPAN));
+    return __float_as_uint(own) - 1 < __float_as_uint(low) - 1;      // (a zero wraps around)
+}
 __device__ __forceinline__ u32x4 lds_read_b128(uint32_t addr) {
     return *reinterpret_cast<__attribute__((address_space(3))) const u32x4*>((uintptr_t)addr);
 }
@@ -164,7 +173,8 @@ struct Geo {
     static constexpr int V_BASE = 2 * STAGE;                    // two stages of K, then two of V
     static constexpr int F_BASE = 4 * STAGE;                    // row factors: [2 stages][K, tK][32] floats
     static constexpr int RED_BASE = F_BASE + 2 * 2 * BC * 4;    // scratch of the workgroup's reductions and votes
-    static constexpr int DUMMY_BASE = RED_BASE + 64;
+    static constexpr int UNEVEN_BASE = RED_BASE + 64;           // bits of the uneven keys of a block, by its index % 4
+    static constexpr int DUMMY_BASE = UNEVEN_BASE + 16;
     static constexpr int LDS_BYTES = DUMMY_BASE + 256 + 2 * 2 * BC * 4;
     static constexpr int WG_PER_CU = TAN == TAN_NONE || (TAN == TAN_QUERY && D == 32) ? 2 : 1;     // as the registers allow
     static constexpr int LPR = D == 96 ? 16 : D / 8;            // lanes that convert one K row, 8 elements each (D = 96: 12 of 16)
@@ -277,7 +287,8 @@ __global__ __launch_bounds__(NTHREADS, (Geo<D, TAN>::WG_PER_CU)) void attn_jvp_m
     uint64_t v_heed = ~0ull;     // (0: the block under way is one key, and one value of a column may well be small)
     uint64_t v_small[G::V_PASSES];       // lanes whose V of the block under way is small or zero
     uint32_t cv_h[4], cv_l[4];
-    float cv_mx, cv_m2, cv_sc;
+    float cv_mx, cv_m2, cv_sc, cv_own;
+    uint64_t uneven[N_KJ];       // lanes of the block under way that have met elements below their row's span
     // row factors: written by the first lane of a row (the others write to a place nobody reads: to one address their
     // writes would queue up)
     const uint32_t f_write = lds0 + (tid % G::LPR == 0 ? G::F_BASE + 4 * k_row : G::DUMMY_BASE + 4 * lane);
@@ -293,6 +304,7 @@ __global__ __launch_bounds__(NTHREADS, (Geo<D, TAN>::WG_PER_CU)) void attn_jvp_m
         if constexpr (part == 0) { cv_mx = max_abs3(e[0], e[1], e[2]); cv_m2 = max_abs3(e[3], e[4], e[5]); }
         if constexpr (part == 1) cv_mx = max_abs3(cv_mx, e[6], e[7]);
         if constexpr (part == 2) cv_mx = max_abs3(cv_mx, cv_m2, cv_m2);
+        if constexpr (part == 3) cv_own = cv_mx;
         if constexpr (part == 3) cv_mx = max_dpp<0xB1>(cv_mx);             // lanes ^ 1, ^ 2, mirrored in 8, mirrored in 16
         if constexpr (part == 4) cv_mx = max_dpp<0x4E>(cv_mx);
         if constexpr (part == 5 && G::LPR >= 8) cv_mx = max_dpp<0x141>(cv_mx);
@@ -300,6 +312,7 @@ __global__ __launch_bounds__(NTHREADS, (Geo<D, TAN>::WG_PER_CU)) void attn_jvp_m
         if constexpr (part == 7) {
             const int ex = top_exponent(cv_mx);
             cv_sc = pow2(254 + ROW_TOP - ex);
+            uneven[jb] = __builtin_amdgcn_ballot_w64(below_span(cv_own, cv_mx));
             lds_write_f32(f_write + (st * 2 + x) * (BC * 4) + 4 * p * G::K_ROWS, pow2(ex - ROW_TOP));
         }
         if constexpr (part >= 8 && part < 12) split_part(e, cv_sc, std::integral_constant<int, part - 8>{});
@@ -307,6 +320,24 @@ __global__ __launch_bounds__(NTHREADS, (Geo<D, TAN>::WG_PER_CU)) void attn_jvp_m
             const uint32_t at = k_write + st * G::STAGE + 2 * x * G::PLANE + p * G::K_ROWS * 2 * D;
             lds_write_b128(at, u32x4{cv_h[0], cv_h[1], cv_h[2], cv_h[3]});
             lds_write_b128(at + G::PLANE, u32x4{cv_l[0], cv_l[1], cv_l[2], cv_l[3]});
+        }
+    };
+    // The uneven keys of block blk into its word (as a rule there are none).  The word is cleared in the iteration after the
+    // one that reads it (uneven_done), two before those of block blk + 4 may come.
+    const uint32_t uneven_base = lds0 + G::UNEVEN_BASE;
+    if (tid < 4) lds_write_f32(uneven_base + 4 * tid, 0.f);
+    auto post_uneven = [&](int blk) __attribute__((always_inline)) {
+        uint64_t any = 0;
+#pragma unroll
+        for (int j = 0; j < N_KJ; ++j) any |= uneven[j];
+        if (__builtin_expect(any != 0, 0)) {
+            uint32_t row = k_row;
+            asm volatile("" : "+v"(row));
+#pragma unroll
+            for (int j = 0; j < N_KJ; ++j)
+                if (uneven[j] >> lane & 1)
+                    __hip_atomic_fetch_or(reinterpret_cast<__attribute__((address_space(3))) uint32_t*>((uintptr_t)(uneven_base + 4 * (blk & 3))),
+                                          1u << (row + j % G::K_PASSES * G::K_ROWS), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
         }
     };
     auto v_part = [&](auto J, auto ST, auto PART, const float (&e)[8]) __attribute__((always_inline)) {
@@ -388,12 +419,18 @@ __global__ __launch_bounds__(NTHREADS, (Geo<D, TAN>::WG_PER_CU)) void attn_jvp_m
     static_for<N_KJ>([&](auto J) { fetch_k(1, J, k1[decltype(J)::value]); });
     FENCE();
     auto split_query = [&](const float4 (*a)[2], u32x4* hi, u32x4* lo, float& f) __attribute__((always_inline)) {
-        float mx = 0.f;
+        float own[NT], mx = 0.f;
 #pragma unroll
-        for (int t = 0; t < NT; ++t)
-#pragma unroll
-            for (int u = 0; u < 2; ++u) mx = max_abs3(max_abs3(mx, a[t][u].x, a[t][u].y), a[t][u].z, a[t][u].w);
+        for (int t = 0; t < NT; ++t) {
+            const float4 a0 = a[t][0], a1 = a[t][1];
+            own[t] = max_abs3(max_abs3(a0.x, a0.y, a0.z), max_abs3(a0.w, a1.x, a1.y), max_abs3(a1.z, a1.w, a1.w));
+            mx = fmaxf(mx, own[t]);
+        }
         mx = xhalf_max(mx);
+        bool low = false;
+#pragma unroll
+        for (int t = 0; t < NT; ++t) low |= below_span(own[t], mx);
+        misfit |= __builtin_amdgcn_ballot_w64(low);
         const int ex = top_exponent(mx);
         const float s = sgn * pow2(254 + ROW_TOP - ex);
         f = pow2(ex - ROW_TOP);
@@ -492,6 +529,9 @@ __global__ __launch_bounds__(NTHREADS, (Geo<D, TAN>::WG_PER_CU)) void attn_jvp_m
     float go = 1.f, gt = 1.f, gr = 1.f / P_GAIN;                        // factors of the accumulators
     float alpha = 1.f;
     bool moved = false;
+    float w_uneven = 0.f;        // this lane's weights on uneven keys
+    uint32_t uneven_word = 0;    // of the block under way
+    uint32_t uneven_done = 0;    // address of a word to be cleared, or 0
     f32x16 acc_o[NC], acc_t[TANGENT ? NC : 1];
 #pragma unroll
     for (int n = 0; n < NC; ++n) {
@@ -544,7 +584,7 @@ __global__ __launch_bounds__(NTHREADS, (Geo<D, TAN>::WG_PER_CU)) void attn_jvp_m
             const float m_new = up ? mb : m;
             alpha = __builtin_amdgcn_exp2f((m - m_new) * LOG2E);
             m = m_new;
-            l *= alpha; r *= alpha;
+            l *= alpha; r *= alpha; w_uneven *= alpha;
             moved = true;
         }
     };
@@ -615,18 +655,45 @@ __global__ __launch_bounds__(NTHREADS, (Geo<D, TAN>::WG_PER_CU)) void attn_jvp_m
             if constexpr (TANGENT) { hh[4 + i] = nhh[i]; hl[4 + i] = nhl[i]; }
         }
     };
+    // Weights of the uneven keys of a block, from the high terms of the split ones: pairs 0-3 in ph, 4-7 still in nph.  Such a
+    // key's score may lack up to 2^-25 of each of its scaled elements times the query's (2^13 at most), and its weight that
+    // many nats: UNEVEN_SHARE leaves room for eight of them (a weight of zero is below 2^-37 of the row's reference), and
+    // where there may be more the tile is redone.  Keys that a channel masks weigh zero and cost nothing.
+    auto weigh_uneven = [&](uint32_t keys, uint32_t factors) __attribute__((always_inline)) {
+        uint32_t mine = keys >> (4 * g);
+        float most = 0.f;
+        asm volatile("" : "+v"(mine), "+v"(factors));        // (nothing of this is computed ahead: registers are short)
+        static_for<16>([&](auto E) {
+            constexpr int e = decltype(E)::value, key = 8 * (e / 4) + e % 4;
+            FENCE();
+            const f16x2 w = __builtin_bit_cast(f16x2, e < 8 ? ph[e / 2] : nph[e / 2 & 3]);
+            const float f = lds_read_f32(factors + 32 * (e / 4) + 4 * (e % 4));
+            w_uneven += mine & 1u << key ? (float)w[e & 1] : 0.f;
+            most = fmaxf(most, mine & 1u << key ? f : 0.f);
+        });
+        FENCE();
+        if (most * sq * (D * 0x1p-12f) > 8.f) w_uneven = INFINITY;
+    };
+    auto note_uneven = [&](int blk) __attribute__((always_inline)) {
+        const uint32_t keys = __builtin_amdgcn_readfirstlane(uneven_word);
+        if (__builtin_expect(keys != 0, 0)) {
+            weigh_uneven(keys, faddr + (blk & 1) * (2 * BC * 4));
+            uneven_done = uneven_base + 4 * (blk & 3);
+        }
+    };
     // the softmax of a block as a flat list: key factors by pairs, the row maximum, pairs 4-7, then pairs 0-3 (whose
     // registers the first half of the value products has read by the time the list gets there: see the assertion below)
     constexpr int S_PRE = 10, S_PARTS = S_PRE + 8 * W_PARTS;
     float mx_row;
     auto softmax_part = [&](auto IDX, auto ST, int blk) __attribute__((always_inline)) {
         constexpr int idx = decltype(IDX)::value;
+        if constexpr (idx == 0) uneven_word = __float_as_uint(lds_read_f32(uneven_base + 4 * (blk & 3)));
         if constexpr (idx < 8) key_factors(IDX, ST);
         else if constexpr (idx == 8) {
             if ((blk + 1) * BC > Lkv) mask_tail(blk);
             mx_row = row_max();
         } else if constexpr (idx == 9) follow_max(mx_row);
-        else weight_part(std::integral_constant<int, ((idx - S_PRE) / W_PARTS + 4) & 7>{}, ST, std::integral_constant<int, (idx - S_PRE) % W_PARTS>{});
+        if constexpr (idx >= S_PRE) weight_part(std::integral_constant<int, ((idx - S_PRE) / W_PARTS + 4) & 7>{}, ST, std::integral_constant<int, (idx - S_PRE) % W_PARTS>{});
     };
 
     // ---- value products of a block, small terms first ----------------------------------------------------------------
@@ -689,7 +756,8 @@ __global__ __launch_bounds__(NTHREADS, (Geo<D, TAN>::WG_PER_CU)) void attn_jvp_m
 #pragma unroll
             for (int i = 0; i < 8; i += 2) vm[x] = max_abs3(vm[x], v0[j][i], v0[j][i + 1]);
         });
-        __syncthreads();                                 // K(0) and its row factors are in
+        __syncthreads();                                 // K(0) and its row factors are in, the words of uneven keys cleared
+        post_uneven(0);
         scores(I0{}, nothing, nothing);
         static_for<3>([&](auto Qi) { read_factors(Qi, I0{}); });
         static_for<8>([&](auto E2) { key_factors(E2, I0{}); });
@@ -754,6 +822,9 @@ __global__ __launch_bounds__(NTHREADS, (Geo<D, TAN>::WG_PER_CU)) void attn_jvp_m
             constexpr int j = decltype(IDX)::value / K_PARTS;
             k_part(std::integral_constant<int, j>{}, I1{}, std::integral_constant<int, decltype(IDX)::value % K_PARTS>{}, k1[j]);
         });
+        post_uneven(1);
+        uneven_word = __float_as_uint(lds_read_f32(uneven_base));
+        note_uneven(0);
         __syncthreads();
     }
 
@@ -765,6 +836,10 @@ __global__ __launch_bounds__(NTHREADS, (Geo<D, TAN>::WG_PER_CU)) void attn_jvp_m
         using Nxt = std::integral_constant<int, par ^ 1>;
         next_weights();
         pin_accumulators();
+        if (__builtin_expect(uneven_done != 0, 0)) {
+            lds_write_f32(uneven_done, 0.f);
+            uneven_done = 0;
+        }
         if (__builtin_expect(b + 3 >= n_blocks - 1, 0)) {        // from here on requests may be for the last block
             set_k_rows(b + 3);
             set_v_rows(b + 1 + V_AHEAD);
@@ -785,6 +860,8 @@ __global__ __launch_bounds__(NTHREADS, (Geo<D, TAN>::WG_PER_CU)) void attn_jvp_m
             static_for<last - first>([&](auto I) { softmax_part(std::integral_constant<int, first + decltype(I)::value>{}, Nxt{}, b + 1); });
         });
         rescale();
+        post_uneven(b + 2);
+        note_uneven(b + 1);
         __syncthreads();     // the next block's planes are written by all, this one's read by all
     };
     // (The last iteration prepares a block past the end: a copy of the last one, all of whose keys are masked.  One loop
@@ -820,7 +897,7 @@ __global__ __launch_bounds__(NTHREADS, (Geo<D, TAN>::WG_PER_CU)) void attn_jvp_m
         }
     float l_row = xhalf_sum(l), r_row = xhalf_sum(r);
     top_o = xhalf_max(top_o);
-    if (misfit != 0 || too_small(top_o, l_row)) bad = 1.f;
+    if (misfit != 0 || too_small(top_o, l_row) || !(xhalf_sum(w_uneven) <= l_row * (P_GAIN * UNEVEN_SHARE))) bad = 1.f;
     if constexpr (TANGENT) {
         top_t = xhalf_max(top_t);
         if (too_small(top_t, l_row) && (r_row != 0.f || top_t != 0.f)) bad = 1.f;

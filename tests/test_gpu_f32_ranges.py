@@ -160,3 +160,26 @@ def test_rows_without_tangents(d):
     t = inputs(8, 150, 256, d)
     t["tq"][:, :, 100:] = 0.0
     check(t, "rows without tangents", names=("q", "k", "v", "tq"), columns=False)
+
+
+@DIMS
+@pytest.mark.parametrize("f", [1e4, 1e6, 1e9])
+@pytest.mark.parametrize("which", ["q", "k", "tq", "tk", "some keys"])
+def test_large_channel_that_the_other_side_leaves_out(which, f, d):
+    """One channel of `which` is large and meets zeros: it adds nothing to any score."""
+    t = inputs(9, 150, 256, d)
+    for n in ("q", "k", "tq", "tk"):
+        t[n][..., 1] = 0.0
+    if which == "some keys":
+        t["k"][:, :, 3::7, 1] = f
+    else:
+        t[which][..., 1] = f
+    check(t, f"channel of {which} at {f:g}")
+
+
+@DIMS
+def test_mask_in_a_channel(d):
+    """A channel masks every third key with -1e9; what the keys hold besides does not matter."""
+    t = inputs(10, 150, 256, d)
+    drop(t, slice(0, 256, 3), 1e9 / d ** 0.5)
+    check(t, "mask of -1e9")
