@@ -14,12 +14,13 @@
 //   weights: P~ 2^12 with P~ = exp(S - m) against a row reference m that trails the row maximum by at most 2.68 nats
 //     (so that keys 25 nats below the maximum still count); H~ 2^(12 - eH) with 2^eH from the first block's tangent
 //     scores and |tV| / |V|.
-// Values that these scales do not suit send the workgroup's tile to a pass with fp32 MFMAs at the end (redo_fp32: Alg. 2 as
-// printed, slow), as do infinities and NaN in the inputs.  Too large a value becomes inf in fp16 and shows in l, r or
-// the accumulators.  Too small ones would sink into fp16 subnormals unseen: the conversion looks at the largest of each
-// eight values of V and tV that it splits, and a row whose results come out small against what the split resolves is
-// found at the end (the weights of keys that hold the scale up may be nil).  Likewise the rows of Q, tQ, K and tK are looked
-// at for elements far below their row's largest; where it is keys, their weights decide.  l and r are summed in fp32 from the
+// Values that these scales do not suit send the workgroup's tile to a pass with fp32 MFMAs (fp32_tile), as do infinities
+// and NaN in the inputs.  Too large a value becomes inf in fp16 and shows in l, r or the accumulators.  Too small ones would
+// sink into fp16 subnormals unseen: the conversion looks at the largest of each eight values of V and tV that it splits, and
+// a row whose results come out small against what the split resolves is found at the end (the weights of keys that hold the
+// scale up may be nil).  Likewise the rows of Q, tQ, K and tK are looked at for elements far below their row's largest; where
+// it is keys, their weights decide.  What the conversion sees ends the sweep soon, what the end of the sweep sees
+// costs the sweep on top (B2 H16 L4096 d128: 6.4 ms for fp32 products alone).  l and r are summed in fp32 from the
 // unrounded weights.
 //
 // Work split: a workgroup of 4 waves owns 128 query rows, 32 per wave; key blocks of BC = 32 rows.  Products are taken
@@ -62,14 +63,13 @@ constexpr int EVEN_SPAN = 15;    // a row's eight neighbouring elements are know
                                  // row's or more (2^-3 scaled); a row with smaller ones is called uneven
 constexpr float UNEVEN_SHARE = 0x1p-32f;    // share of a row's weights that uneven keys may have (2^-20 e^-8)
 constexpr int V_TOP = 11;        // first block of V: largest element in [2^11, 2^12), 4 binades in hand for later blocks
-constexpr int V_FLOOR = -3;      // eight keys of a column are known to 2^-22 of their largest if that is 2^-3 or more, scaled,
-constexpr uint32_t V_SPAN = 19u << 23;    // ... and fit into fp16 up to 2^16: 19 binades
-constexpr uint32_t V_AMPLE = 9u << 23;    // 2^6: where V is that large tV may be smaller than 2^-3, its share of tO is known well enough
+constexpr int V_FLOOR = -3;      // eight keys of a column are known to 2^-22 of their largest if that is 2^-3 or more, scaled
+constexpr uint32_t V_AMPLE = 9u << 23;    // 2^6 in units of that: where V is as large tV may be smaller, its share of tO is known well enough
 constexpr float ROW_FLOOR = 16384.f;      // (2^7)^2: see the check at the end of the sweep
 constexpr int T_HEADROOM = 4;    // the first block's largest tangent score is scaled to [2^-4, 2^-3)
 constexpr float P_GAIN = 4096.f;          // the split weights are P~ 2^12 ...
 constexpr float P_SLACK = 2.68f;          // ... and stay below 2^16: nats by which a block may exceed the reference before it moves
-constexpr float FP32_SLACK = 32.f;        // redo_fp32: nats by which scores may exceed the reference
+constexpr float FP32_SLACK = 32.f;        // fp32_tile: nats by which scores may exceed the reference
 
 #define FENCE() __builtin_amdgcn_sched_barrier(0)      // no instruction is scheduled across this point
 
@@ -141,10 +141,9 @@ __device__ __forceinline__ int top_exponent(float mx) {
     return e < 24 ? 24 : e;
 }
 __device__ __forceinline__ float pow2(int biased) { return __int_as_float(biased << 23); }
-// is the largest of some elements, not zero, below what the scale that the row's largest element sets suits?
-__device__ __forceinline__ bool below_span(float own, float row) {
-    const float low = fmaxf(row * pow2(127 - EVEN_SPAN), pow2(24 - EVEN_SPAN));
-    return __float_as_uint(own) - 1 < __float_as_uint(low) - 1;      // (a zero wraps around)
+// is the largest of some elements of a row, not zero, below what the row's scale suits?  (factor: pow2(its exponent - ROW_TOP))
+__device__ __forceinline__ bool below_span(float own, float factor) {
+    return __float_as_uint(own) - 1 < __float_as_uint(factor) - ((uint32_t)(EVEN_SPAN - ROW_TOP) << 23) - 1;      // (a zero wraps around)
 }
 __device__ __forceinline__ u32x4 lds_read_b128(uint32_t addr) {
     return *reinterpret_cast<__attribute__((address_space(3))) const u32x4*>((uintptr_t)addr);
@@ -173,8 +172,8 @@ struct Geo {
     static constexpr int V_BASE = 2 * STAGE;                    // two stages of K, then two of V
     static constexpr int F_BASE = 4 * STAGE;                    // row factors: [2 stages][K, tK][32] floats
     static constexpr int RED_BASE = F_BASE + 2 * 2 * BC * 4;    // scratch of the workgroup's reductions and votes
-    static constexpr int UNEVEN_BASE = RED_BASE + 64;           // bits of the uneven keys of a block, by its index % 4
-    static constexpr int DUMMY_BASE = UNEVEN_BASE + 16;
+    static constexpr int NOTE_BASE = RED_BASE + 64;             // [block % 4]: bits of its uneven keys; not 0: the sweep is to end
+    static constexpr int DUMMY_BASE = NOTE_BASE + 32;
     static constexpr int LDS_BYTES = DUMMY_BASE + 256 + 2 * 2 * BC * 4;
     static constexpr int WG_PER_CU = TAN == TAN_NONE || (TAN == TAN_QUERY && D == 32) ? 2 : 1;     // as the registers allow
     static constexpr int LPR = D == 96 ? 16 : D / 8;            // lanes that convert one K row, 8 elements each (D = 96: 12 of 16)
@@ -186,6 +185,208 @@ struct Geo {
         return D == 128 ? (row & 15) : D == 64 ? ((row >> 1) & 7) : ((row >> 2) & 3);
     }
 };
+
+// 128-bit direct-to-LDS load: 64 lanes x 16 B land at lds_base + 16 * lane (M0 carries lds_base); uniform 64-bit base
+// in scalar registers plus a per-lane 32-bit byte offset.  Inline assembly so that the pass below keeps its own account of
+// these loads: an explicit wait plus the barrier at the end of each block publish a stage before anyone reads it.
+__device__ __forceinline__ void load_lds_b128(const void* uniform_base, uint32_t lane_off, uint32_t lds_base) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+                 :: "s"(lds_base), "v"(lane_off), "s"(uniform_base) : "memory");
+}
+
+// Alg. 2 in fp32 throughout for the workgroup's 128 query rows, v_mfma_f32_32x32x2_f32: what the split products cannot do.
+//   score step 4u + e (u < D/8, e < 4): A = K[key = c][8u + 4g + e], B = Q[query = c][8u + 4g + e]
+//   value step t < 16, column block n: A = V[key = 8(t/4) + 4g + t%4][32n + c], B = weight register t
+// Blocks of 32 keys go through two LDS stages as fp32, by direct-to-LDS loads; chunk x of a row sits at x ^ (row & 7), which
+// spreads the reads of either side over the banks.  Operands are read one step ahead; the weights of step t + 1 are computed
+// behind step t's products.  The row reference trails the running maximum by up to FP32_SLACK nats.  On entry the workgroup
+// has passed a barrier behind its last use of the LDS; l and r come back as this lane's part of the row sums.
+// (B2 H16 L4096 d128: 6.4 ms if every tile comes here; with unstaged loads it took 12.5.)
+template <int D, int TAN>
+__device__ __forceinline__ void fp32_tile(
+    const float* __restrict__ Q, const float* __restrict__ K, const float* __restrict__ V,
+    const float* __restrict__ tQ, const float* __restrict__ tK, const float* __restrict__ tV,
+    long q_row, long kv_base, long row_elems, int Lkv, float scale, uint32_t lds0, int lane, int wave,
+    f32x16 (&acc_o)[D / 32], f32x16 (&acc_t)[TAN != TAN_NONE ? D / 32 : 1], float& m, float& l, float& r) {
+#pragma clang fp contract(off)
+    constexpr bool TANGENT = TAN != TAN_NONE, KV_TANGENT = TAN == TAN_ALL;
+    constexpr int CH = D / 4;                        // 16-byte chunks per row
+    constexpr int TILE = BC * D * 4;                 // bytes of a tensor's staged block
+    constexpr int PT = BC * CH / NTHREADS;           // chunks each lane moves per tensor and block
+    constexpr int NT = KV_TANGENT ? 4 : 2;           // tensors staged: K, V (, tK, tV)
+    constexpr int NC = D / 32;
+    constexpr int T_K = 0, T_V = 1, T_TK = 2, T_TV = 3;
+    static_assert(2 * PT < D / 8 && 2 * PT < 16, "a block's parts fit the steps they are issued behind");
+    const int c = lane & 31, g = lane >> 5;
+
+    f32x4 q[D / 8], tq[TANGENT ? D / 8 : 1];         // columns 8u + 4g .. + 3 of the lane's row
+#pragma unroll
+    for (int u = 0; u < D / 8; ++u) {
+        q[u] = *reinterpret_cast<const f32x4*>(Q + q_row + 4 * g + 8 * u);
+        if constexpr (TANGENT) tq[u] = *reinterpret_cast<const f32x4*>(tQ + q_row + 4 * g + 8 * u);
+    }
+#pragma unroll
+    for (int u = 0; u < D / 8; ++u) asm volatile("" : "+a"(q[u]));       // only MFMAs read it
+
+    uint32_t g_off[PT];                              // byte offsets of the lane's chunks from the block's first row
+    int s_row[PT];
+    const int tid = 64 * wave + lane;
+#pragma unroll
+    for (int n = 0; n < PT; ++n) {
+        const int idx = tid + NTHREADS * n, row = idx / CH, pc = idx % CH;
+        s_row[n] = row;
+        g_off[n] = (uint32_t)((row * row_elems + 4 * (pc ^ (row & 7))) * (long)sizeof(float));
+    }
+    auto stage_part = [&](const float* base, int j0, int stage, int tensor, int n) __attribute__((always_inline)) {
+        const char* blk = reinterpret_cast<const char*>(base + kv_base + (long)j0 * row_elems);
+        const uint32_t dst = __builtin_amdgcn_readfirstlane(lds0 + (uint32_t)((stage * NT + tensor) * TILE + (64 * wave + NTHREADS * n) * 16));
+        // rows past the end re-read the block's first row (their weight is zero)
+        const bool dead = j0 + BC > Lkv && j0 + s_row[n] >= Lkv;
+        load_lds_b128(blk, dead ? g_off[n] - (uint32_t)(s_row[n] * row_elems * (long)sizeof(float)) : g_off[n], dst);
+    };
+    auto stage_in = [&](const float* base, int j0, int stage, int tensor) __attribute__((always_inline)) {
+#pragma unroll
+        for (int n = 0; n < PT; ++n) stage_part(base, j0, stage, tensor, n);
+    };
+#pragma unroll
+    for (int n = 0; n < NC; ++n) {
+        acc_o[n] = f32x16{};
+        if constexpr (TANGENT) acc_t[n] = f32x16{};
+    }
+    m = -INFINITY; l = 0.f; r = 0.f;
+    const int n_blocks = (Lkv + BC - 1) / BC;
+    stage_in(K, 0, 0, T_K);
+    stage_in(V, 0, 0, T_V);
+    if constexpr (KV_TANGENT) {
+        stage_in(tK, 0, 0, T_TK);
+        stage_in(tV, 0, 0, T_TV);
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+#pragma unroll 1
+    for (int blk = 0; blk < n_blocks; ++blk) {
+        const int cur = blk & 1, nxt = cur ^ 1, j0 = blk * BC;
+        const bool has_next = blk + 1 < n_blocks;
+        // ---- S^T = K Q^T, tS^T = K tQ^T + tK Q^T (three chains in turn); the next block's K, tK travel meanwhile
+        f32x16 s = f32x16{}, ts = f32x16{}, ts2 = f32x16{};
+        {
+            uint32_t lk[4];                          // chunk (2u + g) ^ (c & 7) = 8 (u/4) + ((2 (u%4) + g) ^ (c & 7))
+#pragma unroll
+            for (int w = 0; w < 4; ++w) lk[w] = lds0 + (uint32_t)((cur * NT + T_K) * TILE + (c * CH + ((2 * w + g) ^ (c & 7))) * 16);
+            f32x4 ka[2], tka[2];
+            ka[0] = lds_read_f32x4(lk[0]);
+            if constexpr (KV_TANGENT) tka[0] = lds_read_f32x4(lk[0] + (T_TK - T_K) * TILE);
+#pragma unroll
+            for (int u = 0; u < D / 8; ++u) {
+                if (u + 1 < D / 8) {
+                    const uint32_t at = lk[(u + 1) & 3] + 128 * ((u + 1) >> 2);
+                    ka[(u + 1) & 1] = lds_read_f32x4(at);
+                    if constexpr (KV_TANGENT) tka[(u + 1) & 1] = lds_read_f32x4(at + (T_TK - T_K) * TILE);
+                }
+                if (has_next) {                      // one 1-KiB part per wave and step
+                    if (u >= 1 && u <= PT) stage_part(K, j0 + BC, nxt, T_K, u - 1);
+                    if constexpr (KV_TANGENT)
+                        if (u > PT && u <= 2 * PT) stage_part(tK, j0 + BC, nxt, T_TK, u - PT - 1);
+                }
+                FENCE();
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    s = mfma32(ka[u & 1][e], q[u][e], s);
+                    if constexpr (TANGENT) ts = mfma32(ka[u & 1][e], tq[u][e], ts);
+                    if constexpr (KV_TANGENT) ts2 = mfma32(tka[u & 1][e], q[u][e], ts2);
+                }
+                FENCE();
+            }
+            asm volatile("" : "+v"(s));              // the vector ALU reads them: in arithmetic registers
+            if constexpr (TANGENT) asm volatile("" : "+v"(ts));
+            if constexpr (KV_TANGENT) {
+                asm volatile("" : "+v"(ts2));
+                ts += ts2;
+            }
+        }
+        // ---- online softmax on this lane's 16 keys: register e holds key j0 + 8(e/4) + 4g + e%4
+        const bool ragged = j0 + BC > Lkv;
+        float mb = -INFINITY;
+#pragma unroll
+        for (int e = 0; e < 16; ++e) mb = fmaxf(mb, ragged && j0 + 8 * (e / 4) + 4 * g + (e % 4) >= Lkv ? -INFINITY : s[e] * scale);
+        mb = xhalf_max(mb);
+        const float m_new = mb > m + FP32_SLACK ? mb : m;
+        const float alpha = __builtin_amdgcn_exp2f((m - m_new) * LOG2E);    // 0 on the first block (m = -inf), else 1 or tiny
+        m = m_new;
+        if (__builtin_expect(__builtin_amdgcn_ballot_w64(alpha != 1.f) != 0, 0)) {
+#pragma unroll
+            for (int n = 0; n < NC; ++n) {
+                asm volatile("" : "+a"(acc_o[n]));
+                acc_o[n] *= alpha;
+                asm volatile("" : "+a"(acc_o[n]));
+                if constexpr (TANGENT) {
+                    asm volatile("" : "+a"(acc_t[n]));
+                    acc_t[n] *= alpha;
+                    asm volatile("" : "+a"(acc_t[n]));
+                }
+            }
+        }
+        float p[16], h[16], row_p = 0.f, row_h = 0.f;
+        auto weigh = [&](auto E) __attribute__((always_inline)) {
+            constexpr int e = decltype(E)::value;
+            const bool dead = ragged && j0 + 8 * (e / 4) + 4 * g + (e % 4) >= Lkv;
+            p[e] = dead ? 0.f : __builtin_amdgcn_exp2f(fmaf(s[e], scale, -m_new) * LOG2E);
+            row_p += p[e];
+            if constexpr (TANGENT) {
+                h[e] = dead ? 0.f : p[e] * (ts[e] * scale);
+                row_h += h[e];
+            }
+        };
+        // ---- O^T += V^T P~^T, (A+B)^T += V^T H~^T + tV^T P~^T; the next block's V, tV travel meanwhile
+        {
+            uint32_t lv[4];                          // key row 8 (t/4) + 4g + t%4, column 32n + c at chunk ^ (row & 7)
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                lv[i] = lds0 + (uint32_t)((cur * NT + T_V) * TILE + (4 * g + i) * (D * 4) + (((c >> 2) ^ (4 * g + i)) << 4) + 4 * (c & 3));
+            constexpr int TV_OFF = (T_TV - T_V) * TILE;
+            float va[2][NC], tva[2][NC];
+#pragma unroll
+            for (int n = 0; n < NC; ++n) {
+                va[0][n] = lds_read_f32(lv[0] + 128 * n);
+                if constexpr (KV_TANGENT) tva[0][n] = lds_read_f32(lv[0] + 128 * n + TV_OFF);
+            }
+            weigh(std::integral_constant<int, 0>{});
+            static_for<16>([&](auto Tt) {
+                constexpr int t = decltype(Tt)::value;
+                if constexpr (t + 1 < 16) {
+#pragma unroll
+                    for (int n = 0; n < NC; ++n) {
+                        const uint32_t at = lv[(t + 1) & 3] + 8 * ((t + 1) >> 2) * (D * 4) + 128 * n;
+                        va[(t + 1) & 1][n] = lds_read_f32(at);
+                        if constexpr (KV_TANGENT) tva[(t + 1) & 1][n] = lds_read_f32(at + TV_OFF);
+                    }
+                }
+                if (has_next) {
+                    if (t >= 1 && t <= PT) stage_part(V, j0 + BC, nxt, T_V, t - 1);
+                    if constexpr (KV_TANGENT)
+                        if (t > PT && t <= 2 * PT) stage_part(tV, j0 + BC, nxt, T_TV, t - PT - 1);
+                }
+                FENCE();
+#pragma unroll
+                for (int n = 0; n < NC; ++n) acc_o[n] = mfma32(va[t & 1][n], p[t], acc_o[n]);
+                if constexpr (TANGENT) {
+#pragma unroll
+                    for (int n = 0; n < NC; ++n) acc_t[n] = mfma32(va[t & 1][n], h[t], acc_t[n]);
+                }
+                if constexpr (KV_TANGENT) {
+#pragma unroll
+                    for (int n = 0; n < NC; ++n) acc_t[n] = mfma32(tva[t & 1][n], p[t], acc_t[n]);
+                }
+                if constexpr (t + 1 < 16) weigh(std::integral_constant<int, t + 1>{});
+                FENCE();
+            });
+        }
+        l = fmaf(alpha, l, row_p);
+        r = fmaf(alpha, r, row_h);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");    // this wave's share of the next stage has landed
+        __syncthreads();     // next stage written by all, this stage read by all
+    }
+}
 
 template <int D, int TAN>
 __global__ __launch_bounds__(NTHREADS, (Geo<D, TAN>::WG_PER_CU)) void attn_jvp_mfma_f32_kernel(
@@ -282,13 +483,12 @@ __global__ __launch_bounds__(NTHREADS, (Geo<D, TAN>::WG_PER_CU)) void attn_jvp_m
     const uint32_t v_write = lds0 + G::V_BASE + (uint32_t)(lane * 64 + ((wave ^ ((lane >> 2) & 3)) << 4));
     const uint32_t v_write_last = lds0 + G::V_BASE + (uint32_t)(v_lane_last * 64 + ((wave ^ ((v_lane_last >> 2) & 3)) << 4));
     float v_scale[NX];                                   // set from the first block
-    uint32_t v_low[NX];          // (bits of) the smallest value that the scale suits, 2^V_FLOOR scaled
+    uint32_t v_low[NX], v_high[NX], v_ample;     // bits of 2^V_FLOOR, 2^16 and 2^6, scaled (v_low: less 1)
     uint64_t misfit = 0;         // lanes that have met values their tensor's scale does not suit
-    uint64_t v_heed = ~0ull;     // (0: the block under way is one key, and one value of a column may well be small)
     uint64_t v_small[G::V_PASSES];       // lanes whose V of the block under way is small or zero
     uint32_t cv_h[4], cv_l[4];
     float cv_mx, cv_m2, cv_sc, cv_own;
-    uint64_t uneven[N_KJ];       // lanes of the block under way that have met elements below their row's span
+    uint64_t uneven[G::K_PASSES];        // lanes of the block under way that have met elements below their row's span
     // row factors: written by the first lane of a row (the others write to a place nobody reads: to one address their
     // writes would queue up)
     const uint32_t f_write = lds0 + (tid % G::LPR == 0 ? G::F_BASE + 4 * k_row : G::DUMMY_BASE + 4 * lane);
@@ -312,8 +512,10 @@ __global__ __launch_bounds__(NTHREADS, (Geo<D, TAN>::WG_PER_CU)) void attn_jvp_m
         if constexpr (part == 7) {
             const int ex = top_exponent(cv_mx);
             cv_sc = pow2(254 + ROW_TOP - ex);
-            uneven[jb] = __builtin_amdgcn_ballot_w64(below_span(cv_own, cv_mx));
-            lds_write_f32(f_write + (st * 2 + x) * (BC * 4) + 4 * p * G::K_ROWS, pow2(ex - ROW_TOP));
+            const float factor = pow2(ex - ROW_TOP);
+            const uint64_t low = __builtin_amdgcn_ballot_w64(below_span(cv_own, factor));
+            uneven[p] = x ? uneven[p] | low : low;
+            lds_write_f32(f_write + (st * 2 + x) * (BC * 4) + 4 * p * G::K_ROWS, factor);
         }
         if constexpr (part >= 8 && part < 12) split_part(e, cv_sc, std::integral_constant<int, part - 8>{});
         if constexpr (part == 12) {
@@ -322,22 +524,24 @@ __global__ __launch_bounds__(NTHREADS, (Geo<D, TAN>::WG_PER_CU)) void attn_jvp_m
             lds_write_b128(at + G::PLANE, u32x4{cv_l[0], cv_l[1], cv_l[2], cv_l[3]});
         }
     };
-    // The uneven keys of block blk into its word (as a rule there are none).  The word is cleared in the iteration after the
-    // one that reads it (uneven_done), two before those of block blk + 4 may come.
-    const uint32_t uneven_base = lds0 + G::UNEVEN_BASE;
-    if (tid < 4) lds_write_f32(uneven_base + 4 * tid, 0.f);
-    auto post_uneven = [&](int blk) __attribute__((always_inline)) {
-        uint64_t any = 0;
+    // What the conversion of block blk has found, as a rule nothing, is noted for the next iteration, which weighs the block: its
+    // uneven keys, and that the rest of the sweep is for nothing.  The iteration after that clears the keys (noted), two
+    // before those of block blk + 4 may be noted in the same place.
+    const uint32_t note_base = lds0 + G::NOTE_BASE;
+    if (tid < 8) lds_write_f32(note_base + 4 * tid, 0.f);
+    auto write_note = [&](int blk) __attribute__((always_inline)) {
+        uint64_t any = misfit;
 #pragma unroll
-        for (int j = 0; j < N_KJ; ++j) any |= uneven[j];
+        for (int p = 0; p < G::K_PASSES; ++p) any |= uneven[p];
         if (__builtin_expect(any != 0, 0)) {
+            typedef __attribute__((address_space(3))) uint32_t lds_u32;
             uint32_t row = k_row;
             asm volatile("" : "+v"(row));
+            lds_u32* note = reinterpret_cast<lds_u32*>((uintptr_t)(note_base + 8 * (blk & 3)));
 #pragma unroll
-            for (int j = 0; j < N_KJ; ++j)
-                if (uneven[j] >> lane & 1)
-                    __hip_atomic_fetch_or(reinterpret_cast<__attribute__((address_space(3))) uint32_t*>((uintptr_t)(uneven_base + 4 * (blk & 3))),
-                                          1u << (row + j % G::K_PASSES * G::K_ROWS), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            for (int p = 0; p < G::K_PASSES; ++p)
+                if (uneven[p] >> lane & 1) __hip_atomic_fetch_or(note, 1u << (row + p * G::K_ROWS), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            if (misfit != 0) note[1] = 1;
         }
     };
     auto v_part = [&](auto J, auto ST, auto PART, const float (&e)[8]) __attribute__((always_inline)) {
@@ -345,13 +549,13 @@ __global__ __launch_bounds__(NTHREADS, (Geo<D, TAN>::WG_PER_CU)) void attn_jvp_m
         constexpr int st = decltype(ST)::value, part = decltype(PART)::value;
         if constexpr (part == 0) {                       // do the eight values, one column of eight keys, suit the scale?
             const uint32_t top = __float_as_uint(max_abs3(max_abs3(max_abs3(max_abs3(e[0], e[1], e[2]), e[3], e[4]), e[5], e[6]), e[7], e[7]));
-            const uint32_t above = top - v_low[x];       // (wraps around for smaller ones)
+            const uint64_t below = __builtin_amdgcn_ballot_w64(top - 1 < v_low[x]);      // (a zero wraps around)
+            misfit |= __builtin_amdgcn_ballot_w64(top >= v_high[x]);
             if constexpr (x == 0) {
-                misfit |= __builtin_amdgcn_ballot_w64(above >= V_SPAN && top != 0) & v_heed;
-                if constexpr (KV_TANGENT) v_small[p] = __builtin_amdgcn_ballot_w64(top < v_low[0] + V_AMPLE);
+                misfit |= below;
+                if constexpr (KV_TANGENT) v_small[p] = __builtin_amdgcn_ballot_w64(top < v_ample);
             } else {
-                misfit |= __builtin_amdgcn_ballot_w64(top >= v_low[1] + V_SPAN) |
-                          (__builtin_amdgcn_ballot_w64(above >= V_SPAN && top != 0) & v_small[p] & v_heed);
+                misfit |= below & v_small[p];
             }
         }
         if constexpr (part >= 1 && part < 5) split_part(e, v_scale[x], std::integral_constant<int, part - 1>{});
@@ -427,13 +631,13 @@ __global__ __launch_bounds__(NTHREADS, (Geo<D, TAN>::WG_PER_CU)) void attn_jvp_m
             mx = fmaxf(mx, own[t]);
         }
         mx = xhalf_max(mx);
-        bool low = false;
-#pragma unroll
-        for (int t = 0; t < NT; ++t) low |= below_span(own[t], mx);
-        misfit |= __builtin_amdgcn_ballot_w64(low);
         const int ex = top_exponent(mx);
         const float s = sgn * pow2(254 + ROW_TOP - ex);
         f = pow2(ex - ROW_TOP);
+        bool low = false;
+#pragma unroll
+        for (int t = 0; t < NT; ++t) low |= below_span(own[t], f);
+        misfit |= __builtin_amdgcn_ballot_w64(low);
 #pragma unroll
         for (int t = 0; t < NT; ++t) {
             const float e[8] = {a[t][0].x, a[t][0].y, a[t][0].z, a[t][0].w, a[t][1].x, a[t][1].y, a[t][1].z, a[t][1].w};
@@ -530,8 +734,8 @@ __global__ __launch_bounds__(NTHREADS, (Geo<D, TAN>::WG_PER_CU)) void attn_jvp_m
     float alpha = 1.f;
     bool moved = false;
     float w_uneven = 0.f;        // this lane's weights on uneven keys
-    uint32_t uneven_word = 0;    // of the block under way
-    uint32_t uneven_done = 0;    // address of a word to be cleared, or 0
+    f32x2 note;                  // of the block under way
+    bool noted = false;          // the last block's note is to be cleared
     f32x16 acc_o[NC], acc_t[TANGENT ? NC : 1];
 #pragma unroll
     for (int n = 0; n < NC; ++n) {
@@ -547,20 +751,22 @@ __global__ __launch_bounds__(NTHREADS, (Geo<D, TAN>::WG_PER_CU)) void attn_jvp_m
             if constexpr (TANGENT) asm volatile("" : "+a"(acc_t[n]));
         }
     };
-    // key factors by quarters of the block (registers 4 q .. + 3), requested three quarters ahead of their use
-    f32x4 kf[3];
+    // key factors by quarters of the block (registers 4 q .. + 3), requested three quarters ahead of their use (two where
+    // registers are shortest: D = 128 without tangents 867 -> 843 us on B2 H16 L4096)
+    constexpr int KF = TAN == TAN_NONE && D == 128 ? 2 : 3;
+    f32x4 kf[KF];
     auto read_factors = [&](auto Qi, auto ST) __attribute__((always_inline)) {
         constexpr int qi = decltype(Qi)::value;
-        if constexpr (qi < 4) kf[qi % 3] = lds_read_f32x4(faddr + decltype(ST)::value * (2 * BC * 4) + 32 * qi);
+        if constexpr (qi < 4) kf[qi % KF] = lds_read_f32x4(faddr + decltype(ST)::value * (2 * BC * 4) + 32 * qi);
     };
     auto key_factors = [&](auto E2, auto ST) __attribute__((always_inline)) {     // registers 2 E2, 2 E2 + 1
         constexpr int e0 = 2 * decltype(E2)::value, qi = e0 / 4;
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
-            s[e0 + i] *= kf[qi % 3][e0 % 4 + i];
-            if constexpr (TANGENT) ts1[e0 + i] *= kf[qi % 3][e0 % 4 + i];
+            s[e0 + i] *= kf[qi % KF][e0 % 4 + i];
+            if constexpr (TANGENT) ts1[e0 + i] *= kf[qi % KF][e0 % 4 + i];
         }
-        if constexpr (e0 % 4 == 2) read_factors(std::integral_constant<int, qi + 3>{}, ST);
+        if constexpr (e0 % 4 == 2) read_factors(std::integral_constant<int, qi + KF>{}, ST);
     };
     auto mask_tail = [&](int blk) __attribute__((always_inline)) {         // keys past the end weigh nothing
         const int jb = blk * BC + 4 * g;
@@ -674,12 +880,13 @@ __global__ __launch_bounds__(NTHREADS, (Geo<D, TAN>::WG_PER_CU)) void attn_jvp_m
         FENCE();
         if (most * sq * (D * 0x1p-12f) > 8.f) w_uneven = INFINITY;
     };
-    auto note_uneven = [&](int blk) __attribute__((always_inline)) {
-        const uint32_t keys = __builtin_amdgcn_readfirstlane(uneven_word);
-        if (__builtin_expect(keys != 0, 0)) {
-            weigh_uneven(keys, faddr + (blk & 1) * (2 * BC * 4));
-            uneven_done = uneven_base + 4 * (blk & 3);
-        }
+    auto read_note = [&](int blk) __attribute__((always_inline)) { note = lds_read_f32x2(note_base + 8 * (blk & 3)); };
+    auto heed_note = [&](int blk) __attribute__((always_inline)) -> bool {      // true: the sweep is to end
+        const uint32_t keys = __float_as_uint(note[0]), stop = __float_as_uint(note[1]);
+        if (__builtin_expect(__builtin_amdgcn_readfirstlane(keys | stop) == 0, 1)) return false;
+        weigh_uneven(keys, faddr + (blk & 1) * (2 * BC * 4));
+        noted = true;
+        return __builtin_amdgcn_readfirstlane(stop) != 0;
     };
     // the softmax of a block as a flat list: key factors by pairs, the row maximum, pairs 4-7, then pairs 0-3 (whose
     // registers the first half of the value products has read by the time the list gets there: see the assertion below)
@@ -687,7 +894,7 @@ __global__ __launch_bounds__(NTHREADS, (Geo<D, TAN>::WG_PER_CU)) void attn_jvp_m
     float mx_row;
     auto softmax_part = [&](auto IDX, auto ST, int blk) __attribute__((always_inline)) {
         constexpr int idx = decltype(IDX)::value;
-        if constexpr (idx == 0) uneven_word = __float_as_uint(lds_read_f32(uneven_base + 4 * (blk & 3)));
+        if constexpr (idx == S_PARTS - 4) read_note(blk);
         if constexpr (idx < 8) key_factors(IDX, ST);
         else if constexpr (idx == 8) {
             if ((blk + 1) * BC > Lkv) mask_tail(blk);
@@ -757,9 +964,9 @@ __global__ __launch_bounds__(NTHREADS, (Geo<D, TAN>::WG_PER_CU)) void attn_jvp_m
             for (int i = 0; i < 8; i += 2) vm[x] = max_abs3(vm[x], v0[j][i], v0[j][i + 1]);
         });
         __syncthreads();                                 // K(0) and its row factors are in, the words of uneven keys cleared
-        post_uneven(0);
+        write_note(0);
         scores(I0{}, nothing, nothing);
-        static_for<3>([&](auto Qi) { read_factors(Qi, I0{}); });
+        static_for<KF>([&](auto Qi) { read_factors(Qi, I0{}); });
         static_for<8>([&](auto E2) { key_factors(E2, I0{}); });
         if (BC > Lkv) mask_tail(0);
         m = row_max() * sq;
@@ -800,11 +1007,14 @@ __global__ __launch_bounds__(NTHREADS, (Geo<D, TAN>::WG_PER_CU)) void attn_jvp_m
         go = ldexpf(1.f, eV - 12);
         gt = ldexpf(1.f, eV + eH - 12);
         v_scale[0] = ldexpf(1.f, -eV);
-        v_low[0] = (uint32_t)(eV + V_FLOOR + 127) << 23;
-        if constexpr (KV_TANGENT) {
-            v_scale[1] = ldexpf(1.f, -(eV + eH));
-            v_low[1] = (uint32_t)(eV + eH + V_FLOOR + 127) << 23;
+        if constexpr (KV_TANGENT) v_scale[1] = ldexpf(1.f, -(eV + eH));
+#pragma unroll
+        for (int x = 0; x < NX; ++x) {
+            const uint32_t one = (uint32_t)(eV + x * eH + 127) << 23;
+            v_low[x] = __builtin_amdgcn_readfirstlane(one + (uint32_t)V_FLOOR * (1u << 23) - 1);
+            v_high[x] = __builtin_amdgcn_readfirstlane(one < (239u << 23) ? one + (16u << 23) : 255u << 23);
         }
+        v_ample = v_low[0] + V_AMPLE;
         ftqh = ldexpf(abs_scale * ftq, 12 - eH);
         fqh = ldexpf(abs_scale * fq, 12 - eH);
         static_for<8 * W_PARTS>([&](auto IDX) {
@@ -822,28 +1032,31 @@ __global__ __launch_bounds__(NTHREADS, (Geo<D, TAN>::WG_PER_CU)) void attn_jvp_m
             constexpr int j = decltype(IDX)::value / K_PARTS;
             k_part(std::integral_constant<int, j>{}, I1{}, std::integral_constant<int, decltype(IDX)::value % K_PARTS>{}, k1[j]);
         });
-        post_uneven(1);
-        uneven_word = __float_as_uint(lds_read_f32(uneven_base));
-        note_uneven(0);
+        write_note(1);
+        read_note(0);
+        heed_note(0);
         __syncthreads();
     }
 
     // ---- sweep: iteration b does the scores of block b + 1 over the conversion of K(b + 2) and V(b + 1), then the values of
     // block b over the softmax of block b + 1.  Stage of a block: its index & 1.
-    auto iteration = [&](auto PAR, int b) __attribute__((always_inline)) {
+    auto iteration = [&](auto PAR, int b) __attribute__((always_inline)) -> bool {
         constexpr int par = decltype(PAR)::value;
         using Cur = std::integral_constant<int, par>;
         using Nxt = std::integral_constant<int, par ^ 1>;
         next_weights();
         pin_accumulators();
-        if (__builtin_expect(uneven_done != 0, 0)) {
-            lds_write_f32(uneven_done, 0.f);
-            uneven_done = 0;
+        if (__builtin_expect(noted, 0)) {
+            lds_write_f32(note_base + 8 * (b & 3), 0.f);
+            noted = false;
         }
         if (__builtin_expect(b + 3 >= n_blocks - 1, 0)) {        // from here on requests may be for the last block
             set_k_rows(b + 3);
             set_v_rows(b + 1 + V_AHEAD);
-            if (b + 1 >= n_blocks - 1 && Lkv % BC == 1) v_heed = 0;
+            if (b + 1 >= n_blocks - 1 && Lkv % BC == 1) {      // one key, and one value of a column may well be small
+                v_low[0] = 0;
+                if constexpr (KV_TANGENT) v_low[1] = 0;
+            }
         }
         scores(Nxt{}, [&](auto Kk) __attribute__((always_inline)) {
             constexpr int k = decltype(Kk)::value;
@@ -851,7 +1064,7 @@ __global__ __launch_bounds__(NTHREADS, (Geo<D, TAN>::WG_PER_CU)) void attn_jvp_m
             static_for<last - first>([&](auto I) { convert_part(std::integral_constant<int, first + decltype(I)::value>{}, Cur{}, Nxt{}, b + 2, b + 1); });
         }, [&](auto LO) __attribute__((always_inline)) {
             read_v(I0{}, Cur{}, LO);
-            if constexpr (decltype(LO)::value) static_for<3>([&](auto Qi) { read_factors(Qi, Nxt{}); });
+            if constexpr (decltype(LO)::value) static_for<KF>([&](auto Qi) { read_factors(Qi, Nxt{}); });
         });
         static_assert((S_PRE + 4 * W_PARTS) * M2 / S_PARTS >= M2 / 2, "pairs 0-3 come behind the second half of the value products");
         values(Cur{}, [&](auto Kk) __attribute__((always_inline)) {
@@ -860,17 +1073,17 @@ __global__ __launch_bounds__(NTHREADS, (Geo<D, TAN>::WG_PER_CU)) void attn_jvp_m
             static_for<last - first>([&](auto I) { softmax_part(std::integral_constant<int, first + decltype(I)::value>{}, Nxt{}, b + 1); });
         });
         rescale();
-        post_uneven(b + 2);
-        note_uneven(b + 1);
+        if constexpr (TANGENT) misfit |= __builtin_amdgcn_ballot_w64(!(fabsf(rb) < 0x1p20f));      // sixteen H~ of fp16 size stay below
+        write_note(b + 2);
+        const bool stop = heed_note(b + 1);
         __syncthreads();     // the next block's planes are written by all, this one's read by all
+        return stop;
     };
     // (The last iteration prepares a block past the end: a copy of the last one, all of whose keys are masked.  One loop
     // body for all blocks; a copy of it for the tail made the register allocator move accumulators and operands around.)
     for (int b = 0;;) {
-        iteration(I0{}, b);
-        if (++b >= n_blocks) break;
-        iteration(I1{}, b);
-        if (++b >= n_blocks) break;
+        if (iteration(I0{}, b) || ++b >= n_blocks) break;
+        if (iteration(I1{}, b) || ++b >= n_blocks) break;
     }
 
     // ---- did the scales suit?  If not, the workgroup redoes its tile ------------------------------------------------------
@@ -906,83 +1119,12 @@ __global__ __launch_bounds__(NTHREADS, (Geo<D, TAN>::WG_PER_CU)) void attn_jvp_m
     __syncthreads();
     const bool redo = __builtin_amdgcn_readfirstlane(__float_as_int(lds_read_f32(lds0 + G::RED_BASE + 48))) != 0;
     if (__builtin_expect(redo, 0)) {
-        // ---- Alg. 2 in fp32 throughout: operands straight from memory, v_mfma_f32_32x32x2_f32.  Score step 4u + e: A =
-        // K[key = c][8u + 4g + e], B = Q[query = c][8u + 4g + e]; value step t: A = V[key 8(t/4) + 4g + t%4][32n + c],
-        // B = weight register t.  The row reference trails the running maximum by up to FP32_SLACK nats.
-#pragma unroll
-        for (int n = 0; n < NC; ++n) {
-            acc_o[n] = f32x16{};
-            if constexpr (TANGENT) acc_t[n] = f32x16{};
-        }
-        m = -INFINITY; l_row = 0.f; r_row = 0.f; go = 1.f; gt = 1.f; gr = 1.f;
-        const float* qp = Q + q_base + (long)qload * row_elems + 4 * g;
-        const float* tqp = TANGENT ? tQ + q_base + (long)qload * row_elems + 4 * g : nullptr;
-        for (int blk = 0; blk < n_blocks; ++blk) {
-            const int j0 = blk * BC;
-            const int krow = j0 + c < Lkv ? j0 + c : Lkv - 1;
-            const long koff = kv_base + (long)krow * row_elems + 4 * g;
-            s = f32x16{}; ts1 = f32x16{};
-#pragma unroll 1
-            for (int u = 0; u < D / 8; ++u) {
-                const float4 ka = *reinterpret_cast<const float4*>(K + koff + 8 * u);
-                const float4 qa = *reinterpret_cast<const float4*>(qp + 8 * u);
-                const float kv[4] = {ka.x, ka.y, ka.z, ka.w}, qv[4] = {qa.x, qa.y, qa.z, qa.w};
-#pragma unroll
-                for (int e = 0; e < 4; ++e) s = mfma32(kv[e], qv[e], s);
-                if constexpr (TANGENT) {
-                    const float4 ta = *reinterpret_cast<const float4*>(tqp + 8 * u);
-                    const float tv[4] = {ta.x, ta.y, ta.z, ta.w};
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) ts1 = mfma32(kv[e], tv[e], ts1);
-                }
-                if constexpr (KV_TANGENT) {
-                    const float4 tka = *reinterpret_cast<const float4*>(tK + koff + 8 * u);
-                    const float tkv[4] = {tka.x, tka.y, tka.z, tka.w};
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) ts1 = mfma32(tkv[e], qv[e], ts1);
-                }
-            }
-            float mb = -INFINITY;
-#pragma unroll
-            for (int e = 0; e < 16; ++e) {
-                const bool dead = j0 + 8 * (e / 4) + 4 * g + (e % 4) >= Lkv;
-                mb = fmaxf(mb, dead ? -INFINITY : s[e] * scale);
-            }
-            mb = xhalf_max(mb);
-            const float m_new = mb > m + FP32_SLACK ? mb : m;
-            alpha = __builtin_amdgcn_exp2f((m - m_new) * LOG2E);    // 0 on the first block (m = -inf), else 1 or tiny
-            m = m_new;
-            moved = __builtin_amdgcn_ballot_w64(alpha != 1.f) != 0;
-            rescale();
-            float p[16], h[16];
-            float row_p = 0.f, row_h = 0.f;
-#pragma unroll
-            for (int e = 0; e < 16; ++e) {
-                const bool dead = j0 + 8 * (e / 4) + 4 * g + (e % 4) >= Lkv;
-                p[e] = dead ? 0.f : __builtin_amdgcn_exp2f(fmaf(s[e], scale, -m) * LOG2E);
-                row_p += p[e];
-                if constexpr (TANGENT) {
-                    h[e] = dead ? 0.f : p[e] * (ts1[e] * scale);
-                    row_h += h[e];
-                }
-            }
-            l_row = fmaf(alpha, l_row, row_p);
-            r_row = fmaf(alpha, r_row, row_h);
-#pragma unroll
-            for (int t = 0; t < 16; ++t) {
-                FENCE();       // (few registers are left for loads issued ahead)
-                int row = j0 + 8 * (t / 4) + 4 * g + (t % 4);
-                row = row < Lkv ? row : Lkv - 1;
-                const long voff = kv_base + (long)row * row_elems + c;
-#pragma unroll
-                for (int n = 0; n < NC; ++n) {
-                    const float va = V[voff + 32 * n];
-                    acc_o[n] = mfma32(va, p[t], acc_o[n]);
-                    if constexpr (TANGENT) acc_t[n] = mfma32(va, h[t], acc_t[n]);
-                    if constexpr (KV_TANGENT) acc_t[n] = mfma32(tV[voff + 32 * n], p[t], acc_t[n]);
-                }
-            }
-        }
+        static_assert(2 * (KV_TANGENT ? 4 : 2) * BC * D * 4 <= G::F_BASE, "its stages fit, clear of the vote");
+        go = 1.f; gt = 1.f; gr = 1.f;
+        int here = lane, row = qload, w = wave;      // (nothing that it derives from these is kept across the sweep)
+        asm volatile("" : "+v"(here), "+v"(row), "+s"(w));
+        fp32_tile<D, TAN>(Q, K, V, tQ, tK, tV, q_base + (long)row * row_elems, kv_base, row_elems, Lkv, scale, lds0, here, w,
+                          acc_o, acc_t, m, l_row, r_row);
         l_row = xhalf_sum(l_row);
         r_row = xhalf_sum(r_row);
     }
