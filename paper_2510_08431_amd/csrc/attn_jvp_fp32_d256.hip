@@ -29,7 +29,10 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 constexpr int D = 256, BR = 64, BC = 16, NTHREADS = 256;
 constexpr int CH = D / 4;                    // 16-byte chunks of an fp32 row
 constexpr int TAN_NONE = 0, TAN_QUERY = 1, TAN_ALL = 2;
-constexpr float MAX_SLACK = 32.f;            // nats by which a row's scores may exceed its reference m before m is moved
+// Nats by which a row's scores may exceed m before m is moved.  The weights are exp(S - (m + MAX_SLACK)), never above 1, so that
+// values up to the end of the fp32 range stay in it; the price, weights that flush to zero MAX_SLACK nats earlier, is why
+// there are few.
+constexpr float MAX_SLACK = 4.f;
 
 template <typename T> struct In;             // four consecutive elements as they are in memory, and upcast
 template <> struct In<float> {
@@ -162,7 +165,7 @@ __global__ __launch_bounds__(NTHREADS, 1) void attn_jvp_fp32_d256_kernel(
             if constexpr (TANGENT) ts_part[level] = tu;
         }
         const f32x4 s = s_part[4], ts = ts_part[TANGENT ? 4 : 0];
-        // ---- online softmax on the lane's four keys; the reference trails the row maximum by up to MAX_SLACK
+        // ---- online softmax on the lane's four keys; m trails the row maximum by up to MAX_SLACK
         float mb = -INFINITY;
         bool dead[4];
 #pragma unroll
@@ -176,7 +179,7 @@ __global__ __launch_bounds__(NTHREADS, 1) void attn_jvp_fp32_d256_kernel(
         const float m_new = mb > m + MAX_SLACK ? mb : m;
         const float alpha = m_new == m ? 1.f : expf(m - m_new);         // 0 when the first finite score comes (m = -inf)
         m = m_new;
-        const float m_ref = m == -INFINITY ? 0.f : m;    // (scores of -inf so far: weight 0, not NaN)
+        const float m_ref = m == -INFINITY ? 0.f : m + MAX_SLACK;       // (scores of -inf so far: weight 0, not NaN)
         if (__builtin_amdgcn_ballot_w64(alpha != 1.f) != 0) {
 #pragma unroll
             for (int n = 0; n < 16; ++n) {
@@ -242,7 +245,7 @@ __global__ __launch_bounds__(NTHREADS, 1) void attn_jvp_fp32_d256_kernel(
                 store4(op + 64 * cq + 4 * r, o4);
                 if constexpr (TANGENT) store4(top + 64 * cq + 4 * r, t4);
             }
-        if (gg == 0) LSE[bh * Lq + qrow] = row_top + logf(l_row * expf(m - row_top));
+        if (gg == 0) LSE[bh * Lq + qrow] = row_top + logf(l_row * expf(m + MAX_SLACK - row_top));
     }
 }
 

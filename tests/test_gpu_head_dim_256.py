@@ -89,3 +89,21 @@ def test_keys_at_minus_infinity_weigh_nothing():
     ref = attn_jvp_ref(*cut, SCALE)
     assert np.abs(o.cpu().double().numpy() - ref[0]).max() <= 1e-5 * np.sqrt((ref[0] ** 2).mean())
     assert np.abs(lse.cpu().double().numpy() - ref[2]).max() <= 1e-5
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+def test_values_near_the_end_of_the_range_under_rising_scores(dtype):
+    """Scores rise by 25 nats along the keys (the reference follows, the weights stay at most 1): V, tV of 1e36 must not
+    overflow, as they do not in O and tO.  Inputs scaled down by the same factor give the same numbers, up to the rounding
+    of that factor."""
+    t = inputs(14, 1, 2, 40, 100, dtype, gain=0.25)
+    t[0][..., 0] = 4.0
+    t[1][..., 0] = torch.arange(100).to(dtype) * (1 / SCALE) / 4 * 0.25
+    for x in (t[3], t[4]):
+        x.mul_(2.0 ** -6)
+    big = [x * 2.0 ** 119 if i in (2, 5) else x for i, x in enumerate(t)]       # (an exact factor)
+    small, large = run(t), run(big)
+    check(small, t, "rising scores", tol=1e-5 + 40 * 2.0 ** -24 * 30)
+    for a, b in zip(small[:2], large[:2]):
+        assert torch.isfinite(b).all() and torch.equal(b, a * 2.0 ** 119)
+    assert torch.equal(small[2], large[2])
