@@ -143,7 +143,7 @@ def test_auto_takes_this_kernel_for_fp32_inputs():
     for a, b in zip(auto, mfma):
         np.testing.assert_array_equal(a, b)
     assert any((a != b).any() for a, b in zip(auto, vec)), "AUTO gave the vector kernel's bits"
-    # d = 256 is not built for the matrix cores: AUTO falls back to the vector kernel, an explicit request fails
+    # d = 256 is not one of this kernel's: AUTO takes the kernel of its own, an explicit request fails
     t = random_inputs(9, 1, 1, 40, 50, 256)
     compare(to_np(run(t, 1 / 16, kernel=binding.KERNEL_AUTO)), oracle(t, 1 / 16), "auto fp32 d=256", 50)
     with pytest.raises(binding.AttnJvpError):
@@ -225,6 +225,7 @@ def test_video_length_key_sequence():
 
 # The kernel splits every operand into two fp16 terms, scaled by powers of two that come from the row (Q, tQ, K, tK) or
 # from the first key block (V, tV, the tangent scores); what does not fit must end in the fp32 pass over the tile.
+# (Magnitudes that differ between keys, rows, columns or channels, row by row and column by column: test_gpu_f32_ranges.py.)
 RANGE_CASES = ["v-grows", "v-starts-at-zero", "v-shrinks", "k-rows-spread", "tiny-tangents", "huge-tangents", "late-tangents",
                "tiny-queries", "one-dominant-key"]
 

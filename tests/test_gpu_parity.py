@@ -706,7 +706,7 @@ def test_f16_path_error_margin_over_seeds(case):
 @pytest.mark.parametrize("case", ["f16", "bf16-pairs", "f16-declined-to-pairs", "f16-declined-to-online", "f16-null-kv", "f16-d64",
                                   "pairs-d64", "f16-five-keys", "f16-mixed-heads"])
 def test_resident_workgroups_walk_their_tiles_like_one_workgroup_per_tile(case):
-    """With at least two query tiles per compute unit (four at head dimension 64) the sweep runs with resident workgroups
+    """With at least two query tiles per compute unit (four at head dimension 64 and without tangents) the sweep runs with resident workgroups
     that walk through their tiles and request the next tile's first rows ahead of time; with short key sequences the
     hand-over launches of the fp16 path do the same.  Nothing of that may change a bit: the outputs equal those of a
     launch with one workgroup per tile (ATTN_JVP_FLAG_NO_RESIDENT), in both layouts, heads and tiles ragged; plus
@@ -781,9 +781,9 @@ def test_mfma_bf16_outputs_are_the_rounded_fp32_outputs(variant):
 
 @pytest.mark.parametrize("case", ["f16", "bf16-pairs", "fast", "pairs-null-kv", "no-tangents", "blhd-bf16-out", "default-long"])
 @pytest.mark.parametrize("d", [32, 64, 96])
-def test_mfma_small_head_dims_through_zero_padded_copies(d, case):
-    """d = 64 is built natively; d in {32, 96}: given a workspace the MFMA kernel runs on copies of the inputs padded
-    with zero columns to 128 (the padding adds exact zeros to every product) and stores only the first d columns."""
+def test_mfma_head_dims_that_need_a_workspace(d, case):
+    """d = 64 and 96 are built natively, 96 like 32 only given a workspace; at 32 the MFMA kernel runs on copies of the inputs
+    padded with zero columns to 64 (the padding adds exact zeros to every product) and stores only the first d columns."""
     B, H, Lq, Lkv, flags, kw, null_kv, no_tan = 2, 2, 150, 333, 0, {}, False, False
     if case == "f16":
         flags = binding.FLAG_F16_ALWAYS
