@@ -81,7 +81,7 @@ extern "C" {
 
 /* attn_jvp_opts.kernel */
 #define ATTN_JVP_KERNEL_AUTO 0    /* bf16, scale > 0 and d in {64, 128} (or d in {32, 96} with a workspace) -> bf16 MFMA kernel;
-                                     fp32 and d in {32, 64, 96, 128} -> fp32 MFMA kernel; everything else -> vector kernel */
+                                     fp32 and d in {32, 64, 96, 128} -> split-operand MFMA kernel; everything else -> KERNEL_FP32 */
 #define ATTN_JVP_KERNEL_FP32 1    /* fp32 streaming kernels, any dtype: d in {32, 64, 128} on the vector ALU (slow), d = 256
                                      on fp32 matrix instructions */
 #define ATTN_JVP_KERNEL_MFMA 2    /* matrix-core kernels.
@@ -91,9 +91,13 @@ extern "C" {
                                      padding adds zeros to every product; half of the matrix work is spent on zeros).
                                      fp32 inputs: d in {32, 64, 96, 128}, any finite scale, fp32 outputs; every product
                                      as three 16-bit products of operands split into two fp16 terms each (22 to 23
-                                     bits), fp32 accumulation, no workspace, flags ignored.  Tiles whose values do not
-                                     fit the scaled fp16 ranges (a key block with values 16 times those of the first,
-                                     infinities, NaN) are computed again with fp32 products, at several times the cost.
+                                     bits), fp32 accumulation, no workspace, flags ignored.  Tiles (128 query rows)
+                                     whose values do not suit the scaled fp16 ranges are computed with fp32 products
+                                     instead: V of later keys 16 times or 2^-14 of the first 32 keys' (zeros in front
+                                     are enough), whole columns of V 2^-14 of the largest, rows of q or tq that span
+                                     more than 2^15, infinities and NaN take about three times the time; rows whose
+                                     weight lies on keys with V near zero, whose tangents are 2^-9 of their
+                                     neighbours', or whose weight lies on keys that span more than 2^15, four times.
                                      Accuracy contract of this path: l, r and the accumulators are fp32 running sums
                                      over the keys, so max |x - x_exact| / RMS(x) of o and to is within 1e-5 up to
                                      256 keys and grows like sqrt(Lkv) beyond: within 1.5e-5 sqrt(Lkv / 256)
@@ -130,10 +134,11 @@ extern "C" {
                                      the GPU is otherwise idle.  If it does not hold, only speed is lost. */
 
 #define ATTN_JVP_FLAG_NO_RESIDENT 16 /* MFMA kernel only: launch one workgroup per 128-row query tile and let the hardware hand
-                                     them out, instead of one resident workgroup per compute unit that walks through
-                                     its share of the tiles (the default from two tiles per compute unit on).
+                                     them out, instead of resident workgroups, one per compute unit, that walk through
+                                     their share of the tiles (the default from two tiles per compute unit on; two per
+                                     unit, from four tiles on, at d = 64 and without tangents).
                                      Results are identical.  For callers that run other kernels on the same GPU at
-                                     the same time: resident workgroups assume they get a compute unit each. */
+                                     the same time: resident workgroups assume they get the units to themselves. */
 
 typedef struct attn_jvp_opts {
     int    in_dtype;        /* ATTN_JVP_BF16 or ATTN_JVP_FP32: dtype of q, k, v, tq, tk, tv */

@@ -296,7 +296,9 @@ hipError_t launch_f16_prepass(const Problem& p, int cus, F16Workspace* out) {
     float* partials = reinterpret_cast<float*>(ws + l.stats_bytes + l.flags_bytes + 2 * l.vals_bytes);
     // tickets of the online tier's lock-step start: 8 XCDs x one counter per 64 bytes, after the flags
     float* tickets = reinterpret_cast<float*>(ws + l.stats_bytes + l.flags_bytes - 512);
-    out->lockstep_slots = cus % 8 == 0 ? cus / 8 : 0;   // one workgroup per compute unit, eight XCDs
+    // a round of the lock-step start: one workgroup per compute unit of an XCD, which is half of what it holds where two share
+    // a unit (d = 64, and without tangents)
+    out->lockstep_slots = cus % 8 == 0 ? cus / 8 : 0;
     StatsArgs sa;
     const void* xs[6] = {p.v, p.tv, p.q, p.tq, p.k, p.tk};
     for (int i = 0; i < 6; ++i) {
