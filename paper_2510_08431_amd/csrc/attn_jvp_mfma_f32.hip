@@ -64,7 +64,10 @@ constexpr int EVEN_SPAN = 15;    // a row's eight neighbouring elements are know
 constexpr float UNEVEN_SHARE = 0x1p-32f;    // share of a row's weights that uneven keys may have (2^-20 e^-8)
 constexpr int V_TOP = 11;        // first block of V: largest element in [2^11, 2^12), 4 binades in hand for later blocks
 constexpr int V_FLOOR = -3;      // eight keys of a column are known to 2^-22 of their largest if that is 2^-3 or more, scaled
-constexpr uint32_t V_AMPLE = 9u << 23;    // 2^6 in units of that: where V is as large tV may be smaller, its share of tO is known well enough
+constexpr uint32_t V_AMPLE = 5u << 23;    // 2^2 in units of that: where V is as large tV may be smaller, beside H~ V its share of tO is known well enough
+constexpr int V_HITS = 4;        // blocks in which a column has to be found below: one value beside seven zeros is small now and then
+constexpr float ONE_KEY = 1.5f;           // sum of a row's weights over the largest of them, below which the row is one key's,
+constexpr float ONE_KEY_GAIN = 256.f;     // ... and what its A + B may then be smaller by
 constexpr float ROW_FLOOR = 16384.f;      // (2^7)^2: see the check at the end of the sweep
 constexpr int T_HEADROOM = 4;    // the first block's largest tangent score is scaled to [2^-4, 2^-3)
 constexpr float P_GAIN = 4096.f;          // the split weights are P~ 2^12 ...
@@ -485,7 +488,8 @@ __global__ __launch_bounds__(NTHREADS, (Geo<D, TAN>::WG_PER_CU)) void attn_jvp_m
     float v_scale[NX];                                   // set from the first block
     uint32_t v_low[NX], v_high[NX], v_ample;     // bits of 2^V_FLOOR, 2^16 and 2^6, scaled (v_low: less 1)
     uint64_t misfit = 0;         // lanes that have met values their tensor's scale does not suit
-    uint64_t v_small[G::V_PASSES];       // lanes whose V of the block under way is small or zero
+    int v_hits = 0;              // blocks in which values below it were met in this lane's columns
+    bool v_small[G::V_PASSES];   // is V of the block under way small or zero there?
     uint32_t cv_h[4], cv_l[4];
     float cv_mx, cv_m2, cv_sc, cv_own;
     uint64_t uneven[G::K_PASSES];        // lanes of the block under way that have met elements below their row's span
@@ -549,14 +553,11 @@ __global__ __launch_bounds__(NTHREADS, (Geo<D, TAN>::WG_PER_CU)) void attn_jvp_m
         constexpr int st = decltype(ST)::value, part = decltype(PART)::value;
         if constexpr (part == 0) {                       // do the eight values, one column of eight keys, suit the scale?
             const uint32_t top = __float_as_uint(max_abs3(max_abs3(max_abs3(max_abs3(e[0], e[1], e[2]), e[3], e[4]), e[5], e[6]), e[7], e[7]));
-            const uint64_t below = __builtin_amdgcn_ballot_w64(top - 1 < v_low[x]);      // (a zero wraps around)
             misfit |= __builtin_amdgcn_ballot_w64(top >= v_high[x]);
-            if constexpr (x == 0) {
-                misfit |= below;
-                if constexpr (KV_TANGENT) v_small[p] = __builtin_amdgcn_ballot_w64(top < v_ample);
-            } else {
-                misfit |= below & v_small[p];
-            }
+            bool low = top - 1 < v_low[x];               // (a zero wraps around)
+            if constexpr (x == 1) low &= v_small[p];
+            else if constexpr (KV_TANGENT) v_small[p] = top < v_ample;
+            v_hits += low ? 1 : 0;
         }
         if constexpr (part >= 1 && part < 5) split_part(e, v_scale[x], std::integral_constant<int, part - 1>{});
         if constexpr (part == 5) {
@@ -891,7 +892,7 @@ __global__ __launch_bounds__(NTHREADS, (Geo<D, TAN>::WG_PER_CU)) void attn_jvp_m
     // the softmax of a block as a flat list: key factors by pairs, the row maximum, pairs 4-7, then pairs 0-3 (whose
     // registers the first half of the value products has read by the time the list gets there: see the assertion below)
     constexpr int S_PRE = 10, S_PARTS = S_PRE + 8 * W_PARTS;
-    float mx_row;
+    float mx_row, top_row;       // a row's largest score in the block, and so far
     auto softmax_part = [&](auto IDX, auto ST, int blk) __attribute__((always_inline)) {
         constexpr int idx = decltype(IDX)::value;
         if constexpr (idx == S_PARTS - 4) read_note(blk);
@@ -899,7 +900,10 @@ __global__ __launch_bounds__(NTHREADS, (Geo<D, TAN>::WG_PER_CU)) void attn_jvp_m
         else if constexpr (idx == 8) {
             if ((blk + 1) * BC > Lkv) mask_tail(blk);
             mx_row = row_max();
-        } else if constexpr (idx == 9) follow_max(mx_row);
+        } else if constexpr (idx == 9) {
+            follow_max(mx_row);
+            top_row = fmaxf(top_row, mx_row);
+        }
         if constexpr (idx >= S_PRE) weight_part(std::integral_constant<int, ((idx - S_PRE) / W_PARTS + 4) & 7>{}, ST, std::integral_constant<int, (idx - S_PRE) % W_PARTS>{});
     };
 
@@ -969,7 +973,8 @@ __global__ __launch_bounds__(NTHREADS, (Geo<D, TAN>::WG_PER_CU)) void attn_jvp_m
         static_for<KF>([&](auto Qi) { read_factors(Qi, I0{}); });
         static_for<8>([&](auto E2) { key_factors(E2, I0{}); });
         if (BC > Lkv) mask_tail(0);
-        m = row_max() * sq;
+        top_row = row_max();
+        m = top_row * sq;
         float t0 = 0.f;                                  // largest tangent score of the block, unscaled
         if constexpr (TANGENT) {
 #pragma unroll
@@ -1040,6 +1045,8 @@ __global__ __launch_bounds__(NTHREADS, (Geo<D, TAN>::WG_PER_CU)) void attn_jvp_m
 
     // ---- sweep: iteration b does the scores of block b + 1 over the conversion of K(b + 2) and V(b + 1), then the values of
     // block b over the softmax of block b + 1.  Stage of a block: its index & 1.
+    // (the block past the end is the last one again, so a last block of few keys counts twice)
+    const int hits_enough = n_blocks + 1 < V_HITS ? n_blocks + 1 : V_HITS;
     auto iteration = [&](auto PAR, int b) __attribute__((always_inline)) -> bool {
         constexpr int par = decltype(PAR)::value;
         using Cur = std::integral_constant<int, par>;
@@ -1053,10 +1060,6 @@ __global__ __launch_bounds__(NTHREADS, (Geo<D, TAN>::WG_PER_CU)) void attn_jvp_m
         if (__builtin_expect(b + 3 >= n_blocks - 1, 0)) {        // from here on requests may be for the last block
             set_k_rows(b + 3);
             set_v_rows(b + 1 + V_AHEAD);
-            if (b + 1 >= n_blocks - 1 && Lkv % BC == 1) {      // one key, and one value of a column may well be small
-                v_low[0] = 0;
-                if constexpr (KV_TANGENT) v_low[1] = 0;
-            }
         }
         scores(Nxt{}, [&](auto Kk) __attribute__((always_inline)) {
             constexpr int k = decltype(Kk)::value;
@@ -1074,6 +1077,7 @@ __global__ __launch_bounds__(NTHREADS, (Geo<D, TAN>::WG_PER_CU)) void attn_jvp_m
         });
         rescale();
         if constexpr (TANGENT) misfit |= __builtin_amdgcn_ballot_w64(!(fabsf(rb) < 0x1p20f));      // sixteen H~ of fp16 size stay below
+        misfit |= __builtin_amdgcn_ballot_w64(v_hits >= hits_enough);
         write_note(b + 2);
         const bool stop = heed_note(b + 1);
         __syncthreads();     // the next block's planes are written by all, this one's read by all
@@ -1088,13 +1092,16 @@ __global__ __launch_bounds__(NTHREADS, (Geo<D, TAN>::WG_PER_CU)) void attn_jvp_m
 
     // ---- did the scales suit?  If not, the workgroup redoes its tile ------------------------------------------------------
     // Too large: something is inf or NaN.  Too small: the lanes that converted V and tV have seen it (misfit), or a row's
-    // results are small against what the fp16 terms resolve.  These are whole multiples of 2^-24: an accumulator is out by up
-    // to l 2^12 2^-25 for the rounding of V (tV), and for that of the weights by 2^-25 of the V (2^9 as a rule, up to
-    // 2^12) of every key that counts.  A row whose largest |O| or |A + B| is 2^7 max(l, sqrt(l)) knows it to 2^-20 at worst
-    // for the one and 2^-24 sqrt(keys / l) or so for the other.  Ordinary rows are at 2^21 sqrt(l) and 2^16 sqrt(l).
+    // results are small against what the fp16 terms resolve.  These are whole multiples of 2^-24: an accumulator is out by
+    // 2^-25 of the V (2^9 as a rule, up to 2^12) of every key that counts for the rounding of its weight, and by up to
+    // l 2^12 2^-25 for that of V or tV (which average out, unless all keys' are alike).  A row whose largest |O| or |A + B| is
+    // 2^7 sqrt(l), and 2^2 l, knows it to 2^-24 sqrt(keys / l) or so for the one and 2^-15 at worst for the other.  Ordinary
+    // rows (keys / l about 5, S of standard deviation 1) have |O| of 2^23 sqrt(l), |A + B| of 2^16 sqrt(l).
     // It takes weights on keys whose V is small beside the others', a sink without values for one, or tangent scores small
-    // beside those of the tile's first block, to come near the line.  (A row without tangents has exact zeros.)
-    auto too_small = [](float top, float l) __attribute__((always_inline)) { return top * top < ROW_FLOOR * l * fmaxf(l, 1.f); };
+    // beside those of the tile's first block, to come near the line.  A row without tangents has exact zeros.  Where one key
+    // has nearly all of a row's weight its tangent score alone makes A + B, which then is small by chance in one row of
+    // hundreds; few keys count beside it, and A + B cancels against r O to its own rounding anyway: 2^-1 does there.
+    auto too_small = [](float top, float l) __attribute__((always_inline)) { return top * top < ROW_FLOOR * l * fmaxf(l * 0x1p-10f, 1.f); };
     float bad = l * 0.f + r * 0.f;         // NaN once anything is inf or NaN
     float top_o = 0.f, top_t = 0.f;
 #pragma unroll
@@ -1113,7 +1120,8 @@ __global__ __launch_bounds__(NTHREADS, (Geo<D, TAN>::WG_PER_CU)) void attn_jvp_m
     if (misfit != 0 || too_small(top_o, l_row) || !(xhalf_sum(w_uneven) <= l_row * (P_GAIN * UNEVEN_SHARE))) bad = 1.f;
     if constexpr (TANGENT) {
         top_t = xhalf_max(top_t);
-        if (too_small(top_t, l_row) && (r_row != 0.f || top_t != 0.f)) bad = 1.f;
+        const bool one_key = l_row < ONE_KEY * __builtin_amdgcn_exp2f(fmaf(top_row, sq, -m) * LOG2E);
+        if (too_small(one_key ? ONE_KEY_GAIN * top_t : top_t, l_row) && (r_row != 0.f || top_t != 0.f)) bad = 1.f;
     }
     if (__builtin_amdgcn_ballot_w64(bad != 0.f || bad != bad) != 0 && lane == 0) lds_write_f32(lds0 + G::RED_BASE + 48, 1.f);
     __syncthreads();
