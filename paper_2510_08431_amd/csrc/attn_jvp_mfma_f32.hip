@@ -32,9 +32,9 @@
 // them in a lane's registers) go through two LDS stages each.  The four waves fetch fp32 blocks two (K) and one (V)
 // blocks ahead into registers and convert them behind the score MFMAs; behind the value MFMAs run the softmax and
 // weight splitting of the NEXT block.  One barrier per block.  Bound by the matrix pipe at D = 128 (144 MFMAs per wave
-// and block, about 550 other vector instructions): B2 H16 L4096 d128 2.19 ms = 376 TFLOP/s counted
-// (6.40 ms with fp32 MFMAs), the matrix pipe busy 57 % of the time; d = 64 1.17 ms (3.14), d = 32 0.87
-// (1.65).  Errors against 64 bits are 0.6 to 0.7 of those of the fp32-MFMA kernel in o and to, the same in lse.
+// and block, about 590 other vector instructions, 40 of them the checks of the scales, which cost 1 to 3 % here, 6 on
+// few blocks): B2 H16 L4096 d128 2.19 ms = 376 TFLOP/s counted (6.40 ms with fp32 MFMAs), the matrix pipe busy 56 % of
+// the time; d = 64 1.20 ms (3.14), d = 32 0.85 (1.65).  Errors against 64 bits are 0.6 to 0.7 of those of the fp32-MFMA kernel in o and to, the same in lse.
 #include "launchers.h"
 #include <type_traits>
 #include <utility>
