@@ -203,3 +203,24 @@ def test_redone_tiles_at_block_edges(Lkv, d):
         assert np.array_equal(got[2].cpu().double().numpy(), want[2])
         if want[1] is not None:
             assert np.array_equal(got[1].transpose(1, 2).cpu().double().numpy(), want[1])
+
+
+@DIMS
+@pytest.mark.parametrize("names", [NAMES, ("q", "k", "v", "tq")], ids=["all", "query"])
+@pytest.mark.parametrize("f", [1e-3, 1e-4])
+def test_small_tangents_beside_large_ones_in_peaked_rows(f, names, d):
+    """Logit std 8, where one key has most of many rows' weight and A + B cancels against r O: tO of the rows with small
+    tangents together, error over result in the 2-norm.  fp32 products: 1.5e-6 to 3.4e-6; allowed three times that.  (Scaled
+    for the other rows' tangents alone: 8e-6 at 1e-3, 7e-5 at 1e-4.)"""
+    t = inputs(12, 384, 256, d)
+    t["q"] *= 8 ** 0.5
+    t["k"] *= 8 ** 0.5
+    t["tq"][:, :, ::2] *= f
+    t["tk"] *= f
+    t["tv"] *= f
+    full = {n: t[n] if n in names else torch.zeros_like(t[n]) for n in NAMES}
+    ref = attn_jvp_ref(*[full[n] for n in NAMES], sc(d))[1][:, :, ::2]
+    got = run(t, names)[1][:, :, ::2]
+    err = float(np.linalg.norm(got - ref) / np.linalg.norm(ref))
+    print(f"[small tangents x {f:g}, peaked, {len(names)} tensors, d={d}] {err:.1e}", flush=True)
+    assert err <= 1e-5
