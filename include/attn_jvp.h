@@ -81,10 +81,14 @@ extern "C" {
 
 /* attn_jvp_opts.kernel */
 #define ATTN_JVP_KERNEL_AUTO 0    /* bf16, scale > 0 and d in {64, 128} (or d in {32, 96} with a workspace) -> bf16 MFMA kernel;
-                                     fp32 and d in {32, 64, 96, 128} -> split-operand MFMA kernel; everything else -> KERNEL_FP32 */
-#define ATTN_JVP_KERNEL_FP32 1    /* fp32 streaming kernels, any dtype: d in {32, 64, 128} on the vector ALU (slow), d = 256
-                                     on fp32 matrix instructions */
-#define ATTN_JVP_KERNEL_MFMA 2    /* matrix-core kernels.
+                                     fp32 and d in {32, 64, 96, 128} -> split-operand MFMA kernel; calls with few query rows
+                                     (16-row groups up to one to four per compute unit, by dtype and d) and everything
+                                     else (d = 256, scale <= 0, d = 32 without a workspace) -> key-split kernel: products of
+                                     operands split into bf16 terms that sum to them exactly, fp32 accuracy, no workspace */
+#define ATTN_JVP_KERNEL_FP32 1    /* fp32 kernels, any dtype: d in {32, 64, 128} on the vector ALU (slow), d = 256 the key-split
+                                     kernel */
+#define ATTN_JVP_KERNEL_MFMA 2    /* matrix-core kernels (without flags the key-split kernel for few query rows, as AUTO,
+                                     except for bf16 inputs with a workspace).
                                      bf16 inputs: scale > 0, d in {64, 128}; d in {32, 96} given a workspace of
                                      attn_jvp_workspace_bytes(...).  64, 96 and 128 are built natively; at 32 the
                                      inputs are first copied into the workspace zero-padded to 64 columns (exact: the

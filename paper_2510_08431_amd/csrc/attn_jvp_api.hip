@@ -122,6 +122,18 @@ int run(const void* q, const void* k, const void* v, const void* tq, const void*
     if (kernel == ATTN_JVP_KERNEL_AUTO) kernel = mfma_ok ? ATTN_JVP_KERNEL_MFMA : ATTN_JVP_KERNEL_FP32;
 
     hipError_t e;
+    // Calls whose 128-row tiles would leave much of the chip idle, and all that AUTO finds no tile kernel for, go to the kernel
+    // that deals the keys to the waves.  A flag, or an explicit request together with a workspace, asks for the tile kernel.
+    const bool few_rows = kernel == ATTN_JVP_KERNEL_MFMA && mfma_ok && p.flags == 0 &&
+                          (f32 || opts->kernel == ATTN_JVP_KERNEL_AUTO || workspace == nullptr);
+    const bool no_tiles = opts->kernel == ATTN_JVP_KERNEL_AUTO && !mfma_ok && attn_jvp::fp32_vector_supports(p);
+    if (few_rows || no_tiles) {
+        bool take = no_tiles;
+        e = take ? hipSuccess : attn_jvp::keysplit_preferred(p, &take);
+        if (e == hipSuccess && take) e = attn_jvp::launch_keysplit(p);
+        if (e != hipSuccess) return ATTN_JVP_LAUNCH_FAILED;
+        if (take) return ATTN_JVP_OK;
+    }
     if (kernel == ATTN_JVP_KERNEL_MFMA) {
         if (!mfma_ok) return ATTN_JVP_UNSUPPORTED;
         e = f32 ? attn_jvp::launch_mfma_f32(p) : attn_jvp::launch_mfma_bf16(p);

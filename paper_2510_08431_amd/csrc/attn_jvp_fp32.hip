@@ -2,8 +2,7 @@
 //
 // Reference-grade GPU path: every product and sum is an fp32 FMA on the vector ALU, so it meets
 // the fp32 tolerance, and it accepts bf16 inputs too (upcast exactly).  It is the cross-check for the
-// matrix-core kernels and the path for what they do not cover; it is not tuned for speed.  (d = 256
-// runs on fp32 matrix instructions, attn_jvp_fp32_d256.hip.)
+// matrix-core kernels and runs when asked for; it is not tuned for speed.  (d = 256: attn_jvp_keysplit.hip.)
 //
 // Work split: a workgroup of 256 lanes owns BR = 64 query rows; each row is shared by 4
 // neighbouring lanes, lane part p holding the float4 chunks p, p+4, p+8, ... of q, tq and of the
@@ -207,7 +206,7 @@ bool fp32_vector_supports(const Problem& p) {
 
 hipError_t launch_fp32_vector(const Problem& p) {
     if (!fp32_vector_supports(p)) return hipErrorInvalidValue;
-    if (p.d == 256) return launch_fp32_d256(p);
+    if (p.d == 256) return launch_keysplit(p);
     if (p.in_dtype == 1) return launch_d<float, float>(p);                      // fp32 in -> fp32 out either way
     if (p.out_dtype == 0) return launch_d<__hip_bfloat16, float>(p);
     return launch_d<__hip_bfloat16, __hip_bfloat16>(p);

@@ -46,8 +46,9 @@ hipError_t ensure_dynamic_lds(const void* kern, int bytes, int dev);
 
 // Each returns hipSuccess/hip error of the launch, or hipErrorInvalidValue when the
 // (dtype, d) combination is not built for that kernel.
-hipError_t launch_fp32_vector(const Problem& p);      // d = 256: launch_fp32_d256
-hipError_t launch_fp32_d256(const Problem& p);
+hipError_t launch_fp32_vector(const Problem& p);      // d = 256: launch_keysplit
+hipError_t launch_keysplit(const Problem& p);         // head dimensions 32, 64, 96, 128, 256
+hipError_t keysplit_preferred(const Problem& p, bool* yes);      // over the tile kernels of the same head dimension (asks for the device's size)
 hipError_t launch_mfma_bf16(const Problem& p);
 hipError_t launch_mfma_f32(const Problem& p);
 bool mfma_bf16_supports(const Problem& p);

@@ -1,0 +1,124 @@
+"""The kernel that deals the keys of 16 query rows to the waves of a workgroup (calls with few rows, and head dimension 256)
+against the fp64 CPU oracle, and the rule that takes calls to it.
+
+Tolerance: max |x - x_ref| / RMS(x_ref) <= 1e-5 up to 256 keys and 1.5e-5 sqrt(Lkv / 256) beyond, the one of fp32 arithmetic
+everywhere, for bf16 inputs too: their products are exact and their weights carry 24 bits.
+"""
+import numpy as np
+import pytest
+import torch
+
+from oracle.attn_jvp_ref import attn_jvp_ref
+from paper_2510_08431_amd import binding
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+NAMES = ("q", "k", "v", "tq", "tk", "tv")
+DTYPES = pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16], ids=["fp32", "bf16"])
+DIMS = pytest.mark.parametrize("d", [32, 64, 96, 128, 256])
+
+
+def inputs(seed, B, H, Lq, Lkv, d, dtype):
+    g = torch.Generator().manual_seed(seed)
+    return [torch.randn(B, H, Lq if n in ("q", "tq") else Lkv, d, generator=g).to(dtype) for n in NAMES]
+
+
+def run(t, scale, **kw):
+    out = binding.attn_jvp_fwd_ex(*[None if x is None else x.to(DEV) for x in t], scale, **kw)
+    torch.cuda.synchronize()
+    return out
+
+
+def check(got, t, scale, label):
+    full = [torch.zeros_like(t[1 if i in (4, 5) else 0]) if x is None else x for i, x in enumerate(t)]
+    ref = attn_jvp_ref(*full, scale)
+    Lkv = t[1].shape[2]
+    tol = 1e-5 if Lkv <= 256 else 1.5e-5 * (Lkv / 256) ** 0.5
+    for x, r, name in zip(got, ref, ("o", "to", "lse")):
+        if x is None:
+            continue
+        x = x.cpu().double().numpy()
+        # (one key without key tangents: tO is zero, the difference of terms of size |tS V|, here about 1, each known to 2^-23 of it:
+        # with 0.1 as the least RMS those 2^-22 are 2.4e-6)
+        err = np.abs(x - r).max() / (1.0 if name == "lse" else max(np.sqrt((r ** 2).mean()), 0.1))
+        assert np.isfinite(x).all() and err <= tol, f"{label} {name}: {err}"
+
+
+@DTYPES
+@DIMS
+def test_key_and_query_lengths_around_the_edges(d, dtype):
+    """Blocks of 32 keys dealt to four waves (waves without a block, with one, with several), tiles of 16 rows."""
+    scale = float(np.float32(d ** -0.5))
+    for Lq, Lkv in ((1, 1), (15, 31), (16, 32), (17, 33), (31, 64), (33, 97), (5, 127), (16, 128), (20, 129), (18, 161), (40, 300)):
+        t = inputs(Lq + Lkv, 1, 2, Lq, Lkv, d, dtype)
+        for names in (6, 4, 3):
+            u = t[:names] + [None] * (6 - names)
+            got = run(u, scale)
+            check(got, u, scale, f"d={d} Lq={Lq} Lkv={Lkv} {names} tensors")
+        blhd = run([x.transpose(1, 2).contiguous() for x in t], scale, layout=binding.LAYOUT_BLHD)
+        full = run(t, scale)
+        assert torch.equal(blhd[0].transpose(1, 2), full[0]) and torch.equal(blhd[1].transpose(1, 2), full[1]) and torch.equal(blhd[2], full[2])
+
+
+@DTYPES
+@DIMS
+def test_absent_tangents_give_the_bits_of_zero_ones(d, dtype):
+    t = inputs(3, 2, 2, 50, 200, d, dtype)
+    zero = t[:4] + [torch.zeros_like(t[4]), torch.zeros_like(t[5])]
+    full, null, plain = run(zero, 0.1), run(t[:4] + [None, None], 0.1), run(t[:3] + [None] * 3, 0.1)
+    assert all(torch.equal(a, b) for a, b in zip(full, null))
+    assert plain[1] is None and torch.equal(plain[0], full[0]) and torch.equal(plain[2], full[2])
+
+
+@DTYPES
+@DIMS
+def test_infinities_and_nan_stay_in_their_columns(d, dtype):
+    """One element of V: infinite, the column's o is that infinity (its weights are positive); NaN, NaN; the rest is right."""
+    t = inputs(4, 1, 1, 20, 150, d, dtype)
+    scale = float(np.float32(d ** -0.5))
+    want = run(t, scale)
+    for bad in (float("inf"), float("-inf"), float("nan")):
+        u = [x.clone() for x in t]
+        u[2][0, 0, 70, 3] = bad
+        o, to, lse = run(u, scale)
+        col = o[..., 3]
+        assert (torch.isnan(col) if bad != bad else col == bad).all()
+        rest = [i for i in range(d) if i != 3]
+        for a, b in ((o, want[0]), (to, want[1])):
+            assert (a[..., rest] - b[..., rest]).abs().max() <= 2e-5 * b.pow(2).mean().sqrt()
+        assert (lse - want[2]).abs().max() <= 1e-5
+
+
+@pytest.mark.parametrize("d,dtype,kernel", [(64, torch.float32, binding.KERNEL_MFMA), (128, torch.bfloat16, binding.KERNEL_AUTO),
+                                            (32, torch.bfloat16, binding.KERNEL_AUTO), (96, torch.float32, binding.KERNEL_AUTO)])
+def test_route_by_rows_and_flags(d, dtype, kernel):
+    """Few rows come here (fp32 accuracy shows it for bf16 inputs), a flag asks for the tile kernel, many rows go there."""
+    scale = float(np.float32(d ** -0.5))
+    t = inputs(5, 1, 2, 200, 300, d, dtype)
+    few, tile = run(t, scale, kernel=kernel), run(t, scale, kernel=kernel, flags=binding.FLAG_NO_RESIDENT)
+    check(few, t, scale, "few rows")
+    assert not torch.equal(few[0], tile[0])
+    many = inputs(6, 1, 16, 5 * 16 * 17, 40, d, dtype)             # 85 groups of 16 rows a head, 1360 in all
+    a, b = run(many, scale, kernel=kernel), run(many, scale, kernel=kernel, flags=binding.FLAG_NO_RESIDENT)
+    assert all(torch.equal(x, y) for x, y in zip(a, b))
+
+
+def test_static_scratch_and_graph_with_more_rows_than_this_kernel_takes():
+    """The fp16 value path of the tile kernel through the entry point that brings its own scratch, captured in a HIP graph: every
+    replay the bits of an eager call."""
+    B, H, Lq, Lkv, d = 1, 12, 730, 2100, 128
+    t = [x.to(DEV) for x in inputs(7, B, H, Lq, Lkv, d, torch.bfloat16)]
+    out = (torch.empty(B, H, Lq, d, device=DEV), torch.empty(B, H, Lq, d, device=DEV), torch.empty(B, H, Lq, device=DEV))
+    binding.attn_jvp_fwd_static(*t, 0.1, out)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        binding.attn_jvp_fwd_static(*t, 0.1, out)
+    for rep in range(3):
+        t[0].mul_(0.9)
+        eager = binding.attn_jvp_fwd_ex(*t, 0.1)
+        for x in out:
+            x.fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        assert all(torch.equal(a, b) for a, b in zip(out, eager)), rep
