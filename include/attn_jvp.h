@@ -162,7 +162,10 @@ typedef struct attn_jvp_opts {
                                the exact result for probabilities off by 2^-11 and centred tangent scores off by 2^-10 relative, and
                                lse carries the rounding of l (at most 2^-11 absolute).  Without a workspace, and for
                                Lkv < 2048 (Lkv < 256 for calls with at least four 128-row query tiles per compute
-                               unit): hi + lo bf16 pairs everywhere (9 products, ~16-bit weights). */
+                               unit): hi + lo bf16 pairs everywhere (9 products, ~16-bit weights).
+                               Also (AUTO without flags, bf16 and fp32 inputs): calls whose 128-row query tiles do not
+                               fill the chip run with every head's keys in two to eight parts, whose states go through
+                               the workspace and are merged by a second launch; bf16 inputs then take the bf16 pairs. */
     size_t workspace_bytes; /* size of `workspace` */
     void*  timing_events[2]; /* optional hipEvent_t pair (created by the caller, with timing enabled), or NULL:
                                [0] is recorded on `stream` immediately before the main attention kernel and [1]
@@ -203,7 +206,7 @@ int attn_jvp_fwd_ex(const void* q, const void* k, const void* v,
  * results bit for bit as attn_jvp_fwd_ex with a workspace of attn_jvp_workspace_bytes(...).
  * opts may be NULL (defaults); opts->workspace must be NULL (ATTN_JVP_UNSUPPORTED otherwise).  Shapes whose
  * attn_jvp_workspace_bytes(...) exceeds the array are rejected with ATTN_JVP_TOO_LARGE before anything is
- * launched.  All calls on one GPU share that GPU's array: calls whose work overlaps in time (different
+ * launched (the room for keys in parts is no reason to refuse).  All calls on one GPU, fp32 inputs included, share that GPU's array: calls whose work overlaps in time (different
  * streams, different host threads) race on it and must be serialised by the caller; calls on one stream are
  * ordered and safe.  The array keeps the last call's contents; the kernels re-initialise what they read
  * (statistics, tile flags and tickets are cleared by the call's own first kernels).
@@ -223,9 +226,14 @@ size_t attn_jvp_static_scratch_bytes(void);
  * 32 bytes per (batch, head) and 1024 rows of the longer sequence, each part rounded up to 256 bytes, and 512 bytes
  * of counters (d = 64 likewise, with its own row width).  d in {32, 96}: in front of that, room for bf16 copies of the
  * six inputs zero-padded to 64 and 128 columns (used at 32 only; without a workspace of this size the MFMA kernel takes
- * neither head dimension), and the rest sized for the padded width.  Pure host arithmetic.
+ * neither head dimension), and the rest sized for the padded width.  Where the call goes with its keys in parts, the
+ * room for their states instead, if that is more (at most 160 MiB, behind the copies at d in {32, 96}).  Pure host
+ * arithmetic.
  */
 size_t attn_jvp_workspace_bytes(int B, int H, int Lq, int Lkv, int d);
+
+/* The same for fp32 inputs, whose kernels use scratch only for the states of keys in parts (0: no use for any). */
+size_t attn_jvp_workspace_bytes_fp32(int B, int H, int Lq, int Lkv, int d);
 
 /*
  * RMS normalisation with gain and its JVP, the QK-normalisation in front of the attention (paper App. C.2, the

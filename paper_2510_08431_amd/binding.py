@@ -69,6 +69,8 @@ def load_library():
     lib.attn_jvp_mfma_rate_probe.restype = ci
     lib.attn_jvp_workspace_bytes.argtypes = [ci] * 5
     lib.attn_jvp_workspace_bytes.restype = ctypes.c_size_t
+    lib.attn_jvp_workspace_bytes_fp32.argtypes = [ci] * 5
+    lib.attn_jvp_workspace_bytes_fp32.restype = ctypes.c_size_t
     _lib = lib
     return lib
 
@@ -89,8 +91,10 @@ _workspaces = {}
 
 
 @functools.lru_cache(maxsize=1024)
-def _workspace_bytes(B, H, Lq, Lkv, d):
-    return int(load_library().attn_jvp_workspace_bytes(B, H, Lq, Lkv, d))      # (host arithmetic on the five numbers)
+def _workspace_bytes(B, H, Lq, Lkv, d, f32):
+    lib = load_library()
+    entry = lib.attn_jvp_workspace_bytes_fp32 if f32 else lib.attn_jvp_workspace_bytes
+    return int(entry(B, H, Lq, Lkv, d))      # (host arithmetic on the five numbers)
 
 
 def _workspace(device, stream, raw_stream, nbytes):
@@ -197,7 +201,7 @@ def attn_jvp_fwd_ex(q, k, v, tq, tk, tv, scale, out=None, out_dtype=torch.float3
         entry = lib.attn_jvp_fwd_static
         workspace = None
     if isinstance(workspace, str) and workspace == "auto":
-        need = _workspace_bytes(B, H, Lq, Lkv, d) if q.dtype == torch.bfloat16 else 0
+        need = _workspace_bytes(B, H, Lq, Lkv, d, q.dtype == torch.float32)
         workspace = _workspace(device, stream, raw_stream, need) if need else None
     opts = AttnJvpOpts(_DTYPE_CODE[q.dtype], 0 if out_dtype == torch.float32 else 1, raw_stream, int(kernel), int(flags))
     opts.layout = int(layout)

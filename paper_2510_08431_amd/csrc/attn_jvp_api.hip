@@ -71,6 +71,14 @@ namespace {
 
 bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
+// Scratch of the fp16 value path: at d = 32, 96 zero-padded copies of the inputs in front.
+size_t pad_bytes(int B, int H, int Lq, int Lkv, int d) { return d == 32 || d == 96 ? attn_jvp::pad_workspace_bytes(B, H, Lq, Lkv, d) : 0; }
+int kernel_dim(int d) { return d == 32 || d == 96 ? attn_jvp::padded_head_dim_of(d) : d; }
+size_t value_path_bytes(int B, int H, int Lq, int Lkv, int d) {
+    if (B <= 0 || H <= 0 || Lq <= 0 || Lkv <= 0 || (d != 128 && d != 32 && d != 64 && d != 96)) return 0;
+    return pad_bytes(B, H, Lq, Lkv, d) + attn_jvp::f16_workspace_bytes(B, H, Lq, Lkv, kernel_dim(d));
+}
+
 int run(const void* q, const void* k, const void* v, const void* tq, const void* tk, const void* tv,
         void* o, void* to, float* lse, int B, int H, int Lq, int Lkv, int d, float scale,
         const attn_jvp_opts* opts, bool use_static_scratch = false) {
@@ -102,9 +110,10 @@ int run(const void* q, const void* k, const void* v, const void* tq, const void*
     size_t workspace_bytes = opts->workspace ? opts->workspace_bytes : 0;
     if (use_static_scratch) {
         if (opts->workspace) return ATTN_JVP_UNSUPPORTED;      // this entry point brings its own scratch
-        const size_t need = opts->in_dtype == ATTN_JVP_BF16 ? attn_jvp_workspace_bytes(B, H, Lq, Lkv, d) : 0;
-        if (need > (size_t)ATTN_JVP_STATIC_SCRATCH_BYTES) return ATTN_JVP_TOO_LARGE;
-        if (need > 0) {
+        // (room for the states of keys in parts is used where it is there: never a reason to refuse)
+        const bool bf16 = opts->in_dtype == ATTN_JVP_BF16;
+        if (bf16 && value_path_bytes(B, H, Lq, Lkv, d) > (size_t)ATTN_JVP_STATIC_SCRATCH_BYTES) return ATTN_JVP_TOO_LARGE;
+        if ((bf16 ? attn_jvp_workspace_bytes(B, H, Lq, Lkv, d) : attn_jvp::split_bytes(B, H, Lq, Lkv, d, true)) > 0) {
             if (attn_jvp::static_scratch(&workspace) != hipSuccess) return ATTN_JVP_LAUNCH_FAILED;
             workspace_bytes = ATTN_JVP_STATIC_SCRATCH_BYTES;
         }
@@ -114,7 +123,7 @@ int run(const void* q, const void* k, const void* v, const void* tq, const void*
               opts->in_dtype, opts->out_dtype, static_cast<hipStream_t>(opts->stream), opts->flags,
               workspace, workspace_bytes,
               static_cast<hipEvent_t>(opts->timing_events[0]), static_cast<hipEvent_t>(opts->timing_events[1]),
-              opts->layout, d, opts->layout};
+              opts->layout, d, opts->layout, {}};
 
     const bool f32 = opts->in_dtype == ATTN_JVP_FP32;
     const bool mfma_ok = f32 ? attn_jvp::mfma_f32_supports(p) : attn_jvp::mfma_bf16_supports(p);
@@ -122,9 +131,15 @@ int run(const void* q, const void* k, const void* v, const void* tq, const void*
     if (kernel == ATTN_JVP_KERNEL_AUTO) kernel = mfma_ok ? ATTN_JVP_KERNEL_MFMA : ATTN_JVP_KERNEL_FP32;
 
     hipError_t e;
+    // Too few query tiles for the chip's rounds: the tile kernels on keys in parts, given room for the parts' states.
+    if (opts->kernel == ATTN_JVP_KERNEL_AUTO && mfma_ok && p.flags == 0 && workspace != nullptr) {
+        const attn_jvp::KeySplit split = attn_jvp::plan_split(B, H, Lq, Lkv, d, f32, tq != nullptr, tk != nullptr);
+        const size_t before = f32 || d != 32 ? 0 : pad_bytes(B, H, Lq, Lkv, d);
+        if (split.parts > 1 && workspace_bytes >= before + attn_jvp::split_bytes(B, H, Lq, Lkv, d, f32)) p.split = split;
+    }
     // Calls whose 128-row tiles would leave much of the chip idle, and all that AUTO finds no tile kernel for, go to the kernel
     // that deals the keys to the waves.  A flag, or an explicit request together with a workspace, asks for the tile kernel.
-    const bool few_rows = kernel == ATTN_JVP_KERNEL_MFMA && mfma_ok && p.flags == 0 &&
+    const bool few_rows = kernel == ATTN_JVP_KERNEL_MFMA && mfma_ok && p.flags == 0 && p.split.parts == 1 &&
                           (f32 || opts->kernel == ATTN_JVP_KERNEL_AUTO || workspace == nullptr);
     const bool no_tiles = opts->kernel == ATTN_JVP_KERNEL_AUTO && !mfma_ok && attn_jvp::fp32_vector_supports(p);
     if (few_rows || no_tiles) {
@@ -193,11 +208,15 @@ int attn_jvp_mfma_rate_probe(const void* operands, float* out, int f16, int iter
 }
 
 size_t attn_jvp_workspace_bytes(int B, int H, int Lq, int Lkv, int d) {
+    const size_t values = value_path_bytes(B, H, Lq, Lkv, d);
+    if (values == 0) return 0;
+    const size_t parts = pad_bytes(B, H, Lq, Lkv, d) + attn_jvp::split_bytes(B, H, Lq, Lkv, d, false);
+    return values > parts ? values : parts;
+}
+
+size_t attn_jvp_workspace_bytes_fp32(int B, int H, int Lq, int Lkv, int d) {
     if (B <= 0 || H <= 0 || Lq <= 0 || Lkv <= 0) return 0;
-    if (d != 128 && d != 32 && d != 64 && d != 96) return 0;
-    if (d == 32 || d == 96)                 // zero-padded copies of the inputs in front of the fp16 path's scratch
-        return attn_jvp::pad_workspace_bytes(B, H, Lq, Lkv, d) + attn_jvp::f16_workspace_bytes(B, H, Lq, Lkv, attn_jvp::padded_head_dim_of(d));
-    return attn_jvp::f16_workspace_bytes(B, H, Lq, Lkv, d);
+    return attn_jvp::split_bytes(B, H, Lq, Lkv, d, true);
 }
 
 const char* attn_jvp_strerror(int code) {

@@ -338,9 +338,9 @@ __device__ __forceinline__ void attn_jvp_tile(
     const __hip_bfloat16* __restrict__ Q, const __hip_bfloat16* __restrict__ K, const void* __restrict__ V,
     const __hip_bfloat16* __restrict__ tQ, const __hip_bfloat16* __restrict__ tK, const void* __restrict__ tV,
     void* __restrict__ O, void* __restrict__ tO, float* __restrict__ LSE,
-    int Lq, int Lkv, float scale, int q_tiles, const float* __restrict__ stats, int* __restrict__ wg_flags,
+    int Lq, int keys, float scale, int q_tiles, const float* __restrict__ stats, int* __restrict__ wg_flags,
     int H, int blhd, int out_bf16, int d_out, int out_blhd, int online_min_blocks, int lockstep_slots,
-    const int vw, const int n_tiles) {
+    int parts_in, int part_blocks, f32x4* __restrict__ part_state, const int vw, const int n_tiles) {
     using G = Geo<DH, TAN>;
     constexpr int D = DH, ROW_BYTES = G::ROW_BYTES, TENSOR_BYTES = G::TENSOR_BYTES, KV_STAGE_BYTES = G::KV_STAGE_BYTES;
     constexpr int V_RING_BASE = G::V_RING_BASE;
@@ -400,8 +400,14 @@ __device__ __forceinline__ void attn_jvp_tile(
     // K and V do not fit an L2, so every round of 32 co-resident workgroups streams them again either way.)
     const int n_wg = n_tiles;
     const int bid = (n_wg & 7) == 0 ? (vw & 7) * (n_wg >> 3) + (vw >> 3) : vw;
-    const long bh = bid / q_tiles;
+    // The keys of a head in `parts` (bf16 pairs only, see attn_jvp_split.hip; else one): the list is then of (head, part,
+    // query tile), a tile's K and V are those of the part, and its results are a partial state's, row bhp Lq + query.
+    const int parts = SPLIT ? parts_in : 1;
+    const long bhp = bid / q_tiles;
+    const long bh = parts > 1 ? bhp / parts : bhp;
     const int q0 = (bid % q_tiles) * BR + wave * 32;
+    const int key0 = parts > 1 ? (int)(bhp - bh * parts) * part_blocks * BC : 0;
+    const int Lkv = parts > 1 && keys - key0 > part_blocks * BC ? part_blocks * BC : keys - key0;
 
     // Memory layout of the caller's tensors: [B,H,L,d] (rows of a head contiguous) or [B,L,H,d] (rows of a head H*d
     // apart).  Element offset of row r of head (b, h): head_base + r * row_elems.  The fp16 copies of V, tV in the
@@ -409,7 +415,7 @@ __device__ __forceinline__ void attn_jvp_tile(
     const int row_elems = blhd ? H * D : D;
     const long bidx = bh / H, hidx = bh % H;
     const long q_base = blhd ? (bidx * Lq * H + hidx) * D : bh * (long)Lq * D;
-    const long kv_base = blhd ? (bidx * Lkv * H + hidx) * D : bh * (long)Lkv * D;
+    const long kv_base = (blhd ? (bidx * keys * H + hidx) * D : bh * (long)keys * D) + (long)key0 * row_elems;
     const int k_stride = row_elems * 2;                                  // bytes between key rows
     const int n_blocks = (Lkv + BC - 1) / BC;
     const int v_stride = F16 ? ROW_BYTES : k_stride;                     // (fp16 copies: whole transposed blocks, see issue_pair_v16t)
@@ -1181,7 +1187,7 @@ __device__ __forceinline__ void attn_jvp_tile(
         if (vw + (int)gridDim.x < n_tiles) {
             const int vn = vw + (int)gridDim.x;
             const int bidn = (n_wg & 7) == 0 ? (vn & 7) * (n_wg >> 3) + (vn >> 3) : vn;
-            const long bhn = bidn / q_tiles;
+            const long bhpn = bidn / q_tiles, bhn = parts > 1 ? bhpn / parts : bhpn;
             const int rown0 = (bidn % q_tiles) * BR;
             const long qbn = blhd ? ((bhn / H) * Lq * H + bhn % H) * D : bhn * (long)Lq * D;
             constexpr int LINES = (ROW_BYTES + 127) / 128;         // 128-byte lines per row (2, or 1 at head dimension 64)
@@ -1194,11 +1200,11 @@ __device__ __forceinline__ void attn_jvp_tile(
                     const long off = (qbn + (long)row * row_elems) * 2 + (idx % LINES) * 128;
                     ATTN_JVP_LOAD_LDS(reinterpret_cast<const char*>(Q) + off, lds0 + G::RING_BYTES);
                     if constexpr (!PRIMAL) ATTN_JVP_LOAD_LDS(reinterpret_cast<const char*>(tQ) + off, lds0 + G::RING_BYTES);
-                    // ... and the first four key blocks of its head (the same 128 rows of K and tK), if it is another head
-                    if (bhn != bh) {
-                        int krow = idx / LINES;
-                        krow = krow < Lkv ? krow : Lkv - 1;
-                        const long kbn = blhd ? ((bhn / H) * Lkv * H + bhn % H) * D : bhn * (long)Lkv * D;
+                    // ... and its first four key blocks (128 rows of K and tK), if it is of another head or part
+                    if (bhpn != bhp) {
+                        int krow = (parts > 1 ? (int)(bhpn - bhn * parts) * part_blocks * BC : 0) + idx / LINES;
+                        krow = krow < keys ? krow : keys - 1;
+                        const long kbn = blhd ? ((bhn / H) * keys * H + bhn % H) * D : bhn * (long)keys * D;
                         const long koff = (kbn + (long)krow * row_elems) * 2 + (idx % LINES) * 128;
                         ATTN_JVP_LOAD_LDS(reinterpret_cast<const char*>(K) + koff, lds0 + G::RING_BYTES);
                         if constexpr (!ZT) ATTN_JVP_LOAD_LDS(reinterpret_cast<const char*>(tK) + koff, lds0 + G::RING_BYTES);
@@ -1254,9 +1260,10 @@ __device__ __forceinline__ void attn_jvp_tile(
                 const f32x16& sv = SV(B0{});
                 const f32x16& tsv = TSV(B0{});
                 const float tmax = row_max(B0{});
-                const float m_new = fmaxf(m, tmax);
-                const float alpha = __builtin_amdgcn_exp2f(m - m_new);
-                m = m_new;
+                // (scores of -inf only so far, e.g. all of a part's: weights of 0, not NaN)
+                const float m_new = fmaxf(m, tmax), m_ref = m_new == -INFINITY ? 0.f : m_new;
+                const float alpha = m == m_new ? 1.f : __builtin_amdgcn_exp2f(m - m_new);
+                m = m_ref;
                 float lb = 0.f, rb = 0.f;
 #pragma unroll
                 for (int e = 0; e < 16; ++e) {
@@ -1268,7 +1275,7 @@ __device__ __forceinline__ void attn_jvp_tile(
                 r_part = (r_part + r_part2) * alpha; r_part2 = 0.f;
                 const float l_row = xhalf_sum(l_part + lb);
                 const float r_row = xhalf_sum(r_part + rb);
-                const float delta = r_row / l_row;          // gH * (running rowsum(P o tS) minus ctr)
+                const float delta = l_row == 0.f ? 0.f : r_row / l_row;     // gH * (running rowsum(P o tS) minus ctr)
                 ctr_h += delta;
                 r_part = fmaf(-delta, l_part, r_part);
                 const float da = delta * alpha;
@@ -1281,6 +1288,7 @@ __device__ __forceinline__ void attn_jvp_tile(
                     }
                 static_for<8>([&](auto P) { softmax_pair(P, B0{}); });
                 plain_values(off);
+                m = m_new;
             }
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         }
@@ -1327,10 +1335,13 @@ __device__ __forceinline__ void attn_jvp_tile(
                 if constexpr (!PRIMAL) *reinterpret_cast<lds_float4*>((uintptr_t)(stage_t + at)) = f32x4{t4.x, t4.y, t4.z, t4.w};
             }
         // m carries `headroom` binades that l_row lacks: take them out of both before adding (exact scalings)
-        if (g == 0 && qrow < Lq)
-            LSE[bh * Lq + qrow] = ((m - headroom) + __builtin_amdgcn_logf(l_row * __builtin_amdgcn_exp2f(headroom))) * 0.6931471805599453f;
+        if (g == 0 && qrow < Lq) {
+            const float m_row = m - headroom, l_top = l_row * __builtin_amdgcn_exp2f(headroom);
+            if (parts > 1) part_state[bhp * Lq + qrow] = f32x4{m_row, l_top, ctr_h + mu, 0.f};      // (gH = 1 with bf16 weights)
+            else LSE[bh * Lq + qrow] = (m_row + __builtin_amdgcn_logf(l_top)) * 0.6931471805599453f;
+        }
         const int o_row = out_blhd ? H * d_out : d_out;
-        const long o_base = out_blhd ? (bidx * Lq * H + hidx) * d_out : bh * (long)Lq * d_out;
+        const long o_base = out_blhd ? (bidx * Lq * H + hidx) * d_out : bhp * (long)Lq * d_out;
         const int chunk = lane % OUT_CHUNKS;         // 16-byte chunk of the row this lane stores: columns 4 chunk .. +3
         if (4 * chunk < d_out && lane < ROWS_PER_STORE * OUT_CHUNKS) {
 #pragma unroll
@@ -1372,8 +1383,8 @@ __global__ __launch_bounds__(NTHREADS, (Geo<DH, TAN>::WG_PER_CU)) void attn_jvp_
     const __hip_bfloat16* __restrict__ tQ, const __hip_bfloat16* __restrict__ tK, const void* __restrict__ tV,
     void* __restrict__ O, void* __restrict__ tO, float* __restrict__ LSE,
     int Lq, int Lkv, float scale, int q_tiles, const float* __restrict__ stats, int* __restrict__ wg_flags,
-    int H, int blhd, int out_bf16, int d_out, int out_blhd, int online_min_blocks, int lockstep_slots, int n_tiles,
-    int stagger_ticks) {
+    int H, int blhd, int out_bf16, int d_out, int out_blhd, int online_min_blocks, int lockstep_slots, int parts,
+    int part_blocks, f32x4* __restrict__ part_state, int n_tiles, int stagger_ticks) {
     // Resident workgroups all start together and their tiles take the same time, so without this every compute unit
     // would write its 128 KiB of results in the same few microseconds, round after round, and wait for memory while
     // the matrix pipes idle (measured 8 us per tile, against 1-2 us for a compute unit that writes alone).  The
@@ -1386,7 +1397,7 @@ __global__ __launch_bounds__(NTHREADS, (Geo<DH, TAN>::WG_PER_CU)) void attn_jvp_
     }
     auto tile = [&](int vw) __attribute__((always_inline)) {
         attn_jvp_tile<MODE, TAN, DH>(Q, K, V, tQ, tK, tV, O, tO, LSE, Lq, Lkv, scale, q_tiles, stats, wg_flags, H, blhd, out_bf16,
-                                 d_out, out_blhd, online_min_blocks, lockstep_slots, vw, n_tiles);
+                                 d_out, out_blhd, online_min_blocks, lockstep_slots, parts, part_blocks, part_state, vw, n_tiles);
     };
     if constexpr (MODE == MODE_F16_ONLINE || MODE == MODE_BF16_SPLIT) {
         // A hand-over launch of the fp16 path works on flagged tiles only, as a rule on none.  A workgroup looks at the
@@ -1456,7 +1467,7 @@ static hipError_t launch_dh(const Problem& p_in) {
         hipError_t e = device_cus(&dev, &cus);
         if (e == hipSuccess) e = prepare_kernels<DH>(dev);
         if (e != hipSuccess) return e;
-        const long long tiles = (long long)((p_in.Lq + BR - 1) / BR) * p_in.B * p_in.H;
+        const long long tiles = (long long)((p_in.Lq + BR - 1) / BR) * p_in.B * p_in.H * p_in.split.parts;
         if (tiles > 0x7fffffffLL) return hipErrorInvalidValue;
     }
     Problem p = p_in;
@@ -1465,7 +1476,8 @@ static hipError_t launch_dh(const Problem& p_in) {
         if (e != hipSuccess) return e;
     }
     const int q_tiles = (p.Lq + BR - 1) / BR;
-    const long long blocks = (long long)q_tiles * p.B * p.H;
+    const long long blocks = (long long)q_tiles * p.B * p.H * p.split.parts;
+    const PartStates ps = part_states(p);
     int lockstep = 0;   // set for the online launch below
     // The launch that does (nearly) all the tiles runs with resident workgroups, one per compute unit, each walking
     // through its share of the tiles, when there are at least two tiles per unit.  The hand-over launches do the
@@ -1488,14 +1500,14 @@ static hipError_t launch_dh(const Problem& p_in) {
         hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(NTHREADS), G::LDS_BYTES, p.stream,
                            (const __hip_bfloat16*)p.q, (const __hip_bfloat16*)p.k, v,
                            (const __hip_bfloat16*)p.tq, (const __hip_bfloat16*)p.tk, tv,
-                           p.o, p.to, p.lse, p.Lq, p.Lkv, p.scale, q_tiles, stats, wg_flags, p.H, p.layout, p.out_dtype,
-                           p.d_out, p.out_layout, (p.flags & 4) ? 0 : ONLINE_MIN_BLOCKS,   // F16_ALWAYS: never the pairs first
-                           lockstep, (int)blocks, stagger);
+                           ps.o, ps.to, p.lse, p.Lq, p.Lkv, p.scale, q_tiles, stats, wg_flags, p.H, p.layout, ps.out_dtype,
+                           p.d_out, ps.layout, (p.flags & 4) ? 0 : ONLINE_MIN_BLOCKS,   // F16_ALWAYS: never the pairs first
+                           lockstep, p.split.parts, p.split.blocks, (f32x4*)ps.state, (int)blocks, stagger);
         return hipGetLastError();
     };
     // fp16 value path when the caller lent enough scratch (and did not ask for another variant) and the call is
     // large enough to amortise its per-call pre-pass (see F16_MIN_KEYS)
-    const bool f16 = !(p.flags & 3) && p.workspace != nullptr && (long long)p.B * p.H <= 65535 &&   // pre-pass grid.y
+    const bool f16 = !(p.flags & 3) && p.split.parts == 1 && p.workspace != nullptr && (long long)p.B * p.H <= 65535 &&   // pre-pass grid.y
                      (p.Lkv >= F16_MIN_KEYS || (p.flags & 4) ||
                       (p.Lkv >= F16_MIN_KEYS_MANY_TILES && blocks >= (long long)F16_MANY_TILES_PER_CU * cus)) &&
                      p.workspace_bytes >= f16_workspace_bytes(p.B, p.H, p.Lq, p.Lkv, p.d) &&
@@ -1534,6 +1546,7 @@ static hipError_t launch_dh(const Problem& p_in) {
     } else {
         e = run(std::integral_constant<int, TAN_ALL>{}, p.tv, ws.tv16);
     }
+    if (e == hipSuccess && p.split.parts > 1) e = launch_merge_parts(p, ps);
     return timer.finish(e);
 }
 

@@ -314,8 +314,9 @@ __device__ __forceinline__ void fp32_tile(
         for (int e = 0; e < 16; ++e) mb = fmaxf(mb, ragged && j0 + 8 * (e / 4) + 4 * g + (e % 4) >= Lkv ? -INFINITY : s[e] * scale);
         mb = xhalf_max(mb);
         const float m_new = mb > m + FP32_SLACK ? mb : m;
-        const float alpha = __builtin_amdgcn_exp2f((m - m_new) * LOG2E);    // 0 on the first block (m = -inf), else 1 or tiny
+        const float alpha = m_new == m ? 1.f : __builtin_amdgcn_exp2f((m - m_new) * LOG2E);    // 0 on the first block (m = -inf), else 1 or tiny
         m = m_new;
+        const float m_ref = m == -INFINITY ? 0.f : m;       // (scores of -inf only so far, e.g. all of a part's: weight 0, not NaN)
         if (__builtin_expect(__builtin_amdgcn_ballot_w64(alpha != 1.f) != 0, 0)) {
 #pragma unroll
             for (int n = 0; n < NC; ++n) {
@@ -333,7 +334,7 @@ __device__ __forceinline__ void fp32_tile(
         auto weigh = [&](auto E) __attribute__((always_inline)) {
             constexpr int e = decltype(E)::value;
             const bool dead = ragged && j0 + 8 * (e / 4) + 4 * g + (e % 4) >= Lkv;
-            p[e] = dead ? 0.f : __builtin_amdgcn_exp2f(fmaf(s[e], scale, -m_new) * LOG2E);
+            p[e] = dead ? 0.f : __builtin_amdgcn_exp2f(fmaf(s[e], scale, -m_ref) * LOG2E);
             row_p += p[e];
             if constexpr (TANGENT) {
                 h[e] = dead ? 0.f : p[e] * (ts[e] * scale);
@@ -396,7 +397,7 @@ __global__ __launch_bounds__(NTHREADS, (Geo<D, TAN>::WG_PER_CU)) void attn_jvp_m
     const float* __restrict__ Q, const float* __restrict__ K, const float* __restrict__ V,
     const float* __restrict__ tQ, const float* __restrict__ tK, const float* __restrict__ tV,
     float* __restrict__ O, float* __restrict__ tO, float* __restrict__ LSE,
-    int Lq, int Lkv, float scale, int q_tiles, int H, int blhd) {
+    int Lq, int keys, float scale, int q_tiles, int H, int blhd, int parts, int part_blocks, f32x4* __restrict__ part_state) {
     // No implicit fusing of a product with a following sum: the compiler would fuse differently in each instantiation,
     // and the instantiations must agree bit for bit (absent tangents against zero tangents).  fmaf() stays fused.
 #pragma clang fp contract(off)
@@ -417,7 +418,12 @@ __global__ __launch_bounds__(NTHREADS, (Geo<D, TAN>::WG_PER_CU)) void attn_jvp_m
     // workgroups sharing one L2 stream the same heads' keys
     const int n_wg = gridDim.x;
     const int bid = (n_wg & 7) == 0 ? (int)(blockIdx.x & 7) * (n_wg >> 3) + (int)(blockIdx.x >> 3) : (int)blockIdx.x;
-    const long bh = bid / q_tiles;
+    // (keys in parts, see attn_jvp_split.hip: a tile's K and V are those of its part, its results row bhp Lq + query of the
+    // partial states; part_state is null where there is one part)
+    const long bhp = bid / q_tiles;
+    const long bh = parts > 1 ? bhp / parts : bhp;
+    const int key0 = parts > 1 ? (int)(bhp - bh * parts) * part_blocks * BC : 0;
+    const int Lkv = parts > 1 && keys - key0 > part_blocks * BC ? part_blocks * BC : keys - key0;
     const int qrow = (bid % q_tiles) * BR + 32 * wave + c;
     const int qload = qrow < Lq ? qrow : Lq - 1;     // rows past the end repeat the last one and are not stored
 
@@ -425,7 +431,7 @@ __global__ __launch_bounds__(NTHREADS, (Geo<D, TAN>::WG_PER_CU)) void attn_jvp_m
     const long row_elems = blhd ? (long)H * D : D;
     const long bidx = bh / H, hidx = bh % H;
     const long q_base = blhd ? (bidx * Lq * H + hidx) * D : bh * (long)Lq * D;
-    const long kv_base = blhd ? (bidx * Lkv * H + hidx) * D : bh * (long)Lkv * D;
+    const long kv_base = (blhd ? (bidx * keys * H + hidx) * D : bh * (long)keys * D) + (long)key0 * row_elems;
     const int row_bytes = (int)(row_elems * sizeof(float));       // (32 rows are below 2^31 bytes: checked on the host)
     const int n_blocks = (Lkv + BC - 1) / BC;
 
@@ -1142,8 +1148,9 @@ __global__ __launch_bounds__(NTHREADS, (Geo<D, TAN>::WG_PER_CU)) void attn_jvp_m
         const float inv_l = 1.f / l_row;
         const float mu = r_row * inv_l * gr;         // rowsum(P o tS), in the accumulators' scale
         const float fo = go * inv_l, ft = gt * inv_l;
-        float* op = O + q_base + (long)qrow * row_elems + 4 * g;
-        float* top = TANGENT ? tO + q_base + (long)qrow * row_elems + 4 * g : nullptr;
+        const long at = (part_state ? (bhp * Lq + qrow) * D : q_base + (long)qrow * row_elems) + 4 * g;
+        float* op = O + at;
+        float* top = TANGENT ? tO + at : nullptr;
 #pragma unroll
         for (int n = 0; n < NC; ++n) {
 #pragma unroll
@@ -1160,15 +1167,19 @@ __global__ __launch_bounds__(NTHREADS, (Geo<D, TAN>::WG_PER_CU)) void attn_jvp_m
                 *reinterpret_cast<float4*>(op + 32 * n + 8 * k) = o4;
             }
         }
-        if (g == 0) LSE[bh * Lq + qrow] = fmaf(__builtin_amdgcn_logf(l_row), LN2, m);     // v_log_f32 is a binary log
+        if (g == 0) {
+            if (part_state) part_state[bhp * Lq + qrow] = f32x4{m, l_row, mu * (gt / go), 0.f};
+            else LSE[bh * Lq + qrow] = fmaf(__builtin_amdgcn_logf(l_row), LN2, m);     // v_log_f32 is a binary log
+        }
     }
 }
 
 template <int D, int TAN>
 hipError_t launch_one(const Problem& p) {
     const int q_tiles = (p.Lq + BR - 1) / BR;
-    const long long blocks = (long long)q_tiles * p.B * p.H;
+    const long long blocks = (long long)q_tiles * p.B * p.H * p.split.parts;
     if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
+    const PartStates ps = part_states(p);
     constexpr int smem = Geo<D, TAN>::LDS_BYTES;
     auto kern = attn_jvp_mfma_f32_kernel<D, TAN>;
     int dev = 0, cus = 0;
@@ -1179,8 +1190,11 @@ hipError_t launch_one(const Problem& p) {
     hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(NTHREADS), smem, p.stream,
                        (const float*)p.q, (const float*)p.k, (const float*)p.v,
                        (const float*)p.tq, (const float*)p.tk, (const float*)p.tv,
-                       (float*)p.o, (float*)p.to, p.lse, p.Lq, p.Lkv, p.scale, q_tiles, p.H, p.layout);
-    return timer.finish(hipGetLastError());
+                       (float*)ps.o, (float*)ps.to, p.lse, p.Lq, p.Lkv, p.scale, q_tiles, p.H, p.layout, p.split.parts, p.split.blocks,
+                       (f32x4*)ps.state);
+    e = hipGetLastError();
+    if (e == hipSuccess && p.split.parts > 1) e = launch_merge_parts(p, ps);
+    return timer.finish(e);
 }
 
 template <int D>

@@ -5,6 +5,12 @@
 
 namespace attn_jvp {
 
+// The keys of every head in `parts` runs of `blocks` key blocks of 32 (the last run may be shorter): workgroups per 128-row
+// query tile, whose partial states a second launch merges.
+struct KeySplit {
+    int parts = 1, blocks = 0;
+};
+
 struct Problem {
     const void *q, *k, *v, *tq, *tk, *tv;
     void *o, *to;
@@ -21,6 +27,7 @@ struct Problem {
     int layout;     // 0: q, k, v, tq, tk, tv are [B,H,L,d]; 1: they are [B,L,H,d].  lse is [B,H,Lq] either way
     int d_out;      // width of the rows of o, to (= d, except when the inputs are zero-padded copies of a smaller d)
     int out_layout; // layout of o, to (= layout, except for the same case)
+    KeySplit split; // keys of the tile kernels in parts (attn_jvp_split.hip); one part unless the caller lent room for the states
 };
 
 // Records the caller's optional timing events around the main kernel's launch.
@@ -49,6 +56,7 @@ hipError_t ensure_dynamic_lds(const void* kern, int bytes, int dev);
 hipError_t launch_fp32_vector(const Problem& p);      // d = 256: launch_keysplit
 hipError_t launch_keysplit(const Problem& p);         // head dimensions 32, 64, 96, 128, 256
 hipError_t keysplit_preferred(const Problem& p, bool* yes);      // over the tile kernels of the same head dimension (asks for the device's size)
+int keysplit_groups_per_unit(int d, bool f32, bool tangents, bool key_tangents);      // up to how many groups of 16 query rows per compute unit
 hipError_t launch_mfma_bf16(const Problem& p);
 hipError_t launch_mfma_f32(const Problem& p);
 bool mfma_bf16_supports(const Problem& p);
@@ -56,6 +64,19 @@ bool mfma_f32_supports(const Problem& p);
 bool fp32_vector_supports(const Problem& p);
 
 constexpr int MFMA_TILE_ROWS = 128;   // query rows per workgroup of the MFMA kernel
+
+// Keys in parts (attn_jvp_split.hip).  plan_split: the parts that suit a shape (host arithmetic, the same with and without a
+// GPU); split_bytes: room for their states.  part_states: where the tile kernels put what a tile gives (the caller's outputs where
+// there is one part); launch_merge_parts: the second launch.
+KeySplit plan_split(int B, int H, int Lq, int Lkv, int d, bool f32, bool tangents, bool key_tangents);
+size_t split_bytes(int B, int H, int Lq, int Lkv, int d, bool f32);
+struct PartStates {
+    void *o, *to;          // rows (head, part, query) of d_out fp32 numbers: a part's own o and to
+    float* state;          // ... of four: reference, sum of the weights against it, rowsum(P o tS); null where there is one part
+    int out_dtype, layout;
+};
+PartStates part_states(const Problem& p);
+hipError_t launch_merge_parts(const Problem& p, const PartStates& ps);
 
 // fp16 value path: bytes of device scratch it needs, and the pre-pass that fills it.  Workspace layout, each part
 // rounded up to 256 bytes: per-head statistics (8 floats per head) | one int per MFMA workgroup (hand-over flags

@@ -1,0 +1,123 @@
+"""Keys in parts (tile kernels on runs of the keys and a launch that merges them) against the fp64 CPU oracle.
+
+Tolerances: fp32 inputs max |x - x_ref| / RMS(x_ref) <= 1e-5 up to 256 keys and 1.5e-5 sqrt(Lkv / 256) beyond, as the unsplit kernel.
+bf16 inputs run as pairs, weights to 2^-17 of themselves: an o or to of a few effective keys is out by at most 2^-17 sum |w| |x|, with
+|x| up to 5 times the RMS of a value and that up to 6 times the RMS of an o averaged over the keys here: 2.5e-4.
+"""
+import numpy as np
+import pytest
+import torch
+
+from oracle.attn_jvp_ref import attn_jvp_ref
+from paper_2510_08431_amd import binding
+
+DEV = "cuda:0"
+NAMES = ("q", "k", "v", "tq", "tk", "tv")
+F32, BF16 = torch.float32, torch.bfloat16
+
+
+def inputs(seed, B, H, Lq, Lkv, d, dtype, names=6):
+    g = torch.Generator().manual_seed(seed)
+    t = [torch.randn(B, H, Lq if n in ("q", "tq") else Lkv, d, generator=g).to(dtype) for n in NAMES]
+    return t[:names] + [None] * (6 - names)
+
+
+def run(t, scale, **kw):
+    out = binding.attn_jvp_fwd_ex(*[None if x is None else x.to(DEV) for x in t], scale, **kw)
+    torch.cuda.synchronize()
+    return out
+
+
+def check(got, t, scale, dtype):
+    full = [torch.zeros_like(t[1 if i in (4, 5) else 0]) if x is None else x for i, x in enumerate(t)]
+    ref = attn_jvp_ref(*full, scale)
+    Lkv = t[1].shape[2]
+    tol = 2.5e-4 if dtype == BF16 else 1e-5 if Lkv <= 256 else 1.5e-5 * (Lkv / 256) ** 0.5
+    for x, r, name in zip(got, ref, ("o", "to", "lse")):
+        if x is None:
+            continue
+        x = x.cpu().double().numpy()
+        err = np.abs(x - r).max() / (1.0 if name == "lse" else np.sqrt((r ** 2).mean()))
+        assert np.isfinite(x).all() and err <= tol, f"{name}: {err}"
+
+
+# (the last column: keys, with the last part a whole run of blocks, a block and a key, or one key short of a block)
+CASES = [(F32, 128, 1, 300, k) for k in (1024, 1025, 1055)] + [(F32, 64, 3, 129, 2001), (F32, 96, 2, 127, 1500), (F32, 32, 1, 130, 3000)] + \
+        [(BF16, 128, 1, 300, k) for k in (2048, 2049, 2079)] + [(BF16, 64, 2, 257, 3000), (BF16, 96, 1, 128, 2500), (BF16, 32, 1, 200, 4001)]
+IDS = ["%s-d%d-%dx%dx%d" % (("fp32" if c[0] == F32 else "bf16",) + c[1:]) for c in CASES]
+
+
+def scratch_of(H, Lq, Lkv, d, dtype):
+    lib = binding.load_library()
+    return (lib.attn_jvp_workspace_bytes_fp32 if dtype == F32 else lib.attn_jvp_workspace_bytes)(1, H, Lq, Lkv, d)
+
+
+def test_scratch_of_parts():
+    """Host arithmetic: nothing for calls that fill the chip or have few keys, two states or more for the cases here, refused
+    shapes and the ends of the integers included."""
+    f32 = binding.load_library().attn_jvp_workspace_bytes_fp32
+    assert f32(1, 2, 256, 256, 64) == 0 and f32(2, 16, 4096, 4096, 128) == 0 and f32(1, 1, 1000, 40, 128) == 0
+    assert f32(1, 1, 1000, 1000, 256) == 0 and f32(0, 1, 1, 1, 64) == 0 and f32(1, 1, 300, 1024, -128) == 0
+    assert f32(2**31 - 1, 2**31 - 1, 2**31 - 1, 2**31 - 1, 128) == 0
+    for dtype, d, H, Lq, Lkv in CASES:
+        if dtype == F32:
+            assert scratch_of(H, Lq, Lkv, d, dtype) >= 2 * H * Lq * (8 * d + 16)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("names", [6, 4, 3])
+@pytest.mark.parametrize("case", CASES, ids=IDS)
+def test_parts_against_the_oracle(case, names):
+    dtype, d, H, Lq, Lkv = case
+    scale = float(np.float32(d ** -0.5))
+    t = inputs(Lkv + names, 1, H, Lq, Lkv, d, dtype, names)
+    got, whole = run(t, scale), run(t, scale, flags=binding.FLAG_NO_RESIDENT)
+    check(got, t, scale, dtype)
+    assert not torch.equal(got[0], whole[0])                  # (the call went in parts)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("case", [CASES[1], CASES[3], CASES[7], CASES[11]], ids=[IDS[1], IDS[3], IDS[7], IDS[11]])
+def test_layouts_output_types_and_scratch(case):
+    dtype, d, H, Lq, Lkv = case
+    t = inputs(9, 2, H, Lq, Lkv, d, dtype)
+    want = run(t, 0.1)
+    blhd = run([x.transpose(1, 2).contiguous() for x in t], 0.1, layout=binding.LAYOUT_BLHD)
+    assert torch.equal(blhd[0].transpose(1, 2), want[0]) and torch.equal(blhd[1].transpose(1, 2), want[1]) and torch.equal(blhd[2], want[2])
+    low = run(t, 0.1, out_dtype=dtype)
+    assert torch.equal(low[0], want[0].to(dtype)) and torch.equal(low[1], want[1].to(dtype)) and torch.equal(low[2], want[2])
+    out = tuple(torch.empty_like(x) for x in want)
+    dev = [x.to(DEV) for x in t]
+    binding.attn_jvp_fwd_static(*dev, 0.1, out)
+    torch.cuda.synchronize()
+    assert all(torch.equal(a, b) for a, b in zip(out, want))
+    need = scratch_of(2 * H, Lq, Lkv, d, dtype)
+    guarded = torch.full((need + 512,), 0x5a, dtype=torch.uint8, device=DEV)
+    exact = run(t, 0.1, workspace=guarded[:need])
+    assert all(torch.equal(a, b) for a, b in zip(exact, want)) and (guarded[need:] == 0x5a).all()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        binding.attn_jvp_fwd_static(*dev, 0.1, out)
+    for rep in range(3):
+        dev[0].mul_(0.9)
+        eager = binding.attn_jvp_fwd_ex(*dev, 0.1)
+        for x in out:
+            x.fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        assert all(torch.equal(a, b) for a, b in zip(out, eager)), rep
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype,d", [(F32, 128), (F32, 64), (BF16, 128), (BF16, 64)])
+def test_a_part_without_weight(dtype, d):
+    """Keys masked by an infinite element, whole parts of them: what counts is the softmax over the others."""
+    Lkv, live = 3000, 700
+    t = inputs(11, 1, 1, 140, Lkv, d, dtype, 3)
+    t[0][..., 0] = 1.0
+    t[1][:, :, live:, 0] = float("-inf")
+    got = run(t, 0.1)
+    rest = [t[0], t[1][:, :, :live].clone(), t[2][:, :, :live].clone(), None, None, None]
+    check(got, rest, 0.1, dtype)
+    t[1][:, :, 2900, 5] = float("nan")
+    assert all(torch.isnan(x).all() for x in run(t, 0.1) if x is not None)
