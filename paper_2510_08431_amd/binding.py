@@ -1,4 +1,5 @@
-"""ctypes binding of the attn_jvp C-ABI library: argument marshalling only.
+"""Binding of the attn_jvp C-ABI library: argument marshalling only, through ctypes, and for the ordinary calls through the
+extension module _fast_call (csrc/fast_call.cpp), which does the same steps natively.
 
 PyTorch supplies device memory (`data_ptr()`) and the current HIP stream; every step of
 the computation runs inside the library's kernels.  There is no CPU or eager fallback:
@@ -38,11 +39,13 @@ class AttnJvpError(RuntimeError):
 
 
 _lib = None
+_fast = None      # the extension module, once the library is loaded
+_AUTO = "auto"
 
 
 def load_library():
     """Load libattn_jvp.so (built in-tree by __graft_entry__.build()) and declare its symbols."""
-    global _lib
+    global _lib, _fast
     if _lib is not None:
         return _lib
     if not os.path.exists(LIB_PATH):
@@ -71,6 +74,10 @@ def load_library():
     lib.attn_jvp_workspace_bytes.restype = ctypes.c_size_t
     lib.attn_jvp_workspace_bytes_fp32.argtypes = [ci] * 5
     lib.attn_jvp_workspace_bytes_fp32.restype = ctypes.c_size_t
+    from . import _fast_call
+    entries = (lib.attn_jvp_fwd_ex, lib.attn_jvp_rmsnorm_fwd, lib.attn_jvp_workspace_bytes, lib.attn_jvp_workspace_bytes_fp32)
+    _fast_call.init(*[ctypes.cast(e, vp).value for e in entries], _workspaces, _workspace)
+    _fast = _fast_call
     _lib = lib
     return lib
 
@@ -181,6 +188,12 @@ def attn_jvp_fwd_ex(q, k, v, tq, tk, tv, scale, out=None, out_dtype=torch.float3
     Returns (o, to, lse); asynchronous.
     """
     lib = _lib or load_library()
+    if out is None and stream is None and timing_events is None and (workspace is None or workspace is _AUTO):
+        done = _fast.attn(q, k, v, tq, tk, tv, scale, out_dtype, kernel, flags, layout, workspace is _AUTO)
+        if done is not None:      # (None: not an ordinary call)
+            if type(done) is int:
+                raise AttnJvpError(done, attn_jvp_strerror(done))
+            return done
     B, H, Lq, Lkv, d = _check_inputs(q, k, v, tq, tk, tv, layout)
     device = q.device
     if out is None:
@@ -240,6 +253,12 @@ def attn_jvp_rmsnorm_fwd(x, tx, w, eps, out=None, stream=None):
     x, tx: [..., d] bf16 or fp32, contiguous, on the GPU; w: [d] float32.  out: optional (y, ty) to write into
     (may be (x, tx) themselves).  Returns (y, ty); asynchronous."""
     lib = _lib or load_library()
+    if out is None and stream is None:
+        done = _fast.rmsnorm(x, tx, w, eps)
+        if done is not None:
+            if type(done) is int:
+                raise AttnJvpError(done, attn_jvp_strerror(done))
+            return done
     if x.dtype not in _DTYPE_CODE or tx.dtype != x.dtype or tuple(tx.shape) != tuple(x.shape):
         raise ValueError("x and tx must have the same shape and dtype (bf16 or fp32)")
     if not (x.is_cuda and tx.is_cuda and w.is_cuda):
@@ -295,6 +314,13 @@ def attn_jvp_fwd(q, k, v, tq, tk, tv, scale, out=None):
     When torch's current stream is not the default stream the same kernel is enqueued there through
     `attn_jvp_fwd_ex` instead (no workspace either)."""
     lib = load_library()
+    if out is None and getattr(q, "dtype", None) is torch.bfloat16:
+        # (the entry point on the default stream and attn_jvp_fwd_ex without a workspace on the current one are the same call)
+        done = _fast.attn(q, k, v, tq, tk, tv, scale, torch.float32, KERNEL_AUTO, 0, LAYOUT_BHLD, False)
+        if done is not None:
+            if type(done) is int:
+                raise AttnJvpError(done, attn_jvp_strerror(done))
+            return done
     B, H, Lq, Lkv, d = _check_inputs(q, k, v, tq, tk, tv)
     if q.dtype != torch.bfloat16:
         raise ValueError("attn_jvp_fwd takes bf16 inputs; use attn_jvp_fwd_ex for fp32")
