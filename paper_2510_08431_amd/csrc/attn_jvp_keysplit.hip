@@ -4,7 +4,8 @@
 //
 // A workgroup owns 16 query rows of a head; wave w of NW takes the key blocks w, w + NW, ... (32 keys each) through
 // Alg. 2's loop by itself, with its own running reference, and the NW partial states (m, l, r, O~, A + B) meet in LDS at
-// the end: rescale to the largest m and add.  Eight times as many workgroups as 128-row tiles, chains a quarter as long,
+// the end: rescale to the largest m and add (KW = 4 waves to the 16 rows; at head dimension 256 with many rows one or two, and
+// four or two groups of 16 rows to a workgroup).  Eight times as many workgroups as 128-row tiles, chains a quarter as long,
 // no workspace, no second launch.  The price: every 16 rows read all keys from the L2 (a 128-row tile shares them), so the
 // kernels with larger tiles stay ahead wherever they fill the chip.
 //
@@ -188,11 +189,12 @@ template <> struct In<__hip_bfloat16> {
     }
 };
 
-template <typename TIn, int D, int TAN>
+template <typename TIn, int D, int TAN, int KW>      // KW: waves that share 16 query rows and deal their keys among them
 struct Cfg {
     static constexpr bool TANGENT = TAN != TAN_NONE, KV_TANGENT = TAN == TAN_ALL;
     static constexpr bool BF16 = In<TIn>::TERMS == 1;
     static constexpr int NW = 4, NTHREADS = 64 * NW;
+    static constexpr int GROUPS = NW / KW, ROWS = BR * GROUPS;     // of 16 rows to a workgroup; its rows
     static constexpr int OCC = D * sizeof(TIn) <= 256 ? 2 : 1;     // workgroups that share a compute unit, as the registers allow
     static constexpr int NT = D / 32;                              // score steps
     // Columns a lane reads of a key row at once: 16 bytes of them as a rule, as many as divide the row; two where the registers
@@ -209,37 +211,39 @@ struct Cfg {
     static constexpr int V_AHEAD = NCQ * V_GROUP_REGS <= (D == 256 ? 64 : 128) ? NCQ : 1;
     static constexpr int V_SLOTS = V_AHEAD < NCQ ? V_AHEAD + 1 : V_AHEAD;
     static constexpr int Q_PLANE = NT * 1024;                      // bytes: [step][lane] 16-byte operands
-    static constexpr int Q_BYTES = (TANGENT ? 2 : 1) * In<TIn>::TERMS * Q_PLANE;
+    static constexpr int Q_BYTES = (TANGENT ? 2 : 1) * In<TIn>::TERMS * Q_PLANE;      // of a group
     static constexpr int OUT_ROW = D + 4;                          // floats; 4 of padding spread the rows over the banks
     static constexpr int PART_BYTES = (TANGENT ? 2 : 1) * BR * OUT_ROW * 4;       // a wave's O~, A + B
-    static constexpr int STATE_BASE = NW * PART_BYTES > Q_BYTES ? NW * PART_BYTES : Q_BYTES;
+    static constexpr int STATE_BASE = NW * PART_BYTES > GROUPS * Q_BYTES ? NW * PART_BYTES : GROUPS * Q_BYTES;
     static constexpr int LDS_BYTES = STATE_BASE + NW * BR * 16;    // + m, l, r, row maximum of each wave and row
+    static_assert(LDS_BYTES * OCC <= 160 * 1024, "fits a compute unit");
 };
 
-template <typename TIn, int D, int TAN>
-__global__ __launch_bounds__((Cfg<TIn, D, TAN>::NTHREADS), (Cfg<TIn, D, TAN>::OCC)) void attn_jvp_keysplit_kernel(
+template <typename TIn, int D, int TAN, int KW>
+__global__ __launch_bounds__((Cfg<TIn, D, TAN, KW>::NTHREADS), (Cfg<TIn, D, TAN, KW>::OCC)) void attn_jvp_keysplit_kernel(
     const TIn* __restrict__ Q, const TIn* __restrict__ K, const TIn* __restrict__ V,
     const TIn* __restrict__ tQ, const TIn* __restrict__ tK, const TIn* __restrict__ tV,
     void* __restrict__ O, void* __restrict__ tO, float* __restrict__ LSE,
     int Lq, int Lkv, float scale, int q_tiles, int H, int blhd, int out_bf16) {
     // (the instantiations must agree bit for bit, absent tangents against zero ones: no implicit fusing)
 #pragma clang fp contract(off)
-    using C = Cfg<TIn, D, TAN>;
+    using C = Cfg<TIn, D, TAN, KW>;
     using I = In<TIn>;
     using Row8 = typename I::Row8;
     using Cols = typename I::template Cols<C::VW>::type;
     constexpr bool TANGENT = C::TANGENT, KV_TANGENT = C::KV_TANGENT;
-    constexpr int NT = C::NT, VW = C::VW, NCQ = C::NCQ, NW = C::NW, TERMS = I::TERMS, NTILES = D / 16;
+    constexpr int NT = C::NT, VW = C::VW, NCQ = C::NCQ, TERMS = I::TERMS, NTILES = D / 16;
     extern __shared__ __attribute__((aligned(16))) char smem[];
 
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int c = lane & 15, kg = lane >> 4;
+    const int kw = wave % KW, group = wave / KW;       // the wave's share of the keys, and its rows
     // workgroups go round-robin over the 8 XCDs: a contiguous range of tiles for each, so that they share their keys in L2
     const int n_wg = gridDim.x;
     const int bid = (n_wg & 7) == 0 ? (int)(blockIdx.x & 7) * (n_wg >> 3) + (int)(blockIdx.x >> 3) : (int)blockIdx.x;
     const long bh = bid / q_tiles;
-    const int q0 = (bid % q_tiles) * BR;
+    const int q0 = (bid % q_tiles) * C::ROWS;
     // [B,H,L,d]: rows of a head contiguous; [B,L,H,d]: rows of a head H*d elements apart
     const long row_elems = blhd ? (long)H * D : D;
     const long bidx = bh / H, hidx = bh % H;
@@ -277,13 +281,13 @@ __global__ __launch_bounds__((Cfg<TIn, D, TAN>::NTHREADS), (Cfg<TIn, D, TAN>::OC
     };
     using A0 = std::integral_constant<int, 0>;
     using A1 = std::integral_constant<int, 1>;
-    if (wave < n_blocks) load_k(wave);       // (uniform)
+    if (kw < n_blocks) load_k(kw);           // (uniform)
     // ---- Q, tQ into LDS as B operands: lane l of step t holds row l % 16, elements 32 t + 8 (l / 16) .. + 7 ----
-    for (int idx = tid; idx < (TANGENT ? 2 : 1) * NT * 64; idx += C::NTHREADS) {
-        const int which = idx / (NT * 64), t = idx / 64 % NT, l = idx & 63;
-        const int row = q0 + (l & 15) < Lq ? q0 + (l & 15) : Lq - 1;       // rows past the end repeat the last one and are not stored
+    for (int idx = tid; idx < C::GROUPS * (TANGENT ? 2 : 1) * NT * 64; idx += C::NTHREADS) {
+        const int at_group = idx / ((TANGENT ? 2 : 1) * NT * 64), which = idx / (NT * 64) % (TANGENT ? 2 : 1), t = idx / 64 % NT, l = idx & 63;
+        const int wanted = q0 + BR * at_group + (l & 15), row = wanted < Lq ? wanted : Lq - 1;       // rows past the end repeat the last one and are not stored
         const Row8 r = I::load8((which ? tQ : Q) + q_base + (long)row * row_elems + 32 * t + 8 * (l >> 4));
-        char* at = smem + which * TERMS * C::Q_PLANE + t * 1024 + l * 16;
+        char* at = smem + at_group * C::Q_BYTES + which * TERMS * C::Q_PLANE + t * 1024 + l * 16;
         if constexpr (TERMS == 3) {
             Split<1> split;
             u32x4 term[1][3];
@@ -300,7 +304,7 @@ __global__ __launch_bounds__((Cfg<TIn, D, TAN>::NTHREADS), (Cfg<TIn, D, TAN>::OC
     }
     __syncthreads();
     auto q_term = [&](int which, int x, int t) __attribute__((always_inline)) {
-        return *reinterpret_cast<const u32x4*>(smem + (which * TERMS + x) * C::Q_PLANE + t * 1024 + lane * 16);
+        return *reinterpret_cast<const u32x4*>(smem + group * C::Q_BYTES + (which * TERMS + x) * C::Q_PLANE + t * 1024 + lane * 16);
     };
 
     f32x4 acc_o[NTILES], acc_t[TANGENT ? NTILES : 1];      // [VW cq + e][r]: column 16 VW cq + VW (4 kg + r) + e of query c
@@ -358,7 +362,7 @@ __global__ __launch_bounds__((Cfg<TIn, D, TAN>::NTHREADS), (Cfg<TIn, D, TAN>::OC
         long ahead[2] = {0, 0};
         if constexpr (C::ROLL) {
             ahead[0] = key_tile(blk, a);
-            ahead[1] = a == 0 ? key_tile(blk, 1) : key_tile(blk + NW, 0);
+            ahead[1] = a == 0 ? key_tile(blk, 1) : key_tile(blk + KW, 0);
         }
         // the large products on a sum of their own for every two steps (a chain of eight steps would carry twice the rounding
         // error), and the small ones on one
@@ -490,7 +494,7 @@ __global__ __launch_bounds__((Cfg<TIn, D, TAN>::NTHREADS), (Cfg<TIn, D, TAN>::OC
         }
     };
     auto sweep = [&]() __attribute__((always_inline)) {
-        for (int blk = wave; blk < n_blocks; blk += NW) {
+        for (int blk = kw; blk < n_blocks; blk += KW) {
             float s[8], ts[8], p[8], h[8];
             if constexpr (C::V_AHEAD == NCQ) static_for<NCQ>([&](auto G) { load_v(G, blk); });
             FENCE();
@@ -503,7 +507,7 @@ __global__ __launch_bounds__((Cfg<TIn, D, TAN>::NTHREADS), (Cfg<TIn, D, TAN>::OC
             score_tile(A1{}, blk, s, ts);
             FENCE();
             if constexpr (!C::ROLL) {
-                if (blk + NW < n_blocks) load_k(blk + NW);
+                if (blk + KW < n_blocks) load_k(blk + KW);
                 FENCE();
             }
             weights(blk, s, ts, p, h);
@@ -520,9 +524,9 @@ __global__ __launch_bounds__((Cfg<TIn, D, TAN>::NTHREADS), (Cfg<TIn, D, TAN>::OC
     };
     // ---- ... and on fp32 products, for tiles with infinities or NaN: nothing fetched ahead ----
     auto sweep_f32 = [&]() __attribute__((always_inline)) {
-        const int row = q0 + c < Lq ? q0 + c : Lq - 1;
+        const int row = q0 + BR * group + c < Lq ? q0 + BR * group + c : Lq - 1;
         const long qat = q_base + (long)row * row_elems + 8 * kg;
-        for (int blk = wave; blk < n_blocks; blk += NW) {
+        for (int blk = kw; blk < n_blocks; blk += KW) {
             float s[8], ts[8], p[8], h[8];
 #pragma unroll 1
             for (int a = 0; a < 2; ++a) {
@@ -585,22 +589,23 @@ __global__ __launch_bounds__((Cfg<TIn, D, TAN>::NTHREADS), (Cfg<TIn, D, TAN>::OC
         if (kg == 0) state[wave * BR + c] = f32x4{m, l, r_sum, row_top};
         __syncthreads();
         bool bad = false;
-        for (int idx = tid; idx < BR * (D / 4); idx += C::NTHREADS) {
+        for (int idx = tid; idx < C::ROWS * (D / 4); idx += C::NTHREADS) {
             const int row = idx / (D / 4), col = 4 * (idx % (D / 4));
+            const int part0 = row / BR * KW, part_row = row % BR;        // its group's first wave
             float top = -INFINITY, m_all = -INFINITY, l_row = 0.f, r_row = 0.f;
 #pragma unroll
-            for (int w = 0; w < NW; ++w) {
-                m_all = fmaxf(m_all, state[w * BR + row][0]);
-                top = fmaxf(top, state[w * BR + row][3]);
+            for (int w = 0; w < KW; ++w) {
+                m_all = fmaxf(m_all, state[(part0 + w) * BR + part_row][0]);
+                top = fmaxf(top, state[(part0 + w) * BR + part_row][3]);
             }
             f32x4 o = {}, t = {};
 #pragma unroll
-            for (int w = 0; w < NW; ++w) {
-                const f32x4 st = state[w * BR + row];
+            for (int w = 0; w < KW; ++w) {
+                const f32x4 st = state[(part0 + w) * BR + part_row];
                 const float f = st[0] == m_all ? 1.f : exp_nat(st[0] - m_all);
                 l_row = fmaf(f, st[1], l_row);
                 r_row = fmaf(f, st[2], r_row);
-                const float* at = reinterpret_cast<const float*>(smem + w * C::PART_BYTES) + row * C::OUT_ROW + col;
+                const float* at = reinterpret_cast<const float*>(smem + (part0 + w) * C::PART_BYTES) + part_row * C::OUT_ROW + col;
                 const f32x4 po = *reinterpret_cast<const f32x4*>(at);
 #pragma unroll
                 for (int e = 0; e < 4; ++e) o[e] = fmaf(f, po[e], o[e]);
@@ -658,13 +663,13 @@ __global__ __launch_bounds__((Cfg<TIn, D, TAN>::NTHREADS), (Cfg<TIn, D, TAN>::OC
     }
 }
 
-template <typename TIn, int D, int TAN>
-hipError_t launch_one(const Problem& p) {
-    using C = Cfg<TIn, D, TAN>;
-    const int q_tiles = (p.Lq + BR - 1) / BR;
+template <typename TIn, int D, int TAN, int KW>
+hipError_t launch_waves(const Problem& p) {
+    using C = Cfg<TIn, D, TAN, KW>;
+    const int q_tiles = (p.Lq - 1) / C::ROWS + 1;
     const long long blocks = (long long)q_tiles * p.B * p.H;
     if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
-    auto kern = attn_jvp_keysplit_kernel<TIn, D, TAN>;
+    auto kern = attn_jvp_keysplit_kernel<TIn, D, TAN, KW>;
     int dev = 0, cus = 0;
     hipError_t e = device_cus(&dev, &cus);
     if (e == hipSuccess) e = ensure_dynamic_lds(reinterpret_cast<const void*>(kern), C::LDS_BYTES, dev);
@@ -674,6 +679,28 @@ hipError_t launch_one(const Problem& p) {
                        (const TIn*)p.q, (const TIn*)p.k, (const TIn*)p.v, (const TIn*)p.tq, (const TIn*)p.tk, (const TIn*)p.tv,
                        p.o, p.to, p.lse, p.Lq, p.Lkv, p.scale, q_tiles, p.H, p.layout, std::is_same<TIn, float>::value ? 0 : p.out_dtype);
     return timer.finish(hipGetLastError());
+}
+
+template <typename TIn, int D, int TAN>
+hipError_t launch_one(const Problem& p) {
+    if constexpr (D == 256) {
+        // One wave (fp32 with tangents: two, Q and tQ of four groups do not fit the LDS) to 16 rows, so that no wave is without a
+        // block where there are fewer than four, and fewer partial states meet.  Rounds of workgroups over the units times a round's
+        // length in key blocks: a workgroup's fixed part is worth 1.2 blocks, 1.6 with two groups, 4 with four.  Measured, us, four
+        // waves to 16 rows -> this: bf16, no key tangents, H16 Lq26057 Lkv25 1154 -> 719, H8 Lq4000 Lkv60 93 -> 55, Lq2000 Lkv300
+        // 81 -> 64; fp32 H24 Lq2632 Lkv47 234 -> 154, all tangents H24 L300 96 -> 80.  Against the rule: H4 Lq2000 Lkv120
+        // 27 -> 34, bf16 all tangents H8 L1000 101 -> 180.
+        constexpr int KW = std::is_same<TIn, float>::value && TAN != TAN_NONE ? 2 : 1;
+        int dev = 0, cus = 0;
+        const hipError_t e = device_cus(&dev, &cus);
+        if (e != hipSuccess) return e;
+        auto cost = [&](int rows, int waves, double fixed) {
+            const long long rounds = ((long long)((p.Lq - 1) / rows + 1) * p.B * p.H - 1) / cus + 1;
+            return rounds * (fixed + ((p.Lkv - 1) / BC) / waves + 1);
+        };
+        if (cost(BR * 4 / KW, KW, KW == 1 ? 4.0 : 1.6) < 0.93 * cost(BR, 4, 1.2)) return launch_waves<TIn, D, TAN, KW>(p);
+    }
+    return launch_waves<TIn, D, TAN, 4>(p);
 }
 
 template <typename TIn, int D>
