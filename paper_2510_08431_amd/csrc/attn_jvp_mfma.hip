@@ -333,7 +333,7 @@ constexpr int F16_MIN_KEYS = 2048, F16_MIN_KEYS_MANY_TILES = 256, F16_MANY_TILES
 
 // One query tile (128 rows of one head), start to finish.  `vw` is the tile's index in the launch's list of
 // (head, query tile) pairs as a one-workgroup-per-tile launch would number its workgroups; n_tiles their count.
-template <int MODE, int TAN, int DH>
+template <int MODE, int TAN, int DH, bool PARTS>
 __device__ __forceinline__ void attn_jvp_tile(
     const __hip_bfloat16* __restrict__ Q, const __hip_bfloat16* __restrict__ K, const void* __restrict__ V,
     const __hip_bfloat16* __restrict__ tQ, const __hip_bfloat16* __restrict__ tK, const void* __restrict__ tV,
@@ -402,7 +402,8 @@ __device__ __forceinline__ void attn_jvp_tile(
     const int bid = (n_wg & 7) == 0 ? (vw & 7) * (n_wg >> 3) + (vw >> 3) : vw;
     // The keys of a head in `parts` (bf16 pairs only, see attn_jvp_split.hip; else one): the list is then of (head, part,
     // query tile), a tile's K and V are those of the part, and its results are a partial state's, row bhp Lq + query.
-    const int parts = SPLIT ? parts_in : 1;
+    static_assert(SPLIT || !PARTS, "parts are done as bf16 pairs");
+    const int parts = PARTS ? parts_in : 1;
     const long bhp = bid / q_tiles;
     const long bh = parts > 1 ? bhp / parts : bhp;
     const int q0 = (bid % q_tiles) * BR + wave * 32;
@@ -1377,7 +1378,8 @@ __device__ __forceinline__ void attn_jvp_tile(
 // behind them.  A tile ends with every wave past a workgroup barrier that follows its last LDS read, on every
 // path, so the next tile may start filling LDS at once.  Since gridDim.x is then a multiple of 8, tile w + k gridDim.x
 // runs on the same XCD as tile w, as the tile map in attn_jvp_tile assumes.
-template <int MODE, int TAN, int DH>
+// PARTS: an instantiation of its own (its bookkeeping in the one for whole calls cost those of few blocks 1 %).
+template <int MODE, int TAN, int DH, bool PARTS = false>
 __global__ __launch_bounds__(NTHREADS, (Geo<DH, TAN>::WG_PER_CU)) void attn_jvp_mfma_kernel(
     const __hip_bfloat16* __restrict__ Q, const __hip_bfloat16* __restrict__ K, const void* __restrict__ V,
     const __hip_bfloat16* __restrict__ tQ, const __hip_bfloat16* __restrict__ tK, const void* __restrict__ tV,
@@ -1396,7 +1398,7 @@ __global__ __launch_bounds__(NTHREADS, (Geo<DH, TAN>::WG_PER_CU)) void attn_jvp_
         while (wall_clock64() - t0 < wait) __builtin_amdgcn_s_sleep(8);
     }
     auto tile = [&](int vw) __attribute__((always_inline)) {
-        attn_jvp_tile<MODE, TAN, DH>(Q, K, V, tQ, tK, tV, O, tO, LSE, Lq, Lkv, scale, q_tiles, stats, wg_flags, H, blhd, out_bf16,
+        attn_jvp_tile<MODE, TAN, DH, PARTS>(Q, K, V, tQ, tK, tV, O, tO, LSE, Lq, Lkv, scale, q_tiles, stats, wg_flags, H, blhd, out_bf16,
                                  d_out, out_blhd, online_min_blocks, lockstep_slots, parts, part_blocks, part_state, vw, n_tiles);
     };
     if constexpr (MODE == MODE_F16_ONLINE || MODE == MODE_BF16_SPLIT) {
@@ -1444,7 +1446,7 @@ static hipError_t prepare_kernels(int dev) {
     if (done.load(std::memory_order_acquire) >> dev & 1) return hipSuccess;
     auto raise = [&](auto tan) -> hipError_t {
         constexpr int T = decltype(tan)::value;
-        const void* kernels[] = {(const void*)attn_jvp_mfma_kernel<MODE_BF16_SPLIT, T, DH>, (const void*)attn_jvp_mfma_kernel<MODE_F16, T, DH>,
+        const void* kernels[] = {(const void*)attn_jvp_mfma_kernel<MODE_BF16_SPLIT, T, DH>, (const void*)attn_jvp_mfma_kernel<MODE_BF16_SPLIT, T, DH, true>, (const void*)attn_jvp_mfma_kernel<MODE_F16, T, DH>,
                                  (const void*)attn_jvp_mfma_kernel<MODE_F16_ONLINE, T, DH>};
         for (const void* k : kernels) {
             const hipError_t e = ensure_dynamic_lds(k, Geo<DH, T>::LDS_BYTES, dev);
@@ -1527,6 +1529,7 @@ static hipError_t launch_dh(const Problem& p_in) {
     auto run = [&](auto tan, const void* tv, const void* tv16) -> hipError_t {
         constexpr int T = decltype(tan)::value;
         resident = true;
+        if (p.split.parts > 1) return launch(attn_jvp_mfma_kernel<MODE_BF16_SPLIT, T, DH, true>, tan, p.v, tv, nullptr, nullptr);
         if (!f16) return launch(attn_jvp_mfma_kernel<MODE_BF16_SPLIT, T, DH>, tan, p.v, tv, nullptr, nullptr);
         hipError_t err = launch(attn_jvp_mfma_kernel<MODE_F16, T, DH>, tan, ws.v16, tv16, ws.stats, ws.wg_flags);
         resident = false;
