@@ -5,9 +5,11 @@ PyTorch supplies device memory (`data_ptr()`) and the current HIP stream; every 
 the computation runs inside the library's kernels.  There is no CPU or eager fallback:
 if the shared library is missing, loading raises.
 """
+import contextlib
 import ctypes
 import functools
 import os
+import threading
 
 import torch
 
@@ -75,11 +77,16 @@ def load_library():
     lib.attn_jvp_workspace_bytes_fp32.argtypes = [ci] * 5
     lib.attn_jvp_workspace_bytes_fp32.restype = ctypes.c_size_t
     from . import _fast_call
-    entries = (lib.attn_jvp_fwd_ex, lib.attn_jvp_rmsnorm_fwd, lib.attn_jvp_workspace_bytes, lib.attn_jvp_workspace_bytes_fp32)
-    _fast_call.init(*[ctypes.cast(e, vp).value for e in entries], _workspaces, _workspace)
+    _hand_over(_fast_call, lib, lib.attn_jvp_fwd_ex)
     _fast = _fast_call
     _lib = lib
     return lib
+
+
+def _hand_over(fast, lib, fwd_ex):
+    """Give the extension module what it calls: entry points of the library, and this module's workspaces and locks."""
+    entries = (fwd_ex, lib.attn_jvp_rmsnorm_fwd, lib.attn_jvp_workspace_bytes, lib.attn_jvp_workspace_bytes_fp32)
+    fast.init(*[ctypes.cast(e, ctypes.c_void_p).value for e in entries], _workspaces, _workspace, _workspace_locks, _workspace_lock)
 
 
 def attn_jvp_strerror(code):
@@ -95,6 +102,14 @@ def attn_jvp_workspace_bytes(B, H, Lq, Lkv, d):
 
 
 _workspaces = {}
+_workspace_locks = {}
+
+
+def _workspace_lock(key):
+    """The lock of one (device, stream)'s cached workspace, held from its look-up until a call's last launch is enqueued: the
+    launches of a call hand the workspace on to one another, so those of two threads on one stream must not alternate.  (Both
+    ways of calling drop the GIL meanwhile.  Reentrant: a signal handler or finalizer may make a whole call in between.)"""
+    return _workspace_locks.setdefault(key, threading.RLock())
 
 
 @functools.lru_cache(maxsize=1024)
@@ -107,9 +122,9 @@ def _workspace_bytes(B, H, Lq, Lkv, d, f32):
 def _workspace(device, stream, raw_stream, nbytes):
     """A scratch tensor from torch's allocator per (device, stream), grown on demand and reused across calls.
 
-    Calls enqueued on one stream run in order, so they can share scratch; calls on different streams may overlap
-    and get separate buffers.  Callers that want to own the memory pass their own `workspace`.  `stream` may be None:
-    the current one, whose handle raw_stream is."""
+    Whole calls enqueued on one stream run in order, so they can share scratch (under _workspace_lock, which the caller holds);
+    calls on different streams may overlap and get separate buffers.  Callers that want to own the memory pass their own
+    `workspace`.  `stream` may be None: the current one, whose handle raw_stream is."""
     key = (device, raw_stream)
     ws = _workspaces.get(key)
     if ws is None or ws.numel() < nbytes:
@@ -213,23 +228,25 @@ def attn_jvp_fwd_ex(q, k, v, tq, tk, tv, scale, out=None, out_dtype=torch.float3
     if isinstance(workspace, str) and workspace == "static":
         entry = lib.attn_jvp_fwd_static
         workspace = None
-    if isinstance(workspace, str) and workspace == "auto":
-        need = _workspace_bytes(B, H, Lq, Lkv, d, q.dtype == torch.float32)
-        workspace = _workspace(device, stream, raw_stream, need) if need else None
     opts = AttnJvpOpts(_DTYPE_CODE[q.dtype], 0 if out_dtype == torch.float32 else 1, raw_stream, int(kernel), int(flags))
     opts.layout = int(layout)
-    if workspace is not None:
-        opts.workspace = workspace.data_ptr()
-        opts.workspace_bytes = workspace.numel() * workspace.element_size()
     if timing_events is not None:
-        if stream is None:
-            stream = torch.cuda.current_stream(device)
         for i, ev in enumerate(timing_events):
             if not ev.cuda_event:      # torch creates the HIP event lazily, at its first record
-                ev.record(stream)
+                ev.record(torch.cuda.current_stream(device) if stream is None else stream)
             opts.timing_events[i] = ev.cuda_event
-    rc = _call(device, entry, q.data_ptr(), k.data_ptr(), v.data_ptr(), _ptr(tq), _ptr(tk), _ptr(tv),
-               o.data_ptr(), _ptr(to), lse.data_ptr(), B, H, Lq, Lkv, d, float(scale), ctypes.byref(opts))
+    need = 0
+    if isinstance(workspace, str) and workspace == "auto":
+        need = _workspace_bytes(B, H, Lq, Lkv, d, q.dtype == torch.float32)
+        workspace = None
+    with _workspace_lock((device, raw_stream)) if need else contextlib.nullcontext():
+        if need:
+            workspace = _workspace(device, stream, raw_stream, need)
+        if workspace is not None:
+            opts.workspace = workspace.data_ptr()
+            opts.workspace_bytes = workspace.numel() * workspace.element_size()
+        rc = _call(device, entry, q.data_ptr(), k.data_ptr(), v.data_ptr(), _ptr(tq), _ptr(tk), _ptr(tv),
+                   o.data_ptr(), _ptr(to), lse.data_ptr(), B, H, Lq, Lkv, d, float(scale), ctypes.byref(opts))
     if rc != 0:
         raise AttnJvpError(rc, attn_jvp_strerror(rc))
     return o, to, lse

@@ -18,24 +18,31 @@
 
 namespace {
 
-// what binding.py hands over at its first call: entry points of the library it has loaded, its workspace cache and the function that fills it
+// what binding.py hands over at its first call: entry points of the library it has loaded, its workspace cache, the locks of its entries,
+// and the functions that fill both
 decltype(&attn_jvp_fwd_ex) fwd_ex;
 decltype(&attn_jvp_rmsnorm_fwd) rmsnorm_fwd;
 decltype(&attn_jvp_workspace_bytes) bytes_bf16, bytes_fp32;
-PyObject *workspaces, *new_workspace;
+PyObject *workspaces, *new_workspace, *locks, *new_lock, *name_acquire, *name_release;
 
 PyObject* init(PyObject*, PyObject* args) {
     unsigned long long at[4];
-    PyObject *cache, *fill;
-    if (!PyArg_ParseTuple(args, "KKKKOO", &at[0], &at[1], &at[2], &at[3], &cache, &fill)) return nullptr;
+    PyObject *cache, *fill, *cache_locks, *fill_lock;
+    if (!PyArg_ParseTuple(args, "KKKKOOOO", &at[0], &at[1], &at[2], &at[3], &cache, &fill, &cache_locks, &fill_lock)) return nullptr;
+    if (!name_acquire && !(name_acquire = PyUnicode_InternFromString("acquire"))) return nullptr;
+    if (!name_release && !(name_release = PyUnicode_InternFromString("release"))) return nullptr;
     fwd_ex = reinterpret_cast<decltype(fwd_ex)>(at[0]);
     rmsnorm_fwd = reinterpret_cast<decltype(rmsnorm_fwd)>(at[1]);
     bytes_bf16 = reinterpret_cast<decltype(bytes_bf16)>(at[2]);
     bytes_fp32 = reinterpret_cast<decltype(bytes_fp32)>(at[3]);
-    Py_INCREF(cache);
-    Py_INCREF(fill);
-    Py_XSETREF(workspaces, cache);
-    Py_XSETREF(new_workspace, fill);
+    const auto keep = [](PyObject*& slot, PyObject* o) {
+        Py_INCREF(o);
+        Py_XSETREF(slot, o);
+    };
+    keep(workspaces, cache);
+    keep(new_workspace, fill);
+    keep(locks, cache_locks);
+    keep(new_lock, fill_lock);
     Py_RETURN_NONE;
 }
 
@@ -70,25 +77,59 @@ size_t scratch_bytes(int B, int H, int Lq, int Lkv, int d, bool f32) {
     return e.bytes;
 }
 
-// binding.py's workspace of the device and stream, at least `need` bytes; a new reference, or null with a Python error.
-PyObject* workspace_for(PyObject* q, const at::Tensor& t, hipStream_t stream, size_t need) {
-    PyObject* device = PyObject_GetAttrString(q, "device");
-    if (!device) return nullptr;
-    PyObject* raw = PyLong_FromVoidPtr(stream);
-    PyObject* key = raw ? PyTuple_Pack(2, device, raw) : nullptr;
-    PyObject* ws = key ? PyDict_GetItemWithError(workspaces, key) : nullptr;      // (borrowed)
-    Py_XINCREF(ws);
-    if (key && !PyErr_Occurred() && (!ws || (size_t)THPVariable_Unpack(ws).numel() < need)) {
-        Py_CLEAR(ws);
-        PyObject* n = PyLong_FromSize_t(need);
-        if (n) ws = PyObject_CallFunctionObjArgs(new_workspace, device, Py_None, raw, n, nullptr);
-        Py_XDECREF(n);
+// binding.py's workspace of a device and stream, with its lock held until the object goes: the launches of a call hand the
+// workspace on to one another, and another thread's on the same stream must not come between them (the GIL is released
+// meanwhile).
+class Workspace {
+    PyObject *lock = nullptr, *tensor = nullptr;
+
+public:
+    // At least `need` bytes; false with a Python error.
+    bool take(PyObject* q, hipStream_t stream, size_t need) {
+        PyObject* device = PyObject_GetAttrString(q, "device");
+        PyObject* raw = device ? PyLong_FromVoidPtr(stream) : nullptr;
+        PyObject* key = raw ? PyTuple_Pack(2, device, raw) : nullptr;
+        if (key) {
+            PyObject* l = PyDict_GetItemWithError(locks, key);      // (borrowed)
+            if (l) Py_INCREF(l);
+            else if (!PyErr_Occurred()) l = PyObject_CallOneArg(new_lock, key);
+            PyObject* got = l ? PyObject_CallMethodNoArgs(l, name_acquire) : nullptr;
+            if (got) lock = l;
+            else Py_XDECREF(l);
+            Py_XDECREF(got);
+        }
+        if (lock) {
+            tensor = PyDict_GetItemWithError(workspaces, key);
+            Py_XINCREF(tensor);
+            if (!PyErr_Occurred() && (!tensor || (size_t)THPVariable_Unpack(tensor).numel() < need)) {
+                Py_CLEAR(tensor);
+                PyObject* n = PyLong_FromSize_t(need);
+                if (n) tensor = PyObject_CallFunctionObjArgs(new_workspace, device, Py_None, raw, n, nullptr);
+                Py_XDECREF(n);
+            }
+        }
+        Py_XDECREF(key);
+        Py_XDECREF(raw);
+        Py_XDECREF(device);
+        return tensor != nullptr;
     }
-    Py_XDECREF(key);
-    Py_XDECREF(raw);
-    Py_DECREF(device);
-    return ws;
-}
+    const at::Tensor& get() const { return THPVariable_Unpack(tensor); }
+    Workspace() = default;
+    Workspace(const Workspace&) = delete;
+    ~Workspace() {
+        if (!lock && !tensor) return;
+        PyObject *type, *value, *trace;      // (an error on its way stays)
+        PyErr_Fetch(&type, &value, &trace);
+        Py_XDECREF(tensor);
+        if (lock) {
+            PyObject* r = PyObject_CallMethodNoArgs(lock, name_release);
+            if (!r) PyErr_WriteUnraisable(lock);
+            Py_XDECREF(r);
+            Py_DECREF(lock);
+        }
+        PyErr_Restore(type, value, trace);
+    }
+};
 
 // attn(q, k, v, tq, tk, tv, scale, out_dtype, kernel, flags, layout, with_workspace) -> (o, to, lse), an error code, or None
 PyObject* attn(PyObject*, PyObject* const* a, Py_ssize_t n) {
@@ -131,15 +172,13 @@ PyObject* attn(PyObject*, PyObject* const* a, Py_ssize_t n) {
     opts.kernel = (int)kernel;
     opts.flags = (int)flags;
     opts.layout = (int)layout;
-    PyObject* ws = nullptr;
+    Workspace ws;
     if (a[11] == Py_True) {
         const size_t need = scratch_bytes((int)B, (int)H, (int)Lq, (int)Lkv, (int)d, f32);
         if (need > 0) {
-            ws = workspace_for(a[0], q, stream, need);
-            if (!ws) return nullptr;
-            const at::Tensor& w = THPVariable_Unpack(ws);
-            opts.workspace = w.data_ptr();
-            opts.workspace_bytes = (size_t)w.numel();
+            if (!ws.take(a[0], stream, need)) return nullptr;
+            opts.workspace = ws.get().data_ptr();
+            opts.workspace_bytes = (size_t)ws.get().numel();
         }
     }
     const void* in[6];
@@ -151,7 +190,6 @@ PyObject* attn(PyObject*, PyObject* const* a, Py_ssize_t n) {
     Py_BEGIN_ALLOW_THREADS      // (the tensors are held by the caller's arguments, the workspace by `ws`)
     rc = fwd_ex(in[0], in[1], in[2], in[3], in[4], in[5], po, pto, plse, (int)B, (int)H, (int)Lq, (int)Lkv, (int)d, scale, &opts);
     Py_END_ALLOW_THREADS
-    Py_XDECREF(ws);
     if (rc != ATTN_JVP_OK) return PyLong_FromLong(rc);
     PyObject* out = PyTuple_New(3);
     if (!out) return nullptr;
