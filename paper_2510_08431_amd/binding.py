@@ -126,14 +126,42 @@ def _workspace(device, stream, raw_stream, nbytes):
     calls on different streams may overlap and get separate buffers.  Callers that want to own the memory pass their own
     `workspace`.  `stream` may be None: the current one, whose handle raw_stream is."""
     key = (device, raw_stream)
-    ws = _workspaces.get(key)
+    capturing = _capturing(device, stream, raw_stream)
+    ws = None if capturing else _workspaces.get(key)
     if ws is None or ws.numel() < nbytes:
         if stream is None:
             stream = torch.cuda.current_stream(device)
         with torch.cuda.stream(stream):      # so that torch's caching allocator ties the block to this stream
             ws = torch.empty(nbytes, dtype=torch.uint8, device=device)
-        _workspaces[key] = ws
+        if not capturing:
+            _workspaces[key] = ws
+        elif not _of_a_graph(ws):
+            _kept.append(ws)
     return ws
+
+
+_kept = []
+
+
+def _capturing(device, stream, raw_stream):
+    """Whether the call is recorded into a graph: it then gets a buffer of its own, not the cached one, which a later call may
+    replace while the graph still writes to it, and which other graphs and eager calls would share."""
+    if raw_stream == 0:      # (the default stream cannot be captured)
+        return False
+    if device.index == torch.cuda.current_device() and raw_stream == _raw_stream(device):
+        return torch.cuda.is_current_stream_capturing()
+    with torch.cuda.stream(torch.cuda.current_stream(device) if stream is None else stream):
+        return torch.cuda.is_current_stream_capturing()
+
+
+def _of_a_graph(ws):
+    """Whether ws lies in a graph's private pool, whose memory eager work never gets, so that nobody needs to hold it.  (Under a capture
+    that torch does not know of it does not, and _kept holds it until the process ends: nobody says when such a graph goes.)"""
+    try:
+        segments = torch.cuda.memory_snapshot()
+    except RuntimeError:      # (an allocator that cannot say)
+        return False
+    return any(s["address"] <= ws.data_ptr() < s["address"] + s["total_size"] and tuple(s["segment_pool_id"]) != (0, 0) for s in segments)
 
 
 def _raw_stream(device):
@@ -195,7 +223,7 @@ def attn_jvp_fwd_ex(q, k, v, tq, tk, tv, scale, out=None, out_dtype=torch.float3
     q, tq: [B, H, Lq, d]; k, v, tk, tv: [B, H, Lkv, d]; bf16 or fp32, contiguous, on the GPU.  tk and tv may both be
     None: zero key/value tangents (cross-attention onto a context without tangent); tq, tk, tv all None: plain
     attention forward, the returned `to` is None.
-    out: optional (o, to, lse) to write into.  workspace: "auto" (a cached per-device torch buffer), None (no
+    out: optional (o, to, lse) to write into.  workspace: "auto" (a torch buffer cached per device and stream; one of its own for a call that is captured), None (no
     scratch: the kernel then uses its bf16-pair path), a uint8 CUDA tensor, or "static" (the C entry point
     attn_jvp_fwd_static: the library's own static device array; with `out` given the call allocates nothing).  layout=LAYOUT_BLHD: all eight
     tensors are [B, L, H, d] instead (lse stays [B, H, Lq]).  timing_events: optional pair of

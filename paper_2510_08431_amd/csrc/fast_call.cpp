@@ -1,7 +1,7 @@
 // The ordinary calls of binding.py without its Python and ctypes steps: new outputs from torch's allocator, the current stream,
 // the cached workspace.  attn() and rmsnorm() do what attn_jvp_fwd_ex and attn_jvp_rmsnorm_fwd of binding.py do for plain
 // contiguous GPU tensors that fit together; for anything else (other tensor types, modes that watch torch's calls, functorch's
-// wrapped tensors, another current device, arguments that do not fit) they return None, and binding.py does the whole call,
+// wrapped tensors, another current device, calls recorded into a graph, arguments that do not fit) they return None, and binding.py does the whole call,
 // errors included.  A call's host time is what bounds small shapes: 13.1 -> 7.1 us a call back to back (8 heads, 300 queries,
 // 77 keys, d = 64, whose kernel takes 5), 8.5 -> 5.4 for the normalisation.
 #include <Python.h>
@@ -10,6 +10,7 @@
 #include <c10/core/impl/LocalDispatchKeySet.h>
 #include <c10/core/impl/TorchDispatchModeTLS.h>
 #include <c10/hip/HIPFunctions.h>
+#include <c10/hip/HIPGraphsC10Utils.h>
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/Dtype.h>
 #include <torch/csrc/Exceptions.h>
@@ -160,6 +161,10 @@ PyObject* attn(PyObject*, PyObject* const* a, Py_ssize_t n) {
         if (t[i] && (t[i]->scalar_type() != dtype || t[i]->device() != q.device() || t[i]->sizes() != (i == 3 ? q : k).sizes())) Py_RETURN_NONE;
     const auto index = q.device().index();
     if (c10::hip::current_device() != index) Py_RETURN_NONE;
+    const hipStream_t stream = c10::hip::getCurrentHIPStream(index).stream();
+    const size_t need = a[11] == Py_True ? scratch_bytes((int)B, (int)H, (int)Lq, (int)Lkv, (int)d, f32) : 0;
+    // (a call that is recorded into a graph has a workspace of its own; the default stream cannot be captured)
+    if (need > 0 && stream && c10::hip::currentStreamCaptureStatusMayInitCtx() != c10::hip::CaptureStatus::None) Py_RETURN_NONE;
 
     const at::Tensor o = at::empty_like(q, q.options().dtype(out_dtype), at::MemoryFormat::Contiguous);
     const at::Tensor to = t[3] ? at::empty_like(o) : at::Tensor();
@@ -167,19 +172,15 @@ PyObject* attn(PyObject*, PyObject* const* a, Py_ssize_t n) {
     attn_jvp_opts opts = {};
     opts.in_dtype = f32 ? ATTN_JVP_FP32 : ATTN_JVP_BF16;
     opts.out_dtype = out_dtype == at::kFloat ? ATTN_JVP_OUT_FP32 : ATTN_JVP_OUT_INPUT;
-    const hipStream_t stream = c10::hip::getCurrentHIPStream(index).stream();
     opts.stream = stream;
     opts.kernel = (int)kernel;
     opts.flags = (int)flags;
     opts.layout = (int)layout;
     Workspace ws;
-    if (a[11] == Py_True) {
-        const size_t need = scratch_bytes((int)B, (int)H, (int)Lq, (int)Lkv, (int)d, f32);
-        if (need > 0) {
-            if (!ws.take(a[0], stream, need)) return nullptr;
-            opts.workspace = ws.get().data_ptr();
-            opts.workspace_bytes = (size_t)ws.get().numel();
-        }
+    if (need > 0) {
+        if (!ws.take(a[0], stream, need)) return nullptr;
+        opts.workspace = ws.get().data_ptr();
+        opts.workspace_bytes = (size_t)ws.get().numel();
     }
     const void* in[6];
     for (int i = 0; i < 6; ++i) in[i] = t[i] ? t[i]->data_ptr() : nullptr;
