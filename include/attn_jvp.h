@@ -203,13 +203,15 @@ int attn_jvp_fwd_ex(const void* q, const void* k, const void* v,
  * up to B*H*Lkv = 409 000 keys at d = 128, e.g. the 32760-token shape with 12 heads); every GPU the library is
  * used on holds its copy from the first use until the process ends.  The call allocates nothing (no hipMalloc,
  * no hipFree, no allocating library routine) and is otherwise attn_jvp_fwd_ex: same arguments, same kernels, same
- * results bit for bit as attn_jvp_fwd_ex with a workspace of attn_jvp_workspace_bytes(...).
+ * results bit for bit as attn_jvp_fwd_ex with a workspace of attn_jvp_workspace_bytes(...).  Calls that could do without
+ * scratch (fp32 inputs; bf16 inputs with fewer than 2048 keys and d other than 32, but for those with four query tiles
+ * per compute unit) never go with their keys in parts here: they leave the array alone and may overlap.
  * opts may be NULL (defaults); opts->workspace must be NULL (ATTN_JVP_UNSUPPORTED otherwise).  Shapes whose
  * attn_jvp_workspace_bytes(...) exceeds the array are rejected with ATTN_JVP_TOO_LARGE before anything is
- * launched (the room for keys in parts is no reason to refuse).  All calls on one GPU, fp32 inputs included, share that GPU's array: calls whose work overlaps in time (different
- * streams, different host threads) race on it and must be serialised by the caller; calls on one stream are
- * ordered and safe.  The array keeps the last call's contents; the kernels re-initialise what they read
- * (statistics, tile flags and tickets are cleared by the call's own first kernels).
+ * launched (the room for keys in parts is no reason to refuse).  All calls on one GPU that use scratch share that GPU's
+ * array: such calls whose work overlaps in time (different streams, different host threads) race on it and must be
+ * serialised by the caller; calls that one thread makes on one stream are ordered and safe.  The array keeps the last
+ * call's contents; the kernels re-initialise what they read (statistics, tile flags and tickets are cleared by the call's own first kernels).
  */
 int attn_jvp_fwd_static(const void* q, const void* k, const void* v,
                         const void* tq, const void* tk, const void* tv,

@@ -106,14 +106,18 @@ int run(const void* q, const void* k, const void* v, const void* tq, const void*
     for (const void* p : ptrs)
         if (!aligned16(p)) return ATTN_JVP_MISALIGNED;
 
+    const bool f32 = opts->in_dtype == ATTN_JVP_FP32;
     void* workspace = opts->workspace;
     size_t workspace_bytes = opts->workspace ? opts->workspace_bytes : 0;
+    bool parts_allowed = workspace != nullptr;
     if (use_static_scratch) {
         if (opts->workspace) return ATTN_JVP_UNSUPPORTED;      // this entry point brings its own scratch
         // (room for the states of keys in parts is used where it is there: never a reason to refuse)
-        const bool bf16 = opts->in_dtype == ATTN_JVP_BF16;
-        if (bf16 && value_path_bytes(B, H, Lq, Lkv, d) > (size_t)ATTN_JVP_STATIC_SCRATCH_BYTES) return ATTN_JVP_TOO_LARGE;
-        if ((bf16 ? attn_jvp_workspace_bytes(B, H, Lq, Lkv, d) : attn_jvp::split_bytes(B, H, Lq, Lkv, d, true)) > 0) {
+        const size_t need = f32 ? 0 : value_path_bytes(B, H, Lq, Lkv, d);
+        if (need > (size_t)ATTN_JVP_STATIC_SCRATCH_BYTES) return ATTN_JVP_TOO_LARGE;
+        // One array for all streams and threads: a call that needs no scratch leaves it alone, so that such calls may overlap.
+        parts_allowed = need > 0 && (d == 32 || Lkv >= attn_jvp::F16_MIN_KEYS);
+        if (need > 0) {
             if (attn_jvp::static_scratch(&workspace) != hipSuccess) return ATTN_JVP_LAUNCH_FAILED;
             workspace_bytes = ATTN_JVP_STATIC_SCRATCH_BYTES;
         }
@@ -125,14 +129,13 @@ int run(const void* q, const void* k, const void* v, const void* tq, const void*
               static_cast<hipEvent_t>(opts->timing_events[0]), static_cast<hipEvent_t>(opts->timing_events[1]),
               opts->layout, d, opts->layout, {}};
 
-    const bool f32 = opts->in_dtype == ATTN_JVP_FP32;
     const bool mfma_ok = f32 ? attn_jvp::mfma_f32_supports(p) : attn_jvp::mfma_bf16_supports(p);
     int kernel = opts->kernel;
     if (kernel == ATTN_JVP_KERNEL_AUTO) kernel = mfma_ok ? ATTN_JVP_KERNEL_MFMA : ATTN_JVP_KERNEL_FP32;
 
     hipError_t e;
     // Too few query tiles for the chip's rounds: the tile kernels on keys in parts, given room for the parts' states.
-    if (opts->kernel == ATTN_JVP_KERNEL_AUTO && mfma_ok && p.flags == 0 && workspace != nullptr) {
+    if (opts->kernel == ATTN_JVP_KERNEL_AUTO && mfma_ok && p.flags == 0 && parts_allowed) {
         const attn_jvp::KeySplit split = attn_jvp::plan_split(B, H, Lq, Lkv, d, f32, tq != nullptr, tk != nullptr);
         const size_t before = f32 || d != 32 ? 0 : pad_bytes(B, H, Lq, Lkv, d);
         if (split.parts > 1 && workspace_bytes >= before + attn_jvp::split_bytes(B, H, Lq, Lkv, d, f32)) p.split = split;

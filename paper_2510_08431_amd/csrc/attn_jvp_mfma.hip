@@ -329,7 +329,7 @@ constexpr int STAGGER_MIN_ROUNDS_OF_PAIRS = 5;
 // tile; per key block it is a quarter faster than the bf16 pairs.  It pays from 2048 keys on, and from 256 keys on when
 // the call has at least four tiles per compute unit to spread the pre-pass over (measured per tile, 12 tiles per unit:
 // 8 key blocks 24.8 against 27.9 us, 16 blocks 33.6 against 37.8 us); below that the bf16 pairs run unless the caller insists.
-constexpr int F16_MIN_KEYS = 2048, F16_MIN_KEYS_MANY_TILES = 256, F16_MANY_TILES_PER_CU = 4;
+constexpr int F16_MIN_KEYS_MANY_TILES = 256, F16_MANY_TILES_PER_CU = 4;      // (F16_MIN_KEYS: launchers.h)
 
 // One query tile (128 rows of one head), start to finish.  `vw` is the tile's index in the launch's list of
 // (head, query tile) pairs as a one-workgroup-per-tile launch would number its workgroups; n_tiles their count.

@@ -105,9 +105,8 @@ constexpr size_t MAX_BYTES = (size_t)160 << 20;       // of states: what the lib
 constexpr double WORTH = 0.92;                        // estimated share of the unsplit time from which on it is not worth it
 
 struct BlockCost {
-    double tile, unsplit, keysplit;      // us per key block: a tile in parts; a tile as it runs unsplit from F16_KEYS on; 16 rows of the key-split kernel
+    double tile, unsplit, keysplit;      // us per key block: a tile in parts; a tile as it runs unsplit from F16_MIN_KEYS on; 16 rows of the key-split kernel
 };
-constexpr int F16_KEYS = 2048;
 BlockCost block_cost(int d, bool f32, bool plain) {
     const int i = d / 32 - 1;
     static const BlockCost bf16_all[4] = {{.95, .58, .28}, {.95, .58, .33}, {1.15, .77, .45}, {1.6, 1.05, .76}};
@@ -139,7 +138,7 @@ KeySplit plan_split(int B, int H, int Lq, int Lkv, int d, bool f32, bool tangent
     double unsplit;
     if (groups <= (long long)keysplit_groups_per_unit(d, f32, tangents, key_tangents) * UNITS)
         unsplit = 8 + c.keysplit * blocks * std::max(1.0, (double)groups / UNITS);
-    else if (!f32 && Lkv >= F16_KEYS)      // the fp16 value path: its pre-pass, and more to do at a tile's start and end
+    else if (!f32 && Lkv >= F16_MIN_KEYS)      // the fp16 value path: its pre-pass, and more to do at a tile's start and end
         unsplit = 34 + rounds_cost((double)tiles, 5, blocks * c.unsplit);
     else
         unsplit = rounds_cost((double)tiles, fixed, blocks * c.tile);

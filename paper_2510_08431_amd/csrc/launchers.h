@@ -64,6 +64,7 @@ bool mfma_f32_supports(const Problem& p);
 bool fp32_vector_supports(const Problem& p);
 
 constexpr int MFMA_TILE_ROWS = 128;   // query rows per workgroup of the MFMA kernel
+constexpr int F16_MIN_KEYS = 2048;    // keys from which on a bf16 call with a workspace takes the fp16 value path, however few its tiles
 
 // Keys in parts (attn_jvp_split.hip).  plan_split: the parts that suit a shape (host arithmetic, the same with and without a
 // GPU); split_bytes: room for their states.  part_states: where the tile kernels put what a tile gives (the caller's outputs where

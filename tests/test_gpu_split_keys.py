@@ -90,7 +90,8 @@ def test_layouts_output_types_and_scratch(case):
     dev = [x.to(DEV) for x in t]
     binding.attn_jvp_fwd_static(*dev, 0.1, out)
     torch.cuda.synchronize()
-    assert all(torch.equal(a, b) for a, b in zip(out, want))
+    own = {} if dtype == BF16 else {"workspace": None}      # (fp32: the entry point leaves its array alone)
+    assert all(torch.equal(a, b) for a, b in zip(out, run(t, 0.1, **own)))
     need = scratch_of(2 * H, Lq, Lkv, d, dtype)
     guarded = torch.full((need + 512,), 0x5a, dtype=torch.uint8, device=DEV)
     exact = run(t, 0.1, workspace=guarded[:need])
@@ -100,12 +101,25 @@ def test_layouts_output_types_and_scratch(case):
         binding.attn_jvp_fwd_static(*dev, 0.1, out)
     for rep in range(3):
         dev[0].mul_(0.9)
-        eager = binding.attn_jvp_fwd_ex(*dev, 0.1)
+        eager = binding.attn_jvp_fwd_ex(*dev, 0.1, **own)
         for x in out:
             x.fill_(float("nan"))
         graph.replay()
         torch.cuda.synchronize()
         assert all(torch.equal(a, b) for a, b in zip(out, eager)), rep
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("case", [(F32, 128, 1, 300, 1024), (F32, 32, 1, 300, 3000), (BF16, 128, 4, 1100, 1100), (BF16, 64, 4, 1900, 1900)],
+                         ids=["fp32-d128", "fp32-d32", "bf16-d128", "bf16-d64"])
+def test_static_calls_that_need_no_scratch_leave_it_alone(case):
+    """The library's array is one for all streams: only a call that has to use it does, so that the others may overlap."""
+    dtype, d, H, Lq, Lkv = case
+    t = [x.to(DEV) for x in inputs(10, 1, H, Lq, Lkv, d, dtype)]
+    out = tuple(torch.empty(s, device=DEV) for s in ((1, H, Lq, d), (1, H, Lq, d), (1, H, Lq)))
+    binding.attn_jvp_fwd_static(*t, 0.1, out)
+    alone, parts = run(t, 0.1, workspace=None), run(t, 0.1)
+    assert all(torch.equal(a, b) for a, b in zip(out, alone)) and not torch.equal(parts[0], alone[0])
 
 
 @pytest.mark.gpu
