@@ -87,15 +87,16 @@ extern "C" {
                                      operands split into bf16 terms that sum to them exactly, fp32 accuracy, no workspace */
 #define ATTN_JVP_KERNEL_FP32 1    /* fp32 kernels, any dtype: d in {32, 64, 128} on the vector ALU (slow), d = 256 the key-split
                                      kernel */
-#define ATTN_JVP_KERNEL_MFMA 2    /* matrix-core kernels (without flags the key-split kernel for few query rows, as AUTO,
-                                     except for bf16 inputs with a workspace).
+#define ATTN_JVP_KERNEL_MFMA 2    /* matrix-core kernels (without FAST, NO_F16 or F16_ALWAYS the key-split kernel for few query
+                                     rows, as AUTO, except for bf16 inputs with a workspace).
                                      bf16 inputs: scale > 0, d in {64, 128}; d in {32, 96} given a workspace of
                                      attn_jvp_workspace_bytes(...).  64, 96 and 128 are built natively; at 32 the
                                      inputs are first copied into the workspace zero-padded to 64 columns (exact: the
                                      padding adds zeros to every product; half of the matrix work is spent on zeros).
                                      fp32 inputs: d in {32, 64, 96, 128}, any finite scale, fp32 outputs; every product
                                      as three 16-bit products of operands split into two fp16 terms each (22 to 23
-                                     bits), fp32 accumulation, no workspace, flags ignored.  Tiles (128 query rows)
+                                     bits), fp32 accumulation, no workspace; FAST, NO_F16 and F16_ALWAYS ask for this kernel
+                                     whatever the rows, and change nothing else in it.  Tiles (128 query rows)
                                      whose values do not suit the scaled fp16 ranges are computed with fp32 products
                                      instead: V of later keys 16 times or 2^-14 of the first 32 keys' (zeros in front
                                      are enough), whole columns of V 2^-14 of the largest, rows of q or tq that span
@@ -109,7 +110,8 @@ extern "C" {
                                      which one key carries the weight add up to 40 x 2^-24 x max|S| (the rounding of
                                      the fp32 score itself, which the exponential turns into a relative error) */
 
-/* attn_jvp_opts.flags */
+/* attn_jvp_opts.flags.  FAST, NO_F16 and F16_ALWAYS name an arithmetic of the kernel with 128-row query tiles: AUTO then
+ * takes neither the key-split kernel nor keys in parts in its place.  NO_LOCKSTEP and NO_RESIDENT leave the choice as it is. */
 #define ATTN_JVP_FLAG_FAST 1      /* EXPERIMENTAL, outside the accuracy contract (O within 1e-2, tO within 2e-2 of RMS): kept for
                                      measurements only.
                                      MFMA kernel only (not with absent tangents): round the weights P~ and H~ = P~ o tS to ONE bf16 term each
@@ -163,7 +165,7 @@ typedef struct attn_jvp_opts {
                                lse carries the rounding of l (at most 2^-11 absolute).  Without a workspace, and for
                                Lkv < 2048 (Lkv < 256 for calls with at least four 128-row query tiles per compute
                                unit): hi + lo bf16 pairs everywhere (9 products, ~16-bit weights).
-                               Also (AUTO without flags, bf16 and fp32 inputs): calls whose 128-row query tiles do not
+                               Also (AUTO without FAST, NO_F16 or F16_ALWAYS, bf16 and fp32 inputs): calls whose 128-row query tiles do not
                                fill the chip run with every head's keys in two to eight parts, whose states go through
                                the workspace and are merged by a second launch; bf16 inputs then take the bf16 pairs. */
     size_t workspace_bytes; /* size of `workspace` */

@@ -134,15 +134,18 @@ int run(const void* q, const void* k, const void* v, const void* tq, const void*
     if (kernel == ATTN_JVP_KERNEL_AUTO) kernel = mfma_ok ? ATTN_JVP_KERNEL_MFMA : ATTN_JVP_KERNEL_FP32;
 
     hipError_t e;
+    // Flags that name an arithmetic of the tile kernel on whole keys ask for that kernel.  The other two change how it is launched, never a
+    // result, and so not the kernel.
+    const bool tile_asked = p.flags & (ATTN_JVP_FLAG_FAST | ATTN_JVP_FLAG_NO_F16 | ATTN_JVP_FLAG_F16_ALWAYS);
     // Too few query tiles for the chip's rounds: the tile kernels on keys in parts, given room for the parts' states.
-    if (opts->kernel == ATTN_JVP_KERNEL_AUTO && mfma_ok && p.flags == 0 && parts_allowed) {
+    if (opts->kernel == ATTN_JVP_KERNEL_AUTO && mfma_ok && !tile_asked && parts_allowed) {
         const attn_jvp::KeySplit split = attn_jvp::plan_split(B, H, Lq, Lkv, d, f32, tq != nullptr, tk != nullptr);
         const size_t before = f32 || d != 32 ? 0 : pad_bytes(B, H, Lq, Lkv, d);
         if (split.parts > 1 && workspace_bytes >= before + attn_jvp::split_bytes(B, H, Lq, Lkv, d, f32)) p.split = split;
     }
     // Calls whose 128-row tiles would leave much of the chip idle, and all that AUTO finds no tile kernel for, go to the kernel
-    // that deals the keys to the waves.  A flag, or an explicit request together with a workspace, asks for the tile kernel.
-    const bool few_rows = kernel == ATTN_JVP_KERNEL_MFMA && mfma_ok && p.flags == 0 && p.split.parts == 1 &&
+    // that deals the keys to the waves.  (An explicit request together with a workspace asks for the tile kernel too.)
+    const bool few_rows = kernel == ATTN_JVP_KERNEL_MFMA && mfma_ok && !tile_asked && p.split.parts == 1 &&
                           (f32 || opts->kernel == ATTN_JVP_KERNEL_AUTO || workspace == nullptr);
     const bool no_tiles = opts->kernel == ATTN_JVP_KERNEL_AUTO && !mfma_ok && attn_jvp::fp32_vector_supports(p);
     if (few_rows || no_tiles) {

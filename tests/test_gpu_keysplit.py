@@ -15,6 +15,7 @@ pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
 NAMES = ("q", "k", "v", "tq", "tk", "tv")
 DTYPES = pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16], ids=["fp32", "bf16"])
+LAUNCH_FLAGS = (binding.FLAG_NO_RESIDENT, binding.FLAG_NO_LOCKSTEP, binding.FLAG_NO_RESIDENT | binding.FLAG_NO_LOCKSTEP)      # results are identical
 DIMS = pytest.mark.parametrize("d", [32, 64, 96, 128, 256])
 
 
@@ -95,11 +96,13 @@ def test_route_by_rows_and_flags(d, dtype, kernel):
     """Few rows come here (fp32 accuracy shows it for bf16 inputs), a flag asks for the tile kernel, many rows go there."""
     scale = float(np.float32(d ** -0.5))
     t = inputs(5, 1, 2, 200, 300, d, dtype)
-    few, tile = run(t, scale, kernel=kernel), run(t, scale, kernel=kernel, flags=binding.FLAG_NO_RESIDENT)
+    few, tile = run(t, scale, kernel=kernel), run(t, scale, kernel=kernel, flags=binding.FLAG_NO_F16)
     check(few, t, scale, "few rows")
     assert not torch.equal(few[0], tile[0])
+    for flags in LAUNCH_FLAGS:
+        assert all(torch.equal(x, y) for x, y in zip(few, run(t, scale, kernel=kernel, flags=flags)))
     many = inputs(6, 1, 16, 5 * 16 * 17, 40, d, dtype)             # 85 groups of 16 rows a head, 1360 in all
-    a, b = run(many, scale, kernel=kernel), run(many, scale, kernel=kernel, flags=binding.FLAG_NO_RESIDENT)
+    a, b = run(many, scale, kernel=kernel), run(many, scale, kernel=kernel, flags=binding.FLAG_NO_F16)
     assert all(torch.equal(x, y) for x, y in zip(a, b))
 
 

@@ -71,7 +71,7 @@ def test_parts_against_the_oracle(case, names):
     dtype, d, H, Lq, Lkv = case
     scale = float(np.float32(d ** -0.5))
     t = inputs(Lkv + names, 1, H, Lq, Lkv, d, dtype, names)
-    got, whole = run(t, scale), run(t, scale, flags=binding.FLAG_NO_RESIDENT)
+    got, whole = run(t, scale), run(t, scale, flags=binding.FLAG_NO_F16)
     check(got, t, scale, dtype)
     assert not torch.equal(got[0], whole[0])                  # (the call went in parts)
 
@@ -84,6 +84,8 @@ def test_layouts_output_types_and_scratch(case):
     want = run(t, 0.1)
     blhd = run([x.transpose(1, 2).contiguous() for x in t], 0.1, layout=binding.LAYOUT_BLHD)
     assert torch.equal(blhd[0].transpose(1, 2), want[0]) and torch.equal(blhd[1].transpose(1, 2), want[1]) and torch.equal(blhd[2], want[2])
+    for flags in (binding.FLAG_NO_RESIDENT, binding.FLAG_NO_LOCKSTEP):
+        assert all(torch.equal(a, b) for a, b in zip(run(t, 0.1, flags=flags), want))
     low = run(t, 0.1, out_dtype=dtype)
     assert torch.equal(low[0], want[0].to(dtype)) and torch.equal(low[1], want[1].to(dtype)) and torch.equal(low[2], want[2])
     out = tuple(torch.empty_like(x) for x in want)
