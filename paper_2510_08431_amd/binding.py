@@ -1,5 +1,6 @@
 """Binding of the attn_jvp C-ABI library: argument marshalling only, through ctypes, and for the ordinary calls through the
-extension module _fast_call (csrc/fast_call.cpp), which does the same steps natively.
+extension module _fast_call (csrc/fast_call.cpp), which does the same steps natively (where it does not load, with a warning,
+every call takes the first way).
 
 PyTorch supplies device memory (`data_ptr()`) and the current HIP stream; every step of
 the computation runs inside the library's kernels.  There is no CPU or eager fallback:
@@ -10,6 +11,7 @@ import ctypes
 import functools
 import os
 import threading
+import warnings
 
 import torch
 
@@ -38,6 +40,11 @@ class AttnJvpError(RuntimeError):
     def __init__(self, code, message):
         super().__init__(f"attn_jvp error {code}: {message}")
         self.code = code
+
+
+class _NoFastCall:
+    """In the extension module's place where it cannot be used: no call is an ordinary one."""
+    attn = rmsnorm = staticmethod(lambda *a: None)
 
 
 _lib = None
@@ -76,11 +83,25 @@ def load_library():
     lib.attn_jvp_workspace_bytes.restype = ctypes.c_size_t
     lib.attn_jvp_workspace_bytes_fp32.argtypes = [ci] * 5
     lib.attn_jvp_workspace_bytes_fp32.restype = ctypes.c_size_t
-    from . import _fast_call
-    _hand_over(_fast_call, lib, lib.attn_jvp_fwd_ex)
-    _fast = _fast_call
+    _fast = _load_fast_call()
+    if _fast is not _NoFastCall:
+        _hand_over(_fast, lib, lib.attn_jvp_fwd_ex)
     _lib = lib
     return lib
+
+
+def _load_fast_call():
+    """The extension module, or _NoFastCall: it only saves host time, and is tied to the torch and Python it was built with."""
+    try:
+        from . import _fast_call
+        if _fast_call.torch_version == torch.__version__:
+            return _fast_call
+        reason = f"built for torch {_fast_call.torch_version}, this is {torch.__version__}"
+    except (ImportError, AttributeError) as e:
+        reason = str(e)
+    warnings.warn(f"attn_jvp: host time per call is higher without the extension module _fast_call ({reason}); "
+                  "build it: python -c 'import __graft_entry__ as g; g.build()'", RuntimeWarning, stacklevel=3)
+    return _NoFastCall
 
 
 def _hand_over(fast, lib, fwd_ex):

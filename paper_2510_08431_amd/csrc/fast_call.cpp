@@ -242,4 +242,8 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_fast_call", nullptr, -1, methods,
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__fast_call() { return PyModule_Create(&module); }
+PyMODINIT_FUNC PyInit__fast_call() {
+    PyObject* m = PyModule_Create(&module);
+    if (m && PyModule_AddStringConstant(m, "torch_version", BUILT_FOR_TORCH) != 0) Py_CLEAR(m);      // (binding.py compares it)
+    return m;
+}

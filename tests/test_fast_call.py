@@ -1,4 +1,7 @@
 """The native way of an ordinary call (csrc/fast_call.cpp) against the Python one, which takes every call that names a stream."""
+import os
+import subprocess
+import sys
 import threading
 
 import pytest
@@ -111,3 +114,39 @@ def test_streams_and_threads():
     [x.start() for x in threads]
     [x.join() for x in threads]
     assert not wrong
+
+
+CHILD = """
+import sys, warnings
+sys.path.insert(0, sys.argv[1])
+import torch
+from paper_2510_08431_amd import binding
+with warnings.catch_warnings(record=True) as seen:
+    warnings.simplefilter("always")
+    assert binding.load_library().attn_jvp_version() > 0
+assert binding.__file__.startswith(sys.argv[1])
+x = torch.zeros(1, 1, 8, 64)
+for call in (lambda: binding.attn_jvp_fwd_ex(x, x, x, x, x, x, 0.1), lambda: binding.attn_jvp_rmsnorm_fwd(x, x, torch.ones(64), 1e-6),
+             lambda: binding.attn_jvp_fwd(*[x.bfloat16()] * 6, 0.1)):
+    try:
+        call()
+        raise SystemExit("accepted CPU tensors")
+    except ValueError as e:
+        assert "must live on the GPU" in str(e)
+print([str(w.message) for w in seen if "_fast_call" in str(w.message)])
+"""
+
+
+@pytest.mark.parametrize("module,content,reason", [(None, None, "cannot import name '_fast_call'"), ("_fast_call.so", b"not a library", "file too short"),
+                                                   ("_fast_call.py", b"torch_version = '1.0.0'", "built for torch 1.0.0"), ("_fast_call.py", b"", "no attribute 'torch_version'")])
+def test_the_library_alone_serves(tmp_path, module, content, reason):
+    """Without the extension module, or with one that does not load or fits another torch: a warning, and every call the Python way."""
+    binding.load_library()
+    here, there = os.path.dirname(binding.__file__), tmp_path / "paper_2510_08431_amd"
+    there.mkdir()
+    for name in ("__init__.py", "binding.py", "libattn_jvp.so"):
+        os.symlink(os.path.join(here, name), there / name)
+    if module:
+        (there / module).write_bytes(content)
+    res = subprocess.run([sys.executable, "-c", CHILD, str(tmp_path)], capture_output=True, text=True, timeout=300)
+    assert res.returncode == 0 and reason in res.stdout, res.stdout + res.stderr
