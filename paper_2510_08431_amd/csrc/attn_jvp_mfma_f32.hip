@@ -392,12 +392,14 @@ __device__ __forceinline__ void fp32_tile(
     }
 }
 
-template <int D, int TAN>
+// PARTS: keys in parts, an instantiation of its own (its bookkeeping in the one for whole calls cost those of few blocks: fp32 d64
+// without tangents, H8 L2668, 98.4 -> 101.1 us; d128, query tangents, H20 Lq1700 Lkv77 52.5 -> 53.2).
+template <int D, int TAN, bool PARTS>
 __global__ __launch_bounds__(NTHREADS, (Geo<D, TAN>::WG_PER_CU)) void attn_jvp_mfma_f32_kernel(
     const float* __restrict__ Q, const float* __restrict__ K, const float* __restrict__ V,
     const float* __restrict__ tQ, const float* __restrict__ tK, const float* __restrict__ tV,
     float* __restrict__ O, float* __restrict__ tO, float* __restrict__ LSE,
-    int Lq, int keys, float scale, int q_tiles, int H, int blhd, int parts, int part_blocks, f32x4* __restrict__ part_state) {
+    int Lq, int keys, float scale, int q_tiles, int H, int blhd, int parts_in, int part_blocks, f32x4* __restrict__ part_state) {
     // No implicit fusing of a product with a following sum: the compiler would fuse differently in each instantiation,
     // and the instantiations must agree bit for bit (absent tangents against zero tangents).  fmaf() stays fused.
 #pragma clang fp contract(off)
@@ -419,7 +421,8 @@ __global__ __launch_bounds__(NTHREADS, (Geo<D, TAN>::WG_PER_CU)) void attn_jvp_m
     const int n_wg = gridDim.x;
     const int bid = (n_wg & 7) == 0 ? (int)(blockIdx.x & 7) * (n_wg >> 3) + (int)(blockIdx.x >> 3) : (int)blockIdx.x;
     // (keys in parts, see attn_jvp_split.hip: a tile's K and V are those of its part, its results row bhp Lq + query of the
-    // partial states; part_state is null where there is one part)
+    // partial states)
+    const int parts = PARTS ? parts_in : 1;
     const long bhp = bid / q_tiles;
     const long bh = parts > 1 ? bhp / parts : bhp;
     const int key0 = parts > 1 ? (int)(bhp - bh * parts) * part_blocks * BC : 0;
@@ -1148,7 +1151,7 @@ __global__ __launch_bounds__(NTHREADS, (Geo<D, TAN>::WG_PER_CU)) void attn_jvp_m
         const float inv_l = 1.f / l_row;
         const float mu = r_row * inv_l * gr;         // rowsum(P o tS), in the accumulators' scale
         const float fo = go * inv_l, ft = gt * inv_l;
-        const long at = (part_state ? (bhp * Lq + qrow) * D : q_base + (long)qrow * row_elems) + 4 * g;
+        const long at = (PARTS ? (bhp * Lq + qrow) * D : q_base + (long)qrow * row_elems) + 4 * g;
         float* op = O + at;
         float* top = TANGENT ? tO + at : nullptr;
 #pragma unroll
@@ -1168,20 +1171,20 @@ __global__ __launch_bounds__(NTHREADS, (Geo<D, TAN>::WG_PER_CU)) void attn_jvp_m
             }
         }
         if (g == 0) {
-            if (part_state) part_state[bhp * Lq + qrow] = f32x4{m, l_row, mu * (gt / go), 0.f};
+            if constexpr (PARTS) part_state[bhp * Lq + qrow] = f32x4{m, l_row, mu * (gt / go), 0.f};
             else LSE[bh * Lq + qrow] = fmaf(__builtin_amdgcn_logf(l_row), LN2, m);     // v_log_f32 is a binary log
         }
     }
 }
 
-template <int D, int TAN>
-hipError_t launch_one(const Problem& p) {
+template <int D, int TAN, bool PARTS>
+hipError_t launch_parts(const Problem& p) {
     const int q_tiles = (p.Lq + BR - 1) / BR;
     const long long blocks = (long long)q_tiles * p.B * p.H * p.split.parts;
     if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
     const PartStates ps = part_states(p);
     constexpr int smem = Geo<D, TAN>::LDS_BYTES;
-    auto kern = attn_jvp_mfma_f32_kernel<D, TAN>;
+    auto kern = attn_jvp_mfma_f32_kernel<D, TAN, PARTS>;
     int dev = 0, cus = 0;
     hipError_t e = device_cus(&dev, &cus);
     if (e == hipSuccess) e = ensure_dynamic_lds(reinterpret_cast<const void*>(kern), smem, dev);
@@ -1193,8 +1196,13 @@ hipError_t launch_one(const Problem& p) {
                        (float*)ps.o, (float*)ps.to, p.lse, p.Lq, p.Lkv, p.scale, q_tiles, p.H, p.layout, p.split.parts, p.split.blocks,
                        (f32x4*)ps.state);
     e = hipGetLastError();
-    if (e == hipSuccess && p.split.parts > 1) e = launch_merge_parts(p, ps);
+    if (e == hipSuccess && PARTS) e = launch_merge_parts(p, ps);
     return timer.finish(e);
+}
+
+template <int D, int TAN>
+hipError_t launch_one(const Problem& p) {
+    return p.split.parts > 1 ? launch_parts<D, TAN, true>(p) : launch_parts<D, TAN, false>(p);
 }
 
 template <int D>
