@@ -19,12 +19,12 @@
 // block while its scores are formed, K of the next one behind them.  Q and tQ are the same for all waves: in LDS, as the
 // MFMAs read them.
 //
-// fp32 accuracy from bf16 products: an fp32 number is EXACTLY the sum of three bf16 numbers (x = hi + mid + lo, each the
-// leading 8 bits of what is left), with fp32's exponent range, so there is no scale to choose and nothing to
-// check.  fp32 x fp32: the six products down to 2^-24 of the largest (hi hi, hi mid, mid hi, mid mid, hi lo, lo hi).  bf16
+// fp32 accuracy from bf16 products: an fp32 number from 2^-110 up is EXACTLY the sum of three bf16 numbers (x = hi + mid + lo,
+// each the leading 8 bits of what is left), so there is no scale to choose.  Below, lo and then mid fall under bf16's smallest
+// subnormal; see SMALL.  fp32 x fp32: the six products down to 2^-24 of the largest (hi hi, hi mid, mid hi, mid mid, hi lo, lo hi).  bf16
 // inputs are one term; their weights P~, H~ are split like fp32 ones, three products.  Against the fp32 MFMAs, a sixteenth as
 // fast, that is 2.7 and 5.3 to 16 times less matrix time.  Infinities and NaN do not survive the split (inf - inf): a tile with a
-// result that is not finite is redone with fp32 products.
+// result that is not finite, or that may hang on numbers too small for the split, is redone with fp32 products.
 //
 // Bound by latency (one or two waves per SIMD, 75 % of their time waiting) and by the loads: 64 KiB per wave and block at d = 256 in
 // bf16, twice that in fp32.  Measured, kernel alone, us, before -> now (d <= 128: the tile kernels; d = 256: fp32 MFMAs, 64 rows to
@@ -56,6 +56,18 @@ constexpr float LOG2E_REST = (float)(1.4426950408889634 - (double)LOG2E);
 // values up to the end of the fp32 range stay in it; the price, weights that flush to zero MAX_SLACK nats earlier, is why
 // there are few.
 constexpr float MAX_SLACK = 4.f;
+
+// A term that falls away is below 2^-126, whichever number it is of.  A sum or result of at least SMALL does not show it, unless
+// a factor above LARGE is behind it: K, tK meet Q, tQ, which are looked at one by one (what is small beside others of its
+// sum costs nothing, but that is not known there); V, tV show in o, to (of bf16 inputs, exact as they are, neither) and the tangent
+// scores in rowsum(P o tS), so that the keys cost nothing to check.  Not seen: a weight below 2^-102 of its row's sum whose V is
+// above 2^78 times the row's result, and values below half of bf16's smallest subnormal, which come out as zero.
+// Measured: the check 0 to 2.6 % of a call (fp32 B1 H2 L256 d64 13.6 -> 13.9 us, 8 heads L300 d256 48.5 -> 48.9); a call whose tiles are
+// all redone 2.1 to 2.5 times the time in fp32, 2.9 to 3.8 times in bf16.  fp32 V x 1e-36: o 5e-5 out in the 2-norm -> 6e-7, tangents x 1e-36:
+// to 3e-3 -> 7e-7.
+constexpr float SMALL = 0x1p-80f, LARGE = 0x1p22f;
+// What of a tile is redone: o and lse apart from to, so that they have the same bits with and without tangents, whatever those are.
+constexpr int REDO_O = 1, REDO_TO = 2;
 
 #define FENCE() __builtin_amdgcn_sched_barrier(0)      // no instruction is scheduled across this point
 
@@ -111,6 +123,15 @@ struct Split {
     __device__ __forceinline__ void all(u32x4 (&term)[N][3]) {
         static_for<OPS>([&](auto I) __attribute__((always_inline)) { op<decltype(I)::value>(term); });
     }
+};
+// The smallest magnitude of the numbers given, zeros left out.
+struct Smallest {
+    uint32_t least = ~0u;                                                          // bits without sign, less one
+    __device__ __forceinline__ void see(float x) {
+        const uint32_t bits = 2 * __float_as_uint(x) - 1;
+        least = bits < least ? bits : least;
+    }
+    __device__ __forceinline__ bool below(float limit) const { return least < 2 * __float_as_uint(limit) - 1; }
 };
 // maximum and sum over the four lanes that share a query (lane, lane ^ 16, lane ^ 32, lane ^ 48)
 __device__ __forceinline__ float row_max(float x) {
@@ -282,6 +303,7 @@ __global__ __launch_bounds__((Cfg<TIn, D, TAN, KW>::NTHREADS), (Cfg<TIn, D, TAN,
     using A0 = std::integral_constant<int, 0>;
     using A1 = std::integral_constant<int, 1>;
     if (kw < n_blocks) load_k(kw);           // (uniform)
+    int redo = 0;                            // with fp32 products: REDO_*
     // ---- Q, tQ into LDS as B operands: lane l of step t holds row l % 16, elements 32 t + 8 (l / 16) .. + 7 ----
     for (int idx = tid; idx < C::GROUPS * (TANGENT ? 2 : 1) * NT * 64; idx += C::NTHREADS) {
         const int at_group = idx / ((TANGENT ? 2 : 1) * NT * 64), which = idx / (NT * 64) % (TANGENT ? 2 : 1), t = idx / 64 % NT, l = idx & 63;
@@ -293,8 +315,15 @@ __global__ __launch_bounds__((Cfg<TIn, D, TAN, KW>::NTHREADS), (Cfg<TIn, D, TAN,
             u32x4 term[1][3];
             float x[8];
             I::up(r, x);
+            Smallest small;
+            float top = 0.f;
 #pragma unroll
-            for (int i = 0; i < 8; ++i) split.x[i] = x[i];
+            for (int i = 0; i < 8; ++i) {
+                split.x[i] = x[i];
+                small.see(x[i]);
+                top = fmaxf(top, fabsf(x[i]));
+            }
+            if (__builtin_amdgcn_ballot_w64(small.below(SMALL) || top > LARGE) != 0) redo |= which ? REDO_TO : REDO_O | REDO_TO;      // (`which` is the wave's)
             split.all(term);
 #pragma unroll
             for (int y = 0; y < 3; ++y) *reinterpret_cast<u32x4*>(at + y * C::Q_PLANE) = term[0][y];
@@ -302,6 +331,7 @@ __global__ __launch_bounds__((Cfg<TIn, D, TAN, KW>::NTHREADS), (Cfg<TIn, D, TAN,
             *reinterpret_cast<u32x4*>(at) = __builtin_bit_cast(u32x4, r);
         }
     }
+    redo = __builtin_amdgcn_readfirstlane(redo);
     __syncthreads();
     auto q_term = [&](int which, int x, int t) __attribute__((always_inline)) {
         return *reinterpret_cast<const u32x4*>(smem + group * C::Q_BYTES + (which * TERMS + x) * C::Q_PLANE + t * 1024 + lane * 16);
@@ -568,8 +598,8 @@ __global__ __launch_bounds__((Cfg<TIn, D, TAN, KW>::NTHREADS), (Cfg<TIn, D, TAN,
         }
     };
 
-    // ---- the waves' partial states meet in LDS; true if a result is not finite ----
-    auto finish = [&]() __attribute__((always_inline)) -> bool {
+    // ---- the waves' partial states meet in LDS; returns what is not finite or small.  primal: o and lse are stored too ----
+    auto finish = [&](bool primal) __attribute__((always_inline)) -> int {
         l = row_sum(l);
         r_sum = row_sum(r_sum);
         __syncthreads();                             // everyone is done with Q, tQ (or with the previous states)
@@ -588,7 +618,7 @@ __global__ __launch_bounds__((Cfg<TIn, D, TAN, KW>::NTHREADS), (Cfg<TIn, D, TAN,
         f32x4* state = reinterpret_cast<f32x4*>(smem + C::STATE_BASE);
         if (kg == 0) state[wave * BR + c] = f32x4{m, l, r_sum, row_top};
         __syncthreads();
-        bool bad = false;
+        int odd = 0;
         for (int idx = tid; idx < C::ROWS * (D / 4); idx += C::NTHREADS) {
             const int row = idx / (D / 4), col = 4 * (idx % (D / 4));
             const int part0 = row / BR * KW, part_row = row % BR;        // its group's first wave
@@ -618,15 +648,22 @@ __global__ __launch_bounds__((Cfg<TIn, D, TAN, KW>::NTHREADS), (Cfg<TIn, D, TAN,
             // epilogue (Alg. 2, last lines)
             const float inv_l = 1.f / l_row;
             const float mu = r_row * inv_l;          // rowsum(P o tS)
-            float probe = 0.f;                       // NaN once anything is inf or NaN
+            float probe = 0.f, probe_t = 0.f;        // NaN once anything is inf or NaN
+            Smallest small, small_t;
+            if constexpr (TANGENT) small_t.see(mu);
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 if constexpr (TANGENT) t[e] = fmaf(-mu, o[e], t[e]) * inv_l;
                 o[e] *= inv_l;
                 probe = fmaf(o[e], 0.f, probe);
-                if constexpr (TANGENT) probe = fmaf(t[e], 0.f, probe);
+                if constexpr (TANGENT) probe_t = fmaf(t[e], 0.f, probe_t);
+                if constexpr (TERMS == 3) {
+                    small.see(o[e]);
+                    if constexpr (TANGENT) small_t.see(t[e]);
+                }
             }
-            bad = bad || probe != probe;
+            if (probe != probe || small.below(SMALL)) odd |= REDO_O | REDO_TO;
+            if (probe_t != probe_t || small_t.below(SMALL)) odd |= REDO_TO;
             if (q0 + row < Lq) {
                 const long at = q_base + (long)(q0 + row) * row_elems + col;
                 if (out_bf16) {                      // (uniform)
@@ -636,13 +673,13 @@ __global__ __launch_bounds__((Cfg<TIn, D, TAN, KW>::NTHREADS), (Cfg<TIn, D, TAN,
                         for (int e = 0; e < 4; ++e) b[e] = __float2bfloat16(x[e]);
                         *reinterpret_cast<uint2*>(static_cast<__hip_bfloat16*>(out) + at) = *reinterpret_cast<const uint2*>(b);
                     };
-                    store(O, o);
+                    if (primal) store(O, o);
                     if constexpr (TANGENT) store(tO, t);
                 } else {
-                    *reinterpret_cast<f32x4*>(static_cast<float*>(O) + at) = o;
+                    if (primal) *reinterpret_cast<f32x4*>(static_cast<float*>(O) + at) = o;
                     if constexpr (TANGENT) *reinterpret_cast<f32x4*>(static_cast<float*>(tO) + at) = t;
                 }
-                if (col == 0) {
+                if (primal && col == 0) {
                     // the hardware's logarithm comes out low by up to half an ulp of its base-2 value: one Newton step
                     const float sum = l_row * expf(m_all + MAX_SLACK - top), y = logf(sum), y_rest = fmaf(sum, expf(-y), -1.f);
                     const float z = top + y, z_rest = fabsf(top) > fabsf(y) ? y - (z - top) : top - (z - y);
@@ -650,16 +687,18 @@ __global__ __launch_bounds__((Cfg<TIn, D, TAN, KW>::NTHREADS), (Cfg<TIn, D, TAN,
                 }
             }
         }
-        return bad;
+        return odd;
     };
 
     reset();
     sweep();
-    const bool bad = finish();
-    if (__builtin_expect(__syncthreads_or(bad), 0)) {
+    redo |= finish(true);
+    if (__builtin_expect(__syncthreads_or(redo), 0)) {
+        __syncthreads();                             // everyone has the answer before the next question
+        const bool primal = __syncthreads_or(redo & REDO_O);
         reset();
         sweep_f32();
-        finish();
+        finish(primal);
     }
 }
 
