@@ -67,7 +67,10 @@ constexpr float MAX_SLACK = 4.f;
 // to 3e-3 -> 7e-7.
 constexpr float SMALL = 0x1p-80f, LARGE = 0x1p22f;
 // What of a tile is redone: o and lse apart from to, so that they have the same bits with and without tangents, whatever those are.
-constexpr int REDO_O = 1, REDO_TO = 2;
+constexpr int REDO_O = 1, REDO_TO = 2, O_NOT_FINITE = 4, TO_NOT_FINITE = 8;
+// The factor on V, tV where a result is not finite, so that the sums over up to 2^24 keys of values up to the end of the range stay
+// in it: the weights are at most 1 each, not in all.  (What of that tile is below 2^-102 loses bits to the factor.)
+constexpr float DOWN = 0x1p-24f;
 
 #define FENCE() __builtin_amdgcn_sched_barrier(0)      // no instruction is scheduled across this point
 
@@ -553,7 +556,7 @@ __global__ __launch_bounds__((Cfg<TIn, D, TAN, KW>::NTHREADS), (Cfg<TIn, D, TAN,
         }
     };
     // ---- ... and on fp32 products, for tiles with infinities or NaN: nothing fetched ahead ----
-    auto sweep_f32 = [&]() __attribute__((always_inline)) {
+    auto sweep_f32 = [&](float factor) __attribute__((always_inline)) {
         const int row = q0 + BR * group + c < Lq ? q0 + BR * group + c : Lq - 1;
         const long qat = q_base + (long)row * row_elems + 8 * kg;
         for (int blk = kw; blk < n_blocks; blk += KW) {
@@ -589,17 +592,17 @@ __global__ __launch_bounds__((Cfg<TIn, D, TAN, KW>::NTHREADS), (Cfg<TIn, D, TAN,
                 for (int e = 0; e < VW; ++e)
 #pragma unroll
                     for (int i = 0; i < 8; ++i) {
-                        const float v = I::template col<VW>(vr[slot][i], e);
+                        const float v = I::template col<VW>(vr[slot][i], e) * factor;
                         acc_o[VW * cq + e] = mfma_f32(v, p[i], acc_o[VW * cq + e]);
                         if constexpr (TANGENT) acc_t[VW * cq + e] = mfma_f32(v, h[i], acc_t[VW * cq + e]);
-                        if constexpr (KV_TANGENT) acc_t[VW * cq + e] = mfma_f32(I::template col<VW>(tvr[slot][i], e), p[i], acc_t[VW * cq + e]);
+                        if constexpr (KV_TANGENT) acc_t[VW * cq + e] = mfma_f32(I::template col<VW>(tvr[slot][i], e) * factor, p[i], acc_t[VW * cq + e]);
                     }
             });
         }
     };
 
-    // ---- the waves' partial states meet in LDS; returns what is not finite or small.  primal: o and lse are stored too ----
-    auto finish = [&](bool primal) __attribute__((always_inline)) -> int {
+    // ---- the waves' partial states meet in LDS; returns what is not finite or small ----
+    auto finish = [&](bool primal, float up) __attribute__((always_inline)) -> int {
         l = row_sum(l);
         r_sum = row_sum(r_sum);
         __syncthreads();                             // everyone is done with Q, tQ (or with the previous states)
@@ -648,13 +651,14 @@ __global__ __launch_bounds__((Cfg<TIn, D, TAN, KW>::NTHREADS), (Cfg<TIn, D, TAN,
             // epilogue (Alg. 2, last lines)
             const float inv_l = 1.f / l_row;
             const float mu = r_row * inv_l;          // rowsum(P o tS)
+            const float scaled = inv_l * up;
             float probe = 0.f, probe_t = 0.f;        // NaN once anything is inf or NaN
             Smallest small, small_t;
             if constexpr (TANGENT) small_t.see(mu);
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                if constexpr (TANGENT) t[e] = fmaf(-mu, o[e], t[e]) * inv_l;
-                o[e] *= inv_l;
+                if constexpr (TANGENT) t[e] = fmaf(-mu, o[e], t[e]) * scaled;
+                o[e] *= scaled;
                 probe = fmaf(o[e], 0.f, probe);
                 if constexpr (TANGENT) probe_t = fmaf(t[e], 0.f, probe_t);
                 if constexpr (TERMS == 3) {
@@ -662,8 +666,10 @@ __global__ __launch_bounds__((Cfg<TIn, D, TAN, KW>::NTHREADS), (Cfg<TIn, D, TAN,
                     if constexpr (TANGENT) small_t.see(t[e]);
                 }
             }
-            if (probe != probe || small.below(SMALL)) odd |= REDO_O | REDO_TO;
-            if (probe_t != probe_t || small_t.below(SMALL)) odd |= REDO_TO;
+            if (probe != probe) odd |= O_NOT_FINITE;
+            if (probe_t != probe_t) odd |= TO_NOT_FINITE;
+            if (small.below(SMALL)) odd |= REDO_O | REDO_TO;
+            if (small_t.below(SMALL)) odd |= REDO_TO;
             if (q0 + row < Lq) {
                 const long at = q_base + (long)(q0 + row) * row_elems + col;
                 if (out_bf16) {                      // (uniform)
@@ -692,13 +698,22 @@ __global__ __launch_bounds__((Cfg<TIn, D, TAN, KW>::NTHREADS), (Cfg<TIn, D, TAN,
 
     reset();
     sweep();
-    redo |= finish(true);
+    redo |= finish(true, 1.f);
     if (__builtin_expect(__syncthreads_or(redo), 0)) {
-        __syncthreads();                             // everyone has the answer before the next question
-        const bool primal = __syncthreads_or(redo & REDO_O);
-        reset();
-        sweep_f32();
-        finish(primal);
+        auto any = [&](int what) __attribute__((always_inline)) -> bool {
+            __syncthreads();                         // everyone has the answer before the next question
+            return __syncthreads_or(redo & what);
+        };
+        const bool o_down = any(O_NOT_FINITE), to_down = any(O_NOT_FINITE | TO_NOT_FINITE), o_again = any(REDO_O | O_NOT_FINITE);
+        const bool to_again = TANGENT && !(o_again && o_down == to_down);      // (if nothing of o is flagged, something of to is)
+#pragma unroll 1
+        for (int pass = 0; pass < 2; ++pass) {       // o, lse and to; to alone
+            if (!(pass == 0 ? o_again : to_again)) continue;
+            const bool down = pass == 0 ? o_down : to_down;
+            reset();
+            sweep_f32(down ? DOWN : 1.f);
+            finish(pass == 0, down ? 1.f / DOWN : 1.f);
+        }
     }
 }
 

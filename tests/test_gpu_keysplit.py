@@ -125,3 +125,25 @@ def test_static_scratch_and_graph_with_more_rows_than_this_kernel_takes():
         graph.replay()
         torch.cuda.synchronize()
         assert all(torch.equal(a, b) for a, b in zip(out, eager)), rep
+
+
+@DTYPES
+@DIMS
+def test_sums_of_large_values_stay_finite(d, dtype):
+    """Equal weights on values up to 3e38: o is their mean, however many there are; the same for tV, whose overflow alone must not move o."""
+    kw = {} if d == 96 and dtype == torch.bfloat16 else {"workspace": None}      # (which needs one to be taken at all)
+    for Lkv in (100, 300, 1000) if kw else (100, 300):
+        t = inputs(8, 1, 1, 20, Lkv, d, dtype)
+        t[0].zero_()
+        t[3].mul_(2.0 ** -10)
+        for which in ((2, 5), (5,)):
+            u = list(t)
+            for i in which:
+                u[i] = ((t[i].float().abs().clamp(max=3.0) + 0.1) * 2.0 ** 126).to(dtype)      # 8.5e37 * (0.1 .. 3.1)
+            got = run(u, 0.1, **kw)
+            ref = attn_jvp_ref(*u, 0.1)
+            for x, r, name in zip(got[:2], ref, ("o", "to")):
+                x = x.cpu().double().numpy()
+                assert np.isfinite(x).all() and np.abs(x - r).max() <= 2e-5 * np.sqrt((r ** 2).mean()), f"{name} {which} Lkv={Lkv}"
+            plain = run(u[:3] + [None] * 3, 0.1, **kw)
+            assert torch.equal(plain[0], got[0]) and torch.equal(plain[2], got[2])
