@@ -689,7 +689,7 @@ __global__ __launch_bounds__((Cfg<TIn, D, TAN, KW>::NTHREADS), (Cfg<TIn, D, TAN,
                     // the hardware's logarithm comes out low by up to half an ulp of its base-2 value: one Newton step
                     const float sum = l_row * expf(m_all + MAX_SLACK - top), y = logf(sum), y_rest = fmaf(sum, expf(-y), -1.f);
                     const float z = top + y, z_rest = fabsf(top) > fabsf(y) ? y - (z - top) : top - (z - y);
-                    LSE[bh * Lq + q0 + row] = z + (z_rest + y_rest);
+                    LSE[bh * Lq + q0 + row] = l_row == 0.f ? -INFINITY : z + (z_rest + y_rest);      // (0: every score is -inf)
                 }
             }
         }

@@ -147,3 +147,18 @@ def test_sums_of_large_values_stay_finite(d, dtype):
                 assert np.isfinite(x).all() and np.abs(x - r).max() <= 2e-5 * np.sqrt((r ** 2).mean()), f"{name} {which} Lkv={Lkv}"
             plain = run(u[:3] + [None] * 3, 0.1, **kw)
             assert torch.equal(plain[0], got[0]) and torch.equal(plain[2], got[2])
+
+
+@DTYPES
+@DIMS
+def test_rows_without_a_finite_score(d, dtype):
+    """lse is the logarithm of an empty sum, whichever kernel has the call; o has no value."""
+    own = {} if d == 96 and dtype == torch.bfloat16 else {"workspace": None}      # (which needs one to be taken at all)
+    for Lkv in (1, 100, 1500):
+        t = [x.to(dtype) for x in (torch.ones(1, 1, 20, d), torch.randn(1, 1, Lkv, d), torch.randn(1, 1, Lkv, d))] + [None] * 3
+        t[1][..., 0] = float("-inf")
+        for kw in ({}, own) + (({"flags": binding.FLAG_NO_F16},) if d in (64, 128) else ()):
+            o, _, lse = run(t, 0.1, **kw)
+            assert torch.isnan(o).all() and (lse == float("-inf")).all(), (Lkv, kw)
+        t[1][0, 0, Lkv - 1] = float("nan")
+        assert torch.isnan(run(t, 0.1, **own)[2]).all()
