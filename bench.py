@@ -286,21 +286,18 @@ def main():
 
     peak = (PEAK_F32_SPLIT_TFLOPS if d in (32, 64, 96, 128) else PEAK_FP32_TFLOPS) if f32 else PEAK_BF16_TFLOPS
     # what the path computes in (inputs; matrix products; accumulation), by the route the library takes for this call
-    groups = B * H * ((Lq + 15) // 16)          # the library's rule for the key-split kernel (a call without flags), in 16-row groups per unit
-    per_cu = (3 if f32 else 4) if d == 32 else (2 if d == 64 else 1) if f32 else (1 if d == 128 and not args.null_kv_tangents else 2)
-    keysplit = not (d in (32, 64, 96, 128) and (f32 or cfg.scale > 0)) or (args.variant == "default" and groups <= per_cu * 256)
-    if keysplit:
-        arithmetic = ("f32 (six bf16 MFMA products per fp32 product, fp32 accumulate)" if f32 else
-                      "bf16 in, bf16 MFMA (weights as three bf16 terms in the value products), f32 accumulate")
-    elif f32:
-        arithmetic = "f32 (three fp16 MFMA products per fp32 product, fp32 accumulate)"
-    elif args.variant == "fast":
-        arithmetic = "bf16 in, bf16 MFMA (single bf16 weights), f32 accumulate"
-    elif args.variant == "bf16-pairs" or not (Lkv >= 2048 or (Lkv >= 256 and B * H * ((Lq + 127) // 128) >= 4 * 256)):   # the library's rule
-        arithmetic = "bf16 in, bf16 MFMA (weights as hi+lo bf16 pairs in the value products), f32 accumulate"
-    else:
-        arithmetic = "bf16 in, bf16 score MFMA + fp16 value MFMA (fp16 weights, V and tV as scaled fp16 copies), f32 accumulate"
-    kernel_name = "attn_jvp_keysplit_kernel" if keysplit else "attn_jvp_mfma_f32_kernel" if f32 else "attn_jvp_mfma_kernel"
+    route, parts = binding.attn_jvp_route(B, H, Lq, Lkv, d, cfg.scale, torch.float32 if f32 else torch.bfloat16,
+                                          tangents=1 if args.null_kv_tangents else 2, flags=flags)
+    arithmetic = {
+        "keysplit": ("f32 (six bf16 MFMA products per fp32 product, fp32 accumulate)" if f32 else
+                     "bf16 in, bf16 MFMA (weights as three bf16 terms in the value products), f32 accumulate"),
+        "f32-tiles": "f32 (three fp16 MFMA products per fp32 product, fp32 accumulate)",
+        "bf16-single": "bf16 in, bf16 MFMA (single bf16 weights), f32 accumulate",
+        "bf16-pairs": "bf16 in, bf16 MFMA (weights as hi+lo bf16 pairs in the value products), f32 accumulate",
+        "f16-values": "bf16 in, bf16 score MFMA + fp16 value MFMA (fp16 weights, V and tV as scaled fp16 copies), f32 accumulate"}[route]
+    if parts > 1:
+        arithmetic += f", keys in {parts} parts"
+    kernel_name = {"keysplit": "attn_jvp_keysplit_kernel", "f32-tiles": "attn_jvp_mfma_f32_kernel"}.get(route, "attn_jvp_mfma_kernel")
     out = {
         "metric": f"attention+JVP TFLOP/s ({'fp32' if f32 else 'bf16'}, 12*Lq*Lkv*d/head)", "value": round(tflops, 2),
         "unit": "TFLOP/s",

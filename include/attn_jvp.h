@@ -29,10 +29,11 @@
  * tk and tv may BOTH be NULL: zero key/value tangents.  The paper's kernel serves self- and cross-attention (Sec. 3.2,
  * Flash Attention paragraph); in cross-attention onto a context that does not depend on the differentiated variable
  * the keys and values carry no tangent, which is App. C.1's equations with tK = tV = 0.
- * The result is bit-identical to passing zero tensors; the MFMA kernel then streams only K and V and runs 4 of the
- * 6 matrix products (tS = s tQ K^T, tO = tP V).
+ * The result is bit-identical to passing zero tensors where both calls run as the same kernel (attn_jvp_route; calls with
+ * few query rows or tiles may not: AUTO chooses by the products there are to do); the MFMA kernel then streams only K and V
+ * and runs 4 of the 6 matrix products (tS = s tQ K^T, tO = tP V).
  * tq, tk and tv may ALL be NULL: no tangents, the plain attention forward that Alg. 2 extends (2 of the 6 products).
- * o and lse are the same bits as with tangents; `to` is not written and may be NULL.
+ * o and lse are the same bits as with tangents, with the same proviso; `to` is not written and may be NULL.
  *
  * Execution: a call validates its arguments on the host, enqueues its kernels on the given
  * HIP stream and returns without synchronising.  A return value of 0 means "enqueued".
@@ -172,7 +173,8 @@ typedef struct attn_jvp_opts {
     void*  timing_events[2]; /* optional hipEvent_t pair (created by the caller, with timing enabled), or NULL:
                                [0] is recorded on `stream` immediately before the main attention kernel and [1]
                                immediately after it, so a profiler can time that kernel apart from the fp16
-                               path's pre-pass kernels, which are enqueued before [0] */
+                               path's pre-pass kernels, which are enqueued before [0].  Where several launches share the
+                               work (the fp16 path's hand-overs, keys in parts and their merge), [1] follows the last */
     int    layout;          /* ATTN_JVP_LAYOUT_*: memory layout of q, k, v, tq, tk, tv, o, to */
     int    reserved;        /* must be zero */
 } attn_jvp_opts;
@@ -238,6 +240,19 @@ size_t attn_jvp_workspace_bytes(int B, int H, int Lq, int Lkv, int d);
 
 /* The same for fp32 inputs, whose kernels use scratch only for the states of keys in parts (0: no use for any). */
 size_t attn_jvp_workspace_bytes_fp32(int B, int H, int Lq, int Lkv, int d);
+
+/*
+ * What a call runs as, for reports and tests: one of ATTN_JVP_ROUTE_* for attn_jvp_fwd_ex with these arguments (tangents: 0 none, 1 the
+ * query's, 2 all; opts may be NULL; opts->workspace counts as lent and is not touched), or minus the error code that the call
+ * would return.  *parts (may be NULL): in how many parts the tile kernel takes the keys.  Nothing is launched.
+ */
+#define ATTN_JVP_ROUTE_VECTOR      0  /* fp32 products on the vector ALU */
+#define ATTN_JVP_ROUTE_KEYSPLIT    1  /* key-split kernel: operands as exact sums of bf16 terms */
+#define ATTN_JVP_ROUTE_F32_TILES   2  /* fp32 inputs, 128-row tiles, operands as two fp16 terms */
+#define ATTN_JVP_ROUTE_BF16_PAIRS  3  /* bf16 inputs, 128-row tiles, weights as hi + lo bf16 pairs */
+#define ATTN_JVP_ROUTE_F16_VALUES  4  /* bf16 inputs, 128-row tiles, fp16 weights and values */
+#define ATTN_JVP_ROUTE_BF16_SINGLE 5  /* bf16 inputs, 128-row tiles, single bf16 weights (FAST) */
+int attn_jvp_route(int B, int H, int Lq, int Lkv, int d, float scale, int tangents, const attn_jvp_opts* opts, int* parts);
 
 /*
  * RMS normalisation with gain and its JVP, the QK-normalisation in front of the attention (paper App. C.2, the

@@ -83,6 +83,8 @@ def load_library():
     lib.attn_jvp_workspace_bytes.restype = ctypes.c_size_t
     lib.attn_jvp_workspace_bytes_fp32.argtypes = [ci] * 5
     lib.attn_jvp_workspace_bytes_fp32.restype = ctypes.c_size_t
+    lib.attn_jvp_route.argtypes = [ci] * 5 + [cf, ci, ctypes.POINTER(AttnJvpOpts), ctypes.POINTER(ci)]
+    lib.attn_jvp_route.restype = ci
     _fast = _load_fast_call()
     if _fast is not _NoFastCall:
         _hand_over(_fast, lib, lib.attn_jvp_fwd_ex)
@@ -120,6 +122,23 @@ def attn_jvp_version():
 
 def attn_jvp_workspace_bytes(B, H, Lq, Lkv, d):
     return int(load_library().attn_jvp_workspace_bytes(B, H, Lq, Lkv, d))
+
+
+ROUTES = ("vector", "keysplit", "f32-tiles", "bf16-pairs", "f16-values", "bf16-single")      # ATTN_JVP_ROUTE_*
+
+
+def attn_jvp_route(B, H, Lq, Lkv, d, scale, dtype=torch.bfloat16, tangents=2, kernel=KERNEL_AUTO, flags=0, workspace="auto"):
+    """What attn_jvp_fwd_ex runs for such a call: (one of ROUTES, the parts its keys go in).  tangents: 0 none, 1 the query's,
+    2 all; workspace: "auto" or None."""
+    opts = AttnJvpOpts(_DTYPE_CODE[dtype], 0, None, int(kernel), int(flags))
+    if workspace == "auto":
+        opts.workspace_bytes = _workspace_bytes(B, H, Lq, Lkv, d, dtype == torch.float32)
+        opts.workspace = 256 if opts.workspace_bytes else None      # (an aligned address; nobody looks there)
+    parts = ctypes.c_int(1)
+    route = load_library().attn_jvp_route(B, H, Lq, Lkv, d, float(scale), int(tangents), ctypes.byref(opts), ctypes.byref(parts))
+    if route < 0:
+        raise AttnJvpError(-route, attn_jvp_strerror(-route))
+    return ROUTES[route], parts.value
 
 
 _workspaces = {}

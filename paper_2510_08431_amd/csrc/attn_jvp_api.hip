@@ -79,9 +79,18 @@ size_t value_path_bytes(int B, int H, int Lq, int Lkv, int d) {
     return pad_bytes(B, H, Lq, Lkv, d) + attn_jvp::f16_workspace_bytes(B, H, Lq, Lkv, kernel_dim(d));
 }
 
+struct Route {
+    int kernel = -1, parts = 1;      // ATTN_JVP_ROUTE_*
+};
+
+// With `asked` the call goes up to where the first kernel would be enqueued, and says there which one that is.
 int run(const void* q, const void* k, const void* v, const void* tq, const void* tk, const void* tv,
         void* o, void* to, float* lse, int B, int H, int Lq, int Lkv, int d, float scale,
-        const attn_jvp_opts* opts, bool use_static_scratch = false) {
+        const attn_jvp_opts* opts, bool use_static_scratch = false, Route* asked = nullptr) {
+    auto answer = [&](int kernel, int parts) {
+        *asked = Route{kernel, parts};
+        return ATTN_JVP_OK;
+    };
     attn_jvp_opts def = {};
     def.in_dtype = ATTN_JVP_BF16;
     def.out_dtype = ATTN_JVP_OUT_FP32;
@@ -151,15 +160,23 @@ int run(const void* q, const void* k, const void* v, const void* tq, const void*
     if (few_rows || no_tiles) {
         bool take = no_tiles;
         e = take ? hipSuccess : attn_jvp::keysplit_preferred(p, &take);
+        if (e == hipSuccess && take && asked) return answer(ATTN_JVP_ROUTE_KEYSPLIT, 1);
         if (e == hipSuccess && take) e = attn_jvp::launch_keysplit(p);
         if (e != hipSuccess) return ATTN_JVP_LAUNCH_FAILED;
         if (take) return ATTN_JVP_OK;
     }
     if (kernel == ATTN_JVP_KERNEL_MFMA) {
         if (!mfma_ok) return ATTN_JVP_UNSUPPORTED;
+        if (asked) {
+            bool f16 = false;
+            if (!f32 && p.split.parts == 1 && attn_jvp::mfma_bf16_takes_f16(p, &f16) != hipSuccess) return ATTN_JVP_LAUNCH_FAILED;
+            return answer(f32 ? ATTN_JVP_ROUTE_F32_TILES : f16 ? ATTN_JVP_ROUTE_F16_VALUES :
+                          (p.flags & ATTN_JVP_FLAG_FAST) && tk ? ATTN_JVP_ROUTE_BF16_SINGLE : ATTN_JVP_ROUTE_BF16_PAIRS, p.split.parts);
+        }
         e = f32 ? attn_jvp::launch_mfma_f32(p) : attn_jvp::launch_mfma_bf16(p);
     } else if (kernel == ATTN_JVP_KERNEL_FP32) {
         if (!attn_jvp::fp32_vector_supports(p)) return ATTN_JVP_UNSUPPORTED;
+        if (asked) return answer(d == 256 ? ATTN_JVP_ROUTE_KEYSPLIT : ATTN_JVP_ROUTE_VECTOR, 1);
         e = attn_jvp::launch_fp32_vector(p);
     } else {
         return ATTN_JVP_UNSUPPORTED;
@@ -186,6 +203,18 @@ int attn_jvp_fwd_static(const void* q, const void* k, const void* v, const void*
                         void* o, void* to, float* lse, int B, int H, int Lq, int Lkv, int d, float scale,
                         const attn_jvp_opts* opts) {
     return run(q, k, v, tq, tk, tv, o, to, lse, B, H, Lq, Lkv, d, scale, opts, true);
+}
+
+int attn_jvp_route(int B, int H, int Lq, int Lkv, int d, float scale, int tangents, const attn_jvp_opts* opts, int* parts) {
+    alignas(16) static char somewhere[16];      // (addresses that pass the checks and are never followed)
+    void* at = somewhere;
+    if (tangents < 0 || tangents > 2) return -ATTN_JVP_UNSUPPORTED;
+    Route route;
+    const int rc = run(at, at, at, tangents > 0 ? at : nullptr, tangents > 1 ? at : nullptr, tangents > 1 ? at : nullptr, at, at, (float*)at,
+                       B, H, Lq, Lkv, d, scale, opts, false, &route);
+    if (rc != ATTN_JVP_OK) return -rc;
+    if (parts) *parts = route.parts;
+    return route.kernel;
 }
 
 size_t attn_jvp_static_scratch_bytes(void) { return ATTN_JVP_STATIC_SCRATCH_BYTES; }

@@ -1462,6 +1462,32 @@ static hipError_t prepare_kernels(int dev) {
     return e;
 }
 
+// fp16 value path when the caller lent enough scratch (and did not ask for another variant) and the call is
+// large enough to amortise its per-call pre-pass (see F16_MIN_KEYS)
+static bool takes_f16(const Problem& p, int cus) {
+    const long long tiles = (long long)((p.Lq + BR - 1) / BR) * p.B * p.H;
+    return !(p.flags & 3) && p.split.parts == 1 && p.workspace != nullptr && (long long)p.B * p.H <= 65535 &&   // pre-pass grid.y
+           (p.Lkv >= F16_MIN_KEYS || (p.flags & 4) ||
+            (p.Lkv >= F16_MIN_KEYS_MANY_TILES && tiles >= (long long)F16_MANY_TILES_PER_CU * cus)) &&
+           p.workspace_bytes >= f16_workspace_bytes(p.B, p.H, p.Lq, p.Lkv, p.d) &&
+           (reinterpret_cast<uintptr_t>(p.workspace) & 255u) == 0;
+}
+
+hipError_t mfma_bf16_takes_f16(const Problem& p, bool* yes) {
+    int dev = 0, cus = 0;
+    const hipError_t e = device_cus(&dev, &cus);
+    if (e != hipSuccess) return e;
+    Problem padded = p;
+    if (p.d == 32) {      // (what launch_pad_inputs leaves; supported only with room for the copies)
+        padded.d = padded_head_dim_of(p.d);
+        const size_t copies = pad_workspace_bytes(p.B, p.H, p.Lq, p.Lkv, p.d);
+        padded.workspace = static_cast<char*>(p.workspace) + copies;
+        padded.workspace_bytes = p.workspace_bytes - copies;
+    }
+    *yes = takes_f16(padded, cus);
+    return hipSuccess;
+}
+
 template <int DH>
 static hipError_t launch_dh(const Problem& p_in) {
     int dev = 0, cus = 0;
@@ -1507,13 +1533,7 @@ static hipError_t launch_dh(const Problem& p_in) {
                            lockstep, p.split.parts, p.split.blocks, (f32x4*)ps.state, (int)blocks, stagger);
         return hipGetLastError();
     };
-    // fp16 value path when the caller lent enough scratch (and did not ask for another variant) and the call is
-    // large enough to amortise its per-call pre-pass (see F16_MIN_KEYS)
-    const bool f16 = !(p.flags & 3) && p.split.parts == 1 && p.workspace != nullptr && (long long)p.B * p.H <= 65535 &&   // pre-pass grid.y
-                     (p.Lkv >= F16_MIN_KEYS || (p.flags & 4) ||
-                      (p.Lkv >= F16_MIN_KEYS_MANY_TILES && blocks >= (long long)F16_MANY_TILES_PER_CU * cus)) &&
-                     p.workspace_bytes >= f16_workspace_bytes(p.B, p.H, p.Lq, p.Lkv, p.d) &&
-                     (reinterpret_cast<uintptr_t>(p.workspace) & 255u) == 0;
+    const bool f16 = takes_f16(p, cus);
     F16Workspace ws{};
     if (f16) {
         hipError_t e = launch_f16_prepass(p, cus, &ws);

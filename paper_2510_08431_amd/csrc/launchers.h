@@ -60,6 +60,7 @@ int keysplit_groups_per_unit(int d, bool f32, bool tangents, bool key_tangents);
 hipError_t launch_mfma_bf16(const Problem& p);
 hipError_t launch_mfma_f32(const Problem& p);
 bool mfma_bf16_supports(const Problem& p);
+hipError_t mfma_bf16_takes_f16(const Problem& p, bool* yes);      // the fp16 value path, not bf16 pairs (asks for the device's size)
 bool mfma_f32_supports(const Problem& p);
 bool fp32_vector_supports(const Problem& p);
 

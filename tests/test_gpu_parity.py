@@ -158,11 +158,14 @@ def test_mfma_default_entry_point_and_preallocated_outputs():
 
 
 @pytest.mark.parametrize("scale", [0.0, -0.11])
-def test_non_positive_scale_takes_the_vector_kernel(scale):
+def test_non_positive_scale(scale):
     """The MFMA kernel is written for scale > 0; AUTO must route scale <= 0 (uniform or inverted attention, ragged
-    key tail included) to the fp32 vector kernel, and the result must still match the definition."""
+    key tail included) to the key-split kernel, the vector kernel takes it too, and the results must still match the definition."""
     t = random_inputs(61, 1, 2, 150, 77, 128, torch.bfloat16)
+    assert binding.attn_jvp_route(1, 2, 150, 77, 128, scale) == ("keysplit", 1)
+    assert binding.attn_jvp_route(1, 2, 150, 77, 128, scale, kernel=binding.KERNEL_FP32) == ("vector", 1)
     check_full(t, scale, binding.KERNEL_AUTO, f"auto kernel, scale={scale}")
+    check_full(t, scale, binding.KERNEL_FP32, f"vector kernel, scale={scale}")
     dev = {n: x.to(DEV) for n, x in t.items()}
     with pytest.raises(binding.AttnJvpError):
         binding.attn_jvp_fwd_ex(dev["q"], dev["k"], dev["v"], dev["tq"], dev["tk"], dev["tv"], scale,

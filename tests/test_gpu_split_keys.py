@@ -73,7 +73,7 @@ def test_parts_against_the_oracle(case, names):
     t = inputs(Lkv + names, 1, H, Lq, Lkv, d, dtype, names)
     got, whole = run(t, scale), run(t, scale, flags=binding.FLAG_NO_F16)
     check(got, t, scale, dtype)
-    assert not torch.equal(got[0], whole[0])                  # (the call went in parts)
+    assert not torch.equal(got[0], whole[0])                  # (not on whole keys; in how many parts: test_numbers_of_parts)
 
 
 @pytest.mark.gpu
@@ -137,3 +137,59 @@ def test_a_part_without_weight(dtype, d):
     check(got, rest, 0.1, dtype)
     t[1][:, :, 2900, 5] = float("nan")
     assert all(torch.isnan(x).all() for x in run(t, 0.1) if x is not None)
+
+
+# the fewest rows and keys that go in each number of parts: (dtype, d, H, Lq, Lkv, tangents, parts)
+COUNTS = [(BF16, 128, 8, 1300, 1033, 2, 2), (BF16, 128, 2, 3300, 1033, 2, 3), (BF16, 128, 2, 2100, 700, 2, 4), (BF16, 128, 2, 2100, 1033, 2, 5),
+          (BF16, 128, 1, 300, 700, 2, 6), (BF16, 128, 1, 300, 1033, 2, 7), (BF16, 128, 1, 300, 1500, 2, 8), (BF16, 128, 8, 1300, 2077, 0, 2),
+          (BF16, 64, 3, 2600, 1500, 0, 3), (BF16, 64, 2, 3300, 2077, 0, 4), (BF16, 64, 4, 1300, 2077, 2, 5), (BF16, 96, 8, 400, 2077, 2, 6),
+          (BF16, 32, 8, 1100, 1500, 2, 3), (F32, 128, 6, 1300, 290, 2, 2), (F32, 128, 2, 2100, 290, 2, 3), (F32, 128, 2, 3300, 520, 2, 4),
+          (F32, 128, 1, 300, 520, 2, 5), (F32, 64, 1, 300, 700, 2, 6), (F32, 96, 6, 1300, 700, 0, 3), (F32, 64, 2, 3300, 1033, 0, 4),
+          (F32, 32, 3, 2100, 1500, 2, 5)]
+COUNT_IDS = ["%s-d%d-%dx%dx%d-%d-%dparts" % (("fp32" if c[0] == F32 else "bf16",) + c[1:]) for c in COUNTS]
+
+
+def route_of(case, tangents):
+    dtype, d, H, Lq, Lkv = case[:5]
+    return binding.attn_jvp_route(1, H, Lq, Lkv, d, 0.1, dtype, tangents=tangents)
+
+
+def test_numbers_of_parts():
+    """What the tests of this file run as (a call in parts is known without a GPU)."""
+    assert {c[-1] for c in COUNTS if c[0] == BF16} == {2, 3, 4, 5, 6, 7, 8} and {c[-1] for c in COUNTS if c[0] == F32} >= {2, 3, 4, 5, 6}
+    for case in COUNTS:
+        assert route_of(case, case[5]) == ("f32-tiles" if case[0] == F32 else "bf16-pairs", case[6]), case
+    for case in CASES:
+        for tangents in (0, 1, 2):
+            assert route_of(case, tangents)[1] >= 7, case
+
+
+def check_rows(t, got, scale, dtype):
+    """Every 29th row and the last one."""
+    Lq = t[0].shape[2]
+    rows = sorted(set(range(0, Lq, 29)) | {Lq - 1})
+    cut = [x if x is None or i in (1, 2, 4, 5) else x[:, :, rows] for i, x in enumerate(t)]
+    check([x if x is None else x[:, :, rows] for x in got], cut, scale, dtype)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("case", COUNTS, ids=COUNT_IDS)
+def test_each_number_of_parts_against_the_oracle(case):
+    dtype, d, H, Lq, Lkv, tangents, parts = case
+    assert route_of(case, tangents)[1] == parts
+    scale = float(np.float32(d ** -0.5))
+    t = inputs(Lkv + parts, 1, H, Lq, Lkv, d, dtype, (3, 4, 6)[tangents])
+    check_rows(t, run(t, scale), scale, dtype)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("d", [128, 96, 64])
+def test_workgroups_that_walk_through_tiles_of_several_parts(d):
+    """Two tiles per compute unit and more, so that a workgroup goes on to another tile, of another part."""
+    case = (BF16, d, 4, 3300, 20000)
+    assert route_of(case, 2) == ("bf16-pairs", 7)                  # 104 query tiles, 728 workgroups' worth
+    scale = float(np.float32(d ** -0.5))
+    t = inputs(d, 1, 4, 3300, 20000, d, BF16)
+    got = run(t, scale)
+    assert all(torch.equal(a, b) for a, b in zip(got, run(t, scale, flags=binding.FLAG_NO_RESIDENT)))
+    check_rows(t, got, scale, BF16)

@@ -166,6 +166,17 @@ def test_argument_validation_returns_codes_without_launching(lib):
         assert _call(lib, scale=bad_scale, opts=o) == 3
 
 
+def test_route_refuses_what_a_call_refuses(lib):
+    """attn_jvp_route: minus the error code of the call, on the host."""
+    from paper_2510_08431_amd import binding
+    ask = lambda d=128, L=8, scale=0.1, tangents=2, opts=None: lib.attn_jvp_route(1, 1, L, L, d, scale, tangents, opts, None)
+    assert ask(d=48) == -3 and ask(L=0) == -2 and ask(scale=float("nan")) == -2 and ask(tangents=3) == -3 and ask(tangents=-1) == -3
+    o = binding.AttnJvpOpts(); o.workspace = 0x10010; o.workspace_bytes = 1 << 20
+    assert ask(opts=ctypes.byref(o)) == -4
+    with pytest.raises(binding.AttnJvpError):
+        binding.attn_jvp_route(1, 1, 8, 8, 48, 0.1)
+
+
 def test_rmsnorm_argument_validation_returns_codes_without_launching(lib):
     """Fake (never dereferenced) addresses: every call here must be rejected on the host."""
     vp = ctypes.c_void_p
