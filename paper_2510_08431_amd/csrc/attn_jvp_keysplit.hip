@@ -742,8 +742,10 @@ hipError_t launch_one(const Problem& p) {
         // block where there are fewer than four, and fewer partial states meet.  Rounds of workgroups over the units times a round's
         // length in key blocks: a workgroup's fixed part is worth 1.2 blocks, 1.6 with two groups, 4 with four.  Measured, us, four
         // waves to 16 rows -> this: bf16, no key tangents, H16 Lq26057 Lkv25 1154 -> 719, H8 Lq4000 Lkv60 93 -> 55, Lq2000 Lkv300
-        // 81 -> 64; fp32 H24 Lq2632 Lkv47 234 -> 154, all tangents H24 L300 96 -> 80.  Against the rule: H4 Lq2000 Lkv120
-        // 27 -> 34, bf16 all tangents H8 L1000 101 -> 180.
+        // 81 -> 64; fp32 H24 Lq2632 Lkv47 234 -> 154, all tangents H24 L300 96 -> 80.  Where it stays with four, one would
+        // take H4 Lq2000 Lkv120 27 -> 34, bf16 all tangents H8 L1000 101 -> 180.  Not good enough for fp32 up to about 100 keys: the
+        // fp32-MFMA kernel with 64 rows to a workgroup that was here before took, without tangents, H16 Lq600 Lkv77 24.6 us against
+        // 32.3, all tangents H24 Lq4000 Lkv20 224 against 323 (but was half again as far from 64 bits).
         constexpr int KW = std::is_same<TIn, float>::value && TAN != TAN_NONE ? 2 : 1;
         int dev = 0, cus = 0;
         const hipError_t e = device_cus(&dev, &cus);
