@@ -85,7 +85,10 @@ extern "C" {
                                      fp32 and d in {32, 64, 96, 128} -> split-operand MFMA kernel; calls with few query rows
                                      (16-row groups up to one to four per compute unit, by dtype and d) and everything
                                      else (d = 256, scale <= 0, d = 32 without a workspace) -> key-split kernel: products of
-                                     operands split into bf16 terms that sum to them exactly, fp32 accuracy, no workspace */
+                                     operands split into bf16 terms that sum to them exactly, fp32 accuracy, no workspace.  Tiles
+                                     (16 query rows, up to 64 at d = 256) with infinities or NaN, with a rowsum(P o tS) below 2^-80
+                                     (zeros apart) or, fp32 inputs, an o, to or element of q or tq below that or an element of q
+                                     or tq above 2^22 are computed with fp32 products instead, in two to four times the time */
 #define ATTN_JVP_KERNEL_FP32 1    /* fp32 kernels, any dtype: d in {32, 64, 128} on the vector ALU (slow), d = 256 the key-split
                                      kernel */
 #define ATTN_JVP_KERNEL_MFMA 2    /* matrix-core kernels (without FAST, NO_F16 or F16_ALWAYS the key-split kernel for few query
