@@ -84,7 +84,8 @@ struct Geo {
     static constexpr int WG_PER_CU = DH == 64 || TAN == TAN_NONE ? 2 : 1;
     static constexpr int V_RING_BASE = NSTAGE * KV_STAGE_BYTES;    // K ring first, V ring behind it
     static constexpr int RING_BYTES = 2 * NSTAGE * KV_STAGE_BYTES;
-    static constexpr int LDS_BYTES = RING_BYTES + 1024;           // + a KiB where prefetches land that nobody reads
+    static constexpr int VOTE_BASE = RING_BYTES + 1024;           // behind a KiB where prefetches land that nobody reads: a word per wave
+    static constexpr int LDS_BYTES = VOTE_BASE + 64;
     static constexpr int CHUNKS_PER_ROW = ROW_BYTES / 16;          // 16-byte chunks of a row
     static constexpr int PIECES = TENSOR_BYTES / 1024;             // direct-to-LDS instructions (64 x 16 B) per tensor block: 8, 6 or 4
     // ... and how many a wave issues for a pair (X, tX), or for X alone (WITH_TANGENT false).  At DH = 96, X alone has 6
@@ -131,6 +132,8 @@ constexpr int PRESCAN_BLOCKS = NSTAGE;   // key blocks sampled for the fp16 path
 // (LDS reads, the wait for the copies, the barrier, the first value MFMA) before the first hand-over copy: the
 // build's check of the compiled assembly counts them, so a schedule that came out shorter would fail the build.
 #define SCORE_RESULTS_LAND() asm volatile("s_nop 4" ::: "memory")
+// The same in front of the statistics of the key sample, where nothing follows.
+#define SAMPLE_RESULTS_LAND() asm volatile("s_nop 7\n\ts_nop 3" ::: "memory")
 // value contractions: bf16 or fp16 operands (the fragments are carried as raw 128-bit registers)
 #define VMFMA(a, b, c)                                                                                          \
     (F16 ? __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c, 0, 0, 0) \
@@ -271,23 +274,24 @@ __device__ __forceinline__ void issue_pair_v16t(const char* Xh, const char* tXh,
     }
 }
 // Same copy for a block known to lie entirely inside the sequence: the per-lane byte offsets (row and swizzled
-// chunk) never change, so they are computed once and only the uniform block base advances.
+// chunk) never change, so they are computed once and only the uniform block base advances.  (last_row: the same for a ragged last
+// block, whose rows past it re-read it.)
 template <int DH, bool WITH_TANGENT>
 struct LaneOffsets {
     static constexpr int N = DH == 96 ? Geo<DH>::copies_per_wave(WITH_TANGENT) : Geo<DH>::PIECES / 4;   // different pieces of a wave
     uint32_t k[N], v[N];
 };
 template <int DH, bool WITH_TANGENT, bool V16T>
-__device__ __forceinline__ LaneOffsets<DH, WITH_TANGENT> make_lane_offsets(int wave, int lane, int k_stride, int v_stride) {
+__device__ __forceinline__ LaneOffsets<DH, WITH_TANGENT> make_lane_offsets(int wave, int lane, int k_stride, int v_stride, int last_row = BC - 1) {
     using G = Geo<DH>;
     using L = LaneOffsets<DH, WITH_TANGENT>;
     L o = {};
 #pragma unroll
     for (int i = 0; i < L::N; ++i) {
         const int piece = G::copy_piece(WITH_TANGENT, wave, DH != 96 && WITH_TANGENT ? 2 * i : i);
-        const int row = G::piece_row(piece, lane), pc = G::piece_chunk(piece, lane);
-        o.k[i] = row * k_stride + ((pc ^ G::k_swizzle(row)) << 4);
-        o.v[i] = V16T ? piece * 1024 + v16t_lane_offset(lane) : row * v_stride + ((pc ^ G::v_swizzle(row)) << 4);
+        const int row = G::piece_row(piece, lane), pc = G::piece_chunk(piece, lane), from = row < last_row ? row : last_row;
+        o.k[i] = from * k_stride + ((pc ^ G::k_swizzle(row)) << 4);
+        o.v[i] = V16T ? piece * 1024 + v16t_lane_offset(lane) : from * v_stride + ((pc ^ G::v_swizzle(row)) << 4);
     }
     return o;
 }
@@ -656,6 +660,17 @@ __device__ __forceinline__ void attn_jvp_tile(
         }
     };
 
+    // Does any wave's lane say yes?  One barrier: a wave's answer has a word of its own, which is written again after other barriers only.
+    auto workgroup_any = [&](bool yes) __attribute__((always_inline)) -> bool {
+        typedef __attribute__((address_space(3))) uint32_t lds_u32;
+        typedef __attribute__((address_space(3))) u32x4 lds_u32x4;
+        const uint32_t at = lds0 + G::VOTE_BASE;
+        const uint64_t lanes = __builtin_amdgcn_ballot_w64(yes);
+        if (lane == 0) *reinterpret_cast<lds_u32*>((uintptr_t)(at + 4 * wave)) = lanes != 0;
+        __syncthreads();
+        const u32x4 all = *reinterpret_cast<const lds_u32x4*>((uintptr_t)at);
+        return __builtin_amdgcn_readfirstlane(all[0] | all[1] | all[2] | all[3]) != 0;
+    };
     auto mask_scores = [&](int blk, auto Bc) __attribute__((always_inline)) {   // keys past Lkv: P~ = 0, tangent score 0
         f32x16& sv = SV(Bc);
         f32x16& tsv = TSV(Bc);
@@ -753,54 +768,88 @@ __device__ __forceinline__ void attn_jvp_tile(
     if constexpr (PRESCAN) {
         float sum1 = 0.f, sum2 = 0.f;   // first and second moment of the sampled raw scores (full blocks only)
         int n_stat = 0;
-        // the sample: K(0..3), which sit in the four stages of the K ring
+        // The sample: K(0..3), which sit in the four stages of the K ring.  The scores of blocks 0 and 1, then those of 2 and 3 over
+        // the statistics of the first two, then block 0's tangent scores, which the sweep starts from as from its scores, over
+        // the statistics of the others; a fragment's registers take the next pair's once its product has been issued.  Results in arithmetic registers
+        // as in the sweep.  (Sequences of fewer blocks sample the last one again, which counts once.  Pair by
+        // pair through accumulation registers, and block 0 again for the sweep: 3790 + 2270 cycles from the Q fragments to the
+        // first weights, now 3130 + 1390; cross-attention workload, 12 heads x 32760 queries x 512 keys.)
         const int ns = n_blocks < PRESCAN_BLOCKS ? n_blocks : PRESCAN_BLOCKS;
-        // Two samples per step, software-pipelined: the sixteen fragment reads of a pair go out together, and the
-        // MFMAs of pair p+1 run while the vector unit works through the statistics of pair p.
-        auto scan_one = [&](const float (&x)[16], int blk) __attribute__((always_inline)) {
-            f32x16& sv = SV(B1{});      // (as scratch: the sweep has not started)
-            f32x16& tsv = TSV(B1{});
-#pragma unroll
-            for (int e = 0; e < 16; ++e) { sv[e] = x[e]; tsv[e] = 0.f; }
-            if ((blk + 1) * BC > Lkv) {
-                mask_scores(blk, B1{});
-            } else {
-                float a1 = 0.f, a2 = 0.f;
-#pragma unroll
-                for (int e = 0; e < 16; ++e) { a1 += sv[e]; a2 = fmaf(sv[e], sv[e], a2); }
-                sum1 += a1; sum2 += a2; n_stat += BC;
-            }
-            float t0 = fmaxf(fmaxf(sv[0], sv[1]), fmaxf(sv[2], sv[3]));
-            float t1 = fmaxf(fmaxf(sv[4], sv[5]), fmaxf(sv[6], sv[7]));
-            float t2_ = fmaxf(fmaxf(sv[8], sv[9]), fmaxf(sv[10], sv[11]));
-            float t3 = fmaxf(fmaxf(sv[12], sv[13]), fmaxf(sv[14], sv[15]));
-            m_scan = fmaxf(m_scan, fmaxf(fmaxf(t0, t1), fmaxf(t2_, t3)));   // this lane's half of the row, raw
+        f32x16 s2, s3;
+        f32x16 &s0 = SV(B0{}), &s1 = SV(B1{}), &ts0 = TSV(B0{});
+        bf16x8 ka[NT], kb[NT];
+        auto stage_of = [&](int i) __attribute__((always_inline)) { return (uint32_t)(i < ns ? i : ns - 1) * KV_STAGE_BYTES; };
+        struct Moments { float a1, a2; } mo[4] = {};
+        auto max3 = [](float a, float b, float c) __attribute__((always_inline)) {
+            float d;
+            asm("v_max3_f32 %0, %1, %2, %3" : "=v"(d) : "v"(a), "v"(b), "v"(c));
+            return d;
         };
-        f32x16 s0, s1;
-        auto scores_of_pair = [&](int i) __attribute__((always_inline)) {   // samples i and i+1 (or i twice)
-            const uint32_t off0 = (uint32_t)i * KV_STAGE_BYTES, off1 = (uint32_t)(i + 1 < ns ? i + 1 : i) * KV_STAGE_BYTES;
-            bf16x8 ka[NT], kb[NT];
-#pragma unroll
-            for (int t = 0; t < NT; ++t) { ka[t] = lds_read_b128(kaddr0[t] + off0); kb[t] = lds_read_b128(kaddr0[t] + off1); }
-            FENCE();   // all sixteen reads in flight before the first MFMA waits for one
-#pragma unroll
-            for (int e = 0; e < 16; ++e) { s0[e] = 0.f; s1[e] = 0.f; }
-#pragma unroll
-            for (int t = 0; t < NT; ++t) { s0 = MFMA(ka[t], qf[t], s0); s1 = MFMA(kb[t], qf[t], s1); }
-            FENCE();
+        // statistics of elements E, E + 1 of a block's scores
+        auto take_stats = [&](const f32x16& x, auto E, Moments& to) __attribute__((always_inline)) {
+            constexpr int e = decltype(E)::value;
+            to.a1 += x[e]; to.a2 = fmaf(x[e], x[e], to.a2);
+            to.a1 += x[e + 1]; to.a2 = fmaf(x[e + 1], x[e + 1], to.a2);
+            m_scan = max3(m_scan, x[e], x[e + 1]);      // this lane's half of the row, raw
         };
-        scores_of_pair(0);
-        for (int i = 0; i < ns; i += 2) {
-            float x0[16], x1[16];
+        auto mask_sample = [&](f32x16& x, int i) __attribute__((always_inline)) {      // keys past Lkv
+            const int jbase = (i < ns ? i : ns - 1) * BC + 4 * g;
+            if (jbase - 4 * g + BC > Lkv)            // (uniform)
 #pragma unroll
-            for (int e = 0; e < 16; ++e) { x0[e] = s0[e]; x1[e] = s1[e]; }
+                for (int e = 0; e < 16; ++e)
+                    if (jbase + 8 * (e >> 2) + (e & 3) >= Lkv) x[e] = -INFINITY;
+        };
 #pragma unroll
-            for (int e = 0; e < 16; ++e) asm volatile("" : "+v"(x0[e]), "+v"(x1[e]));   // copied out before s0, s1 are reused
+        for (int t = 0; t < NT; ++t) { ka[t] = lds_read_b128(kaddr0[t] + stage_of(0)); kb[t] = lds_read_b128(kaddr0[t] + stage_of(1)); }
+        FENCE();   // all in flight before the first product waits for one
+        static_for<NT>([&](auto T) __attribute__((always_inline)) {
+            constexpr int t = decltype(T)::value;
+            if constexpr (t == 0) { SMFMA0(ka[t], qf[t], s0); SMFMA0(kb[t], qf[t], s1); }
+            else { SMFMA(ka[t], qf[t], s0); SMFMA(kb[t], qf[t], s1); }
             FENCE();
-            if (i + 2 < ns) scores_of_pair(i + 2);
-            scan_one(x0, i);
-            if (i + 1 < ns) scan_one(x1, i + 1);
+            ka[t] = lds_read_b128(kaddr0[t] + stage_of(2)); kb[t] = lds_read_b128(kaddr0[t] + stage_of(3));
+            FENCE();
+        });
+        SAMPLE_RESULTS_LAND();
+        asm volatile("" : "+v"(s0), "+v"(s1));
+        if (n_blocks <= 2) { mask_sample(s0, 0); mask_sample(s1, 1); }
+        {
+            static_for<NT>([&](auto T) __attribute__((always_inline)) {
+                constexpr int t = decltype(T)::value, EPS = 16 / NT;       // elements per step: 2, 4, or at head dimension 96 2 and the rest behind
+                if constexpr (t == 0) SMFMA0(ka[t], qf[t], s2); else SMFMA(ka[t], qf[t], s2);
+                static_for<EPS / 2>([&](auto I) __attribute__((always_inline)) { take_stats(s0, std::integral_constant<int, EPS * t + 2 * decltype(I)::value>{}, mo[0]); });
+                FENCE();
+                if constexpr (t == 0) SMFMA0(kb[t], qf[t], s3); else SMFMA(kb[t], qf[t], s3);
+                static_for<EPS / 2>([&](auto I) __attribute__((always_inline)) { take_stats(s1, std::integral_constant<int, EPS * t + 2 * decltype(I)::value>{}, mo[1]); });
+                FENCE();
+                if constexpr (!PRIMAL) ka[t] = lds_read_b128(kaddr0[t]);
+                if constexpr (!ZT) kb[t] = lds_read_b128(kaddr0[t] + TENSOR_BYTES);
+                FENCE();
+            });
+            static_for<(16 - NT * (16 / NT)) / 2>([&](auto I) __attribute__((always_inline)) {
+                using E = std::integral_constant<int, NT * (16 / NT) + 2 * decltype(I)::value>;
+                take_stats(s0, E{}, mo[0]); take_stats(s1, E{}, mo[1]);
+            });
         }
+        FENCE();
+        if constexpr (!PRIMAL)
+            static_for<NT>([&](auto T) __attribute__((always_inline)) {
+                constexpr int t = decltype(T)::value;
+                if constexpr (t == 0) SMFMA0(ka[t], tqf[t], ts0); else SMFMA(ka[t], tqf[t], ts0);
+                if constexpr (!ZT) SMFMA(kb[t], qf[t], ts0);
+                FENCE();
+            });
+        SAMPLE_RESULTS_LAND();
+        asm volatile("" : "+v"(s2), "+v"(s3));
+        if constexpr (!PRIMAL) asm volatile("" : "+v"(ts0));
+        if (n_blocks <= 4) { mask_sample(s2, 2); mask_sample(s3, 3); }
+        static_for<8>([&](auto I) __attribute__((always_inline)) {
+            using E = std::integral_constant<int, 2 * decltype(I)::value>;
+            take_stats(s2, E{}, mo[2]); take_stats(s3, E{}, mo[3]);
+        });
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            if (i < ns && (i + 1) * BC <= Lkv) { sum1 += mo[i].a1; sum2 += mo[i].a2; n_stat += BC; }
         m_scan = xhalf_max(m_scan) * c2;
         // Is a fixed reference good enough for this row?  For scores with standard deviation sigma the maximum
         // over all keys exceeds the maximum over a few hundred sampled keys by ~1.2 sigma, rarely by more than
@@ -822,15 +871,7 @@ __device__ __forceinline__ void attn_jvp_tile(
             // an outlying maximum would otherwise push the keys that carry its sum below the fp16 range.
             headroom = fminf(fmaxf(reach - 6.f, -6.f), REF_HEADROOM);
         }
-        // the workgroup's vote, through a word of the V ring's last stage (nothing is there yet; the K ring is live)
-        volatile __attribute__((address_space(3))) int* flag =
-            (volatile __attribute__((address_space(3))) int*)(uintptr_t)(lds0 + V_RING_BASE + 3 * KV_STAGE_BYTES);
-        if (tid == 0) *flag = 0;
-        __syncthreads();
-        if (__builtin_amdgcn_ballot_w64(risky) != 0 && lane == 0) *flag = 1;
-        __syncthreads();
-        const bool decline = *flag != 0;
-        __syncthreads();
+        const bool decline = workgroup_any(risky);
         if (decline) {                       // uniform over the workgroup; nothing is in flight
             if (tid == 0) wg_flags[vw] = n_blocks >= online_min_blocks ? 1 : 2;
             return;
@@ -838,7 +879,7 @@ __device__ __forceinline__ void attn_jvp_tile(
         start_v_ring();
     }
     {
-        plain_scores(0, B0{});
+        if constexpr (!PRESCAN) plain_scores(0, B0{});       // (else they come from the sample)
         if (n_blocks == 1) mask_scores(0, B0{});
         m = (PRESCAN ? m_scan : row_max(B0{})) + headroom;
         const f32x16& sv = SV(B0{});
@@ -936,6 +977,7 @@ __device__ __forceinline__ void attn_jvp_tile(
     static_assert(KPRE < NT && KFIRST + KPRE <= NG && VPRE < NG, "the fragment rings fit the key block's steps and groups");
     const auto lofs = make_lane_offsets<DH, !ZT, F16>(wave, lane, k_stride, v_stride);
     const int n_full = Lkv / BC;                       // blocks that need no row clamping
+    auto lofs_cut = lofs;                              // set before the tail
     bf16x8 kfr[KRING], tkfr[KRING], vfr[VRING], tvfr[VRING];
     auto read_k = [&](auto T, auto ST) __attribute__((always_inline)) {     // score step T of the block in K stage ST
         constexpr int t = decltype(T)::value;
@@ -977,11 +1019,10 @@ __device__ __forceinline__ void attn_jvp_tile(
         } else if constexpr (decltype(FULLc)::value) {
             load_lds_b128(base + (long)blk * (BC * (v_side ? v_stride : k_stride)), v_side ? lofs.v[lo_i] : lofs.k[lo_i], __builtin_amdgcn_readfirstlane(dst));
         } else {
-            const int row = G::piece_row(piece, lane), pc = G::piece_chunk(piece, lane);
-            int grow = blk * BC + row;
-            grow = grow < Lkv ? grow : Lkv - 1;
-            const int chunk = pc ^ (v_side ? G::v_swizzle(row) : G::k_swizzle(row));
-            ATTN_JVP_LOAD_LDS(base + (long)grow * (v_side ? v_stride : k_stride) + (chunk << 4), dst);
+            // past the end: the last block again; the last block, if it is ragged, by the lane offsets that repeat its last row
+            const int bc = blk < n_blocks ? blk : n_blocks - 1;
+            const uint32_t whole = v_side ? lofs.v[lo_i] : lofs.k[lo_i], cut = v_side ? lofs_cut.v[lo_i] : lofs_cut.k[lo_i];
+            load_lds_b128(base + (long)bc * (BC * (v_side ? v_stride : k_stride)), bc >= n_full ? cut : whole, __builtin_amdgcn_readfirstlane(dst));
         }
     };
 
@@ -1145,6 +1186,72 @@ __device__ __forceinline__ void attn_jvp_tile(
         if constexpr (ONLINE) online_apply();     // block b is complete: move the accumulators to the new frame, if any
     };
 
+    // The last block, which no block follows: its value products alone, those of the first half of its keys over the rest of the
+    // softmax.  V of it was published an iteration ago.  (As one more iteration of the sort above, with the scores of a block past
+    // the end, and with a 64-bit row address per copy in all of the tail's, the last four blocks of the cross-attention workload took
+    // 8180 cycles, now 5980.)
+    auto last_iteration = [&]() __attribute__((always_inline)) {
+        constexpr int PRODUCTS = PRIMAL ? 1 : ZT ? 2 : 3, GROUP_MFMAS = SPLIT ? 2 * PRODUCTS : PRODUCTS, SLOTS = NG / 2 * GROUP_MFMAS;
+        // ring stage and score buffer by the block's index here, so that there is one copy of this behind all lengths of the tail
+        uint32_t vlast[F16 ? 2 : NDB];
+#pragma unroll
+        for (int i = 0; i < (F16 ? 2 : NDB); ++i) vlast[i] = vaddr0[i] + (uint32_t)((n_blocks - 1) & 3) * KV_STAGE_BYTES;
+        auto read_v = [&](auto Gi) __attribute__((always_inline)) {
+            constexpr int gi = decltype(Gi)::value, t2 = gi / NDB, db = gi % NDB;
+            const uint32_t a = vlast[F16 ? t2 : db] + (F16 ? db * (32 * 64) : t2 * 16 * ROW_BYTES);
+            if constexpr (!ZT) tvfr[gi % VRING] = read_v_fragment(a + TENSOR_BYTES);
+            vfr[gi % VRING] = read_v_fragment(a);
+        };
+        static_for<VPRE>([&](auto Gi) { read_v(Gi); });
+        if ((n_blocks & 1) == 0)
+#pragma unroll
+            for (int e = 8; e < 16; ++e) {
+                sbuf0[e] = sbuf1[e];
+                if constexpr (!PRIMAL) tsbuf0[e] = tsbuf1[e];
+            }
+        FENCE();
+        static_for<NG>([&](auto Gc) {
+            constexpr int gi = decltype(Gc)::value, t2 = gi / NDB, db = gi % NDB;
+            auto behind = [&](auto SLOT) __attribute__((always_inline)) {
+                constexpr int slot = gi * GROUP_MFMAS + decltype(SLOT)::value;
+                static_for<20>([&](auto Kc) {
+                    constexpr int k = decltype(Kc)::value;
+                    if constexpr (k * SLOTS / 20 == slot) softmax_part(std::integral_constant<int, 4 + k / 5>{}, std::integral_constant<int, k % 5>{}, B0{});
+                });
+                FENCE();
+            };
+            const bf16x8 pb = as_bf16x8(wp[4 * t2], wp[4 * t2 + 1], wp[4 * t2 + 2], wp[4 * t2 + 3]);
+            bf16x8 hb8 = pb;
+            if constexpr (!PRIMAL) hb8 = as_bf16x8(wh[4 * t2], wh[4 * t2 + 1], wh[4 * t2 + 2], wh[4 * t2 + 3]);
+            accO[db] = VMFMA(vfr[gi % VRING], pb, accO[db]);
+            behind(std::integral_constant<int, 0>{});
+            if constexpr (!ZT) {
+                accAB[db] = VMFMA(tvfr[gi % VRING], pb, accAB[db]);
+                behind(std::integral_constant<int, 1>{});
+            }
+            if constexpr (!PRIMAL) {
+                accAB[db] = VMFMA(vfr[gi % VRING], hb8, accAB[db]);
+                behind(std::integral_constant<int, PRODUCTS - 1>{});
+            }
+            if constexpr (SPLIT) {
+                const bf16x8 pl8 = as_bf16x8(wpl[4 * t2], wpl[4 * t2 + 1], wpl[4 * t2 + 2], wpl[4 * t2 + 3]);
+                accO[db] = VMFMA(vfr[gi % VRING], pl8, accO[db]);
+                behind(std::integral_constant<int, PRODUCTS>{});
+                if constexpr (!ZT) {
+                    accAB[db] = VMFMA(tvfr[gi % VRING], pl8, accAB[db]);
+                    behind(std::integral_constant<int, PRODUCTS + 1>{});
+                }
+                if constexpr (!PRIMAL) {
+                    const bf16x8 hl8 = as_bf16x8(whl[4 * t2], whl[4 * t2 + 1], whl[4 * t2 + 2], whl[4 * t2 + 3]);
+                    accAB[db] = VMFMA(vfr[gi % VRING], hl8, accAB[db]);
+                    behind(std::integral_constant<int, 2 * PRODUCTS - 1>{});
+                }
+            }
+            if constexpr (gi + VPRE < NG) read_v(std::integral_constant<int, gi + VPRE>{});
+            FENCE();
+        });
+    };
+
     {
         static_for<KPRE>([&](auto T) { read_k(T, std::integral_constant<int, 1>{}); });   // K(1), landed in the prologue
         FENCE();
@@ -1168,16 +1275,18 @@ __device__ __forceinline__ void attn_jvp_tile(
         // tail (at most 8 blocks, b is a multiple of 4 here): clamped copies, and masking of the keys past Lkv in
         // the scores fetched for block b+1.  Straight-line nested code, not a loop over a switch: around a loop
         // the register allocator moved the accumulators at every iteration.
+        if (n_full < n_blocks) lofs_cut = make_lane_offsets<DH, !ZT, F16>(wave, lane, k_stride, v_stride, Lkv - n_full * BC - 1);
         auto tail = [&](auto self, auto K, int bb) __attribute__((always_inline)) -> void {
             constexpr int k = decltype(K)::value;
-            if constexpr (k < 8) {
-                if (bb < n_blocks) {
+            if constexpr (k < 7) {
+                if (bb + 1 < n_blocks) {
                     iteration(std::integral_constant<int, k & 3>{}, FN{}, bb);
                     self(self, std::integral_constant<int, k + 1>{}, bb + 1);
                 }
             }
         };
         tail(tail, std::integral_constant<int, 0>{}, b);
+        last_iteration();
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         // Resident workgroups: while this tile's results are checked, turned round and stored, bring the next tile's
         // Q and tQ rows into the L2 (one 128-byte line per lane and tensor, as a direct-to-LDS load of 16 bytes of it
@@ -1227,15 +1336,7 @@ __device__ __forceinline__ void attn_jvp_tile(
         // (fp16 weights: l and r are summed from the weights as rounded to fp16, so a weight that overflowed to inf,
         // or a 0 x inf in H~16, shows in l or r and fails the tests above; V16 and tV16 are finite by their scaling,
         // and finite fp16 operands cannot overflow the fp32 accumulators.  The accumulators need no scan of their own.)
-        __syncthreads();                       // everyone is done with the rings
-        volatile __attribute__((address_space(3))) int* flag =
-            (volatile __attribute__((address_space(3))) int*)(uintptr_t)lds0;
-        if (tid == 0) *flag = 0;
-        __syncthreads();
-        if (__builtin_amdgcn_ballot_w64(bad) != 0 && lane == 0) *flag = 1;
-        __syncthreads();
-        const bool redo = *flag != 0;
-        __syncthreads();
+        const bool redo = workgroup_any(bad);  // (and everyone is done with the rings)
         if constexpr (F16) {
             // the fp16 kernels do not repair: they hand the tile to the launch that follows (online fp16, then bf16 pairs)
             if (tid == 0)
