@@ -55,6 +55,8 @@ hipError_t ensure_dynamic_lds(const void* kern, int bytes, int dev);
 // (dtype, d) combination is not built for that kernel.
 hipError_t launch_fp32_vector(const Problem& p);      // d = 256: launch_keysplit
 hipError_t launch_keysplit(const Problem& p);         // head dimensions 32, 64, 96, 128, 256
+hipError_t launch_keysplit_f32(const Problem& p);     // ... of fp32 inputs
+hipError_t launch_keysplit_256(const Problem& p);     // ... head dimension 256
 hipError_t keysplit_preferred(const Problem& p, bool* yes);      // over the tile kernels of the same head dimension (asks for the device's size)
 int keysplit_groups_per_unit(int d, bool f32, bool tangents, bool key_tangents);      // up to how many groups of 16 query rows per compute unit
 hipError_t launch_mfma_bf16(const Problem& p);

@@ -162,3 +162,17 @@ def test_rows_without_a_finite_score(d, dtype):
             assert torch.isnan(o).all() and (lse == float("-inf")).all(), (Lkv, kw)
         t[1][0, 0, Lkv - 1] = float("nan")
         assert torch.isnan(run(t, 0.1, **own)[2]).all()
+
+
+@pytest.mark.parametrize("d,dtype,names", [(64, torch.float32, 6), (128, torch.bfloat16, 4), (32, torch.bfloat16, 4), (64, torch.float32, 3)])
+def test_either_side_of_one_workgroup_per_compute_unit(d, dtype, names):
+    """Up to there a workgroup has a unit's registers to itself, beyond two share them: the same bits for the same rows."""
+    cus = torch.cuda.get_device_properties(DEV).multi_processor_count
+    scale = float(np.float32(d ** -0.5))
+    t = inputs(9, 1, 1, 16 * cus + 5, 130, d, dtype)
+    t = t[:names] + [None] * (6 - names)
+    head = lambda n: [x if x is None else x[:, :, :n].contiguous() if i in (0, 3) else x for i, x in enumerate(t)]
+    two, one = run(t, scale, workspace=None), run(head(16 * cus), scale, workspace=None)
+    for a, b in zip(two, one):
+        assert a is None or torch.equal(a[:, :, :16 * cus], b)
+    check(run(head(40), scale, workspace=None), head(40), scale, "one")
