@@ -60,9 +60,12 @@ hipError_t launch_keysplit_256(const Problem& p);     // ... head dimension 256
 hipError_t keysplit_preferred(const Problem& p, bool* yes);      // over the tile kernels of the same head dimension (asks for the device's size)
 int keysplit_groups_per_unit(int d, bool f32, bool tangents, bool key_tangents);      // up to how many groups of 16 query rows per compute unit
 hipError_t launch_mfma_bf16(const Problem& p);
+hipError_t launch_mfma_bf16_64(const Problem& p);     // ... head dimensions 64 (and 32 padded), 96
+hipError_t launch_mfma_bf16_96(const Problem& p);
 hipError_t launch_mfma_f32(const Problem& p);
 bool mfma_bf16_supports(const Problem& p);
 hipError_t mfma_bf16_takes_f16(const Problem& p, bool* yes);      // the fp16 value path, not bf16 pairs (asks for the device's size)
+bool mfma_f16_path(const Problem& p, int cus);                    // ... of a call as the kernel sees it
 bool mfma_f32_supports(const Problem& p);
 bool fp32_vector_supports(const Problem& p);
 
