@@ -1147,32 +1147,84 @@ __global__ __launch_bounds__(NTHREADS, (Geo<D, TAN>::WG_PER_CU)) void attn_jvp_m
     }
 
     // ---- epilogue (Alg. 2, last lines): accumulator register 4k + i of column block n is column 32n + 8k + 4g + i -----
-    if (qrow < Lq) {
+    // A lane holds 16-byte pieces of one row, so stores from the registers move 32 bytes of each of 32 rows per instruction.  Each
+    // wave turns its 32 rows round through its share of the idle stages (o and to in turn where there are no key tangents and
+    // so half the stages), and stores whole rows, the reads for several stores in flight at once.  LDS operations of a
+    // wave execute in order, so there is no barrier.  (us a call, before -> now: query tangents H20 Lq1700 Lkv77 d128 52.5 -> 45.1, B2 H16
+    // Lq2048 Lkv512 d128 131.7 -> 123, all tangents H8 L700 d128 48.4 -> 45.7, H24 L3000 d32 486 -> 478.)
+    {
         const float inv_l = 1.f / l_row;
         const float mu = r_row * inv_l * gr;         // rowsum(P o tS), in the accumulators' scale
         const float fo = go * inv_l, ft = gt * inv_l;
-        const long at = (PARTS ? (bhp * Lq + qrow) * D : q_base + (long)qrow * row_elems) + 4 * g;
-        float* op = O + at;
-        float* top = TANGENT ? tO + at : nullptr;
-#pragma unroll
-        for (int n = 0; n < NC; ++n) {
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                float4 o4, t4;
-                o4.x = acc_o[n][4 * k + 0]; o4.y = acc_o[n][4 * k + 1];
-                o4.z = acc_o[n][4 * k + 2]; o4.w = acc_o[n][4 * k + 3];
-                if constexpr (TANGENT) {
-                    t4.x = fmaf(-mu, o4.x, acc_t[n][4 * k + 0]) * ft; t4.y = fmaf(-mu, o4.y, acc_t[n][4 * k + 1]) * ft;
-                    t4.z = fmaf(-mu, o4.z, acc_t[n][4 * k + 2]) * ft; t4.w = fmaf(-mu, o4.w, acc_t[n][4 * k + 3]) * ft;
-                    *reinterpret_cast<float4*>(top + 32 * n + 8 * k) = t4;
-                }
-                o4.x *= fo; o4.y *= fo; o4.z *= fo; o4.w *= fo;
-                *reinterpret_cast<float4*>(op + 32 * n + 8 * k) = o4;
-            }
-        }
-        if (g == 0) {
+        int here = lane;                             // (nothing that is derived from it below is kept across the sweep)
+        asm volatile("" : "+v"(here));
+        constexpr bool DIRECT = D == 128 && !TANGENT;
+        const int half = DIRECT ? g : here >> 5;
+        if (half == 0 && qrow < Lq) {
             if constexpr (PARTS) part_state[bhp * Lq + qrow] = f32x4{m, l_row, mu * (gt / go), 0.f};
             else LSE[bh * Lq + qrow] = fmaf(__builtin_amdgcn_logf(l_row), LN2, m);     // v_log_f32 is a binary log
+        }
+        typedef __attribute__((address_space(3))) f32x4 lds_f32x4;
+        constexpr int ROW = D * 4, CHUNKS = D / 4, RPS = 64 / CHUNKS, N = 32 / RPS, BATCH = N < 8 ? N : 8;      // RPS: rows of a store
+        static_assert(4 * 32 * ROW <= 4 * G::STAGE && (!KV_TANGENT || 8 * 32 * ROW <= 4 * G::STAGE), "the waves' shares fit the stages");
+        auto swizzle = [](int row) { return D == 96 ? (row >> 1) & 7 : row & (CHUNKS - 1); };
+        const uint32_t stage_o = lds0 + (uint32_t)wave * (32 * ROW), stage_t = KV_TANGENT ? stage_o + 4 * 32 * ROW : stage_o;
+        const int q0 = __builtin_amdgcn_readfirstlane(qrow);
+        const bool whole = q0 + 32 <= Lq;            // (uniform)
+        auto turn = [&](uint32_t stage, auto&& value) __attribute__((always_inline)) {       // value(n, k): registers 4k .. + 3 of column block n
+#pragma unroll
+            for (int n = 0; n < NC; ++n)
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+                    *reinterpret_cast<lds_f32x4*>((uintptr_t)(stage + (uint32_t)(here & 31) * ROW + (uint32_t)(((8 * n + 2 * k + (here >> 5)) ^ swizzle(here & 31)) << 4))) = value(n, k);
+        };
+        auto store = [&](uint32_t stage, float* to) __attribute__((always_inline)) {
+            const int piece = here % CHUNKS, r0 = here / CHUNKS;
+            if (r0 >= RPS) return;                   // (head dimension 96: 48 lanes)
+            const uint32_t lane_bytes = (uint32_t)r0 * (uint32_t)(PARTS ? ROW : 4 * row_elems) + 16 * piece;
+#pragma unroll
+            for (int i0 = 0; i0 < N; i0 += BATCH) {
+                f32x4 x[BATCH];
+#pragma unroll
+                for (int u = 0; u < BATCH; ++u) {
+                    const int r = RPS * (i0 + u) + r0;
+                    x[u] = *reinterpret_cast<const lds_f32x4*>((uintptr_t)(stage + (uint32_t)r * ROW + (uint32_t)((piece ^ swizzle(r)) << 4)));
+                }
+                FENCE();
+#pragma unroll
+                for (int u = 0; u < BATCH; ++u) {
+                    const int first = q0 + RPS * (i0 + u);
+                    const long at = PARTS ? (bhp * Lq + first) * (long)D : q_base + (long)first * row_elems;
+                    if (whole || first + r0 < Lq) *reinterpret_cast<f32x4*>(reinterpret_cast<char*>(to + at) + lane_bytes) = x[u];
+                }
+                FENCE();
+            }
+        };
+        auto value_o = [&](int n, int k) __attribute__((always_inline)) {
+            return f32x4{acc_o[n][4 * k] * fo, acc_o[n][4 * k + 1] * fo, acc_o[n][4 * k + 2] * fo, acc_o[n][4 * k + 3] * fo};
+        };
+        auto value_t = [&](int n, int k) __attribute__((always_inline)) {
+            return f32x4{fmaf(-mu, acc_o[n][4 * k], acc_t[n][4 * k]) * ft, fmaf(-mu, acc_o[n][4 * k + 1], acc_t[n][4 * k + 1]) * ft,
+                         fmaf(-mu, acc_o[n][4 * k + 2], acc_t[n][4 * k + 2]) * ft, fmaf(-mu, acc_o[n][4 * k + 3], acc_t[n][4 * k + 3]) * ft};
+        };
+        if constexpr (DIRECT) {
+            // (straight from the registers: those that the way through LDS needs were spilled in the sweep, and the other workgroup of
+            // the unit covers these stores; B2 H16 L4096 846 us against 855)
+            if (qrow < Lq) {
+                float* op = O + (PARTS ? (bhp * Lq + qrow) * D : q_base + (long)qrow * row_elems) + 4 * half;
+#pragma unroll
+                for (int n = 0; n < NC; ++n)
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) *reinterpret_cast<f32x4*>(op + 32 * n + 8 * k) = value_o(n, k);
+            }
+        } else {
+            turn(stage_o, value_o);
+            if constexpr (KV_TANGENT) turn(stage_t, value_t);
+            store(stage_o, O);
+            if constexpr (TANGENT) {
+                if constexpr (!KV_TANGENT) turn(stage_t, value_t);
+                store(stage_t, tO);
+            }
         }
     }
 }
