@@ -179,6 +179,10 @@ struct Geo {
     static constexpr int DUMMY_BASE = NOTE_BASE + 32;
     static constexpr int LDS_BYTES = DUMMY_BASE + 256 + 2 * 2 * BC * 4;
     static constexpr int WG_PER_CU = TAN == TAN_NONE || (TAN == TAN_QUERY && D == 32) ? 2 : 1;     // as the registers allow
+    // The last block's value products alone, or as one more iteration with the scores and conversions of a block past the end, which takes
+    // twice the time: alone where that pays.  At head dimensions 32 and 64 with all tangents or none it made the loop itself 1 to 4 %
+    // slower (H24 L3000 d32 478 -> 501 us a call, without tangents H8 L2668 d64 97.5 -> 100.5).
+    static constexpr bool LAST_ALONE = D >= 96 || TAN == TAN_QUERY;
     static constexpr int LPR = D == 96 ? 16 : D / 8;            // lanes that convert one K row, 8 elements each (D = 96: 12 of 16)
     static constexpr int K_ROWS = NTHREADS / LPR < BC ? NTHREADS / LPR : BC;    // rows per conversion pass
     static constexpr int K_PASSES = BC / K_ROWS;
@@ -497,7 +501,8 @@ __global__ __launch_bounds__(NTHREADS, (Geo<D, TAN>::WG_PER_CU)) void attn_jvp_m
     float v_scale[NX];                                   // set from the first block
     uint32_t v_low[NX], v_high[NX], v_ample;     // bits of 2^V_FLOOR, 2^16 and 2^6, scaled (v_low: less 1)
     uint64_t misfit = 0;         // lanes that have met values their tensor's scale does not suit
-    int v_hits = 0;              // blocks in which values below it were met in this lane's columns
+    int v_hits = 0;              // blocks in which values below it were met in this lane's columns,
+    int v_hits_before = 0;       // ... but for the last one converted
     bool v_small[G::V_PASSES];   // is V of the block under way small or zero there?
     uint32_t cv_h[4], cv_l[4];
     float cv_mx, cv_m2, cv_sc, cv_own;
@@ -846,7 +851,9 @@ __global__ __launch_bounds__(NTHREADS, (Geo<D, TAN>::WG_PER_CU)) void attn_jvp_m
             if (j == 3) l += lb;
             wph = split_hi(p0, p1, gain);
         }
-        if constexpr (part == 3) wpl = split_lo(p0, p1, gain, wph);
+        // (the empty statements hold the packing here, behind a product: its results are used by the next iteration or by the last
+        // block's products, and the compiler would move it in front of either)
+        if constexpr (part == 3) { wpl = split_lo(p0, p1, gain, wph); if constexpr (G::LAST_ALONE) asm volatile("" : "+v"(wpl)); }
         if constexpr (TANGENT) {
             if constexpr (part == 4) {
                 if constexpr (KV_TANGENT) { u0 = (ts2[e] * u0) * fqh; u1 = (ts2[e + 1] * u1) * fqh; }
@@ -861,7 +868,7 @@ __global__ __launch_bounds__(NTHREADS, (Geo<D, TAN>::WG_PER_CU)) void attn_jvp_m
                 if (j == 3) r += rb;
                 whh = pack_f16(h0, h1);
             }
-            if constexpr (part == 7) whl = split_lo(h0, h1, one, whh);
+            if constexpr (part == 7) { whl = split_lo(h0, h1, one, whh); if constexpr (G::LAST_ALONE) asm volatile("" : "+v"(whl)); }
         }
     };
     auto next_weights = [&]() __attribute__((always_inline)) {
@@ -927,11 +934,11 @@ __global__ __launch_bounds__(NTHREADS, (Geo<D, TAN>::WG_PER_CU)) void attn_jvp_m
             else fh[gi & 1][x] = lds_read_b128(at);
         }
     };
-    auto values = [&](auto ST, auto&& behind) __attribute__((always_inline)) {
+    auto values = [&](auto&& read, auto&& behind) __attribute__((always_inline)) {      // read(Gi, LO): the fragments of group Gi; those of the first are there
         static_for<2 * NC>([&](auto Gi) {
             constexpr int gi = decltype(Gi)::value, t2 = gi / NC, n = gi % NC;
             using Gn = std::integral_constant<int, gi + 1 < 2 * NC ? gi + 1 : gi>;
-            if constexpr (gi + 1 < 2 * NC) read_v(Gn{}, ST, I0{});
+            if constexpr (gi + 1 < 2 * NC) read(Gn{}, I0{});
             const u32x4 wph = {ph[4 * t2], ph[4 * t2 + 1], ph[4 * t2 + 2], ph[4 * t2 + 3]};
             const u32x4 wpl = {pl[4 * t2], pl[4 * t2 + 1], pl[4 * t2 + 2], pl[4 * t2 + 3]};
             u32x4 whh = wph, whl = wpl;
@@ -943,7 +950,7 @@ __global__ __launch_bounds__(NTHREADS, (Geo<D, TAN>::WG_PER_CU)) void attn_jvp_m
                 constexpr int w = decltype(W)::value;
                 constexpr int k0 = gi * NS + w * (NS / 3);
                 const u32x4 vh = fh[gi & 1][0], vl = fl[0];
-                if constexpr (w == 1 && gi + 1 < 2 * NC) read_v(Gn{}, ST, I1{});
+                if constexpr (w == 1 && gi + 1 < 2 * NC) read(Gn{}, I1{});
                 FENCE();
                 acc_o[n] = mfma16(w == 0 ? vl : vh, w == 1 ? wpl : wph, acc_o[n]);
                 behind(std::integral_constant<int, k0>{});
@@ -1054,12 +1061,13 @@ __global__ __launch_bounds__(NTHREADS, (Geo<D, TAN>::WG_PER_CU)) void attn_jvp_m
 
     // ---- sweep: iteration b does the scores of block b + 1 over the conversion of K(b + 2) and V(b + 1), then the values of
     // block b over the softmax of block b + 1.  Stage of a block: its index & 1.
-    // (the block past the end is the last one again, so a last block of few keys counts twice)
+    // (the last block, which may have few keys, counts twice: as the block past the end, or in the end)
     const int hits_enough = n_blocks + 1 < V_HITS ? n_blocks + 1 : V_HITS;
     auto iteration = [&](auto PAR, int b) __attribute__((always_inline)) -> bool {
         constexpr int par = decltype(PAR)::value;
         using Cur = std::integral_constant<int, par>;
         using Nxt = std::integral_constant<int, par ^ 1>;
+        if constexpr (G::LAST_ALONE) v_hits_before = v_hits;
         next_weights();
         pin_accumulators();
         if (__builtin_expect(noted, 0)) {
@@ -1079,7 +1087,7 @@ __global__ __launch_bounds__(NTHREADS, (Geo<D, TAN>::WG_PER_CU)) void attn_jvp_m
             if constexpr (decltype(LO)::value) static_for<KF>([&](auto Qi) { read_factors(Qi, Nxt{}); });
         });
         static_assert((S_PRE + 4 * W_PARTS) * M2 / S_PARTS >= M2 / 2, "pairs 0-3 come behind the second half of the value products");
-        values(Cur{}, [&](auto Kk) __attribute__((always_inline)) {
+        values([&](auto Gi, auto LO) __attribute__((always_inline)) { read_v(Gi, Cur{}, LO); }, [&](auto Kk) __attribute__((always_inline)) {
             constexpr int k = decltype(Kk)::value;
             constexpr int first = k * S_PARTS / M2, last = (k + 1) * S_PARTS / M2;
             static_for<last - first>([&](auto I) { softmax_part(std::integral_constant<int, first + decltype(I)::value>{}, Nxt{}, b + 1); });
@@ -1092,11 +1100,36 @@ __global__ __launch_bounds__(NTHREADS, (Geo<D, TAN>::WG_PER_CU)) void attn_jvp_m
         __syncthreads();     // the next block's planes are written by all, this one's read by all
         return stop;
     };
-    // (The last iteration prepares a block past the end: a copy of the last one, all of whose keys are masked.  One loop
-    // body for all blocks; a copy of it for the tail made the register allocator move accumulators and operands around.)
-    for (int b = 0;;) {
-        if (iteration(I0{}, b) || ++b >= n_blocks) break;
-        if (iteration(I1{}, b) || ++b >= n_blocks) break;
+    // (One loop body for all blocks, or all but the last: a copy of it for a tail made the register allocator move accumulators and operands
+    // around.  The last block alone stands in straight-line code, from a stage by its index: behind a branch, left out where the sweep
+    // was to end, it made the allocator spill 30 to 1200 bytes in the loop.  us a call, before -> now: all tangents H8 L700 d128 45.7 -> 43.4,
+    // query tangents H20 Lq1700 Lkv77 d128 45.1 -> 42.3, B2 H24 Lq1500 Lkv128 d32 27.8 -> 23.7.)
+    const int iterations = G::LAST_ALONE ? n_blocks - 1 : n_blocks;
+    if (!G::LAST_ALONE || iterations > 0)
+        for (int b = 0;;) {
+            if (iteration(I0{}, b) || ++b >= iterations) break;
+            if (iteration(I1{}, b) || ++b >= iterations) break;
+        }
+    if constexpr (G::LAST_ALONE) {
+        next_weights();              // (for nothing if the sweep was to end)
+        pin_accumulators();
+        const uint32_t shift = (uint32_t)((n_blocks - 1) & 1) * G::STAGE;
+        const uint32_t vlast[2] = {vaddr[0] + shift, vaddr[1] + shift};
+        auto read_last = [&](auto Gi, auto LO) __attribute__((always_inline)) {
+            constexpr int gi = decltype(Gi)::value, t2 = gi / NC, n = gi % NC;
+#pragma unroll
+            for (int x = 0; x < NX; ++x) {
+                const uint32_t at = vlast[t2] + 2 * x * G::PLANE + n * 2048;
+                if constexpr (decltype(LO)::value) fl[x] = lds_read_b128(at + G::PLANE);
+                else fh[gi & 1][x] = lds_read_b128(at);
+            }
+        };
+        read_last(I0{}, I0{});
+        read_last(I0{}, I1{});
+        values(read_last, nothing);
+        pin_accumulators();
+        v_hits += v_hits - v_hits_before;
+        misfit |= __builtin_amdgcn_ballot_w64(v_hits >= hits_enough);
     }
 
     // ---- did the scales suit?  If not, the workgroup redoes its tile ------------------------------------------------------
