@@ -29,7 +29,7 @@
 // terms (MODE_BF16), hi + lo bf16 pairs (MODE_BF16_SPLIT), or fp16 terms against power-of-two-scaled fp16
 // copies of V and tV that a pre-pass left in the caller's workspace (MODE_F16 with a sampled, fixed exponent
 // reference; MODE_F16_ONLINE with a running one, for peaked rows).  On the fp16 path the host launches MODE_F16,
-// MODE_F16_ONLINE and MODE_BF16_SPLIT in turn; per-tile flags in the workspace say which of them finishes a tile.
+// MODE_F16_ONLINE (from ONLINE_MIN_BLOCKS key blocks on) and MODE_BF16_SPLIT in turn; per-tile flags in the workspace say which of them finishes a tile.
 //
 // Numerics: bf16 operands, fp32 accumulation; softmax in base 2 with scale*log2(e) folded into one FMA.
 // The fast sweep fixes the exponent reference m per row after the first block (all of Alg. 2's rescale
@@ -1113,13 +1113,12 @@ __device__ __forceinline__ void attn_jvp_tile(
                         softmax_part(std::integral_constant<int, 2 * gi + 1>{}, std::integral_constant<int, 0>{}, Bnext{});
                     if constexpr (slot == first) {
                         if constexpr (gi == 0) {
-                            // (every lane of the new scores counts as read here, used or not: the score products of the
-                            // last iteration's unused block past the end still write their registers, which must not
-                            // have been handed to something else in the meantime)
+                            // (every lane of the new scores counts as read here, whatever is made of it: the score products' registers
+                            // must not have been handed to something else in the meantime)
                             if constexpr (PRIMAL) asm volatile("" : "+v"(s));
                             else asm volatile("" : "+v"(s), "+v"(ts));
                             if constexpr (!FULL) {
-                                // tail iterations only: keys past Lkv (a ragged last block, or the unused block past the end)
+                                // tail iterations only: keys past Lkv in a ragged last block
                                 if ((b + 2) * BC > Lkv) mask_scores(b + 1, Bnext{});
                             }
                             if constexpr (ONLINE) online_check(Bnext{});
@@ -1273,7 +1272,7 @@ __device__ __forceinline__ void attn_jvp_tile(
                 b += 4;
             } while (b + 8 <= n_full);
         }
-        // tail (at most 8 blocks, b is a multiple of 4 here): clamped copies, and masking of the keys past Lkv in
+        // tail (at most 7 blocks and the last, b is a multiple of 4 here): clamped copies, and masking of the keys past Lkv in
         // the scores fetched for block b+1.  Straight-line nested code, not a loop over a switch: around a loop
         // the register allocator moved the accumulators at every iteration.
         if (n_full < n_blocks) lofs_cut = make_lane_offsets<DH, !ZT, F16>(wave, lane, k_stride, v_stride, Lkv - n_full * BC - 1);
@@ -1627,7 +1626,7 @@ hipError_t launch_dh(const Problem& p_in) {
     }
     MainKernelTimer timer(p);
     hipError_t e;
-    // fp16 path: every tile is finished by exactly one of three launches.  The fp16 kernel with its sampled, fixed
+    // fp16 path: every tile is finished by exactly one of three launches (two on short sequences).  The fp16 kernel with its sampled, fixed
     // reference flags the tiles it declines (scores too spread out) or abandons (overflow found at the end of its
     // sweep); the online fp16 kernel does those, unless it meets an overflow itself (tangent scores beyond the fp16
     // range), which it flags for the bf16-pair kernel; each returns at once from the tiles that are not its own.
