@@ -1228,7 +1228,11 @@ __global__ __launch_bounds__(NTHREADS, (Geo<D, TAN>::WG_PER_CU)) void attn_jvp_m
                 for (int u = 0; u < BATCH; ++u) {
                     const int first = q0 + RPS * (i0 + u);
                     const long at = PARTS ? (bhp * Lq + first) * (long)D : q_base + (long)first * row_elems;
-                    if (whole || first + r0 < Lq) *reinterpret_cast<f32x4*>(reinterpret_cast<char*>(to + at) + lane_bytes) = x[u];
+                    if (whole || first + r0 < Lq) {
+                        f32x4* dst = reinterpret_cast<f32x4*>(reinterpret_cast<char*>(to + at) + lane_bytes);
+                        if constexpr (PARTS) *dst = x[u];          // (the merge reads them next)
+                        else __builtin_nontemporal_store(x[u], dst);
+                    }
                 }
                 FENCE();
             }

@@ -1448,6 +1448,8 @@ __device__ __forceinline__ void attn_jvp_tile(
         // LDS.  The rows of several stores are read before the first of them, and nothing but the last query tile of a head
         // looks at its rows one by one.  (Row by row, each a read, its latency, a branch and a 64-bit address, a tile's 64 stores
         // took 4530 cycles, now 3100, 2250 and 1980 where they are bf16 with and without tangents; 12 heads x 32760 queries x 512 keys.)
+        // Non-temporal, but for states that the merge reads next: what the workgroups re-read from their L2 is keys and values, not results
+        // (that workload 274 -> 260 us a call, B2 H16 L4096 690 -> 684, plain H24 Lq3001 Lkv64 17.1 -> 15.3).
         auto store_rows = [&](auto BF, auto WHOLE) __attribute__((always_inline)) {
             constexpr bool BF16_OUT = decltype(BF)::value;
             constexpr int CPL = BF16_OUT ? 2 : 1, LANES = OUT_CHUNKS / CPL, RPS = ROWS_PER_STORE * CPL, N = 32 / RPS, BATCH = N < 8 / CPL ? N : 8 / CPL;
@@ -1474,9 +1476,10 @@ __device__ __forceinline__ void attn_jvp_tile(
                     auto put = [&](void* to, const f32x4 (&x)[CPL]) __attribute__((always_inline)) {
                         char* p = static_cast<char*>(to) + row_at + lane_bytes;
                         if constexpr (BF16_OUT)
-                            *reinterpret_cast<uint4*>(p) = make_uint4(pack_bf16(x[0][0], x[0][1]), pack_bf16(x[0][2], x[0][3]),
-                                                                      pack_bf16(x[CPL - 1][0], x[CPL - 1][1]), pack_bf16(x[CPL - 1][2], x[CPL - 1][3]));
-                        else *reinterpret_cast<f32x4*>(p) = x[0];
+                            __builtin_nontemporal_store(u32x4{pack_bf16(x[0][0], x[0][1]), pack_bf16(x[0][2], x[0][3]), pack_bf16(x[CPL - 1][0], x[CPL - 1][1]),
+                                                              pack_bf16(x[CPL - 1][2], x[CPL - 1][3])}, reinterpret_cast<u32x4*>(p));
+                        else if constexpr (PARTS) *reinterpret_cast<f32x4*>(p) = x[0];
+                        else __builtin_nontemporal_store(x[0], reinterpret_cast<f32x4*>(p));
                     };
                     if (decltype(WHOLE)::value || q0 + RPS * (i0 + u) + r0 < Lq) {
                         put(O, ov[u]);
