@@ -93,6 +93,8 @@ extern "C" {
                                      kernel */
 #define ATTN_JVP_KERNEL_MFMA 2    /* matrix-core kernels (without FAST, NO_F16 or F16_ALWAYS the key-split kernel for few query
                                      rows, as AUTO, except for bf16 inputs with a workspace).
+                                     bf16 inputs in [B, L, H, d] with H d of 2^25 or more: the key-split kernel, with
+                                     any flags, here and for AUTO (rows too far apart for the tile kernel's offsets).
                                      bf16 inputs: scale > 0, d in {64, 128}; d in {32, 96} given a workspace of
                                      attn_jvp_workspace_bytes(...).  64, 96 and 128 are built natively; at 32 the
                                      inputs are first copied into the workspace zero-padded to 64 columns (exact: the

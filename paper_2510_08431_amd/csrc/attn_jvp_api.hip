@@ -147,7 +147,8 @@ int run(const void* q, const void* k, const void* v, const void* tq, const void*
     // result, and so not the kernel.
     const bool tile_asked = p.flags & (ATTN_JVP_FLAG_FAST | ATTN_JVP_FLAG_NO_F16 | ATTN_JVP_FLAG_F16_ALWAYS);
     // Too few query tiles for the chip's rounds: the tile kernels on keys in parts, given room for the parts' states.
-    if (opts->kernel == ATTN_JVP_KERNEL_AUTO && mfma_ok && !tile_asked && parts_allowed) {
+    const bool far = mfma_ok && !f32 && attn_jvp::rows_far_apart(p);
+    if (opts->kernel == ATTN_JVP_KERNEL_AUTO && mfma_ok && !far && !tile_asked && parts_allowed) {
         const attn_jvp::KeySplit split = attn_jvp::plan_split(B, H, Lq, Lkv, d, f32, tq != nullptr, tk != nullptr);
         const size_t before = f32 || d != 32 ? 0 : pad_bytes(B, H, Lq, Lkv, d);
         if (split.parts > 1 && workspace_bytes >= before + attn_jvp::split_bytes(B, H, Lq, Lkv, d, f32)) p.split = split;
@@ -157,6 +158,10 @@ int run(const void* q, const void* k, const void* v, const void* tq, const void*
     const bool few_rows = kernel == ATTN_JVP_KERNEL_MFMA && mfma_ok && !tile_asked && p.split.parts == 1 &&
                           (f32 || opts->kernel == ATTN_JVP_KERNEL_AUTO || workspace == nullptr);
     const bool no_tiles = opts->kernel == ATTN_JVP_KERNEL_AUTO && !mfma_ok && attn_jvp::fp32_vector_supports(p);
+    if (kernel == ATTN_JVP_KERNEL_MFMA && far) {      // (whatever the flags: the tile kernel cannot)
+        if (asked) return answer(ATTN_JVP_ROUTE_KEYSPLIT, 1);
+        return attn_jvp::launch_keysplit_far(p) == hipSuccess ? ATTN_JVP_OK : ATTN_JVP_LAUNCH_FAILED;
+    }
     if (few_rows || no_tiles) {
         bool take = no_tiles;
         e = take ? hipSuccess : attn_jvp::keysplit_preferred(p, &take);

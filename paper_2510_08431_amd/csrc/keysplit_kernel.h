@@ -252,7 +252,7 @@ struct Cfg {
     static_assert(LDS_BYTES * OCC <= 160 * 1024, "fits a compute unit");
 };
 
-template <typename TIn, int D, int TAN, int KW, int OCC_ASKED>
+template <typename TIn, int D, int TAN, int KW, int OCC_ASKED, bool FAR>      // FAR: 64-bit row offsets (rows_far_apart)
 __global__ __launch_bounds__((Cfg<TIn, D, TAN, KW, OCC_ASKED>::NTHREADS), (Cfg<TIn, D, TAN, KW, OCC_ASKED>::OCC)) void attn_jvp_keysplit_kernel(
     const TIn* __restrict__ Q, const TIn* __restrict__ K, const TIn* __restrict__ V,
     const TIn* __restrict__ tQ, const TIn* __restrict__ tK, const TIn* __restrict__ tV,
@@ -292,27 +292,28 @@ __global__ __launch_bounds__((Cfg<TIn, D, TAN, KW, OCC_ASKED>::NTHREADS), (Cfg<T
     // ---- loads (rows past the end repeat the last key: their weights are zero) ----
     // A row is a uniform address, its block's first row, plus 32 bits that are the lane's own and stay as they are from block to
     // block, up to a ragged last one: per block and row a 64-bit product of row number and stride took 0.3 us of 3.5.  (32 rows are
-    // below 4 GiB: checked on the host.)
+    // below 4 GiB: checked on the host, which takes FAR where they are not.)
+    using Off = std::conditional_t<FAR, uint64_t, uint32_t>;
     const long row_bytes = row_elems * (long)sizeof(TIn);
-    const uint32_t row_step = (uint32_t)row_bytes;
+    const Off row_step = (Off)row_bytes;
     auto my_key = [&](int i) __attribute__((always_inline)) { return 16 * (i >> 2) + 4 * kg + (i & 3); };      // of the block: the lane's i-th
     auto live_of = [&](int blk) __attribute__((always_inline)) { const int left = Lkv - blk * BC; return left < BC ? left : BC; };      // keys of a block that exist
     auto block_at = [&](const TIn* X, int blk) __attribute__((always_inline)) {
         return reinterpret_cast<const char*>(X) + kv_base * (long)sizeof(TIn) + (long)blk * BC * row_bytes;
     };
-    uint32_t k_off[2], v_off[8];
+    Off k_off[2], v_off[8];
     auto set_k_rows = [&](int a, int live) __attribute__((always_inline)) {
         const int row = 16 * a + c;
-        k_off[a] = (uint32_t)(row < live ? row : live - 1) * row_step + 8 * kg * (uint32_t)sizeof(TIn);
+        k_off[a] = (Off)(row < live ? row : live - 1) * row_step + 8 * kg * (uint32_t)sizeof(TIn);
     };
     auto set_v_rows = [&](int live) __attribute__((always_inline)) {
 #pragma unroll
-        for (int i = 0; i < 8; ++i) v_off[i] = (uint32_t)(my_key(i) < live ? my_key(i) : live - 1) * row_step + VW * c * (uint32_t)sizeof(TIn);
+        for (int i = 0; i < 8; ++i) v_off[i] = (Off)(my_key(i) < live ? my_key(i) : live - 1) * row_step + VW * c * (uint32_t)sizeof(TIn);
     };
     Row8 kr[C::K_RING], tkr[KV_TANGENT ? C::K_RING : 1];
     Cols vr[C::V_SLOTS][8], tvr[KV_TANGENT ? C::V_SLOTS : 1][8];
     auto load_k_step = [&](int step, int blk) __attribute__((always_inline)) {      // step NT a + t of a block: key tile a, score step t
-        const uint32_t at = k_off[step / NT];
+        const Off at = k_off[step / NT];
         kr[step % C::K_RING] = I::load8(reinterpret_cast<const TIn*>(block_at(K, blk) + at) + 32 * (step % NT));
         if constexpr (KV_TANGENT) tkr[step % C::K_RING] = I::load8(reinterpret_cast<const TIn*>(block_at(tK, blk) + at) + 32 * (step % NT));
     };
@@ -813,17 +814,18 @@ __global__ __launch_bounds__((Cfg<TIn, D, TAN, KW, OCC_ASKED>::NTHREADS), (Cfg<T
     }
 }
 
-template <typename TIn, int D, int TAN, int KW, int OCC_ASKED = 2>
+template <typename TIn, int D, int TAN, int KW, int OCC_ASKED = 2, bool FAR = false>
 hipError_t launch_waves(const Problem& p) {
     using C = Cfg<TIn, D, TAN, KW, OCC_ASKED>;
     const int q_tiles = (p.Lq - 1) / C::ROWS + 1;
     const long long blocks = (long long)q_tiles * p.B * p.H;
-    // (a block's rows at 32-bit offsets: 65535 heads, or as many as there are groups of rows to be few, are far below)
-    if (blocks > 0x7fffffffLL || (p.layout ? (long long)p.H : 1) * p.d * (long long)sizeof(TIn) * BC + p.d * (long long)sizeof(TIn) > 0xffffffffLL) return hipErrorInvalidValue;
-    auto kern = attn_jvp_keysplit_kernel<TIn, D, TAN, KW, OCC_ASKED>;
+    // (never: head dimension 256, which has no other kernel, and fp32 calls that no tile kernel takes are admitted up to 65535 heads,
+    // fp32_vector_supports; others come up to keysplit_groups_per_unit, or by launch_keysplit_far)
+    if (blocks > 0x7fffffffLL || (!FAR && (p.layout ? (long long)p.H : 1) * p.d * (long long)sizeof(TIn) * BC + p.d * (long long)sizeof(TIn) > 0xffffffffLL)) return hipErrorInvalidValue;
+    auto kern = attn_jvp_keysplit_kernel<TIn, D, TAN, KW, OCC_ASKED, FAR>;
     int dev = 0, cus = 0;
     hipError_t e = device_cus(&dev, &cus);
-    if constexpr (C::OCC == 2 && OCC_ASKED == 2)
+    if constexpr (C::OCC == 2 && OCC_ASKED == 2 && !FAR)
         if (e == hipSuccess && blocks <= cus) return launch_waves<TIn, D, TAN, KW, 1>(p);
     if (e == hipSuccess) e = ensure_dynamic_lds(reinterpret_cast<const void*>(kern), C::LDS_BYTES, dev);
     if (e != hipSuccess) return e;

@@ -57,6 +57,7 @@ hipError_t launch_fp32_vector(const Problem& p);      // d = 256: launch_keyspli
 hipError_t launch_keysplit(const Problem& p);         // head dimensions 32, 64, 96, 128, 256
 hipError_t launch_keysplit_f32(const Problem& p);     // ... of fp32 inputs
 hipError_t launch_keysplit_256(const Problem& p);     // ... head dimension 256
+hipError_t launch_keysplit_far(const Problem& p);     // ... bf16 inputs of head dimensions 32 to 128 whose rows are far apart
 hipError_t keysplit_preferred(const Problem& p, bool* yes);      // over the tile kernels of the same head dimension (asks for the device's size)
 int keysplit_groups_per_unit(int d, bool f32, bool tangents, bool key_tangents);      // up to how many groups of 16 query rows per compute unit
 hipError_t launch_mfma_bf16(const Problem& p);
@@ -64,6 +65,9 @@ hipError_t launch_mfma_bf16_64(const Problem& p);     // ... head dimensions 64 
 hipError_t launch_mfma_bf16_96(const Problem& p);
 hipError_t launch_mfma_f32(const Problem& p);
 bool mfma_bf16_supports(const Problem& p);
+// [B,L,H,d] with so many heads that byte offsets inside 32 rows of inputs or outputs (4 bytes an element) pass 2^32.  The bf16 tile kernel
+// has them in 32 bits, the bytes of 32 input rows in 31: it leaves such calls to launch_keysplit_far.  (fp32: mfma_f32_supports.)
+inline bool rows_far_apart(const Problem& p) { return p.layout != 0 && (long long)p.H * p.d >= 1LL << 25; }
 hipError_t mfma_bf16_takes_f16(const Problem& p, bool* yes);      // the fp16 value path, not bf16 pairs (asks for the device's size)
 bool mfma_f16_path(const Problem& p, int cus);                    // ... of a call as the kernel sees it
 bool mfma_f32_supports(const Problem& p);

@@ -177,6 +177,27 @@ def test_route_refuses_what_a_call_refuses(lib):
         binding.attn_jvp_route(1, 1, 8, 8, 48, 0.1)
 
 
+@pytest.mark.parametrize("d", [32, 64, 96, 128])
+def test_rows_far_apart_leave_the_tile_kernel(lib, d):
+    """[B,L,H,d] in bf16 from 2^25 elements between rows on: the tile kernel's 32-bit offsets do not reach, and the answer comes from
+    the host, without a look at the device.  Below that, and in [B,H,L,d], and in fp32, the rules are as ever."""
+    from paper_2510_08431_amd import binding
+    def ask(H, d=d, L=70, **kw):
+        o = binding.AttnJvpOpts(**{"layout": binding.LAYOUT_BLHD, "workspace": 256, "workspace_bytes": 1 << 50, **kw})
+        return lib.attn_jvp_route(1, H, L, L, d, 0.1, 2, ctypes.byref(o), None)
+    heads = -(-(1 << 25) // d)
+    keysplit = binding.ROUTES.index("keysplit")
+    for kernel in (binding.KERNEL_AUTO, binding.KERNEL_MFMA):
+        for flags in (0, binding.FLAG_FAST, binding.FLAG_NO_F16, binding.FLAG_F16_ALWAYS):
+            assert ask(heads, kernel=kernel, flags=flags) == keysplit
+            assert ask(2 * heads, L=20, kernel=kernel, flags=flags) == keysplit
+    assert ask(heads - 1, flags=binding.FLAG_NO_F16) != keysplit
+    assert ask(heads, flags=binding.FLAG_NO_F16, layout=binding.LAYOUT_BHLD) != keysplit
+    assert ask(heads, kernel=binding.KERNEL_FP32) == -3                     # 65535 heads at most
+    assert ask(heads, d=256) == ask(heads, d=256, in_dtype=1) == -3
+    assert ask(heads, in_dtype=1) == -3                                     # fp32: no kernel, with an error
+
+
 def test_rmsnorm_argument_validation_returns_codes_without_launching(lib):
     """Fake (never dereferenced) addresses: every call here must be rejected on the host."""
     vp = ctypes.c_void_p
