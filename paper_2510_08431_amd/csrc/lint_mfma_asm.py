@@ -13,7 +13,15 @@ states (one per issued instruction, N + 1 for `s_nop N`):
       read or write its destination registers for 11 wait states.
 
 Both are checked along straight-line code; a label or branch ends the window of R1 (nothing is known about the
-other path) and R2 keeps scanning through fall-through labels.  Usage: python lint_mfma_asm.py file.s [...]
+other path) and R2 keeps scanning through fall-through labels.
+
+The bf16 tile kernel's waves turn their results round through LDS that holds the key and value rings during the sweep, which all
+waves read and fill.  Checked over all paths of a kernel (unshared_staging):
+
+  R3  between a transposing LDS read (V of a block) or a direct-to-LDS copy and a 16-byte LDS write (results) there is a
+      workgroup barrier.
+
+Usage: python lint_mfma_asm.py file.s [...]
 """
 import re
 import sys
@@ -136,6 +144,61 @@ def lint(text, name="<asm>"):
     return problems
 
 
+def unshared_staging(text, name="<asm>"):
+    """R3: violation strings, one per offending 16-byte LDS write of a kernel with direct-to-LDS copies."""
+    problems, where, blocks, label_of = [], "", [], {}      # blocks of a function: (label or None, [(line, op, branch target)])
+
+    def check():
+        starts = [False] * len(blocks)          # may a read or copy be unguarded where the block starts?
+        seen = [False] * len(blocks)
+        todo = [0] if blocks else []
+        if blocks:
+            seen[0] = True
+        bad = set()
+        while todo:
+            i = todo.pop()
+            dirty, goes_on = starts[i], True
+
+            def enter(j, d):
+                if not seen[j] or (d and not starts[j]):
+                    seen[j], starts[j] = True, starts[j] or d
+                    todo.append(j)
+            for no, op, target in blocks[i]:
+                if op == "s_barrier":
+                    dirty = False
+                elif op.startswith(("ds_read_b64_tr", "global_load_lds")):
+                    dirty = True
+                elif op == "ds_write_b128" and dirty:
+                    bad.add(no)
+                elif op.startswith(("s_cbranch", "s_branch")):
+                    enter(label_of[target], dirty)
+                    goes_on = op.startswith("s_cbranch")
+                elif op == "s_endpgm":
+                    goes_on = False
+                if not goes_on:
+                    break
+            if goes_on and i + 1 < len(blocks):
+                enter(i + 1, dirty)
+        problems.extend(f"{name}:{no}: results staged in LDS that other waves may still read or fill (no barrier on some path), {where}" for no in sorted(bad))
+
+    for no, raw in enumerate(text.split("\n"), 1):
+        l = raw.split(";")[0].strip()
+        m = re.match(r"^([\w.$]+):", l)
+        if m and m.group(1).startswith(".Lfunc_end"):
+            check()
+            blocks, label_of = [], {}
+        elif m and not m.group(1).startswith("."):
+            where, blocks, label_of = m.group(1), [[]], {}
+        elif m and blocks:
+            label_of[m.group(1)] = len(blocks)
+            blocks.append([])
+        elif blocks and l and not l.startswith("."):
+            op, operands = split_operands(l)
+            blocks[-1].append((no, op, operands[0] if operands else None))
+    check()
+    return problems
+
+
 def count_asm_mfma(text):
     n, in_asm = 0, False
     for raw in text.split("\n"):
@@ -154,7 +217,7 @@ def main(argv):
     for path in argv:
         with open(path) as f:
             text = f.read()
-        problems = lint(text, path)
+        problems = lint(text, path) + (unshared_staging(text, path) if "f32" not in path else [])
         print(f"{path}: {count_asm_mfma(text)} assembly MFMAs checked, {len(problems)} problem(s)")
         for p in problems[:20]:
             print("  " + p)

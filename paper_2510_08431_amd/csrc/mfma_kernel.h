@@ -1393,6 +1393,7 @@ __device__ __forceinline__ void attn_jvp_tile(
                 m = m_new;
             }
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            __syncthreads();                   // every wave has read the last block, and its copies have landed: the rings are free
         }
     }
 
@@ -1412,7 +1413,7 @@ __device__ __forceinline__ void attn_jvp_tile(
     // writes whole rows.  Each wave therefore turns its 32 x 128 results round through its own 32 KiB of the (now
     // idle) LDS: written as held (row c, 16-byte chunk 8 db + 2 v4 + g, at chunk position chunk ^ c so that neither
     // direction meets bank conflicts), read back two whole rows per instruction.  LDS operations of one wave execute
-    // in order, so the wave needs no barrier of its own; the workgroup barrier at the end keeps the next tile's
+    // in order, so there is no barrier in between (the one in front is the vote's or the safe sweep's last); the workgroup barrier at the end keeps the next tile's
     // first copies (resident workgroups) off the staging areas of waves that are still reading.
     {
         typedef __attribute__((address_space(3))) f32x4 lds_float4;

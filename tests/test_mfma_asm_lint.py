@@ -55,6 +55,44 @@ def test_a_compiler_mfma_reading_the_result_is_caught_but_a_chain_is_not():
     assert any("v_mfma_f32_32x32x16_f16 touches" in p for p in lint.lint(bad))
 
 
+STAGING = """
+kernel:
+.LBB0_1:
+	global_load_lds_dwordx4 v1, s[0:1]
+	s_barrier
+	ds_read_b64_tr_b16 v[4:5], v9
+	s_cbranch_scc0 .LBB0_1
+	s_cbranch_vccz .LBB0_3
+	s_barrier
+	s_branch .LBB0_3
+.LBB0_2:
+	s_barrier
+.LBB0_3:
+	ds_write_b128 v10, v[12:15]
+	s_endpgm
+.Lfunc_end0:
+"""
+
+
+def test_results_staged_without_a_barrier_on_one_path():
+    assert len(lint.unshared_staging(STAGING)) == 1                                # the branch past the barrier
+    assert lint.unshared_staging(STAGING.replace("s_cbranch_vccz .LBB0_3", "s_cbranch_vccz .LBB0_2")) == []
+    copy = STAGING.replace("s_cbranch_vccz .LBB0_3", "s_nop 0").replace("\ts_barrier\n\ts_branch", "\ts_barrier\n\tglobal_load_lds_dwordx4 v1, s[0:1]\n\ts_branch")
+    assert len(lint.unshared_staging(copy)) == 1                                   # a copy behind it
+
+
+@pytest.mark.parametrize("source", ["attn_jvp_mfma", "attn_jvp_mfma_64", "attn_jvp_mfma_96"])
+def test_built_library_stages_results_behind_a_barrier(source):
+    """(The redo of a tile went from its last block's reads to the staging without one.)"""
+    asm = os.path.join(ROOT, "_build", source + "-hip-amdgcn-amd-amdhsa-gfx950.s")
+    if not os.path.exists(asm):
+        pytest.skip("no compiled assembly under _build/ (run __graft_entry__.build())")
+    with open(asm) as f:
+        text = f.read()
+    assert "ds_write_b128" in text and "ds_read_b64_tr_b16" in text
+    assert lint.unshared_staging(text, asm) == []
+
+
 def test_built_library_passes():
     asm = os.path.join(ROOT, "_build", "attn_jvp_mfma-hip-amdgcn-amd-amdhsa-gfx950.s")
     if not os.path.exists(asm):
