@@ -1,6 +1,6 @@
 // The ordinary calls of binding.py without its Python and ctypes steps: new outputs from torch's allocator, the current stream,
 // the cached workspace.  attn() and rmsnorm() do what attn_jvp_fwd_ex and attn_jvp_rmsnorm_fwd of binding.py do for plain
-// contiguous GPU tensors that fit together; for anything else (other tensor types, modes that watch torch's calls, functorch's
+// contiguous GPU tensors that fit together; for anything else (other tensor types, named dimensions, modes that watch torch's calls, functorch's
 // wrapped tensors, another current device, calls recorded into a graph, arguments that do not fit) they return None, and binding.py does the whole call,
 // errors included.  A call's host time is what bounds small shapes: 13.1 -> 7.1 us a call back to back (8 heads, 300 queries,
 // 77 keys, d = 64, whose kernel takes 4.5), 8.5 -> 5.4 for the normalisation; outputs without torch's dispatcher another 0.8 of the former.
@@ -53,12 +53,12 @@ bool plain_mode() {
     return !at::impl::torch_function_mode_enabled() && !c10::impl::TorchDispatchModeTLS::any_modes_set() &&
            !c10::impl::tls_is_dispatch_key_included(c10::DispatchKey::FuncTorchDynamicLayerFrontMode);
 }
-// A torch.Tensor or Parameter that is a plain contiguous array in GPU memory (no subclass, no wrapper).
+// A torch.Tensor or Parameter that is a plain contiguous array in GPU memory (no subclass, no wrapper, no names for outputs to take over).
 const at::Tensor* plain_tensor(PyObject* o) {
     if (!THPVariable_CheckExact(o)) return nullptr;
     const at::Tensor& t = THPVariable_Unpack(o);
     return t.defined() && t.is_cuda() && t.layout() == at::kStrided && t.has_storage() &&
-           !t.key_set().has(c10::DispatchKey::Python) && t.is_contiguous() ? &t : nullptr;
+           !t.key_set().has(c10::DispatchKey::Python) && !t.has_names() && t.is_contiguous() ? &t : nullptr;
 }
 // at::empty without its way through the dispatcher, 0.3 us each: plain_mode() has found nothing there that would have a say.
 at::Tensor fresh(at::IntArrayRef sizes, at::ScalarType dtype, c10::Device device) {

@@ -92,6 +92,25 @@ def test_refused_calls_and_watched_calls():
 
 
 @pytest.mark.gpu
+@pytest.mark.filterwarnings("ignore:Named tensors")
+def test_outputs_take_over_what_the_python_way_takes_over():
+    """Dimension names of q and x; in inference mode the outputs are inference tensors."""
+    stream = torch.cuda.current_stream()
+    q, w = inputs(BF16, Lkv=37)[0], torch.ones(64, device=DEV)
+    for named in (False, True):
+        x = q.rename("B", "H", "L", "D") if named else q
+        calls = (lambda **kw: binding.attn_jvp_fwd_ex(*[x] * 6, 0.1, **kw), lambda **kw: binding.attn_jvp_rmsnorm_fwd(x, x, w, 1e-6, **kw))
+        for call in calls:
+            for mode in (torch.no_grad, torch.inference_mode):
+                with mode():
+                    got, want = call(), call(stream=stream)
+                for a, b in zip(got, want):
+                    assert a.names == b.names and a.is_inference() == b.is_inference() == (mode is torch.inference_mode)
+                    assert torch.equal(a.rename(None), b.rename(None))
+        assert (got[0].names == x.names) and (got[0].names[-1] == "D") == named
+
+
+@pytest.mark.gpu
 def test_streams_and_threads():
     """Every thread its own stream: each call on its thread's current stream with that stream's workspace."""
     t = inputs(BF16, Lq=300, Lkv=2100, d=128, H=1)
