@@ -78,7 +78,7 @@ constexpr float FP32_SLACK = 32.f;        // fp32_tile: nats by which scores may
 
 // Score products with the result in ARITHMETIC registers (the vector ALU reads every score; left to itself the compiler
 // puts the results of MFMAs into accumulation registers, which Q, tQ and the accumulators fill, and spills).  It does
-// not see inside: SCORE_RESULTS_LAND supplies the 11 wait states an 8-pass MFMA needs before its result may be read,
+// not see inside: SCORE_RESULTS_LAND supplies the 12 wait states an 8-pass MFMA needs before its result may be read,
 // and the statements that follow it keep every result register live until then.  The build checks the compiled
 // assembly for both (lint_mfma_asm.py).  SMFMA0 starts a chain (C = 0), SMFMA continues it.
 #define SMFMA0(a, b, c) asm volatile("v_mfma_f32_32x32x16_f16 %0, %1, %2, 0" : "=&v"(c) : "v"(a), "a"(b))

@@ -10,7 +10,8 @@ states (one per issued instruction, N + 1 for `s_nop N`):
   R1  a vector-ALU instruction that writes a register an assembly MFMA reads (A, B or C operand) must be at least
       2 wait states before it;
   R2  after an assembly MFMA, no instruction other than an MFMA accumulating into exactly the same registers may
-      read or write its destination registers for 11 wait states.
+      read or write its destination registers for 12 wait states (what the compiler puts behind its own:
+      s_nop 11 in front of a vector-ALU read or another MFMA's operand).
 
 Both are checked along straight-line code; a label or branch ends the window of R1 (nothing is known about the
 other path) and R2 keeps scanning through fall-through labels.
@@ -27,7 +28,7 @@ import re
 import sys
 
 VALU_WRITE_TO_MFMA_READ = 2
-MFMA8_WRITE_TO_OTHER_ACCESS = 11
+MFMA8_WRITE_TO_OTHER_ACCESS = 12
 
 _REG = re.compile(r"\b([va])(?:\[(\d+):(\d+)\]|(\d+)\b)")
 

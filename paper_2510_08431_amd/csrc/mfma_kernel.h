@@ -119,7 +119,7 @@ constexpr int PRESCAN_BLOCKS = NSTAGE;   // key blocks sampled for the fp16 path
 // the compiler, once a kernel uses accumulation registers at all, places every MFMA result there: 32 single-register
 // copies per key block to get the scores out.  Written as assembly, the MFMA delivers them where they are needed.
 // The compiler does not see inside: it still orders the LDS reads that produce operand `a` (they are register
-// operands of the statement), but it knows nothing of the 11 wait states an 8-pass MFMA needs before the vector ALU
+// operands of the statement), but it knows nothing of the 12 wait states an 8-pass MFMA needs before the vector ALU
 // may read its result; the loop provides them itself (SCORE_RESULTS_LAND and what follows it) after the last score
 // product of a block.
 // Nor does it know that the result registers are busy until then: a result lane nobody reads later would be handed
@@ -129,7 +129,7 @@ constexpr int PRESCAN_BLOCKS = NSTAGE;   // key blocks sampled for the fp16 path
 // `b` (a Q or tQ fragment) lives in accumulation registers.  SMFMA0 starts a chain (C = 0), SMFMA continues it.
 #define SMFMA0(a, b, c) asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&v"(c) : "a"(a), "a"(b))
 #define SMFMA(a, b, c) asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(c) : "a"(a), "a"(b))
-// 5 wait states of its own; the other 6 or more of the 11 are the instructions that follow in every instantiation
+// 5 wait states of its own; the other 7 or more of the 12 are the instructions that follow in every instantiation
 // (LDS reads, the wait for the copies, the barrier, the first value MFMA) before the first hand-over copy: the
 // build's check of the compiled assembly counts them, so a schedule that came out shorter would fail the build.
 #define SCORE_RESULTS_LAND() asm volatile("s_nop 4" ::: "memory")

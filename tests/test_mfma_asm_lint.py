@@ -34,8 +34,8 @@ def test_accepts_a_correct_sequence():
 
 
 def test_catches_a_result_read_too_early():
-    bad = GOOD.replace("\ts_nop 7\n", "")
-    assert any("v_fma_f32 touches" in p for p in lint.lint(bad))
+    for bad in (GOOD.replace("\ts_nop 7\n", ""), GOOD.replace("\ts_nop 3\n", "\ts_nop 2\n")):      # 4 of the 12 wait states; 11
+        assert any("v_fma_f32 touches" in p for p in lint.lint(bad))
 
 
 def test_catches_a_register_of_the_result_reused_too_early():
@@ -93,8 +93,9 @@ def test_built_library_stages_results_behind_a_barrier(source):
     assert lint.unshared_staging(text, asm) == []
 
 
-def test_built_library_passes():
-    asm = os.path.join(ROOT, "_build", "attn_jvp_mfma-hip-amdgcn-amd-amdhsa-gfx950.s")
+@pytest.mark.parametrize("source", ["attn_jvp_mfma", "attn_jvp_mfma_64", "attn_jvp_mfma_96", "attn_jvp_mfma_f32"])
+def test_built_library_passes(source):
+    asm = os.path.join(ROOT, "_build", source + "-hip-amdgcn-amd-amdhsa-gfx950.s")
     if not os.path.exists(asm):
         pytest.skip("no compiled assembly under _build/ (run __graft_entry__.build())")
     with open(asm) as f:
