@@ -60,7 +60,9 @@ const at::Tensor* plain_tensor(PyObject* o) {
     return t.defined() && t.is_cuda() && t.layout() == at::kStrided && t.has_storage() &&
            !t.key_set().has(c10::DispatchKey::Python) && !t.has_names() && t.is_contiguous() ? &t : nullptr;
 }
-// at::empty without its way through the dispatcher, 0.3 us each: plain_mode() has found nothing there that would have a say.
+// at::empty without its way through the dispatcher, 0.3 us each, by torch's internal interface.  What would have a say there has been
+// looked for (plain_mode(), plain_tensor()), but for torch.utils.deterministic.fill_uninitialized_memory, whose fill is left out: the
+// kernels write every element.
 at::Tensor fresh(at::IntArrayRef sizes, at::ScalarType dtype, c10::Device device) {
     return at::Tensor(at::detail::empty_cuda(sizes, dtype, device, std::nullopt));
 }

@@ -87,6 +87,7 @@ struct Geo {
     static constexpr int RING_BYTES = 2 * NSTAGE * KV_STAGE_BYTES;
     static constexpr int VOTE_BASE = RING_BYTES + 1024;           // behind a KiB where prefetches land that nobody reads: a word per wave
     static constexpr int LDS_BYTES = VOTE_BASE + 64;
+    static_assert(VOTE_BASE >= RING_BYTES + 1024, "the vote words lie behind the rings and the spare KiB");
     static constexpr int CHUNKS_PER_ROW = ROW_BYTES / 16;          // 16-byte chunks of a row
     static constexpr int PIECES = TENSOR_BYTES / 1024;             // direct-to-LDS instructions (64 x 16 B) per tensor block: 8, 6 or 4
     // ... and how many a wave issues for a pair (X, tX), or for X alone (WITH_TANGENT false).  At DH = 96, X alone has 6
@@ -1503,8 +1504,9 @@ __device__ __forceinline__ void attn_jvp_tile(
 // = n_tiles) that is one tile each, handed out by the hardware as compute units fall free; with fewer, the workgroups
 // stay resident and walk through their tiles themselves: no workgroup launch between tiles, the tile-independent
 // set-up is done once, and a tile's output stores drain while the next tile's first loads are already queued
-// behind them.  A tile ends with every wave past a workgroup barrier that follows its last LDS read, on every
-// path, so the next tile may start filling LDS at once.  Since gridDim.x is then a multiple of 8, tile w + k gridDim.x
+// behind them.  On every path, decline and abandonment included, a tile ends with every wave past a workgroup barrier that follows
+// its last read of the rings, so the next tile may start filling them at once.  The vote words are read behind that barrier: they
+// lie outside the rings, and are written again only behind a further barrier (a tile's start has one before its first vote).  Since gridDim.x is then a multiple of 8, tile w + k gridDim.x
 // runs on the same XCD as tile w, as the tile map in attn_jvp_tile assumes.
 // PARTS: an instantiation of its own (its bookkeeping in the one for whole calls cost those of few blocks 1 %).
 template <int MODE, int TAN, int DH, bool PARTS = false>
