@@ -69,3 +69,20 @@ def test_key_blocks_fp32(d, names):
             t = inputs(Lkv, d, names, torch.float32)
             tol = 1e-5 if Lkv <= 256 else 1.5e-5 * (Lkv / 256) ** 0.5
             check(run(t, scale, flags=binding.FLAG_NO_F16), t, scale, (tol, tol, tol))
+
+
+@pytest.mark.parametrize("names", [6, 4, 3])
+@pytest.mark.parametrize("d", [64, 96, 128])
+def test_redone_tiles(d, names):
+    """Scores of later keys far above the first block's: every tile is redone with the running maximum.  576 tiles, so that workgroups
+    share a unit where they may; the heads repeat each other and must have the same bits."""
+    scale = float(np.float32(d ** -0.5))
+    g = torch.Generator().manual_seed(d)
+    t = [torch.randn(1, 4, L, d, generator=g) for L in (700, 300, 300, 700, 300, 300)]
+    t[1][:, :, 32:] *= 40.0
+    t = [x.to(torch.bfloat16) for x in t][:names] + [None] * (6 - names)
+    got = binding.attn_jvp_fwd_ex(*[None if x is None else x.repeat(1, 24, 1, 1).to(DEV) for x in t], scale, flags=binding.FLAG_NO_F16)
+    few = [None if x is None else x[:, :4] for x in got]
+    check(few, t, scale, (1e-2, 2e-2, 1e-3))
+    for x, y in zip(got, few):
+        assert x is None or (x.view(24, *y.shape[1:]) == y).all()
