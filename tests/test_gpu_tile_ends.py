@@ -86,3 +86,24 @@ def test_redone_tiles(d, names):
     check(few, t, scale, (1e-2, 2e-2, 1e-3))
     for x, y in zip(got, few):
         assert x is None or (x.view(24, *y.shape[1:]) == y).all()
+
+
+@pytest.mark.parametrize("names,Lkv", [(6, 70), (4, 70), (3, 70), (3, 300)])
+@pytest.mark.parametrize("d", [64, 128])
+def test_rows_almost_too_far_apart(d, names, Lkv):
+    """[B,L,H,d] with just under 2^25 elements between rows, the most that the bf16 tile kernel takes: offsets inside a block of 32 rows
+    come up to 2^31 bytes, in the tail (70 keys) and in the main loop (300).  The heads repeat each other, and each has the bits of few heads."""
+    some, scale, Lq = 100, float(np.float32(d ** -0.5)), 3
+    heads = ((1 << 25) // d - 1) // some * some
+    g = torch.Generator().manual_seed(d)
+    t = [torch.randn(1, some, L, d, generator=g).to(torch.bfloat16) for L in (Lq, Lkv, Lkv, Lq, Lkv, Lkv)][:names] + [None] * (6 - names)
+    few = binding.attn_jvp_fwd_ex(*[None if x is None else x.to(DEV) for x in t], scale, flags=binding.FLAG_NO_F16, workspace=None)
+    check([None if x is None else x[:, :4] for x in few], [None if x is None else x[:, :4] for x in t], scale, (1e-2, 2e-2, 1e-3))
+    many = [None if x is None else x.to(DEV).transpose(1, 2).repeat(1, 1, heads // some, 1) for x in t]
+    got = binding.attn_jvp_fwd_ex(*many, scale, flags=binding.FLAG_NO_F16, workspace=None, layout=binding.LAYOUT_BLHD)
+    for x, want in zip(got[:2], few[:2]):
+        if x is not None:
+            assert (x.view(1, Lq, -1, some, d) == want.transpose(1, 2)[:, :, None]).all()
+    assert (got[2].view(1, -1, some, Lq) == few[2][:, None]).all()
+    del many, got
+    torch.cuda.empty_cache()
